@@ -19,79 +19,24 @@
 // Bound: HBM (one streaming read of the target rows per pass).
 #include "common.h"
 #include "hashkey.h"
+#include "rowlists.h"
 #include "scan.h"
 
 namespace gnnhot {
 
-// Sixteen lanes per target row, four rows per wavefront (the paper's graphs have 15-50 neighbours
-// per vertex).  Loops run to the longest row of the wavefront so that ballots and shuffles stay
-// convergent; shorter rows are predicated off.
-constexpr int kSbLanes = 16;
-
-__device__ __forceinline__ uint32_t group_ballot(bool p, int sub) {
-    return (uint32_t)((__ballot(p) >> (sub * kSbLanes)) & 0xffffu);
-}
-
-constexpr int kSbShort = 4 * kSbLanes;   // rows up to this length stay with their sixteen lanes
-constexpr int kSbMedium = 16 * kWave;    // rows up to this length get a wavefront, longer ones a workgroup
-constexpr int kSbRowsPerWg = 256 / kSbLanes;   // rows one workgroup of the first launch takes per step
-constexpr int kSbListCap = 1024;         // entries of a workgroup's LDS list per class; what does not fit goes out one by one
-
-struct SbCtrl {
-    int32_t n_medium;
-    int32_t n_hub;
-    int32_t pad[6];
-};
-
-// A workgroup's lists of the rows it leaves to the wavefront-per-row and workgroup-per-row launches.
-struct SbLists {
-    int32_t med[kSbListCap], hub[kSbListCap];
-    int32_t n_med, n_hub, base_med, base_hub;
-};
-
-__device__ __forceinline__ void sb_lists_init(SbLists& L) {
-    if (threadIdx.x == 0) L.n_med = L.n_hub = 0;
-    __syncthreads();
-}
-
-// one lane per row calls this
-__device__ __forceinline__ void sb_lists_push(SbLists& L, int32_t i, int32_t len, int32_t* __restrict__ medq, int32_t* __restrict__ hubq,
-                                              SbCtrl* ctrl) {
-    if (len <= kSbMedium) {
-        const int pos = atomicAdd(&L.n_med, 1);
-        if (pos < kSbListCap) L.med[pos] = i;
-        else medq[atomicAdd(&ctrl->n_medium, 1)] = i;
-    } else {
-        const int pos = atomicAdd(&L.n_hub, 1);
-        if (pos < kSbListCap) L.hub[pos] = i;
-        else hubq[atomicAdd(&ctrl->n_hub, 1)] = i;
-    }
-}
-
-// every thread of the workgroup calls this once, after its last push
-__device__ __forceinline__ void sb_lists_flush(SbLists& L, int32_t* __restrict__ medq, int32_t* __restrict__ hubq, SbCtrl* ctrl) {
-    __syncthreads();
-    const int nm = L.n_med < kSbListCap ? L.n_med : kSbListCap, nh = L.n_hub < kSbListCap ? L.n_hub : kSbListCap;
-    if (threadIdx.x == 0) {
-        L.base_med = nm ? atomicAdd(&ctrl->n_medium, nm) : 0;
-        L.base_hub = nh ? atomicAdd(&ctrl->n_hub, nh) : 0;
-    }
-    __syncthreads();
-    for (int k = threadIdx.x; k < nm; k += blockDim.x) medq[L.base_med + k] = L.med[k];
-    for (int k = threadIdx.x; k < nh; k += blockDim.x) hubq[L.base_hub + k] = L.hub[k];
-}
-
+// Sixteen lanes per target row, four rows per wavefront (the paper's graphs have 15-50 neighbours per vertex): the
+// length classes and the queues are those of rowlists.h.
 __global__ __launch_bounds__(256) void sb_count_kernel(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
                                                        int32_t n, const uint32_t* __restrict__ tbits,
                                                        const int32_t* __restrict__ targets, int32_t n_targets, int32_t fanout,
                                                        int32_t* __restrict__ counts, int32_t* __restrict__ medq,
-                                                       int32_t* __restrict__ hubq, SbCtrl* ctrl) {
-    __shared__ SbLists lists;
-    sb_lists_init(lists);
-    const int lane = lane_id(), sub = lane / kSbLanes, sl = lane % kSbLanes;
-    const int grp = (int)threadIdx.x / kSbLanes;
-    for (int64_t c = blockIdx.x; c * kSbRowsPerWg < n_targets; c += gridDim.x) {   // uniform over the workgroup
-        const int64_t i = c * kSbRowsPerWg + grp;
+                                                       int32_t* __restrict__ hubq, RowCtrl* ctrl) {
+    __shared__ RowLists lists;
+    row_lists_init(lists);
+    const int lane = lane_id(), sub = lane / kRowLanes, sl = lane % kRowLanes;
+    const int grp = (int)threadIdx.x / kRowLanes;
+    for (int64_t c = blockIdx.x; c * kRowsPerWg < n_targets; c += gridDim.x) {   // uniform over the workgroup
+        const int64_t i = c * kRowsPerWg + grp;
         int32_t s = 0, e = 0;
         if (i < n_targets) {
             const int32_t v = targets[i];
@@ -100,28 +45,28 @@ __global__ __launch_bounds__(256) void sb_count_kernel(const int32_t* __restrict
                 e = row_ptr[v + 1];
             }
         }
-        const bool is_long = e - s > kSbShort;   // uniform over the 16-lane group
+        const bool is_long = e - s > kRowShort;   // uniform over the 16-lane group
         if (is_long) {
-            if (sl == 0) sb_lists_push(lists, (int32_t)i, e - s, medq, hubq, ctrl);
+            if (sl == 0) row_lists_push(lists, (int32_t)i, e - s, medq, hubq, ctrl);
             s = e = 0;
         }
         int32_t n_in = 0, n_ext = 0;
         int32_t ru[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {  // all four loads of a lane in flight together
-            const int32_t p = s + r * kSbLanes + sl;
+            const int32_t p = s + r * kRowLanes + sl;
             ru[r] = p < e ? col_idx[p] : 0;
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const bool valid = s + r * kSbLanes + sl < e;
+            const bool valid = s + r * kRowLanes + sl < e;
             const bool inner = valid && in_set(tbits, ru[r]);
             n_in += __popc(group_ballot(inner, sub));
             n_ext += __popc(group_ballot(valid && !inner, sub));
         }
         if (sl == 0 && i < n_targets && !is_long) counts[i] = n_in + (n_ext < fanout ? n_ext : fanout);
     }
-    sb_lists_flush(lists, medq, hubq, ctrl);
+    row_lists_flush(lists, medq, hubq, ctrl);
 }
 
 
@@ -130,13 +75,13 @@ __global__ __launch_bounds__(256) void sb_fill_kernel(const int32_t* __restrict_
                                                       const int32_t* __restrict__ targets, int32_t n_targets, int32_t fanout,
                                                       uint64_t seed_hop_mixed, const int32_t* __restrict__ out_row_ptr,
                                                       int32_t* __restrict__ out_col_idx, int64_t capacity,
-                                                      int32_t* __restrict__ medq, int32_t* __restrict__ hubq, SbCtrl* ctrl) {
-    __shared__ SbLists lists;
-    sb_lists_init(lists);
-    const int lane = lane_id(), sub = lane / kSbLanes, sl = lane % kSbLanes;
-    const int grp = (int)threadIdx.x / kSbLanes;
-    for (int64_t c = blockIdx.x; c * kSbRowsPerWg < n_targets; c += gridDim.x) {   // uniform over the workgroup
-    const int64_t i = c * kSbRowsPerWg + grp;
+                                                      int32_t* __restrict__ medq, int32_t* __restrict__ hubq, RowCtrl* ctrl) {
+    __shared__ RowLists lists;
+    row_lists_init(lists);
+    const int lane = lane_id(), sub = lane / kRowLanes, sl = lane % kRowLanes;
+    const int grp = (int)threadIdx.x / kRowLanes;
+    for (int64_t c = blockIdx.x; c * kRowsPerWg < n_targets; c += gridDim.x) {   // uniform over the workgroup
+    const int64_t i = c * kRowsPerWg + grp;
     int32_t v = 0, s = 0, e = 0;
     if (i < n_targets) {
         v = targets[i];
@@ -145,8 +90,8 @@ __global__ __launch_bounds__(256) void sb_fill_kernel(const int32_t* __restrict_
             e = row_ptr[v + 1];
         }
     }
-    if (e - s > kSbShort) {   // uniform over the 16-lane group: a wavefront or a workgroup of the later launches takes this row
-        if (sl == 0) sb_lists_push(lists, (int32_t)i, e - s, medq, hubq, ctrl);
+    if (e - s > kRowShort) {   // uniform over the 16-lane group: a wavefront or a workgroup of the later launches takes this row
+        if (sl == 0) row_lists_push(lists, (int32_t)i, e - s, medq, hubq, ctrl);
         s = e = 0;
     }
     // each lane holds up to four entries of its row in registers, so the selection rounds need no further memory traffic
@@ -156,12 +101,12 @@ __global__ __launch_bounds__(256) void sb_fill_kernel(const int32_t* __restrict_
     int32_t n_out = 0;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int32_t p = s + r * kSbLanes + sl;
+        const int32_t p = s + r * kRowLanes + sl;
         ru[r] = p < e ? col_idx[p] : 0;
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int32_t p = s + r * kSbLanes + sl;
+        const int32_t p = s + r * kRowLanes + sl;
         rf[r] = p < e ? (in_set(tbits, ru[r]) ? 1 : 2) : 0;
         rk[r] = rf[r] == 2 ? edge_key(seed_hop_mixed, (uint64_t)v, (uint64_t)ru[r]) : ~0ull;
         n_out += __popc(group_ballot(rf[r] == 2, sub));
@@ -188,7 +133,7 @@ __global__ __launch_bounds__(256) void sb_fill_kernel(const int32_t* __restrict_
                 }
             }
 #pragma unroll
-            for (int d = kSbLanes / 2; d >= 1; d >>= 1) {
+            for (int d = kRowLanes / 2; d >= 1; d >>= 1) {
                 const uint64_t ok = __shfl_xor(best_k, d, kWave);
                 const int32_t ou = __shfl_xor(best_u, d, kWave);
                 if (pair_less(ok, ou, best_k, best_u)) {
@@ -214,18 +159,18 @@ __global__ __launch_bounds__(256) void sb_fill_kernel(const int32_t* __restrict_
         at += __popc(m);
     }
     }   // grid-stride loop
-    sb_lists_flush(lists, medq, hubq, ctrl);
+    row_lists_flush(lists, medq, hubq, ctrl);
 }
 
 // ---- rows of 65 to 1024 entries: one wavefront per queued row, sixteen entries per lane, everything in registers --------
 template <bool FILL>
 __global__ __launch_bounds__(256) void sb_medium_rows_kernel(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
                                                              const uint32_t* __restrict__ tbits, const int32_t* __restrict__ targets,
-                                                             const int32_t* __restrict__ medq, const SbCtrl* __restrict__ ctrl,
+                                                             const int32_t* __restrict__ medq, const RowCtrl* __restrict__ ctrl,
                                                              int32_t fanout, uint64_t seed_hop_mixed, int32_t* __restrict__ counts,
                                                              const int32_t* __restrict__ out_row_ptr, int32_t* __restrict__ out_col_idx,
                                                              int64_t capacity) {
-    constexpr int EPL = kSbMedium / kWave;   // entries per lane
+    constexpr int EPL = kRowMedium / kWave;   // entries per lane
     const int lane = lane_id();
     const int64_t wave_g = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int64_t n_waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
@@ -358,7 +303,7 @@ __device__ __forceinline__ void block_min_pair(uint64_t& k, int32_t& u, uint64_t
 template <bool FILL>
 __global__ __launch_bounds__(256) void sb_long_rows_kernel(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
                                                            const uint32_t* __restrict__ tbits, const int32_t* __restrict__ targets,
-                                                           const int32_t* __restrict__ hubq, const SbCtrl* __restrict__ ctrl,
+                                                           const int32_t* __restrict__ hubq, const RowCtrl* __restrict__ ctrl,
                                                            int32_t fanout, uint64_t seed_hop_mixed, int32_t* __restrict__ counts,
                                                            const int32_t* __restrict__ out_row_ptr, int32_t* __restrict__ out_col_idx,
                                                            int64_t capacity) {
@@ -469,15 +414,15 @@ extern "C" int32_t gnn_sample_boundary(const gnn_csr* g, const uint32_t* target_
     int32_t* sums = carve.take<int32_t>((size_t)n_blocks + 1);
     int32_t* medq = carve.take<int32_t>((size_t)n_targets + 1);   // positions (in `targets`) of the rows of 65 to 1024 entries
     int32_t* hubq = carve.take<int32_t>((size_t)n_targets + 1);   // ... and of the longer ones
-    SbCtrl* ctrl = carve.take<SbCtrl>(1);
+    RowCtrl* ctrl = carve.take<RowCtrl>(1);
     bool query;
     GNN_CHECK(ws_protocol(ws, ws_bytes, carve.used, &query));
     if (query) return GNN_OK;
     GNN_REQUIRE(out_row_ptr != nullptr, GNN_ERR_INVALID_ARG, "out_row_ptr is NULL");
     GNN_REQUIRE(n_targets == 0 || (targets != nullptr && target_bitmap != nullptr), GNN_ERR_INVALID_ARG, "targets / bitmap is NULL");
-    const int wave_grid = grid_for((int64_t)n_targets * kSbLanes, 256, 4096);   // grid-stride: one queue append per workgroup
+    const int wave_grid = grid_for((int64_t)n_targets * kRowLanes, 256, 4096);   // grid-stride: one queue append per workgroup
     if (n_targets > 0) {   // both passes queue their long rows afresh (workspace contents do not survive a call)
-        fill_kernel<int32_t><<<1, 64, 0, stream>>>((int32_t*)ctrl, (int64_t)(sizeof(SbCtrl) / sizeof(int32_t)), 0);
+        fill_kernel<int32_t><<<1, 64, 0, stream>>>((int32_t*)ctrl, (int64_t)(sizeof(RowCtrl) / sizeof(int32_t)), 0);
         GNN_LAUNCH_CHECK("fill_kernel");
     }
     const int long_grid = 2048;   // grid-stride over the queues, whose lengths only the device knows

@@ -103,17 +103,51 @@ static __global__ __launch_bounds__(256) void scan_offsets_kernel(const int32_t*
     if (blockIdx.x == 0 && threadIdx.x == 0) offsets[n] = sums[n_blocks];
 }
 
-// Enqueues the three launches.  With n == 0: offsets[0] = 0 and *out_total = 0.
+// Short arrays: one block does it all (a launch costs as much as the scan of these).  Sixteen counts per thread and
+// sweep keep a sweep's latency at one trip to memory.
+constexpr int32_t kScanOneBlock = 32768;
+
+static __global__ __launch_bounds__(1024) void scan_one_block_kernel(const int32_t* __restrict__ counts, int32_t n,
+                                                                      int32_t* __restrict__ offsets, int64_t* __restrict__ out_total) {
+    __shared__ int s_part[16];
+    int base = 0;
+    for (int32_t lo = 0; lo < n; lo += 16 * 1024) {   // uniform over the block
+        const int32_t at = lo + (int32_t)threadIdx.x * 16;
+        int c[16], tot = 0;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            c[k] = at + k < n ? counts[at + k] : 0;
+            tot += c[k];
+        }
+        int total;
+        int run = base + block_exclusive_scan<1024>(tot, s_part, &total);
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            if (at + k < n) offsets[at + k] = run;
+            run += c[k];
+        }
+        base += total;
+    }
+    if (threadIdx.x == 0) {
+        offsets[n] = base;
+        *out_total = base;
+    }
+}
+
+// Enqueues the three launches (one for a short array).  With n == 0: offsets[0] = 0 and *out_total = 0.
 inline int32_t counts_to_offsets(const int32_t* counts, int32_t n, int32_t* sums, int32_t* offsets, int64_t* out_total,
                                  hipStream_t stream) {
     const int32_t n_blocks = offsets_scan_blocks(n);
-    if (n > 0) {
-        scan_block_sums_kernel<<<n_blocks, 256, 0, stream>>>(counts, n, sums);
-        GNN_LAUNCH_CHECK("scan_block_sums_kernel");
+    if (n <= kScanOneBlock) {
+        scan_one_block_kernel<<<1, 1024, 0, stream>>>(counts, n, offsets, out_total);
+        GNN_LAUNCH_CHECK("scan_one_block_kernel");
+        return GNN_OK;
     }
-    scan_sums_kernel<<<1, 1024, 0, stream>>>(sums, n > 0 ? n_blocks : 0, out_total);
+    scan_block_sums_kernel<<<n_blocks, 256, 0, stream>>>(counts, n, sums);
+    GNN_LAUNCH_CHECK("scan_block_sums_kernel");
+    scan_sums_kernel<<<1, 1024, 0, stream>>>(sums, n_blocks, out_total);
     GNN_LAUNCH_CHECK("scan_sums_kernel");
-    scan_offsets_kernel<<<n_blocks, 256, 0, stream>>>(counts, n, sums, n > 0 ? n_blocks : 0, offsets);
+    scan_offsets_kernel<<<n_blocks, 256, 0, stream>>>(counts, n, sums, n_blocks, offsets);
     GNN_LAUNCH_CHECK("scan_offsets_kernel");
     return GNN_OK;
 }

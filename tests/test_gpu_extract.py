@@ -197,3 +197,65 @@ def test_training_step_after_sampling_and_extraction():
     for l, gr in enumerate(grads_o):
         for k, want in gr.items():
             check(m.grads[l][k].double().cpu().numpy(), want, dtype, f"layer {l + 1} {k}", calls=L - l)
+
+
+# ---- row-length classes ---------------------------------------------------------------------------------------
+
+@pytest.mark.parametrize("L", [1, 4, 30])
+def test_rows_at_the_edges_of_the_length_classes(L):
+    """Rows of 64 / 65 (sixteen lanes / wavefront), 1024 / 1025 (wavefront / workgroup) and 2048 / 2049 entries (one step /
+    two of the workgroup), each with neighbours at several distances."""
+    n, lengths = 9000, [1, 16, 63, 64, 65, 1023, 1024, 1025, 2047, 2048, 2049, 6500]
+    rng = np.random.default_rng(L)
+    base = gg.random_directed(n, 1.2, 90 + L)
+    r = np.repeat(np.arange(n, dtype=np.int64), np.diff(base.row_ptr))
+    keep = r >= 200                                      # the first rows get the lengths in question
+    rows, cols = [r[keep]], [base.col_idx[keep].astype(np.int64)]
+    for k, ln in enumerate(lengths):
+        rows.append(np.full(ln, 10 * k, dtype=np.int64))
+        cols.append(np.sort(rng.choice(n, ln, replace=False)).astype(np.int64))
+    g = gg.csr_from_edges(n, n, np.concatenate(rows), np.concatenate(cols))
+    assert [int(g.degrees()[10 * k]) for k in range(len(lengths))] == lengths
+    some = np.sort(rng.choice(np.arange(200, n), 5, replace=False))
+    _extract_case(g, np.concatenate([[0, 40, 80], some]), L, "length classes, some of them targets")
+    _extract_case(g, 10 * np.arange(len(lengths)), L, "length classes, all targets")
+
+
+def test_reverse_rows_at_the_edges_of_the_length_classes_and_cut_by_the_capacity():
+    """Outside vertices that 1, 2, 64, 65, 1024, 1025 and 3000 targets kept, and outputs with less room than entries: what
+    fits is written in order, nothing beyond it."""
+    import ctypes as C
+    import paper_2311_06837_amd as P
+    from paper_2311_06837_amd import binding as B
+    n, nt, lengths = 8000, 4000, [1, 2, 15, 16, 17, 64, 65, 1024, 1025, 3000]
+    rng = np.random.default_rng(91)
+    a, b = [], []
+    for k, ln in enumerate(lengths):                     # outside vertex nt + 7 k next to ln targets
+        t = rng.choice(nt, ln, replace=False)
+        a.append(t), b.append(np.full(ln, nt + 7 * k))
+    inner = rng.integers(0, nt, size=(2, 6000))
+    a, b = np.concatenate(a + [inner[0][inner[0] != inner[1]]]), np.concatenate(b + [inner[1][inner[0] != inner[1]]])
+    g = gg.csr_from_edges(n, n, np.concatenate([a, b]).astype(np.int64), np.concatenate([b, a]).astype(np.int64))
+    T = np.arange(nt)
+    local, l2g_d, (rp, ci, l2g, off, dl) = _sampled_case(g, T, 100, 3, "reverse lengths")
+    assert sorted(np.diff(rp)[nt:].tolist()) == lengths
+    # the same fill pass into smaller outputs
+    G = P.Graph.from_numpy(g.row_ptr, g.col_idx)
+    Td = dev(T.astype(np.int32))
+    srp, sci = P.gnn_sample_boundary(G, P.gnn_make_bitmap(Td, n), Td, 100, 3)
+    gs = B.Graph(P.gnn_expand_row_ptr(n, Td, srp), sci.contiguous(), n_cols=n, sorted_columns=True)
+    dist, ring, _, hop = P.gnn_build_active_sets(gs, Td, 1)
+    n_local, nnz = int(hop[-1]), ci.size
+    new_id = torch.empty(n, dtype=torch.int32, device="cuda")
+    out_rp = torch.empty(n_local + 1, dtype=torch.int32, device="cuda")
+    nnz_dev = torch.empty(1, dtype=torch.int64, device="cuda")
+    common = (C.byref(G.c), C.byref(gs.c), B._ptr(ring), C.c_int32(n_local), B._ptr(dist), B._ptr(new_id), B._ptr(out_rp))
+    B._with_ws(B.lib().gnn_extract_sampled_partition, common + (None, C.c_int64(0), B._ptr(nnz_dev), None), (B._stream(),), None)
+    starts = [int(rp[j]) for j in range(nt, n_local)]
+    for cap in sorted({0, 1, int(rp[nt]) - 1, nnz - 1, nnz} | {s + d for s in starts for d in (1, 40)}):
+        if cap > nnz:
+            continue
+        out = torch.full((nnz,), -7, dtype=torch.int32, device="cuda")
+        B._with_ws(B.lib().gnn_extract_sampled_partition, common + (B._ptr(out), C.c_int64(cap), B._ptr(nnz_dev), None), (B._stream(),), None)
+        got = out.cpu().numpy()
+        assert np.array_equal(got[:cap], ci[:cap]) and (got[cap:] == -7).all(), cap
