@@ -2,9 +2,9 @@
 // (paper section 6, figure 7c: step 1 extracts the multi-hop dependency from the inner
 // vertices, step 4 generates the per-layer mask).
 //
-// Data layout.  In the workspace: two bitmaps of n bits, `visited` (everything reached by the
-// levels before the one being expanded, read-only while it expands) and `frontier` (the ring
-// the last level found), and `seen`, ONE BYTE per vertex (`visited` plus what the level has
+// Data layout.  In the workspace: bitmaps of n bits, `visited` (everything reached by the
+// levels before the one being expanded, read-only while it expands; two copies that the levels
+// use in turn) and `frontier` (the ring the last level found), and `seen`, ONE BYTE per vertex (`visited` plus what the level has
 // found so far).  `seen` is bytes because every lane that finds a vertex marks it: a byte takes
 // a plain store of 1 - whoever comes first, the byte ends up the same - where a bit needs an
 // atomic OR, and a ring of a few million new vertices packs those atomics onto a few thousand
@@ -12,11 +12,18 @@
 // The byte accesses are ordinary loads and stores on purpose: a stale 0 from the vector cache
 // only means one more store of the same 1 (relaxed atomic loads, which bypass that cache, were
 // measured 15 to 50 % slower per construction); kernel boundaries order the levels.
-// A level is: expand -> count / scan / emit, a compaction of seen & ~visited that lists the
+// A level is: expand -> count / emit, a compaction of seen & ~visited that lists the
 // new ring in ascending id order without any sort, so the output does not depend on which
-// wave found a vertex first; emit then brings visited up to seen.  Ring sizes stay on
+// wave found a vertex first; emit also writes the next visited.  Ring sizes stay on
 // the device (hop_offsets); every kernel has a fixed grid and reads its bounds from there, so
 // the whole construction is enqueued without a host round trip.
+// With few vertices or many rings a construction is as long as its launches (about 5 us each,
+// the gap included), so a level is four of them: expansion in whichever direction, its long
+// rows, count, emit (which adds up the counts before its own and, for the direction switch, the
+// row lengths of the ring it writes) - three where emit counts for itself (kAsSelfCount).  With a
+// launch per direction, per scan and per plan it was eight: eight rings of a 1M-vertex graph
+// 342 -> 269 us, two of a 10 000-vertex graph 119 -> 95 us, three of a 5M-vertex graph 688 -> 650 us
+// (with the call's own host work and its copy of the ring sizes).
 //
 // A level expands in one of two directions; the sets are the same either way.
 //   push  (from the frontier)  EDGE-parallel: a wavefront takes up to 64 frontier vertices, reads
@@ -30,10 +37,9 @@
 //         reach it - and stop at the first one that is in `frontier`.  Once the frontier is
 //         most of the graph, nearly every edge of a push level points at a vertex that is
 //         already in the set; the pull level only touches the few vertices still outside.
-// The direction is chosen on the device, per level, from exact integer sums (as_plan_kernel):
+// The direction is chosen on the device, per level, from exact integer sums (made by emit):
 // pull when the frontier's edges outnumber what a pull can touch at most, the transposed
-// rows of the unreached vertices plus sixteen lanes for each of them.  Both kernels of a level
-// are enqueued; the one whose turn it is not returns at once.
+// rows of the unreached vertices plus sixteen lanes for each of them.
 //
 // Bound: a push level reads each edge of the frontier once (4 B, streaming) and makes one
 // 1-byte probe per edge into n bytes that stay in L2: the probes, not the bytes, are what
@@ -47,21 +53,30 @@ namespace gnnhot {
 constexpr int kAsWordsPerBlock = 256;   // one bitmap word per thread: 8192 vertices per block
 constexpr int kAsHubDegree = 2048;      // longer rows are queued and expanded by a whole workgroup each
 
-struct AsCtrl {
-    int32_t n_hubs;
+// A graph of up to this many blocks: emit counts the blocks before its own itself instead of reading what a count launch
+// left (a block reads 9 KB per block before it: cheaper than the launch up to about 16).
+constexpr int64_t kAsSelfCount = 16;
+
+struct AsLevel {
+    unsigned long long frontier_edges;   // entries of the ring's rows
+    int32_t n_hubs;                      // rows queued while the ring is expanded
     int32_t pad;
-    unsigned long long frontier_edges;   // entries of the frontier's rows (graph), this level
-    unsigned long long reached_edges_t;  // entries of the transposed rows of everything reached so far
-    unsigned long long pad2;
 };
 
-// True when this level runs in the pull direction.  frontier = ring `ring_prev`.  A pull touches at most the transposed
-// rows of the unreached vertices, sixteen lanes at a time.
-__device__ __forceinline__ bool as_pull_level(const AsCtrl* ctrl, const int64_t* __restrict__ hop_offsets, int32_t ring_prev,
-                                              int64_t n, int64_t nnz_t) {
-    const int64_t unreached = n - hop_offsets[ring_prev + 1];
+struct AsCtrl {
+    unsigned long long reached_edges_t;  // entries of the transposed rows of everything reached so far
+    unsigned long long pad;
+    AsLevel level[1];                    // one per ring (L + 1 of them)
+};
+
+inline size_t as_ctrl_words(int32_t L) { return (sizeof(AsCtrl) + (size_t)(L + 1) * sizeof(AsLevel)) / sizeof(int64_t); }
+
+// True when ring `ring` is expanded in the pull direction.  A pull touches at most the transposed rows of the unreached
+// vertices, sixteen lanes at a time.
+__device__ __forceinline__ bool as_pull_level(const AsCtrl* ctrl, const int64_t* __restrict__ hop_offsets, int32_t ring, int64_t n, int64_t nnz_t) {
+    const int64_t unreached = n - hop_offsets[ring + 1];
     const int64_t unreached_edges = nnz_t - (int64_t)ctrl->reached_edges_t;
-    return (int64_t)ctrl->frontier_edges > unreached_edges + 16 * unreached;
+    return (int64_t)ctrl->level[ring].frontier_edges > unreached_edges + 16 * unreached;
 }
 
 // Bit b of the result = byte b of the 32 bytes at p (each 0 or 1); p is 32-byte aligned.
@@ -76,7 +91,7 @@ __device__ __forceinline__ uint32_t as_mask_of_bytes(const uint8_t* __restrict__
 }
 
 __global__ __launch_bounds__(256) void as_init_kernel(int32_t* __restrict__ dist, int32_t n, uint32_t* __restrict__ visited,
-                                                      uint8_t* __restrict__ seen, int64_t nw, AsCtrl* ctrl,
+                                                      uint8_t* __restrict__ seen, int64_t nw, int64_t* __restrict__ ctrl, int32_t ctrl_words,
                                                       int64_t* __restrict__ hop_offsets, int32_t L) {
     const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -86,12 +101,8 @@ __global__ __launch_bounds__(256) void as_init_kernel(int32_t* __restrict__ dist
         ((uint4*)seen)[2 * w] = make_uint4(0u, 0u, 0u, 0u);   // 32 bytes per bitmap word, the tail of the last word included
         ((uint4*)seen)[2 * w + 1] = make_uint4(0u, 0u, 0u, 0u);
     }
-    if (tid == 0) {
-        ctrl->n_hubs = 0;
-        ctrl->frontier_edges = 0ull;
-        ctrl->reached_edges_t = 0ull;
-    }
-    if (tid <= L + 1) hop_offsets[tid] = 0;
+    for (int64_t i = tid; i < ctrl_words; i += stride) ctrl[i] = 0;
+    for (int64_t i = tid; i <= L + 1; i += stride) hop_offsets[i] = 0;
 }
 
 __global__ __launch_bounds__(256) void as_seed_kernel(const int32_t* __restrict__ targets, int32_t n_targets, int32_t n,
@@ -102,6 +113,7 @@ __global__ __launch_bounds__(256) void as_seed_kernel(const int32_t* __restrict_
     }
 }
 
+constexpr unsigned kAsPushBlocks = 2048;   // workgroups of a push level: what the chip holds at once
 constexpr int kAsU = 8;   // edges per lane and step: their index loads, then their probes, are issued together
 
 // Push level.  One wavefront per batch of up to 64 entries of the frontier list (grid-stride), edge-parallel inside
@@ -110,21 +122,18 @@ constexpr int kAsU = 8;   // edges per lane and step: their index loads, then th
 // while every batch still finds a wavefront of its own (a power of two, at least 1) - 29 000 frontier vertices of
 // 490 entries each are 122 steps per wavefront in batches of 64 and 4 in batches of 4 (measured on the 8-level
 // workload, 62 500 frontier vertices of 27 entries: 0.28 -> 0.08 ms for the level).
-// nnz_t < 0: no transposed graph was given, every level is a push level.
-__global__ __launch_bounds__(256) void as_expand_kernel(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
-                                                        const int32_t* __restrict__ ring_ids,
-                                                        const int64_t* __restrict__ hop_offsets, int32_t ring,
-                                                        uint8_t* __restrict__ seen, int32_t* __restrict__ hubq, AsCtrl* ctrl,
-                                                        int32_t n, int64_t nnz_t) {
+__device__ __forceinline__ void as_push(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
+                                        const int32_t* __restrict__ ring_ids, const int64_t* __restrict__ hop_offsets, int32_t ring,
+                                        uint8_t* __restrict__ seen, int32_t* __restrict__ hubq, AsCtrl* ctrl) {
     __shared__ int32_t s_start[4][kWave];
     __shared__ int32_t s_excl[4][kWave + 1];
-    if (nnz_t >= 0 && as_pull_level(ctrl, hop_offsets, ring, n, nnz_t)) return;   // uniform over the grid
     const int64_t begin = hop_offsets[ring], end = hop_offsets[ring + 1];
     const int lane = lane_id(), wave = (int)(threadIdx.x >> 6);
     int32_t* st = s_start[wave];
     int32_t* ex = s_excl[wave];
     const int64_t wave_g = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int64_t n_waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+    const int64_t n_waves = ((int64_t)(gridDim.x < kAsPushBlocks ? gridDim.x : kAsPushBlocks) * blockDim.x) >> 6;
+    if (wave_g >= n_waves) return;   // (a pull may use a larger grid)
     int batch = kWave;
     while (batch > 1 && (int64_t)(batch >> 1) * n_waves >= end - begin) batch >>= 1;
     for (int64_t b = begin + wave_g * batch; b < end; b += n_waves * batch) {   // uniform over the wavefront
@@ -135,7 +144,7 @@ __global__ __launch_bounds__(256) void as_expand_kernel(const int32_t* __restric
             s = row_ptr[v];
             len = row_ptr[v + 1] - s;
             if (len > kAsHubDegree) {   // a whole workgroup of the next launch takes this row
-                hubq[atomicAdd(&ctrl->n_hubs, 1)] = v;
+                hubq[atomicAdd(&ctrl->level[ring].n_hubs, 1)] = v;
                 len = 0;
             }
         }
@@ -175,13 +184,9 @@ __global__ __launch_bounds__(256) void as_expand_kernel(const int32_t* __restric
 }
 
 // Hub rows of a push level: the queued rows are cut into as many equal pieces as the grid has workgroups per row, a
-// workgroup per piece (grid-stride), threads across the piece, kAsU entries per thread and step.  (In a pull level the
-// queue is empty when this kernel runs.)
-__global__ __launch_bounds__(256) void as_expand_hubs_kernel(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
-                                                             uint8_t* __restrict__ seen, const int32_t* __restrict__ hubq,
-                                                             const AsCtrl* ctrl) {
-    const int32_t n_hubs = ctrl->n_hubs;
-    if (n_hubs <= 0) return;
+// workgroup per piece (grid-stride), threads across the piece, kAsU entries per thread and step.
+__device__ __forceinline__ void as_push_hubs(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
+                                             uint8_t* __restrict__ seen, const int32_t* __restrict__ hubq, int32_t n_hubs) {
     const int32_t parts = (int32_t)gridDim.x / n_hubs > 1 ? (int32_t)gridDim.x / n_hubs : 1;
     for (int64_t job = blockIdx.x; job < (int64_t)n_hubs * parts; job += gridDim.x) {   // uniform over the workgroup
         const int32_t v = hubq[job / parts];
@@ -202,47 +207,12 @@ __global__ __launch_bounds__(256) void as_expand_hubs_kernel(const int32_t* __re
     }
 }
 
-// Exact sums the direction switch needs, over the ring the next level expands: entries of its rows (what a push
-// reads) and entries of its transposed rows (added to the running total of everything reached).  Integer atomics:
-// the totals do not depend on the order of the additions.
-__global__ __launch_bounds__(256) void as_plan_kernel(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ row_ptr_t,
-                                                      const int32_t* __restrict__ ring_ids, const int64_t* __restrict__ hop_offsets,
-                                                      int32_t ring, AsCtrl* ctrl) {
-    __shared__ unsigned long long s_a[4], s_b[4];
-    const int64_t begin = hop_offsets[ring], end = hop_offsets[ring + 1];
-    unsigned long long a = 0ull, b = 0ull;
-    for (int64_t i = begin + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < end; i += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t v = ring_ids[i];
-        a += (unsigned long long)(row_ptr[v + 1] - row_ptr[v]);
-        b += (unsigned long long)(row_ptr_t[v + 1] - row_ptr_t[v]);
-    }
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        a += __shfl_xor(a, d, kWave);
-        b += __shfl_xor(b, d, kWave);
-    }
-    if (lane_id() == 0) {
-        s_a[threadIdx.x >> 6] = a;
-        s_b[threadIdx.x >> 6] = b;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        a = s_a[0] + s_a[1] + s_a[2] + s_a[3];
-        b = s_b[0] + s_b[1] + s_b[2] + s_b[3];
-        if (a) atomicAdd(&ctrl->frontier_edges, a);
-        if (b) atomicAdd(&ctrl->reached_edges_t, b);
-    }
-}
-
 // Pull level.  A wavefront per bitmap word (grid-stride), sixteen lanes per vertex: for each vertex of the word that is
 // not in the set yet, scan its transposed row 64 entries at a time and stop at the first entry that is in the frontier.  A lane group
 // is the only writer of its vertices' bytes in this kernel.  Rows longer than kAsHubDegree go to the queue.
-__global__ __launch_bounds__(256) void as_pull_kernel(const int32_t* __restrict__ row_ptr_t, const int32_t* __restrict__ col_idx_t,
-                                                      int32_t n, int64_t nw, const uint32_t* __restrict__ visited,
-                                                      uint8_t* __restrict__ seen, const uint32_t* __restrict__ frontier,
-                                                      const int64_t* __restrict__ hop_offsets, int32_t ring, int64_t nnz_t,
-                                                      int32_t* __restrict__ hubq, AsCtrl* ctrl) {
-    if (!as_pull_level(ctrl, hop_offsets, ring, n, nnz_t)) return;   // uniform over the grid
+__device__ __forceinline__ void as_pull(const int32_t* __restrict__ row_ptr_t, const int32_t* __restrict__ col_idx_t, int32_t n, int64_t nw,
+                                        const uint32_t* __restrict__ visited, uint8_t* __restrict__ seen,
+                                        const uint32_t* __restrict__ frontier, int32_t ring, int32_t* __restrict__ hubq, AsCtrl* ctrl) {
     const int lane = lane_id(), sub = lane / 16, sl = lane % 16;
     const int64_t waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
     for (int64_t w = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; w < nw; w += waves) {   // uniform over the wave
@@ -262,7 +232,7 @@ __global__ __launch_bounds__(256) void as_pull_kernel(const int32_t* __restrict_
             const int32_t v = (int32_t)(w * 32 + b);
             const int32_t s = row_ptr_t[v], e = row_ptr_t[v + 1];
             if (e - s > kAsHubDegree) {
-                if (sl == 0) hubq[atomicAdd(&ctrl->n_hubs, 1)] = v;
+                if (sl == 0) hubq[atomicAdd(&ctrl->level[ring].n_hubs, 1)] = v;
                 continue;
             }
             bool found = false;
@@ -281,12 +251,9 @@ __global__ __launch_bounds__(256) void as_pull_kernel(const int32_t* __restrict_
 }
 
 // Long rows of a pull level: one workgroup per queued vertex, 256 entries per step, until one is in the frontier.
-__global__ __launch_bounds__(256) void as_pull_hubs_kernel(const int32_t* __restrict__ row_ptr_t, const int32_t* __restrict__ col_idx_t,
-                                                           uint8_t* __restrict__ seen, const uint32_t* __restrict__ frontier,
-                                                           const int64_t* __restrict__ hop_offsets, int32_t ring, int32_t n,
-                                                           int64_t nnz_t, const int32_t* __restrict__ hubq, const AsCtrl* ctrl) {
-    if (!as_pull_level(ctrl, hop_offsets, ring, n, nnz_t)) return;
-    const int32_t n_hubs = ctrl->n_hubs;
+__device__ __forceinline__ void as_pull_hubs(const int32_t* __restrict__ row_ptr_t, const int32_t* __restrict__ col_idx_t,
+                                             uint8_t* __restrict__ seen, const uint32_t* __restrict__ frontier,
+                                             const int32_t* __restrict__ hubq, int32_t n_hubs) {
     for (int32_t h = blockIdx.x; h < n_hubs; h += gridDim.x) {   // uniform over the workgroup
         const int32_t v = hubq[h];
         const int32_t s = row_ptr_t[v], e = row_ptr_t[v + 1];
@@ -301,6 +268,38 @@ __global__ __launch_bounds__(256) void as_pull_hubs_kernel(const int32_t* __rest
     }
 }
 
+struct AsArgs {
+    const int32_t *row_ptr, *col_idx;       // the graph
+    const int32_t *row_ptr_t, *col_idx_t;   // its transpose, or NULL: every level pushes
+    int32_t n;
+    int64_t nw, nnz_t;
+    const int32_t* ring_ids;
+    const int64_t* hop_offsets;
+    const uint32_t* visited;
+    uint8_t* seen;
+    const uint32_t* frontier;
+    int32_t* hubq;
+    AsCtrl* ctrl;
+};
+
+// Expansion of ring `ring`, in the direction that costs less.
+__global__ __launch_bounds__(256) void as_expand_kernel(AsArgs a, int32_t ring) {
+    if (a.row_ptr_t != nullptr && as_pull_level(a.ctrl, a.hop_offsets, ring, a.n, a.nnz_t))   // uniform over the grid
+        as_pull(a.row_ptr_t, a.col_idx_t, a.n, a.nw, a.visited, a.seen, a.frontier, ring, a.hubq, a.ctrl);
+    else
+        as_push(a.row_ptr, a.col_idx, a.ring_ids, a.hop_offsets, ring, a.seen, a.hubq, a.ctrl);
+}
+
+// The rows that the expansion queued.
+__global__ __launch_bounds__(256) void as_expand_hubs_kernel(AsArgs a, int32_t ring) {
+    const int32_t n_hubs = a.ctrl->level[ring].n_hubs;
+    if (n_hubs <= 0) return;
+    if (a.row_ptr_t != nullptr && as_pull_level(a.ctrl, a.hop_offsets, ring, a.n, a.nnz_t))
+        as_pull_hubs(a.row_ptr_t, a.col_idx_t, a.seen, a.frontier, a.hubq, n_hubs);
+    else
+        as_push_hubs(a.row_ptr, a.col_idx, a.seen, a.hubq, n_hubs);
+}
+
 __global__ __launch_bounds__(kAsWordsPerBlock) void as_count_kernel(const uint8_t* __restrict__ seen,
                                                                     const uint32_t* __restrict__ visited, int64_t nw,
                                                                     int32_t* __restrict__ blk_cnt) {
@@ -313,40 +312,100 @@ __global__ __launch_bounds__(kAsWordsPerBlock) void as_count_kernel(const uint8_
     if (threadIdx.x == 0) blk_cnt[blockIdx.x] = total;
 }
 
-__global__ __launch_bounds__(1024) void as_scan_kernel(int32_t* __restrict__ blk_cnt, int64_t n_blocks,
-                                                       int64_t* __restrict__ hop_offsets, int32_t ring, AsCtrl* ctrl) {
-    __shared__ int s_part[1024 / kWave];
-    const int64_t total = single_block_exclusive_scan(blk_cnt, n_blocks, s_part);
-    if (threadIdx.x == 0) {
-        hop_offsets[ring + 1] = hop_offsets[ring] + total;
-        ctrl->n_hubs = 0;
-        ctrl->frontier_edges = 0ull;
-    }
+// Sum over the workgroup; every thread gets it.  Two barriers.
+__device__ __forceinline__ unsigned long long as_block_sum(unsigned long long x, unsigned long long* s_sum) {
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d, kWave);
+    if (lane_id() == 0) s_sum[threadIdx.x >> 6] = x;
+    __syncthreads();
+    x = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
+    __syncthreads();
+    return x;
 }
 
-__global__ __launch_bounds__(kAsWordsPerBlock) void as_emit_kernel(const uint8_t* __restrict__ seen, uint32_t* __restrict__ visited,
-                                                                   int64_t nw, const int32_t* __restrict__ blk_cnt,
-                                                                   const int64_t* __restrict__ hop_offsets, int32_t ring,
-                                                                   int32_t* __restrict__ ring_ids, int32_t* __restrict__ dist,
-                                                                   uint32_t* __restrict__ frontier) {
+// Lists ring `ring` (seen & ~visited) in ascending id order behind the rings before it and writes the next `visited`.
+// Every block adds up the counts of the blocks before it (blk_cnt NULL: counts them); the last one knows the ring's end.
+// With row_ptr_t (a later pull is possible): the ring as a bitmap, and the exact sums the direction switch needs, the
+// entries of the ring's rows and of its transposed rows (integer atomics: the totals do not depend on their order).
+__global__ __launch_bounds__(kAsWordsPerBlock) void as_emit_kernel(const uint8_t* __restrict__ seen, const uint32_t* __restrict__ visited,
+                                                                   uint32_t* __restrict__ visited_next, int64_t nw,
+                                                                   const int32_t* __restrict__ blk_cnt, int64_t* __restrict__ hop_offsets,
+                                                                   int32_t ring, int32_t* __restrict__ ring_ids, int32_t* __restrict__ dist,
+                                                                   uint32_t* __restrict__ frontier, const int32_t* __restrict__ row_ptr,
+                                                                   const int32_t* __restrict__ row_ptr_t, AsCtrl* ctrl) {
+    static_assert(kAsWordsPerBlock == 256, "as_block_sum adds four wavefronts");
     __shared__ int s_part[kAsWordsPerBlock / kWave];
+    __shared__ unsigned long long s_sum[kAsWordsPerBlock / kWave];
+    __shared__ uint32_t s_fresh[kAsWordsPerBlock];
+    __shared__ int s_before[kAsWordsPerBlock];
+    unsigned long long base = 0ull;
+    if (blk_cnt != nullptr) {
+        for (int64_t b = threadIdx.x; b < blockIdx.x; b += kAsWordsPerBlock) base += (unsigned long long)blk_cnt[b];
+    } else {
+        for (int64_t w = threadIdx.x; w < (int64_t)blockIdx.x * kAsWordsPerBlock; w += kAsWordsPerBlock)
+            base += (unsigned long long)__popc(as_mask_of_bytes(seen + 32 * w) & ~visited[w]);
+    }
+    base = as_block_sum(base, s_sum);
     const int64_t w = (int64_t)blockIdx.x * kAsWordsPerBlock + threadIdx.x;
     uint32_t fresh = 0u;
     if (w < nw) {
         const uint32_t sn = as_mask_of_bytes(seen + 32 * w), vis = visited[w];
         fresh = sn & ~vis;
-        if (fresh) visited[w] = vis | sn;
-        if (frontier != nullptr) frontier[w] = fresh;   // the ring a pull level looks for
+        visited_next[w] = vis | sn;
+        if (row_ptr_t != nullptr) frontier[w] = fresh;   // the ring a pull level looks for
     }
     int total;
     const int before = block_exclusive_scan<kAsWordsPerBlock>(__popc(fresh), s_part, &total);
-    int64_t pos = hop_offsets[ring] + blk_cnt[blockIdx.x] + before;
-    while (fresh) {
-        const int b = __ffs(fresh) - 1;
-        fresh &= fresh - 1;
-        const int32_t v = (int32_t)(w * 32 + b);
-        ring_ids[pos++] = v;
-        dist[v] = ring;
+    const int64_t begin = hop_offsets[ring] + (int64_t)base;
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) hop_offsets[ring + 1] = begin + total;
+    if (total == 0) return;   // uniform over the workgroup
+    // a lane per vertex, not per word (32 vertices after each other, each with its loads, took 17 us whatever the size),
+    // eight vertices at a time with all their loads in flight (a lane without a vertex of the ring reads the first row)
+    s_fresh[threadIdx.x] = fresh;
+    s_before[threadIdx.x] = before;
+    __syncthreads();
+    unsigned long long edges = 0ull, edges_t = 0ull;
+    const int bit = (int)(threadIdx.x & 31);
+    const uint32_t below = (1u << bit) - 1u;
+    constexpr int kBatch = 8;
+    for (int r0 = 0; r0 < 32; r0 += kBatch) {
+        bool in[kBatch];
+        int32_t v[kBatch], lo[kBatch], hi[kBatch], lo_t[kBatch], hi_t[kBatch];
+        bool any = false;
+#pragma unroll
+        for (int r = 0; r < kBatch; ++r) {
+            const int k = (r0 + r) * (kAsWordsPerBlock / 32) + (int)(threadIdx.x >> 5);
+            const uint32_t word = s_fresh[k];
+            in[r] = (word >> bit) & 1u;
+            any |= in[r];
+            v[r] = (int32_t)(((int64_t)blockIdx.x * kAsWordsPerBlock + k) * 32 + bit);
+            if (in[r]) {
+                ring_ids[begin + s_before[k] + __popc(word & below)] = v[r];
+                dist[v[r]] = ring;
+            }
+        }
+        if (row_ptr_t == nullptr || __ballot(any) == 0ull) continue;   // uniform over the wavefront
+#pragma unroll
+        for (int r = 0; r < kBatch; ++r) {
+            const int32_t u = in[r] ? v[r] : 0;
+            lo[r] = row_ptr[u];
+            hi[r] = row_ptr[u + 1];
+            lo_t[r] = row_ptr_t[u];
+            hi_t[r] = row_ptr_t[u + 1];
+        }
+#pragma unroll
+        for (int r = 0; r < kBatch; ++r) {
+            edges += in[r] ? (unsigned long long)(hi[r] - lo[r]) : 0ull;
+            edges_t += in[r] ? (unsigned long long)(hi_t[r] - lo_t[r]) : 0ull;
+        }
+    }
+    if (row_ptr_t != nullptr) {   // uniform over the grid
+        edges = as_block_sum(edges, s_sum);
+        edges_t = as_block_sum(edges_t, s_sum);
+        if (threadIdx.x == 0) {
+            atomicAdd(&ctrl->level[ring].frontier_edges, edges);
+            atomicAdd(&ctrl->reached_edges_t, edges_t);
+        }
     }
 }
 
@@ -560,6 +619,20 @@ __global__ __launch_bounds__(256) void eas_expand_long_kernel(const int32_t* __r
     }
 }
 
+// count (unless the blocks are few) and emit
+static int32_t as_emit(const uint8_t* seen, const uint32_t* visited, uint32_t* visited_next, int64_t nw, int64_t nb, int32_t* blk_cnt,
+                       int64_t* hop_offsets, int32_t ring, int32_t* ring_ids, int32_t* dist, uint32_t* frontier, const int32_t* row_ptr,
+                       const int32_t* row_ptr_t, AsCtrl* ctrl, hipStream_t stream) {
+    if (nb > kAsSelfCount) {
+        as_count_kernel<<<(int)nb, kAsWordsPerBlock, 0, stream>>>(seen, visited, nw, blk_cnt);
+        GNN_LAUNCH_CHECK("as_count_kernel");
+    }
+    as_emit_kernel<<<(int)nb, kAsWordsPerBlock, 0, stream>>>(seen, visited, visited_next, nw, nb > kAsSelfCount ? blk_cnt : nullptr,
+                                                             hop_offsets, ring, ring_ids, dist, frontier, row_ptr, row_ptr_t, ctrl);
+    GNN_LAUNCH_CHECK("as_emit_kernel");
+    return GNN_OK;
+}
+
 }  // namespace gnnhot
 
 using namespace gnnhot;
@@ -583,12 +656,14 @@ extern "C" int32_t gnn_build_active_sets(const gnn_csr* g, const gnn_csr* gt, co
     const int64_t nb = nw > 0 ? (nw + kAsWordsPerBlock - 1) / kAsWordsPerBlock : 1;
 
     WsCarver carve(ws);
-    uint32_t* visited = carve.take<uint32_t>((size_t)nw + 1);
+    uint32_t* visited[2];
+    for (int k = 0; k < 2; ++k) visited[k] = carve.take<uint32_t>((size_t)nw + 1);
     uint8_t* seen = carve.take<uint8_t>((size_t)nw * 32 + 32);
     uint32_t* frontier = carve.take<uint32_t>((size_t)nw + 1);
     int32_t* blk_cnt = carve.take<int32_t>((size_t)nb + 1);
     int32_t* hubq = carve.take<int32_t>((size_t)n + 1);
-    AsCtrl* ctrl = carve.take<AsCtrl>(1);
+    const size_t ctrl_words = as_ctrl_words(L);
+    int64_t* ctrl = carve.take<int64_t>(ctrl_words);
     bool query;
     GNN_CHECK(ws_protocol(ws, ws_bytes, carve.used, &query));
     if (query) return GNN_OK;
@@ -597,42 +672,33 @@ extern "C" int32_t gnn_build_active_sets(const gnn_csr* g, const gnn_csr* gt, co
     GNN_REQUIRE(n == 0 || (dist != nullptr && ring_ids != nullptr), GNN_ERR_INVALID_ARG, "dist / ring_ids is NULL");
     GNN_REQUIRE(n_targets == 0 || targets != nullptr, GNN_ERR_INVALID_ARG, "targets is NULL");
 
-    as_init_kernel<<<grid_for(n > L + 2 ? n : L + 2, 256, 2048), 256, 0, stream>>>(dist, n, visited, seen, nw, ctrl, hop_offsets, L);
+    as_init_kernel<<<grid_for(n > L + 2 ? n : L + 2, 256, 2048), 256, 0, stream>>>(dist, n, visited[0], seen, nw, ctrl, (int32_t)ctrl_words,
+                                                                                   hop_offsets, L);
     GNN_LAUNCH_CHECK("as_init_kernel");
     if (n > 0) {
         if (n_targets > 0) {
             as_seed_kernel<<<grid_for(n_targets, 256, 2048), 256, 0, stream>>>(targets, n_targets, n, seen);
             GNN_LAUNCH_CHECK("as_seed_kernel");
         }
-        const int expand_grid = 2048;  // 8 waves per CU-slot; bounds are read on the device
-        const int64_t nnz_t = gt != nullptr ? gt->nnz : -1;   // < 0: every level pushes
+        AsArgs a;
+        a.row_ptr = g->row_ptr; a.col_idx = g->col_idx;
+        a.row_ptr_t = gt != nullptr ? gt->row_ptr : nullptr; a.col_idx_t = gt != nullptr ? gt->col_idx : nullptr;
+        a.n = n; a.nw = nw; a.nnz_t = gt != nullptr ? gt->nnz : 0;
+        a.ring_ids = ring_ids; a.hop_offsets = hop_offsets; a.seen = seen; a.frontier = frontier; a.hubq = hubq; a.ctrl = (AsCtrl*)ctrl;
+        const int pull_grid = gt != nullptr ? grid_for(nw * kWave, 256, 8192) : 1;   // a wavefront per 32 vertices
+        const int grid = pull_grid > (int)kAsPushBlocks ? pull_grid : (int)kAsPushBlocks;
         for (int32_t ring = 0; ring <= L; ++ring) {
+            a.visited = visited[ring & 1];
             if (ring > 0) {
-                if (gt != nullptr) {
-                    as_plan_kernel<<<512, 256, 0, stream>>>(g->row_ptr, gt->row_ptr, ring_ids, hop_offsets, ring - 1, ctrl);
-                    GNN_LAUNCH_CHECK("as_plan_kernel");
-                }
-                as_expand_kernel<<<expand_grid, 256, 0, stream>>>(g->row_ptr, g->col_idx, ring_ids, hop_offsets, ring - 1, seen, hubq, ctrl,
-                                                                  n, nnz_t);
+                as_expand_kernel<<<grid, 256, 0, stream>>>(a, ring - 1);
                 GNN_LAUNCH_CHECK("as_expand_kernel");
-                as_expand_hubs_kernel<<<2048, 256, 0, stream>>>(g->row_ptr, g->col_idx, seen, hubq, ctrl);
-                GNN_LAUNCH_CHECK("as_expand_hubs_kernel");
-                if (gt != nullptr) {
-                    as_pull_kernel<<<grid_for(nw * kWave, 256, 8192), 256, 0, stream>>>(gt->row_ptr, gt->col_idx, n, nw, visited, seen,
-                                                                                           frontier, hop_offsets, ring - 1, nnz_t, hubq, ctrl);
-                    GNN_LAUNCH_CHECK("as_pull_kernel");
-                    as_pull_hubs_kernel<<<1024, 256, 0, stream>>>(gt->row_ptr, gt->col_idx, seen, frontier, hop_offsets, ring - 1, n, nnz_t,
-                                                                  hubq, ctrl);
-                    GNN_LAUNCH_CHECK("as_pull_hubs_kernel");
+                if (g->nnz > kAsHubDegree) {   // else no row is long enough to be queued
+                    as_expand_hubs_kernel<<<grid_for(g->nnz / kAsHubDegree * 16, 1, 2048), 256, 0, stream>>>(a, ring - 1);
+                    GNN_LAUNCH_CHECK("as_expand_hubs_kernel");
                 }
             }
-            as_count_kernel<<<(int)nb, kAsWordsPerBlock, 0, stream>>>(seen, visited, nw, blk_cnt);
-            GNN_LAUNCH_CHECK("as_count_kernel");
-            as_scan_kernel<<<1, 1024, 0, stream>>>(blk_cnt, nb, hop_offsets, ring, ctrl);
-            GNN_LAUNCH_CHECK("as_scan_kernel");
-            as_emit_kernel<<<(int)nb, kAsWordsPerBlock, 0, stream>>>(seen, visited, nw, blk_cnt, hop_offsets, ring, ring_ids, dist,
-                                                                     gt != nullptr ? frontier : nullptr);
-            GNN_LAUNCH_CHECK("as_emit_kernel");
+            GNN_CHECK(as_emit(seen, visited[ring & 1], visited[(ring + 1) & 1], nw, nb, blk_cnt, hop_offsets, ring, ring_ids, dist, frontier,
+                              a.row_ptr, a.row_ptr_t, (AsCtrl*)ctrl, stream));
         }
     }
     if (hop_offsets_host != nullptr) {
@@ -657,11 +723,11 @@ extern "C" int32_t gnn_eas_traverse(const gnn_csr* g, const int32_t* targets, in
     const int64_t nb = nw > 0 ? (nw + kAsWordsPerBlock - 1) / kAsWordsPerBlock : 1;
 
     WsCarver carve(ws);
-    uint32_t* visited = carve.take<uint32_t>((size_t)nw + 1);
+    uint32_t* visited2[2];
+    for (int k = 0; k < 2; ++k) visited2[k] = carve.take<uint32_t>((size_t)nw + 1);
     uint8_t* seen = carve.take<uint8_t>((size_t)nw * 32 + 32);
     int32_t* blk_cnt = carve.take<int32_t>((size_t)nb + 1);
     int32_t* conn = carve.take<int32_t>(rule == GNN_EAS_DEGREE ? (size_t)n + 1 : 1);
-    AsCtrl* ctrl = carve.take<AsCtrl>(1);
     bool query;
     GNN_CHECK(ws_protocol(ws, ws_bytes, carve.used, &query));
     if (query) return GNN_OK;
@@ -670,7 +736,7 @@ extern "C" int32_t gnn_eas_traverse(const gnn_csr* g, const int32_t* targets, in
     GNN_REQUIRE(n == 0 || (dist != nullptr && ring_ids != nullptr), GNN_ERR_INVALID_ARG, "dist / ring_ids is NULL");
     GNN_REQUIRE(n_targets == 0 || targets != nullptr, GNN_ERR_INVALID_ARG, "targets is NULL");
 
-    as_init_kernel<<<grid_for(n > hops + 2 ? n : hops + 2, 256, 2048), 256, 0, stream>>>(dist, n, visited, seen, nw, ctrl, hop_offsets, hops);
+    as_init_kernel<<<grid_for(n > hops + 2 ? n : hops + 2, 256, 2048), 256, 0, stream>>>(dist, n, visited2[0], seen, nw, nullptr, 0, hop_offsets, hops);
     GNN_LAUNCH_CHECK("as_init_kernel");
     if (n > 0) {
         if (n_targets > 0) {
@@ -678,6 +744,7 @@ extern "C" int32_t gnn_eas_traverse(const gnn_csr* g, const int32_t* targets, in
             GNN_LAUNCH_CHECK("as_seed_kernel");
         }
         for (int32_t ring = 0; ring <= hops; ++ring) {
+            const uint32_t* visited = visited2[ring & 1];
             if (ring > 0) {
                 if (rule == GNN_EAS_DEGREE) {
                     eas_connections_kernel<<<grid_for((int64_t)n * 16, 256, 1 << 16), 256, 0, stream>>>(g->row_ptr, g->col_idx, n, visited, conn);
@@ -690,12 +757,8 @@ extern "C" int32_t gnn_eas_traverse(const gnn_csr* g, const int32_t* targets, in
                                                                  rule, mix64(seed + (uint64_t)ring), conn);
                 GNN_LAUNCH_CHECK("eas_expand_long_kernel");
             }
-            as_count_kernel<<<(int)nb, kAsWordsPerBlock, 0, stream>>>(seen, visited, nw, blk_cnt);
-            GNN_LAUNCH_CHECK("as_count_kernel");
-            as_scan_kernel<<<1, 1024, 0, stream>>>(blk_cnt, nb, hop_offsets, ring, ctrl);
-            GNN_LAUNCH_CHECK("as_scan_kernel");
-            as_emit_kernel<<<(int)nb, kAsWordsPerBlock, 0, stream>>>(seen, visited, nw, blk_cnt, hop_offsets, ring, ring_ids, dist, nullptr);
-            GNN_LAUNCH_CHECK("as_emit_kernel");
+            GNN_CHECK(as_emit(seen, visited, visited2[(ring + 1) & 1], nw, nb, blk_cnt, hop_offsets, ring, ring_ids, dist, nullptr, nullptr,
+                              nullptr, nullptr, stream));
         }
     }
     if (hop_offsets_host != nullptr) {
