@@ -26,6 +26,109 @@ __device__ __forceinline__ bool pair_less(uint64_t ka, int32_t ua, uint64_t kb, 
     return ka < kb || (ka == kb && ua < ub);
 }
 
+// ---- the k smallest of a row that a lane group holds in registers ------------------------------------------------
+// x's minimum over each group of 16 lanes, in every lane of the group
+__device__ __forceinline__ uint32_t min16(uint32_t x) {
+    x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xf, 0xf, false));   // row_ror:8
+    x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x124, 0xf, 0xf, false));
+    x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x122, 0xf, 0xf, false));
+    return min(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x121, 0xf, 0xf, false));
+}
+
+// ... over the G lanes of a group (16 or the whole wavefront)
+template <int G>
+__device__ __forceinline__ uint32_t group_min(uint32_t x) {
+    x = min16(x);
+    if (G == 16) return x;
+    return min(min((uint32_t)__builtin_amdgcn_readlane((int)x, 0), (uint32_t)__builtin_amdgcn_readlane((int)x, 16)),
+               min((uint32_t)__builtin_amdgcn_readlane((int)x, 32), (uint32_t)__builtin_amdgcn_readlane((int)x, 48)));
+}
+
+// The k-th smallest (key, id) pair of a group's candidates: NP pairs per lane, bit j of `cand` = pair j is a candidate.
+// `need` (uniform over the group): the group has more than k >= 1 candidates and wants the pair; the other groups of the
+// wavefront only take part.  All lanes call it.
+// A round of "smallest above the previous one" over 64-bit keys and ids costs some ten instructions a pair and, lane to
+// lane, three LDS shuffles a step.  The rounds here see the upper halves of the keys only: a subtraction and a minimum a
+// pair (what lies below `base` wraps around to the top), the lanes meet through DPP.  If the candidates up to the k-th
+// upper half are exactly k, that half belongs to the pair in question; otherwise two halves are equal (about n^2 / 2^33 of
+// the rows of n entries) and the rounds over whole pairs decide.
+template <int NP, int G>
+__device__ __forceinline__ void group_kth(const uint64_t (&key)[NP], const int32_t (&id)[NP], uint32_t cand, int32_t k, bool need,
+                                          uint64_t& thr_k, int32_t& thr_u) {
+    const int lane = lane_id(), first = lane / G * G;
+    const uint64_t mine = G == 64 ? ~0ull : ((1ull << (G & 63)) - 1ull) << first;
+    uint32_t base = 0u, top = 0u;
+    for (int32_t round = 0; round < k; ++round) {
+        uint32_t m = ~0u;
+#pragma unroll
+        for (int j = 0; j < NP; ++j) m = min(m, ((cand >> j) & 1u ? (uint32_t)(key[j] >> 32) : ~0u) - base);
+        top = base + group_min<G>(m);
+        base = top + 1u;
+    }
+    int32_t kept = 0;
+    bool has = false;
+    uint64_t pk = 0ull;
+    int32_t pu = 0;
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+        const uint32_t half = (uint32_t)(key[j] >> 32);
+        const bool c = (cand >> j) & 1u;
+        kept += __popcll(__ballot(c && half <= top) & mine);
+        if (c && half == top) {
+            has = true;
+            pk = key[j];
+            pu = id[j];
+        }
+    }
+    const uint64_t holders = __ballot(has) & mine;
+    const int src = holders ? __ffsll((unsigned long long)holders) - 1 : lane;
+    pk = __shfl(pk, src, kWave);
+    pu = __shfl(pu, src, kWave);
+    const bool tie = need && kept != k;
+    if (__ballot(tie) != 0ull) {   // uniform over the wavefront
+        uint64_t prev_k = 0ull;
+        int32_t prev_u = -1;
+        for (int32_t round = 0; round < k; ++round) {
+            uint64_t best_k = ~0ull;
+            int32_t best_u = 0x7fffffff;
+#pragma unroll
+            for (int j = 0; j < NP; ++j) {
+                if (((cand >> j) & 1u) && pair_less(prev_k, prev_u, key[j], id[j]) && pair_less(key[j], id[j], best_k, best_u)) {
+                    best_k = key[j];
+                    best_u = id[j];
+                }
+            }
+#pragma unroll
+            for (int d = G / 2; d >= 1; d >>= 1) {
+                const uint64_t ok = __shfl_xor(best_k, d, kWave);
+                const int32_t ou = __shfl_xor(best_u, d, kWave);
+                if (pair_less(ok, ou, best_k, best_u)) {
+                    best_k = ok;
+                    best_u = ou;
+                }
+            }
+            prev_k = best_k;
+            prev_u = best_u;
+        }
+        if (tie) {
+            pk = prev_k;
+            pu = prev_u;
+        }
+    }
+    if (need) {
+        thr_k = pk;
+        thr_u = pu;
+    }
+}
+
+// A key that about `want` of n uniformly distributed keys lie at or below (n >= want).
+__device__ __forceinline__ uint64_t key_guess(int32_t want, int32_t n) {
+    return want >= n ? ~0ull : (~0ull / (uint64_t)n) * (uint64_t)want;
+}
+
+// How many keys to aim for when the k smallest are wanted: fewer than k come out of it in one of a few million rows.
+__device__ __forceinline__ int32_t guess_count(int32_t k) { return k + 6 * (int32_t)ceilf(sqrtf((float)k)) + 10; }
+
 // ---- a wavefront's list of (key, id) pairs in LDS: the selection step shared by the traversal and the layer masks ----
 
 // The k-th smallest of the n (> k >= 1) distinct pairs of the list: k rounds of "smallest pair above the previous

@@ -2,21 +2,26 @@
 // generated per layer and the layer aggregates through them).  The one-hop graph is never rebuilt: a layer's mask is
 // one bit per CSR entry, which the aggregation kernels test next to their dist filter.
 //
-//   lm_mask_kernel       sixteen lanes per listed row (the boundary sampler's scheme): a row's keep decision is
+//   lm_mask_kernel       sixteen lanes per listed row of up to 64 entries (four per lane): a row's keep decision is
 //                        "(key, id) <= threshold pair".  A tile of sixteen consecutive entries becomes one 16-bit
 //                        ballot that lane 0 ORs into the bitmap (at most two words), so the result does not depend
-//                        on which group runs first.  The threshold rule has a fixed pair and takes this kernel for
-//                        every row; the fanout rule takes it for rows of up to 64 entries, whose ids and keys stay in
-//                        registers (four per lane) while `fanout` rounds of min-above-previous find the row's pair.
-//   lm_fanout_long_kernel  the fanout rule for longer rows, a wavefront per row: one pass over the row with a bounded
-//                        list of pairs in LDS (when it is full it is cut down to its `fanout` smallest, and from then
-//                        on only pairs below the largest of those are listed), then one more pass that writes the bits.
+//                        on which group runs first.  The threshold rule has a fixed pair; the fanout rule selects its
+//                        pair in registers (group_kth).
+//   lm_mask_long_kernel  the longer rows, a wavefront each.  Up to 1024 entries the fanout rule holds the row's keys in
+//                        registers; beyond, one sweep lists the entries below a guessed key in LDS (the keys are uniform:
+//                        the guess holds a few more than `fanout` of them), the pair is selected from that list and a
+//                        second sweep writes the bits.  Where the guess fails, or the fanout is too large for the list,
+//                        `fanout` rounds over the row itself find the pair.
 //   lm_transpose_kernel  the same mask in the positions of the transposed graph (backward aggregation): entry q =
 //                        (row u, column v) of the transposed graph looks up u in row v of the graph by binary search.
 //   lm_mask_t_kernel     the fast way to the same transposed mask: both rules are "(key, id) <= the row's threshold
 //                        pair", so with the pairs of the forward rows kept (12 bytes per row) an entry of the
-//                        transposed graph is decided by one hash and one random 12-byte read.
-// Bound: HBM (one pass over the listed rows; the generic transposition adds log2(row length) cached probes per entry).
+//                        transposed graph is decided by one hash and one random read of a key - the id is read where the
+//                        keys are equal.  A workgroup takes 4096 consecutive entries whatever rows they belong to, so
+//                        every word of the bitmap has one writer: no atomics, nothing to clear, no long rows.
+// Bound: the random reads (transposed), the hash (two 64-bit multiplications a mix) and the selection.  Measured on a
+// 1.2M-vertex / 60M-entry power-law graph, fanout 10: forward and transposed mask 2.61 -> 1.02 ms (short rows
+// 0.40 -> 0.20, long rows 1.11 -> 0.40, transposed 1.09 -> 0.43, its random reads into a 9.6 MB table).
 #include "common.h"
 #include "hashkey.h"
 
@@ -34,8 +39,9 @@ __device__ __forceinline__ void lm_or_bits(uint32_t* __restrict__ bits, int64_t 
     if (sh > 16 && (m >> (32 - sh)) != 0u) atomicOr(&bits[(p0 >> 5) + 1], m >> (32 - sh));
 }
 
-constexpr int kLmShortRow = 64;    // fanout rule: rows up to this length stay in registers, longer ones get a wavefront
-constexpr int kLmListCap = 1024;   // pairs a wavefront lists in LDS
+constexpr int kLmShortRow = 64;              // rows up to this length: sixteen lanes, longer ones: a wavefront
+constexpr int kLmRegRow = 16 * kWave;        // fanout rule: rows up to this length stay in a wavefront's registers
+constexpr int kLmListCap = 256;              // pairs a wavefront lists in LDS
 
 __global__ __launch_bounds__(256) void lm_mask_kernel(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
                                                       const int32_t* __restrict__ rows, int32_t n_active, int32_t rule, int32_t fanout,
@@ -55,81 +61,42 @@ __global__ __launch_bounds__(256) void lm_mask_kernel(const int32_t* __restrict_
             s = row_ptr[v];
             e = row_ptr[v + 1];
         }
+        if (e - s > kLmShortRow) {   // lm_mask_long_kernel takes this row
+            mine = false;
+            e = s;
+        }
+        int32_t u[kPerLane];
+        uint64_t key[kPerLane];
+        uint32_t cand = 0u;
+#pragma unroll
+        for (int j = 0; j < kPerLane; ++j) {
+            const int32_t p = s + j * kLmLanes + sl;
+            u[j] = p < e ? col_idx[p] : -1;
+        }
+#pragma unroll
+        for (int j = 0; j < kPerLane; ++j) {
+            key[j] = edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)(u[j] >= 0 ? u[j] : 0));
+            cand |= u[j] >= 0 ? 1u << j : 0u;
+        }
         // pairs (key, id) <= (thr_k, thr_u) are kept
         uint64_t thr_k = threshold;
         int32_t thr_u = 0x7fffffff;
-        int32_t kept = 0;
         if (rule == GNN_LAYER_MASK_FANOUT) {   // uniform over the grid
-            if (e - s > kLmShortRow) {         // lm_fanout_long_kernel takes this row
-                mine = false;
-                e = s;
-            }
             thr_k = ~0ull;
             if (fanout == 0) {
                 thr_k = 0ull;
                 thr_u = -1;  // nothing is <= (0, -1): ids are non-negative
             }
-            int32_t u[kPerLane];
-            uint64_t key[kPerLane];
-#pragma unroll
-            for (int j = 0; j < kPerLane; ++j) {
-                const int32_t p = s + j * kLmLanes + sl;
-                u[j] = p < e ? col_idx[p] : -1;
-                key[j] = u[j] >= 0 ? edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)u[j]) : ~0ull;
-            }
             const bool need = fanout > 0 && e - s > fanout;  // uniform over the 16-lane group
-            if (__ballot(need) != 0ull) {                     // uniform over the wavefront
-                uint64_t prev_k = 0ull;
-                int32_t prev_u = -1;
-                for (int32_t round = 0; round < fanout; ++round) {
-                    uint64_t best_k = ~0ull;
-                    int32_t best_u = 0x7fffffff;
+            if (__ballot(need) != 0ull) group_kth<kPerLane, kLmLanes>(key, u, cand, fanout, need, thr_k, thr_u);
+        }
+        int32_t kept = 0;
 #pragma unroll
-                    for (int j = 0; j < kPerLane; ++j) {
-                        if (u[j] >= 0 && pair_less(prev_k, prev_u, key[j], u[j]) && pair_less(key[j], u[j], best_k, best_u)) {
-                            best_k = key[j];
-                            best_u = u[j];
-                        }
-                    }
-#pragma unroll
-                    for (int d = kLmLanes / 2; d >= 1; d >>= 1) {
-                        const uint64_t ok = __shfl_xor(best_k, d, kWave);
-                        const int32_t ou = __shfl_xor(best_u, d, kWave);
-                        if (pair_less(ok, ou, best_k, best_u)) {
-                            best_k = ok;
-                            best_u = ou;
-                        }
-                    }
-                    prev_k = best_k;
-                    prev_u = best_u;
-                }
-                if (need) {
-                    thr_k = prev_k;
-                    thr_u = prev_u;
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < kPerLane; ++j) {
-                const bool keep = u[j] >= 0 && !pair_less(thr_k, thr_u, key[j], u[j]);
-                const uint32_t m = lm_group_ballot(keep, sub);
-                kept += __popc(m);
-                if (sl == 0) lm_or_bits(bits, (int64_t)s + j * kLmLanes, m);
-            }
-        } else {
-            int len_max = e - s;
-            len_max = max(len_max, __shfl_xor(len_max, 16, kWave));
-            len_max = max(len_max, __shfl_xor(len_max, 32, kWave));
-            for (int32_t off = 0; off < len_max; off += kLmLanes) {
-                const int32_t p = s + off + sl;
-                bool keep = false;
-                if (p < e) {
-                    const int32_t u = col_idx[p];
-                    keep = !pair_less(thr_k, thr_u, edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)u), u);
-                }
-                const uint32_t m = lm_group_ballot(keep, sub);
-                kept += __popc(m);
-                if (sl == 0) lm_or_bits(bits, (int64_t)s + off, m);
-            }
+        for (int j = 0; j < kPerLane; ++j) {
+            const bool keep = u[j] >= 0 && !pair_less(thr_k, thr_u, key[j], u[j]);
+            const uint32_t m = lm_group_ballot(keep, sub);
+            kept += __popc(m);
+            if (sl == 0) lm_or_bits(bits, (int64_t)s + j * kLmLanes, m);
         }
         if (sl == 0 && mine) {
             kept_len[v] = kept;
@@ -141,103 +108,168 @@ __global__ __launch_bounds__(256) void lm_mask_kernel(const int32_t* __restrict_
     }
 }
 
-// Fanout rule, rows longer than kLmShortRow: one wavefront per listed row.  Pass 1 finds the row's threshold pair
-// with a bounded list (see the head of the file; a fanout within 64 of the list's capacity - the list could not be
-// cut down far enough to take the next 64 entries - finds it by `fanout` rounds over the row itself); pass 2 reads
-// the row again and writes its bits, sixteen entries per atomic.
-__global__ __launch_bounds__(256) void lm_fanout_long_kernel(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
-                                                             const int32_t* __restrict__ rows, int32_t n_active, int32_t fanout,
-                                                             uint64_t seed_layer_mixed, uint32_t* __restrict__ bits,
-                                                             int32_t* __restrict__ kept_len, uint64_t* __restrict__ row_thr_key,
-                                                             int32_t* __restrict__ row_thr_id) {
+// ORs the 64 bits `m` (bit i = entry p0 + i) into the bitmap; called by a whole wavefront, three lanes write
+__device__ __forceinline__ void lm_or_tile(uint32_t* __restrict__ bits, int64_t p0, uint64_t m) {
+    const int lane = lane_id(), sh = (int)(p0 & 31);
+    if (lane > 2) return;
+    const uint64_t low = m << sh;
+    const uint32_t w = lane == 0 ? (uint32_t)low : (lane == 1 ? (uint32_t)(low >> 32) : (sh ? (uint32_t)(m >> (64 - sh)) : 0u));
+    if (w != 0u) atomicOr(&bits[(p0 >> 5) + lane], w);
+}
+
+// The fanout rule's pair of a row of more than kLmRegRow (> fanout) entries; see the head of the file.
+__device__ __forceinline__ void lm_pair_of_hub(const int32_t* __restrict__ col_idx, int32_t v, int32_t s, int32_t e, int32_t fanout,
+                                               uint64_t seed_layer_mixed, uint64_t* key, int32_t* id, uint64_t& thr_k, int32_t& thr_u) {
+    constexpr int kU = 4;
+    const int lane = lane_id();
+    const uint64_t lanes_below = (1ull << lane) - 1ull;
+    const int32_t want = fanout <= kLmListCap / 2 ? guess_count(fanout) : kLmListCap + 1;
+    int32_t n_list = 0;
+    if (want <= kLmListCap / 2) {
+        const uint64_t guess = key_guess(want, e - s);
+        for (int64_t p = s; p < e; p += kU * kWave) {
+            int32_t u[kU];
+#pragma unroll
+            for (int j = 0; j < kU; ++j) u[j] = p + j * kWave + lane < e ? col_idx[p + j * kWave + lane] : -1;
+#pragma unroll
+            for (int j = 0; j < kU; ++j) {
+                const uint64_t k = edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)(u[j] >= 0 ? u[j] : 0));
+                const bool take = u[j] >= 0 && k <= guess;
+                const uint64_t m = __ballot(take);
+                const int32_t pos = n_list + __popcll(m & lanes_below);
+                if (take && pos < kLmListCap) {
+                    key[pos] = k;
+                    id[pos] = u[j];
+                }
+                n_list += __popcll(m);
+            }
+        }
+        wave_lds_sync();
+    }
+    if (n_list >= fanout && n_list <= kLmListCap) {   // uniform over the wavefront
+        constexpr int NP = kLmListCap / kWave;
+        uint64_t k[NP];
+        int32_t u[NP];
+        uint32_t cand = 0u;
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            const bool in = j * kWave + lane < n_list;
+            k[j] = in ? key[j * kWave + lane] : ~0ull;
+            u[j] = in ? id[j * kWave + lane] : 0x7fffffff;
+            cand |= in ? 1u << j : 0u;
+        }
+        group_kth<NP, kWave>(k, u, cand, fanout, true, thr_k, thr_u);
+        wave_lds_sync();   // the list is read before the next row overwrites it
+        return;
+    }
+    uint64_t prev_k = 0ull;
+    int32_t prev_u = -1;
+    for (int32_t round = 0; round < fanout; ++round) {
+        uint64_t best_k = ~0ull;
+        int32_t best_u = 0x7fffffff;
+        for (int32_t p = s + lane; p < e; p += kWave) {
+            const int32_t u = col_idx[p];
+            const uint64_t k = edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)u);
+            if (pair_less(prev_k, prev_u, k, u) && pair_less(k, u, best_k, best_u)) {
+                best_k = k;
+                best_u = u;
+            }
+        }
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) {
+            const uint64_t ok = __shfl_xor(best_k, d, kWave);
+            const int32_t ou = __shfl_xor(best_u, d, kWave);
+            if (pair_less(ok, ou, best_k, best_u)) {
+                best_k = ok;
+                best_u = ou;
+            }
+        }
+        prev_k = best_k;
+        prev_u = best_u;
+    }
+    thr_k = prev_k;
+    thr_u = prev_u;
+}
+
+// Rows longer than kLmShortRow: a wavefront looks at kLmLook rows of the list at a time and takes the long ones one by one.
+constexpr int kLmLook = 16;
+
+__global__ __launch_bounds__(256) void lm_mask_long_kernel(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
+                                                           const int32_t* __restrict__ rows, int32_t n_active, int32_t rule, int32_t fanout,
+                                                           uint64_t threshold, uint64_t seed_layer_mixed, uint32_t* __restrict__ bits,
+                                                           int32_t* __restrict__ kept_len, uint64_t* __restrict__ row_thr_key,
+                                                           int32_t* __restrict__ row_thr_id) {
     __shared__ uint64_t s_key[4][kLmListCap];
     __shared__ int32_t s_id[4][kLmListCap];
     const int lane = lane_id(), wave = (int)(threadIdx.x >> 6);
-    uint64_t* key = s_key[wave];
-    int32_t* id = s_id[wave];
-    const uint64_t lanes_below = (1ull << lane) - 1ull;
     const int64_t waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    const bool streaming = fanout <= kLmListCap - kWave;
-    for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; i < n_active; i += waves) {   // uniform over the wave
-        const int32_t v = rows ? rows[i] : (int32_t)i;
-        const int32_t s = row_ptr[v], e = row_ptr[v + 1];
-        if (e - s <= kLmShortRow) continue;
-        uint64_t thr_k = ~0ull;   // pairs above (thr_k, thr_u) are out
-        int32_t thr_u = 0x7fffffff;
-        if (fanout == 0) {
-            thr_k = 0ull;
-            thr_u = -1;
-        } else if (e - s > fanout && streaming) {
-            int32_t n_list = 0;
-            for (int32_t p = s; p < e; p += kWave) {
-                const int32_t q = p + lane;
-                const int32_t u = q < e ? col_idx[q] : 0;
-                const uint64_t k = q < e ? edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)u) : 0ull;
-                bool take = q < e && !pair_less(thr_k, thr_u, k, u);
-                uint64_t mask = __ballot(take);
-                if (n_list + __popcll(mask) > kLmListCap) {   // uniform: cut the list down to its fanout smallest
-                    wave_lds_sync();
-                    wave_list_kth(key, id, n_list, fanout, lane, thr_k, thr_u);
-                    n_list = wave_list_keep_below(key, id, n_list, thr_k, thr_u, lane);
-                    take = q < e && !pair_less(thr_k, thr_u, k, u);
-                    mask = __ballot(take);
-                }
-                if (take) {
-                    const int32_t pos = n_list + __popcll(mask & lanes_below);
-                    key[pos] = k;
-                    id[pos] = u;
-                }
-                n_list += __popcll(mask);
+    for (int64_t base = (((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6) * kLmLook; base < n_active; base += waves * kLmLook) {
+        int32_t v_l = 0, s_l = 0, e_l = 0;
+        if (lane < kLmLook && base + lane < n_active) {
+            v_l = rows ? rows[base + lane] : (int32_t)(base + lane);
+            s_l = row_ptr[v_l];
+            e_l = row_ptr[v_l + 1];
+        }
+        uint64_t todo = __ballot(e_l - s_l > kLmShortRow);
+        while (todo) {   // uniform over the wavefront
+            const int from = __ffsll((unsigned long long)todo) - 1;
+            todo &= todo - 1ull;
+            const int32_t v = __builtin_amdgcn_readlane(v_l, from), s = __builtin_amdgcn_readlane(s_l, from),
+                          e = __builtin_amdgcn_readlane(e_l, from);
+            uint64_t thr_k = threshold;   // pairs above (thr_k, thr_u) are out
+            int32_t thr_u = 0x7fffffff, kept = 0;
+            const bool by_fanout = rule == GNN_LAYER_MASK_FANOUT;
+            if (by_fanout) {
+                thr_k = fanout == 0 ? 0ull : ~0ull;
+                thr_u = fanout == 0 ? -1 : 0x7fffffff;
             }
-            wave_lds_sync();
-            if (n_list > fanout) wave_list_kth(key, id, n_list, fanout, lane, thr_k, thr_u);
-            wave_lds_sync();   // the list is read before the next row overwrites it
-        } else if (e - s > fanout) {
-            uint64_t prev_k = 0ull;
-            int32_t prev_u = -1;
-            for (int32_t round = 0; round < fanout; ++round) {
-                uint64_t best_k = ~0ull;
-                int32_t best_u = 0x7fffffff;
-                for (int32_t p = s + lane; p < e; p += kWave) {
-                    const int32_t u = col_idx[p];
-                    const uint64_t k = edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)u);
-                    if (pair_less(prev_k, prev_u, k, u) && pair_less(k, u, best_k, best_u)) {
-                        best_k = k;
-                        best_u = u;
-                    }
-                }
+            if (by_fanout && e - s <= kLmRegRow) {
+                constexpr int NP = kLmRegRow / kWave;
+                uint64_t key[NP];
+                int32_t u[NP];
+                uint32_t cand = 0u;
 #pragma unroll
-                for (int d = 32; d >= 1; d >>= 1) {
-                    const uint64_t ok = __shfl_xor(best_k, d, kWave);
-                    const int32_t ou = __shfl_xor(best_u, d, kWave);
-                    if (pair_less(ok, ou, best_k, best_u)) {
-                        best_k = ok;
-                        best_u = ou;
+                for (int j = 0; j < NP; ++j) u[j] = s + j * kWave + lane < e ? col_idx[s + j * kWave + lane] : -1;
+#pragma unroll
+                for (int j = 0; j < NP; ++j) {
+                    key[j] = ~0ull;
+                    if (s + j * kWave < e) {   // uniform over the wavefront
+                        key[j] = edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)(u[j] >= 0 ? u[j] : 0));
+                        cand |= u[j] >= 0 ? 1u << j : 0u;
                     }
                 }
-                prev_k = best_k;
-                prev_u = best_u;
+                if (fanout > 0 && e - s > fanout) group_kth<NP, kWave>(key, u, cand, fanout, true, thr_k, thr_u);
+#pragma unroll
+                for (int j = 0; j < NP; ++j) {
+                    if (s + j * kWave < e) {   // uniform over the wavefront
+                        const uint64_t m = __ballot(u[j] >= 0 && !pair_less(thr_k, thr_u, key[j], u[j]));
+                        kept += __popcll(m);
+                        lm_or_tile(bits, (int64_t)s + j * kWave, m);
+                    }
+                }
+            } else {
+                if (by_fanout && fanout > 0 && e - s > fanout)
+                    lm_pair_of_hub(col_idx, v, s, e, fanout, seed_layer_mixed, s_key[wave], s_id[wave], thr_k, thr_u);
+                constexpr int kU = 4;
+                for (int64_t p = s; p < e; p += kU * kWave) {
+                    int32_t u[kU];
+#pragma unroll
+                    for (int j = 0; j < kU; ++j) u[j] = p + j * kWave + lane < e ? col_idx[p + j * kWave + lane] : -1;
+#pragma unroll
+                    for (int j = 0; j < kU; ++j) {
+                        const uint64_t k = edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)(u[j] >= 0 ? u[j] : 0));
+                        const uint64_t m = __ballot(u[j] >= 0 && !pair_less(thr_k, thr_u, k, u[j]));
+                        kept += __popcll(m);
+                        if (m != 0ull) lm_or_tile(bits, p + j * kWave, m);   // uniform over the wavefront
+                    }
+                }
             }
-            thr_k = prev_k;
-            thr_u = prev_u;
-        }
-        int32_t kept = 0;
-        for (int32_t p = s; p < e; p += kWave) {
-            const int32_t q = p + lane;
-            bool keep = false;
-            if (q < e) {
-                const int32_t u = col_idx[q];
-                keep = !pair_less(thr_k, thr_u, edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)u), u);
-            }
-            const uint64_t m = __ballot(keep);
-            kept += __popcll(m);
-            if (lane < 4) lm_or_bits(bits, (int64_t)p + 16 * lane, (uint32_t)((m >> (16 * lane)) & 0xffffull));
-        }
-        if (lane == 0) {
-            kept_len[v] = kept;
-            if (row_thr_key) {
-                row_thr_key[v] = thr_k;
-                row_thr_id[v] = thr_u;
+            if (lane == 0) {
+                kept_len[v] = kept;
+                if (row_thr_key) {
+                    row_thr_key[v] = thr_k;
+                    row_thr_id[v] = thr_u;
+                }
             }
         }
     }
@@ -245,31 +277,75 @@ __global__ __launch_bounds__(256) void lm_fanout_long_kernel(const int32_t* __re
 
 // The mask of a layer in the positions of the transposed graph, from the per-row threshold pairs the forward pass
 // left: entry q = (row u, column v) of the transposed graph is the forward entry (v <- u), kept iff
-// (key(v, u), u) <= (row_thr_key[v], row_thr_id[v]).  One random 12-byte read per entry instead of a binary search.
-__global__ __launch_bounds__(256) void lm_mask_t_kernel(int32_t n_t, const int32_t* __restrict__ rpT, const int32_t* __restrict__ ciT,
-                                                        const uint64_t* __restrict__ row_thr_key, const int32_t* __restrict__ row_thr_id,
-                                                        uint64_t seed_layer_mixed, uint32_t* __restrict__ keep_t) {
-    const int lane = lane_id(), sub = lane / kLmLanes, sl = lane % kLmLanes;
-    const int64_t groups = ((int64_t)gridDim.x * blockDim.x) / kLmLanes;
-    for (int64_t base = (((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6) * 4; base < n_t; base += groups) {
-        const int64_t u = base + sub;
-        int32_t s = 0, e = 0;
-        if (u < n_t) {
-            s = rpT[u];
-            e = rpT[u + 1];
+// (key(v, u), u) <= (row_thr_key[v], row_thr_id[v]).
+constexpr int kLmChunk = 4096;   // entries per workgroup
+
+__global__ __launch_bounds__(256) void lm_mask_t_kernel(int32_t n_t, int64_t nnz, const int32_t* __restrict__ rpT,
+                                                        const int32_t* __restrict__ ciT, const uint64_t* __restrict__ row_thr_key,
+                                                        const int32_t* __restrict__ row_thr_id, uint64_t seed_layer_mixed,
+                                                        uint32_t* __restrict__ keep_t) {
+    constexpr int kTiles = kLmChunk / 256;          // 64-entry tiles per wavefront
+    __shared__ int32_t s_start[kLmChunk];           // at the first entry of a row: its number relative to the chunk's first row
+    __shared__ int32_t s_last[4], s_row0;
+    const int lane = lane_id(), wave = (int)(threadIdx.x >> 6);
+    const int64_t q0 = (int64_t)blockIdx.x * kLmChunk;
+    const int64_t q1 = q0 + kLmChunk < nnz ? q0 + kLmChunk : nnz;
+    for (int t = threadIdx.x; t < kLmChunk; t += 256) s_start[t] = 0;
+    if (wave == 0) {   // the row that holds entry q0: a search with 64 probes a step; rpT[lo] <= q0 < rpT[hi]
+        int64_t lo = 0, hi = n_t;
+        while (hi - lo > 1) {
+            const int64_t step = (hi - lo + 63) / 64;
+            const int64_t at = lo + step * (lane + 1);
+            const int n_below = __popcll(__ballot(at < hi && (int64_t)rpT[at < hi ? at : lo] <= q0));
+            lo += step * n_below;
+            hi = lo + step < hi ? lo + step : hi;
         }
-        int len_max = e - s;
-        len_max = max(len_max, __shfl_xor(len_max, 16, kWave));
-        len_max = max(len_max, __shfl_xor(len_max, 32, kWave));
-        for (int32_t off = 0; off < len_max; off += kLmLanes) {
-            const int32_t q = s + off + sl;
-            bool bit = false;
-            if (q < e) {
-                const int32_t v = ciT[q];
-                bit = !pair_less(row_thr_key[v], row_thr_id[v], edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)u), (int32_t)u);
-            }
-            const uint32_t m = lm_group_ballot(bit, sub);
-            if (sl == 0) lm_or_bits(keep_t, (int64_t)s + off, m);
+        if (lane == 0) s_row0 = (int32_t)lo;
+    }
+    __syncthreads();
+    const int32_t row0 = s_row0;
+    for (int64_t r = (int64_t)row0 + 1 + threadIdx.x; r < n_t; r += 256) {
+        const int64_t at = rpT[r];
+        if (at >= q1) break;
+        atomicMax(&s_start[at - q0], (int32_t)(r - row0));   // of several rows that start here all but the last are empty
+    }
+    __syncthreads();
+    // the last row that starts in each wavefront's part
+    int32_t last = 0;
+    for (int t = 0; t < kTiles; ++t) last = max(last, s_start[(wave * kTiles + t) * kWave + lane]);
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) last = max(last, __shfl_xor(last, d, kWave));
+    if (lane == 0) s_last[wave] = last;
+    __syncthreads();
+    int32_t row = 0;   // of the entry before the tile, relative to row0
+    for (int w = 0; w < wave; ++w) row = max(row, s_last[w]);
+    constexpr int kU = 4;
+    for (int t = 0; t < kTiles; t += kU) {
+        const int64_t p0 = q0 + (wave * kTiles + t) * kWave;
+        if (p0 >= q1) break;   // uniform over the wavefront
+        int32_t u[kU], v[kU];
+        uint64_t thr[kU];
+#pragma unroll
+        for (int j = 0; j < kU; ++j) v[j] = p0 + j * kWave + lane < q1 ? ciT[p0 + j * kWave + lane] : -1;
+#pragma unroll
+        for (int j = 0; j < kU; ++j) {
+            const int32_t st = s_start[(wave * kTiles + t + j) * kWave + lane];
+            const uint64_t starts = __ballot(st != 0);
+            const uint64_t upto = starts & (~0ull >> (63 - lane));
+            const int32_t mine = __shfl(st, upto ? 63 - __clzll((long long)upto) : 0, kWave);
+            u[j] = row0 + (upto ? mine : row);
+            if (starts) row = __shfl(st, 63 - __clzll((long long)starts), kWave);   // uniform over the wavefront
+        }
+#pragma unroll
+        for (int j = 0; j < kU; ++j) thr[j] = row_thr_key[v[j] >= 0 ? v[j] : 0];
+#pragma unroll
+        for (int j = 0; j < kU; ++j) {
+            const uint64_t k = edge_key(seed_layer_mixed, (uint64_t)(v[j] >= 0 ? v[j] : 0), (uint64_t)u[j]);
+            bool bit = v[j] >= 0 && k <= thr[j];
+            if (bit && k == thr[j]) bit = u[j] <= row_thr_id[v[j]];
+            const uint64_t m = __ballot(bit);
+            const int64_t p = p0 + j * kWave + lane * 32;
+            if (lane < 2 && p < q1) keep_t[p >> 5] = (uint32_t)(m >> (32 * lane));
         }
     }
 }
@@ -348,10 +424,11 @@ extern "C" int32_t gnn_layer_edge_mask(const gnn_csr* g, const int32_t* rows, in
             g->row_ptr, g->col_idx, rows, n_active, rule, fanout, threshold, mix64(seed + (uint64_t)layer), edge_keep, kept_len, row_thr_key,
             row_thr_id);
         GNN_LAUNCH_CHECK("lm_mask_kernel");
-        if (rule == GNN_LAYER_MASK_FANOUT) {
-            lm_fanout_long_kernel<<<grid_for((int64_t)n_active * kWave, 256, 4096), 256, 0, stream>>>(
-                g->row_ptr, g->col_idx, rows, n_active, fanout, mix64(seed + (uint64_t)layer), edge_keep, kept_len, row_thr_key, row_thr_id);
-            GNN_LAUNCH_CHECK("lm_fanout_long_kernel");
+        if (g->nnz > kLmShortRow) {   // else no row is longer
+            lm_mask_long_kernel<<<grid_for(((int64_t)n_active + kLmLook - 1) / kLmLook, 4, 8192), 256, 0, stream>>>(
+                g->row_ptr, g->col_idx, rows, n_active, rule, fanout, threshold, mix64(seed + (uint64_t)layer), edge_keep, kept_len,
+                row_thr_key, row_thr_id);
+            GNN_LAUNCH_CHECK("lm_mask_long_kernel");
         }
     }
     return GNN_OK;
@@ -383,10 +460,8 @@ extern "C" int32_t gnn_layer_edge_mask_transposed(const gnn_csr* gT, const uint6
     const int64_t n_words = (gT->nnz + 31) / 32;
     GNN_REQUIRE(n_words == 0 || (row_thr_key && row_thr_id && keep_t), GNN_ERR_INVALID_ARG, "row_thr_key, row_thr_id or keep_t is NULL");
     if (n_words > 0) {
-        fill_kernel<uint32_t><<<grid_for(n_words, 256, 4096), 256, 0, stream>>>(keep_t, n_words, 0u);
-        GNN_LAUNCH_CHECK("fill_kernel");
-        lm_mask_t_kernel<<<grid_for((int64_t)gT->n_rows * kLmLanes, 256, 1 << 15), 256, 0, stream>>>(
-            gT->n_rows, gT->row_ptr, gT->col_idx, row_thr_key, row_thr_id, mix64(seed + (uint64_t)layer), keep_t);
+        lm_mask_t_kernel<<<(int)((gT->nnz + kLmChunk - 1) / kLmChunk), 256, 0, stream>>>(
+            gT->n_rows, gT->nnz, gT->row_ptr, gT->col_idx, row_thr_key, row_thr_id, mix64(seed + (uint64_t)layer), keep_t);
         GNN_LAUNCH_CHECK("lm_mask_t_kernel");
     }
     return GNN_OK;

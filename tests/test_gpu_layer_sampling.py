@@ -71,6 +71,64 @@ def test_masks_hub_rows_empty_rows_and_nothing_listed():
     _mask_case(empty, None, "threshold", M64, 1, 0)
 
 
+def _mix64(x):
+    with np.errstate(over="ignore"):
+        x = x + np.uint64(0x9E3779B97F4A7C15)
+        x = (x ^ (x >> np.uint64(30))) * np.uint64(0xBF58476D1CE4E5B9)
+        x = (x ^ (x >> np.uint64(27))) * np.uint64(0x94D049BB133111EB)
+        return x ^ (x >> np.uint64(31))
+
+
+@pytest.mark.parametrize("length", [40, 64, 65, 700, 1024, 1025, 3000])
+def test_masks_when_the_upper_halves_of_two_keys_are_equal(length):
+    """The selection compares upper halves of keys and falls back to whole pairs when the k-th is not alone with its half:
+    rows built around two columns whose keys share the upper half, kept both, one of them, or neither.  Lengths on both
+    sides of every class of rows."""
+    n, layer, seed, v = 1_500_000, 1, 77, 5
+    assert int(_mix64(_mix64(_mix64(np.uint64(seed + layer)) ^ np.uint64(v)) ^ np.uint64(123))) == oracle.edge_key(seed, v, 123, layer)
+    keys = _mix64(_mix64(_mix64(np.uint64(seed + layer)) ^ np.uint64(v)) ^ np.arange(n, dtype=np.uint64))
+    order = np.argsort(keys)
+    half = keys[order] >> np.uint64(32)
+    at = np.flatnonzero(half[1:] == half[:-1])
+    assert at.size > 50                                        # about n^2 / 2^33 of them
+    at = int(at[at > length][0])                               # the pair is order[at], order[at + 1]
+    for k in (1, 2, 3, 10, 25):
+        # the k-th smallest key is the first or the second of the pair, or lies before it
+        for before in sorted({max(k - 1, 0), max(k - 2, 0), k}):
+            if before + 2 > length:
+                continue
+            low = order[np.random.default_rng(before).choice(at, before, replace=False)]
+            high = order[at + 2:][np.random.default_rng(k).choice(n - at - 2, length - before - 2, replace=False)]
+            cols = np.sort(np.concatenate([low, order[at: at + 2], high])).astype(np.int32)
+            row_ptr = np.zeros(n + 1, dtype=np.int32)
+            row_ptr[v + 1:] = length
+            _mask_case(gg.CSR(n, n, row_ptr, cols), np.array([v]), "fanout", k, layer, seed)
+
+
+def test_transposed_mask_rows_across_chunks():
+    """A workgroup decides 4096 consecutive entries: rows that span several, runs of empty rows at the joints, a last chunk
+    that ends inside a word."""
+    import paper_2311_06837_amd as P
+    n = 70000
+    lengths = np.zeros(n, dtype=np.int64)
+    lengths[[0, 1, 5, 6, 30000, 30001, n - 2]] = [4095, 1, 12289, 63, 64, 4096, 77]
+    lengths[40000:40300] = np.random.default_rng(1).integers(0, 40, 300)
+    rng = np.random.default_rng(2)
+    cols = np.concatenate([np.sort(rng.choice(n, ln, replace=False)) for ln in lengths if ln] + [np.zeros(0)]).astype(np.int32)
+    gt = gg.CSR(n, n, np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32), cols)
+    assert gt.nnz % 32 not in (0, 1) and gt.nnz > 5 * 4096
+    g = gg.transpose(gt)
+    G, GT = P.Graph.from_numpy(g.row_ptr, g.col_idx), P.Graph.from_numpy(gt.row_ptr, gt.col_idx)
+    for rule, kw in (("threshold", dict(threshold=oracle.keep_threshold(0.5))), ("fanout", dict(fanout=1))):
+        keep, _, tk, tu = P.gnn_layer_edge_mask(G, None, n, rule, 3, 11, with_thresholds=True, **kw)
+        kt = P.gnn_layer_edge_mask_transposed(GT, tk, tu, 3, 11)
+        ok, _ = oracle.layer_edge_mask(g.row_ptr, g.col_idx, None, rule, 3, 11, **kw)
+        assert np.array_equal(_bits(keep, g.nnz), ok), rule
+        assert np.array_equal(_bits(kt, gt.nnz), oracle.transpose_mask(g.row_ptr, g.col_idx, ok, gt.row_ptr, gt.col_idx)), rule
+        tail = int(kt.cpu().numpy().view(np.uint32)[-1]) >> (gt.nnz % 32)
+        assert tail == 0, "bits past the last entry are set"
+
+
 def test_transposed_mask():
     import paper_2311_06837_amd as P
     for g in (gg.random_directed(20000, 6.0, 4), gg.chung_lu(9000, 40.0, 2.1, 5)):
