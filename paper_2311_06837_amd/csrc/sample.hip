@@ -3,20 +3,20 @@
 // target keeps at most `fanout`.  The choice is a seeded counter-based hash of the edge
 // (no generator state, no dependence on thread order): the `fanout` smallest (key, id) win.
 //
-// Rows are handled in three length classes, so that every class keeps its whole row in registers or walks it with many
-// independent loads in flight (a partition grown breadth-first holds the graph's hubs: on the 10M-vertex workload 15 %
-// of the target rows are longer than 64 entries and hold 70 % of all candidates):
+// Rows are handled in three length classes (rowlists.h), so that every class keeps its whole row in registers or walks it
+// with many independent loads in flight (a partition grown breadth-first holds the graph's hubs: on the 10M-vertex
+// workload 15 % of the target rows are longer than 64 entries and hold 70 % of all candidates):
 //   up to 64 entries    sixteen lanes per row, four entries per lane;
 //   65 to 1024          one wavefront per row, sixteen entries per lane (second launch of the pass);
 //   longer              one workgroup per row, which strides the row four entries per thread and step (third launch).
-// The first launch is a grid-stride loop over the targets; the rows it leaves to the other two are collected in LDS
-// lists and appended to the two queues with ONE global atomic per workgroup and class (one atomic per row on a single
-// counter serialised the launch: 184 000 of them took 1.4 ms).  Count pass: ballots give |row in T| and the number of
-// outside neighbours; a three-kernel scan turns counts into row offsets.  Fill pass: a row with more than `fanout`
-// outside neighbours finds the fanout-th smallest (key, id) by `fanout` rounds of "smallest pair above the previous
-// one" over its registers, then emits the row in its original ascending order through a ballot-prefix compaction.
+// Count pass: ballots give |row in T| and the number of outside neighbours; a scan turns counts into row offsets.  Fill
+// pass: a row with more than `fanout` outside neighbours finds the fanout-th smallest (key, id) - among its registers
+// (group_kth), or, a long row, among the few keys below a guessed one - and emits the row in its original ascending
+// order through a ballot-prefix compaction.
 // Which lane group, wavefront or workgroup takes a row does not matter: every row's result depends on the row alone.
-// Bound: HBM (one streaming read of the target rows per pass).
+// Bound: HBM (streaming reads of the target rows) and the hash.  Kernel time of both passes on a 5M-vertex / 75M-entry graph,
+// 625 000 targets, fanout 5: 0.80 -> 0.59 ms against `fanout` rounds over 64-bit pairs with the long rows re-read in every
+// round (long rows 0.33 -> 0.16); 700 000 vertices of 100 entries, fanout 10, with the extraction: 2.26 -> 1.76 ms.
 #include "common.h"
 #include "hashkey.h"
 #include "rowlists.h"
@@ -120,34 +120,10 @@ __global__ __launch_bounds__(256) void sb_fill_kernel(const int32_t* __restrict_
     }
     const bool want = fanout > 0 && n_out > fanout;   // uniform over the 16-lane group
     if (__ballot(want) != 0ull) {                      // uniform over the wavefront
-        uint64_t prev_k = 0ull;
-        int32_t prev_u = -1;
-        for (int32_t round = 0; round < fanout; ++round) {
-            uint64_t best_k = ~0ull;
-            int32_t best_u = 0x7fffffff;
+        uint32_t cand = 0u;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                if (rf[r] == 2 && pair_less(prev_k, prev_u, rk[r], ru[r]) && pair_less(rk[r], ru[r], best_k, best_u)) {
-                    best_k = rk[r];
-                    best_u = ru[r];
-                }
-            }
-#pragma unroll
-            for (int d = kRowLanes / 2; d >= 1; d >>= 1) {
-                const uint64_t ok = __shfl_xor(best_k, d, kWave);
-                const int32_t ou = __shfl_xor(best_u, d, kWave);
-                if (pair_less(ok, ou, best_k, best_u)) {
-                    best_k = ok;
-                    best_u = ou;
-                }
-            }
-            prev_k = best_k;
-            prev_u = best_u;
-        }
-        if (want) {
-            tk = prev_k;
-            tu = prev_u;
-        }
+        for (int r = 0; r < 4; ++r) cand |= rf[r] == 2 ? 1u << r : 0u;
+        group_kth<4, kRowLanes>(rk, ru, cand, fanout, want, tk, tu);
     }
     int64_t at = i < n_targets ? (int64_t)out_row_ptr[i] : 0;
 #pragma unroll
@@ -208,32 +184,10 @@ __global__ __launch_bounds__(256) void sb_medium_rows_kernel(const int32_t* __re
             tu = -1;
         }
         if (fanout > 0 && n_ext > fanout) {   // uniform over the wavefront
-            uint64_t prev_k = 0ull;
-            int32_t prev_u = -1;
-            for (int32_t round = 0; round < fanout; ++round) {
-                uint64_t best_k = ~0ull;
-                int32_t best_u = 0x7fffffff;
+            uint32_t cand = 0u;
 #pragma unroll
-                for (int r = 0; r < EPL; ++r) {
-                    if (rf[r] == 2 && pair_less(prev_k, prev_u, rk[r], ru[r]) && pair_less(rk[r], ru[r], best_k, best_u)) {
-                        best_k = rk[r];
-                        best_u = ru[r];
-                    }
-                }
-#pragma unroll
-                for (int d = kWave / 2; d >= 1; d >>= 1) {
-                    const uint64_t ok = __shfl_xor(best_k, d, kWave);
-                    const int32_t ou = __shfl_xor(best_u, d, kWave);
-                    if (pair_less(ok, ou, best_k, best_u)) {
-                        best_k = ok;
-                        best_u = ou;
-                    }
-                }
-                prev_k = best_k;
-                prev_u = best_u;
-            }
-            tk = prev_k;
-            tu = prev_u;
+            for (int r = 0; r < EPL; ++r) cand |= rf[r] == 2 ? 1u << r : 0u;
+            group_kth<EPL, kWave>(rk, ru, cand, fanout, true, tk, tu);
         }
         int64_t at = out_row_ptr[i];
         const uint64_t below = (1ull << lane) - 1ull;
@@ -296,8 +250,12 @@ __device__ __forceinline__ void block_min_pair(uint64_t& k, int32_t& u, uint64_t
     __syncthreads();
 }
 
-// The same selection as the sixteen-lane kernels, for the queued rows: 256 threads stride the row, four entries per
-// thread and step with all their loads (ids, then target bits) issued before the first use.  FILL false: counts[i];
+constexpr int kSbListCap = 512;   // pairs below the guessed key that a workgroup lists
+
+// The same selection for the queued rows: 256 threads stride the row, four entries per thread and step with all their
+// loads (ids, then target bits) issued before the first use.  The keys are uniform, so the row's pair is among the few
+// below a guessed key: one sweep lists those in LDS and the first wavefront selects from the list; where the guess fails
+// or the fanout is too large for the list, `fanout` sweeps of "smallest pair above the previous one" find it.  FILL false: counts[i];
 // FILL true: the kept ids in ascending position order.  Which workgroup takes which row does not matter: every row's
 // result depends on the row alone.
 template <bool FILL>
@@ -308,8 +266,8 @@ __global__ __launch_bounds__(256) void sb_long_rows_kernel(const int32_t* __rest
                                                            const int32_t* __restrict__ out_row_ptr, int32_t* __restrict__ out_col_idx,
                                                            int64_t capacity) {
     __shared__ int s_a[4], s_b[4], s_part[4];
-    __shared__ uint64_t s_k[4];
-    __shared__ int32_t s_u[4];
+    __shared__ uint64_t s_k[4], s_key[kSbListCap];
+    __shared__ int32_t s_u[4], s_id[kSbListCap], s_n;
     const int tid = (int)threadIdx.x;
     const int32_t n_hub = ctrl->n_hub;
     for (int32_t h = blockIdx.x; h < n_hub; h += gridDim.x) {   // uniform over the workgroup
@@ -344,7 +302,64 @@ __global__ __launch_bounds__(256) void sb_long_rows_kernel(const int32_t* __rest
             thr_k = 0ull;
             thr_u = -1;
         }
-        if (fanout > 0 && n_ext > fanout) {   // uniform over the workgroup
+        const int32_t aim = fanout <= kSbListCap / 2 ? guess_count(fanout) : kSbListCap;
+        bool found = false;
+        if (fanout > 0 && n_ext > fanout && aim <= kSbListCap / 2) {   // uniform over the workgroup
+            const uint64_t guess = key_guess(aim, n_ext);
+            if (tid == 0) s_n = 0;
+            __syncthreads();
+            for (int64_t base = s; base < e; base += 1024) {
+                int32_t u[4];
+                bool ok[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int64_t p = base + r * 256 + tid;
+                    ok[r] = p < e;
+                    u[r] = ok[r] ? col_idx[p] : 0;
+                }
+#pragma unroll
+                for (int r = 0; r < 4; ++r) ok[r] = ok[r] && !in_set(tbits, u[r]);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const uint64_t k = edge_key(seed_hop_mixed, (uint64_t)v, (uint64_t)u[r]);
+                    if (ok[r] && k <= guess) {
+                        const int pos = atomicAdd(&s_n, 1);   // the order of the list does not matter
+                        if (pos < kSbListCap) {
+                            s_key[pos] = k;
+                            s_id[pos] = u[r];
+                        }
+                    }
+                }
+            }
+            __syncthreads();
+            const int32_t n_list = s_n;
+            found = n_list >= fanout && n_list <= kSbListCap;
+            if (found) {
+                if (tid < kWave) {
+                    constexpr int NP = kSbListCap / kWave;
+                    uint64_t k[NP];
+                    int32_t u[NP];
+                    uint32_t cand = 0u;
+#pragma unroll
+                    for (int j = 0; j < NP; ++j) {
+                        const bool in = j * kWave + tid < n_list;
+                        k[j] = in ? s_key[j * kWave + tid] : ~0ull;
+                        u[j] = in ? s_id[j * kWave + tid] : 0x7fffffff;
+                        cand |= in ? 1u << j : 0u;
+                    }
+                    group_kth<NP, kWave>(k, u, cand, fanout, true, thr_k, thr_u);
+                    if (tid == 0) {
+                        s_k[0] = thr_k;
+                        s_u[0] = thr_u;
+                    }
+                }
+                __syncthreads();
+                thr_k = s_k[0];
+                thr_u = s_u[0];
+                __syncthreads();
+            }
+        }
+        if (fanout > 0 && n_ext > fanout && !found) {   // uniform over the workgroup
             uint64_t prev_k = 0ull;
             int32_t prev_u = -1;
             for (int32_t round = 0; round < fanout; ++round) {

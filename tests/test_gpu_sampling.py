@@ -60,7 +60,7 @@ def test_row_lengths_around_the_sixteen_lane_limit():
     of that workgroup's sweep, then two) and an empty one, targets and outside vertices mixed in every row."""
     rng = np.random.default_rng(35)
     n = 5000
-    lens = [63, 64, 65, 0, 1023, 1024, 1025, 1, 256, 257]
+    lens = [63, 64, 65, 0, 1023, 1024, 1025, 1, 256, 257, 4097]
     rows, cols = [], []
     for r, ln in enumerate(lens):
         c = rng.choice(n, size=ln, replace=False)
@@ -69,5 +69,5 @@ def test_row_lengths_around_the_sixteen_lane_limit():
     g = gg.csr_from_edges(n, n, np.concatenate(rows), np.concatenate(cols))
     assert list(g.degrees()[: len(lens)]) == lens
     T = np.concatenate([np.arange(len(lens)), np.arange(100, n, 2)]).astype(np.int32)   # about half of every row is inside
-    for fanout in (0, 3, 40, 600):
+    for fanout in (0, 1, 3, 40, 150, 250, 600):    # the long rows: from the listed keys up to 150, then by sweeps over the row
         _compare(g, T, fanout, 0xABCDEF)
