@@ -18,6 +18,7 @@ LIB_PATH = os.path.join(_HERE, "libgnnhot.so")
 GNN_F32, GNN_BF16 = 0, 1
 GNN_NORM_MEAN, GNN_NORM_SYM = 1, 2
 GNN_CSR_SORTED_COLUMNS = 1
+GNN_ERR_WORKSPACE = 3
 STATUS = {0: "GNN_OK", 1: "GNN_ERR_INVALID_ARG", 2: "GNN_ERR_SHAPE", 3: "GNN_ERR_WORKSPACE",
           4: "GNN_ERR_UNSUPPORTED", 5: "GNN_ERR_HIP"}
 
@@ -33,6 +34,31 @@ class GnnError(RuntimeError):
     def __init__(self, status: int, message: str):
         super().__init__(f"{STATUS.get(status, status)}: {message}")
         self.status = status
+
+
+# argument types of the calls, one letter each: p pointer, i int32, l int64, u uint64, f float (so that plain Python numbers
+# and addresses can be passed; a call takes a dozen or two of them)
+_TYPES = {"p": C.c_void_p, "i": C.c_int32, "l": C.c_int64, "u": C.c_uint64, "f": C.c_float}
+_SIGNATURES = {
+    "gnn_version": "", "gnn_last_error": "",
+    "gnn_build_active_sets": "pppii" + "pppp" + "ppp",
+    "gnn_norm_scales": "ippipp", "gnn_masked_spmm_fwd": "ppi" + "plpl" + "ii" + "pp" + "ppp",
+    "gnn_masked_spmm_fwd_add": "ppi" + "plpl" + "ii" + "pppi" + "ppp",
+    "gnn_masked_spmm_bwd": "ppi" + "pii" + "plpl" + "ii" + "ppi" + "pl" + "ppp",
+    "gnn_linear_fwd": "pi" + "ppli" + "pppi" + "plii" + "ppp", "gnn_linear_fwd_static": "pi" + "ppli" + "pppi" + "plii" + "p",
+    "gnn_linear_bwd": "pi" + "ppli" + "ppli" + "ppi" + "ppp" + "ppli" + "ppp",
+    "gnn_linear_bwd_input": "pi" + "pli" + "pii" + "pl" + "pli" + "ppp",
+    "gnn_linear_bwd_input2": "pi" + "pppp" + "ilii" + "pl" + "pli" + "ppp",
+    "gnn_bias_grad": "pipliip" + "ppp", "gnn_softmax_ce": "pi" + "plip" + "plip" + "ppp", "gnn_make_bitmap": "piipp",
+    "gnn_sample_boundary": "ppp" + "iiiu" + "pplpp" + "ppp", "gnn_eas_traverse": "ppi" + "iiiu" + "pppp" + "ppp",
+    "gnn_layer_edge_mask": "ppiiiuuipppp" + "p", "gnn_layer_edge_mask_transposed": "pppuipp", "gnn_transpose_edge_mask": "ppppp",
+    "gnn_layer_norm_relu_fwd": "pipli" + "ppf" + "pli" + "p",
+    "gnn_layer_norm_relu_bwd": "pi" + "plplpli" + "pf" + "pli" + "plppi" + "ppp",
+    "gnn_add_rows": "piplplii" + "p", "gnn_add_rows_masked": "pipl" + "ipl" + "ipl" + "i" + "p",
+    "gnn_extract_partition": "ppi" + "pip" + "pplpp" + "ppp", "gnn_extract_sampled_partition": "pppi" + "pp" + "pplpp" + "ppp",
+    "gnn_expand_row_ptr": "ipipp" + "ppp", "gnn_gather_rows": "plipiiipl" + "p", "gnn_die_mapping": "pip",
+    "gnn_fused_layer_fwd": "ppi" + "pli" + "pppp" + "pi" + "plii" + "ppp",
+}
 
 
 class gnn_csr(C.Structure):
@@ -53,8 +79,10 @@ def lib() -> C.CDLL:
         _lib = C.CDLL(LIB_PATH)
         _lib.gnn_last_error.restype = C.c_char_p
         for name in EXPORTS:
+            fn = getattr(_lib, name)
+            fn.argtypes = [_TYPES[c] for c in _SIGNATURES[name]]
             if name not in ("gnn_last_error",):
-                getattr(_lib, name).restype = C.c_int32
+                fn.restype = C.c_int32
     return _lib
 
 
@@ -66,12 +94,13 @@ def _check(status: int):
 def _ptr(t):
     if t is None:
         return None
-    assert isinstance(t, torch.Tensor) and t.is_cuda, "device tensor expected"
-    return C.c_void_p(t.data_ptr())
+    assert t.is_cuda, "device tensor expected"
+    return t.data_ptr()
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current stream of the current device, without the torch.cuda.Stream object around it."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _dtype_code(t: torch.Tensor) -> int:
@@ -145,8 +174,13 @@ _default_ws = Workspace()
 
 
 def _with_ws(fn, args_before, args_after, ws: Workspace | None):
-    """Run the (ws, ws_bytes) protocol: query the size, then call with a buffer of that size."""
+    """Run the (ws, ws_bytes) protocol: call with the buffer at hand; only if there is none or it is too small (the call then
+    does nothing but say so) query the size, get a buffer of that size and call again."""
     ws = ws or _default_ws
+    if ws.buf is not None:
+        status = fn(*args_before, ws.buf.data_ptr(), C.byref(C.c_size_t(ws.buf.numel())), *args_after)
+        if status != GNN_ERR_WORKSPACE:
+            return _check(status)
     need = C.c_size_t(0)
     _check(fn(*args_before, None, C.byref(need), *args_after))
     buf = ws.get(need.value)

@@ -73,6 +73,7 @@ class MaskedGNN:
         self.L = len(params)
         self.ws = B.Workspace()
         self.side = torch.cuda.Stream(device=targets.device) if side_stream else None
+        self._ready = torch.cuda.Event() if side_stream else None     # recorded on the step's stream before each call on the side
         self.ws_side = B.Workspace()
         self.dims = [params[0]["W_neigh"].shape[0]] + [p["W_neigh"].shape[1] for p in params]
         self.params = []
@@ -141,10 +142,9 @@ class MaskedGNN:
         and bias gradients): on the side stream, after everything enqueued so far on the step's stream."""
         if self.side is None:
             return self._call(name, fn, *args, ws=self.ws, **kw)
-        ready = torch.cuda.Event()
-        ready.record()
+        self._ready.record()
+        self.side.wait_event(self._ready)
         with torch.cuda.stream(self.side):
-            self.side.wait_event(ready)
             return self._call(name, fn, *args, ws=self.ws_side, **kw)
 
     def _join_side(self):

@@ -30,6 +30,19 @@ def test_every_declared_symbol_is_exported(lib):
         assert hasattr(lib, name), name
 
 
+def test_argument_types_of_the_binding_are_the_headers(lib):
+    header = re.sub(r"/\*.*?\*/", "", open(os.path.join(ROOT, "include", "gnnhot.h")).read(), flags=re.S)
+    letters = {"int32_t": "i", "int64_t": "l", "uint64_t": "u", "float": "f"}
+    seen = set()
+    for name, args in re.findall(r"\b(gnn_[a-z0-9_]+)\s*\(([^)]*)\)\s*;", header):
+        args = [" ".join(a.split()) for a in args.split(",") if a.strip() != "void"]
+        want = "".join("p" if "*" in a or "[" in a else letters[a.split()[-2]] for a in args)
+        assert B._SIGNATURES[name] == want, name
+        assert getattr(lib, name).argtypes == [B._TYPES[c] for c in want], name
+        seen.add(name)
+    assert seen == set(B.EXPORTS)
+
+
 def test_version(lib):
     assert lib.gnn_version() >= 100
 
