@@ -318,7 +318,9 @@ __device__ __forceinline__ void store_part(float* p, int64_t off, const float (&
             *dst = o;
         }
     } else {
-        for (int k = 0; k < n_valid; ++k) p[off + k] = accumulate ? p[off + k] + v[k] : v[k];
+#pragma unroll
+        for (int k = 0; k < VE; ++k)
+            if (k < n_valid) p[off + k] = accumulate ? p[off + k] + v[k] : v[k];
     }
 }
 
@@ -608,286 +610,295 @@ __global__ __launch_bounds__(256, NCH == 1 ? (LPR == 64 ? GNN_SPMM_MINB_WIDE : G
 
 // ---- edge-balanced kernel ------------------------------------------------------------------
 // One workgroup owns up to kStreamMaxRows consecutive entries of the row list, but the work is split
-// by EDGES, not by rows: the rows' neighbour lists are treated as one concatenated stream of E edges and
-// each of the NG lane groups takes a contiguous E/NG stretch of it, LPR edges (one tile) per step.  A row
-// that lies inside one stretch is summed and stored by that group; a row cut by a stretch boundary leaves
-// its pieces in LDS ("carry" slots: at most a head piece and a tail piece per group), and after a barrier the
-// pieces are added in stream order and stored.  So power-law rows cost no imbalance inside the workgroup,
-// tiles are always full, and the result is a fixed-order sum (bit-reproducible).
+// by EDGES, not by rows: the rows' neighbour lists are treated as one concatenated stream, taken in equal pieces of
+// at most kStreamPiece edges, and of a piece each of the NG lane groups takes a contiguous stretch.  A row
+// that lies inside one stretch is summed and stored by that group; of a row cut by stretch boundaries the
+// groups behind its first one leave their sums ("heads") in LDS, and after a barrier the first one adds them in
+// stream order and stores the row, or hands the sum to the next piece.  So power-law rows cost no imbalance inside the
+// workgroup, and the result is a fixed-order sum (bit-reproducible).
 // It serves the column-blocked route: the workgroup id carries (chunk, die) = (id / 8, id % 8); every row is cut to
 // the die's column block through `seg`, and the unscaled float sums go to plane `die` of the partial buffer
 // (a.Y, row index = position in the row list), not to the output matrix.
+//
+// What bounds it: gathers out of a 4 MB L2 run at 33 TB/s on this card and at 17 out of a 7.4 MB block (random 256-byte
+// rows, all dies), so beside the misses every instruction per edge counts: a CU takes 16 clocks for a 1 KB load, the time
+// of 16 vector instructions.  Hence ids are staged for a whole piece at once (one search per lane, then steps along the
+// row ends; the next piece's ids are fetched while this one is gathered), row starts are a bit per edge, tested for the
+// whole wavefront by scalar instructions, and a load's address is one addition to a staged dword.  With a 16-edge tile
+// per group, located by a binary search per edge and tile, 114 M edges of 233 000 rows took (256 columns, the whole call)
+// 8.09 ms in fp32 and 7.67 in bf16 (13.4 backward with a factor per edge), now 7.31, 4.35 and 6.0.  Without
+// misses, row starts and id loads the loop would take 3.9 ms of fp32: the rest is the fabric's (ids are read once a slab).
+// 128-byte slabs, which fit the L2, read the ids twice as often and meet twice the row ends: 8.07 / 4.87 / 7.0.
+// Pieces of 4096 edges, 8 loads in flight, 5 or 7 workgroups per CU, non-temporal id loads: all within 2 % or slower.
 constexpr int kStreamMaxRows = 256;
-#ifndef GNN_SPMM_STREAM_U
-#define GNN_SPMM_STREAM_U 4        // row loads in flight per lane when a lane owns one 16-byte chunk of the row
-#endif
-#ifndef GNN_SPMM_STREAM_MINB
-#define GNN_SPMM_STREAM_MINB 6     // workgroups per CU the register budget is cut for (L2-resident gathers
-                                   // want resident wavefronts more than loads in flight: measured 4/6 > 8/4 > 16/3)
-#endif
-#ifndef GNN_SPMM_WG_EDGES
-#define GNN_SPMM_WG_EDGES 8192     // edges one workgroup aims for when the host picks its row count
-#endif
+constexpr int kStreamLoads = 4;          // row loads in flight per lane
+constexpr int kStreamPiece = 2048;       // edges staged in LDS at a time
+constexpr int kStreamWgEdges = 8192;     // edges one workgroup aims for when the host picks its row count
 
-template <int DT, int VE, int LPR, int NCH, int U, bool SCALED>
-__global__ __launch_bounds__(256, NCH == 1 ? GNN_SPMM_STREAM_MINB : 4) void spmm_stream_kernel(SpmmArgs a) {
+// OFF32: the gathered matrix spans less than 4 GB, so a row's byte offset is a dword beside a scalar base.
+template <int DT, int VE, int LPR, int U, bool SCALED, bool OFF32>
+__global__ __launch_bounds__(256, SCALED ? 4 : 6) void spmm_stream_kernel(SpmmArgs a) {
     using E = Elem<DT, VE>;
     constexpr int RPW = kWave / LPR;
     constexpr int NG = 4 * RPW;
-    constexpr int W = LPR * NCH * VE;  // feature columns per workgroup (grid.y blocks cover F)
-    __shared__ int32_t s_start[kStreamMaxRows], s_voff[kStreamMaxRows + 1], s_v[kStreamMaxRows];
-    __shared__ int32_t s_u_all[4][kWave], s_r_all[4][kWave];   // neighbour id and row slot of every staged edge
-    __shared__ float s_w_all[4][kWave];                        // its scale factor (only with a neighbour scale)
-    __shared__ float s_carry[NG * 2][W];
-    __shared__ int32_t s_ctag[NG * 2];
+    constexpr int W = LPR * VE;              // feature columns per workgroup (grid.y blocks cover F)
+    constexpr int kPiece = kStreamPiece;
+    constexpr int kPad = kPiece / NG + 8;    // a group that ends early reads on to the common length of a stretch
+    constexpr int kIds = kPiece / 256;       // ids a lane fetches for a piece
+    static_assert(8 % U == 0 && kPiece % (NG * 8) == 0, "a stretch is a whole number of rounds");
+    __shared__ int32_t s_delta[kStreamMaxRows], s_voff[kStreamMaxRows + 1], s_row[kStreamMaxRows];
+    __shared__ uint32_t s_empty[kStreamMaxRows / 32];
+    __shared__ __attribute__((aligned(16))) uint32_t s_ent[kPiece + kPad];                       // row offset of every staged edge
+    __shared__ __attribute__((aligned(16))) float s_w[SCALED ? kPiece + kPad : 4];               // its scale factor
+    __shared__ uint32_t s_flag[(kPiece + kPad) / 32 + 3];                                        // bit: the edge begins a row
+    __shared__ __attribute__((aligned(16))) float s_head[NG][W], s_run[2][W];
+    __shared__ int32_t s_head_row[NG], s_run_row[2];
     __shared__ int s_scan[4];
     const int tid = (int)threadIdx.x, lane = lane_id(), wave = tid >> 6;
     const int sub = lane / LPR, sl = lane % LPR;
     const int gi = wave * RPW + sub;
-    int32_t* s_u = s_u_all[wave];
-    int32_t* s_r = s_r_all[wave];
-    float* s_w = s_w_all[wave];
 
-    // ---- phase 0: row descriptors and the exclusive prefix of the row lengths
+    // ---- the rows with edges in this block, and the exclusive prefix of their lengths
     const int rpw = a.rows_per_group;  // rows of the list per workgroup, <= kStreamMaxRows
     const int die = (int)(blockIdx.x % kDies);
     const int64_t chunk0 = (int64_t)(blockIdx.x / kDies) * rpw;
     const int n_chunk = (int)(((int64_t)a.n_active - chunk0) < rpw ? ((int64_t)a.n_active - chunk0) : rpw);
-    float* const part = (float*)a.Y + (int64_t)die * a.n_active * a.ldy;
-    int len = 0;
+    float* const part = (float*)a.Y + ((int64_t)die * a.n_active + chunk0) * a.ldy;
+    int len = 0, first = 0;
     if (tid < n_chunk) {
-        const int32_t v = (int32_t)(chunk0 + tid);
-        const int32_t* cut = a.seg + (int64_t)v * (a.n_blocks + 1) + a.block0 + die;
-        const int32_t s = cut[0];
-        const int32_t e = a.seg_end ? a.seg_end[(int64_t)v * a.n_blocks + a.block0 + die] : cut[1];
-        s_v[tid] = v;
-        s_start[tid] = s;
-        len = e - s;
+        const int64_t v = chunk0 + tid;
+        const int32_t* cut = a.seg + v * (a.n_blocks + 1) + a.block0 + die;
+        first = cut[0];
+        const int32_t e = a.seg_end ? a.seg_end[v * a.n_blocks + a.block0 + die] : cut[1];
+        len = e - first;
     }
-    if (tid < NG * 2) s_ctag[tid] = -1;
-    int n_edges;
+    int n_edges, n_rows;
     const int voff = block_exclusive_scan<256>(len, s_scan, &n_edges);
-    if (tid < n_chunk) s_voff[tid] = voff;
-    if (tid == 0) s_voff[n_chunk] = n_edges;
+    const int slot = block_exclusive_scan<256>(len > 0 ? 1 : 0, s_scan, &n_rows);
+    if (len > 0) {
+        s_voff[slot] = voff;
+        s_delta[slot] = first - voff;
+        s_row[slot] = tid;
+    }
+    if (tid == 0) s_voff[n_rows] = n_edges;
+    if (tid < 2) s_run_row[tid] = -1;
+    const uint64_t empty = __ballot(tid < n_chunk && len == 0);
+    if (lane < 2) s_empty[wave * 2 + lane] = (uint32_t)(empty >> (32 * lane));
     __syncthreads();
 
-    int per = (n_edges + NG - 1) / NG;
-    per = (per + LPR - 1) / LPR * LPR;
-    const int64_t lo64 = (int64_t)gi * per < n_edges ? (int64_t)gi * per : n_edges;
-    const int lo = (int)lo64, hi = (int)(lo64 + per < n_edges ? lo64 + per : n_edges);  // this group's stretch of the stream
-
-    int64_t col_off[NCH];
-    bool col_ok[NCH];
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-        col_off[c] = (int64_t)blockIdx.y * W + (int64_t)(sl + c * LPR) * VE;
-        col_ok[c] = col_off[c] < a.F;
-    }
-    // per-lane base address of its 16-byte chunk(s) of a row of X: column col_off, or column 0 for the lanes past
-    // F (whose sums are never stored); a neighbour's row then adds its offset, staged in 16-byte units
+    const int64_t col_off = (int64_t)blockIdx.y * W + (int64_t)sl * VE;
+    const bool col_ok = col_off < a.F;
+    const int n_valid = (int64_t)a.F - col_off >= VE ? VE : (int)((int64_t)a.F - col_off);
+    // the slab's first column, and a lane's 16 bytes in it (bytes 0 for the lanes past F, whose sums are never stored); a
+    // neighbour's row then adds its offset: bytes, or 16-byte units where a dword of bytes does not reach
     constexpr int ES = DT == GNN_F32 ? 4 : 2;
-    const char* x_lane[NCH];
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) x_lane[c] = (const char*)a.X + (col_ok[c] ? col_off[c] : 0) * ES;
-    const uint32_t row16 = (uint32_t)(a.ldx * ES / 16);
-    float acc[NCH][VE];
-#pragma unroll
-    for (int c = 0; c < NCH; ++c)
-#pragma unroll
-        for (int k = 0; k < VE; ++k) acc[c][k] = 0.f;
-
-    // Row slot and position in col_idx of stream position t0 + sl (rows only move forward: r_hint).
-    int r_hint = 0;
-    auto locate = [&](int t0, int& r, int32_t& p) -> bool {
-        const int t = t0 + sl;
-        r = 0;
-        p = 0;
-        if (t >= hi) return false;
-        int x = r_hint, y = n_chunk;  // s_voff[x] <= t < s_voff[y]
+    const char* const x_slab = (const char*)a.X + (int64_t)blockIdx.y * W * ES;
+    const uint32_t lane_off = col_ok ? (uint32_t)(sl * 16) : 0u;
+    const uint32_t row_units = (uint32_t)(OFF32 ? a.ldx * ES : a.ldx * ES / 16);
+    // slot of the row that holds stream position t
+    auto row_of = [&](int t) {
+        int x = 0, y = n_rows;
         while (y - x > 1) {
             const int m = (x + y) >> 1;
             if (s_voff[m] <= t) x = m;
             else y = m;
         }
-        r_hint = x;
-        r = x;
-        p = s_start[x] + (t - s_voff[x]);
-        return true;
+        return x;
+    };
+    auto store_row = [&](int row, const float (&v)[VE]) {
+        if (col_ok) store_part<VE>(part, (int64_t)s_row[row] * a.ldy + col_off, v, n_valid, a.accumulate != 0);
     };
 
-    int cur = -1;  // row slot the accumulators belong to (uniform over the group)
-    auto flush = [&]() {
-        const int b0 = s_voff[cur], b1 = s_voff[cur + 1];
-        if (b0 >= lo && b1 <= hi) {  // the whole row lies in this stretch
-            const int32_t v = s_v[cur];
+    const int n_pieces = (n_edges + kPiece - 1) / kPiece;
+    const int piece = n_pieces > 0 ? (((n_edges + n_pieces - 1) / n_pieces) + 7) / 8 * 8 : 1;   // equal pieces
+    // a piece's ids: a wave takes a stretch of its own, 64 consecutive edges a step; fetched while the piece before is gathered
+    uint32_t u[kIds];
+    float w[kIds];
+    uint32_t begins = 0;     // bit i: this lane's i-th edge begins a row
+    auto fetch = [&](int t0) {
+        const int n = n_edges - t0 < piece ? n_edges - t0 : piece;
+        const int steps = (n + 255) / 256;
+        const int k = wave * steps * kWave + lane;
+        int x = 0, begin = 0, end = 0, delta = 0;
+        if (k < n) {
+            x = row_of(t0 + k);
+            begin = s_voff[x];
+            end = s_voff[x + 1];
+            delta = s_delta[x];
+        }
+        begins = 0;
 #pragma unroll
-            for (int c = 0; c < NCH; ++c) {
-                if (col_ok[c]) {
-                    const int64_t rest = (int64_t)a.F - col_off[c];
-                    const int n_valid = rest >= VE ? VE : (int)rest;
-                    store_part<VE>(part, (int64_t)v * a.ldy + col_off[c], acc[c], n_valid, a.accumulate != 0);
+        for (int i = 0; i < kIds; ++i) {
+            const int t = t0 + k + i * kWave;
+            int32_t p = 0;
+            if (k + i * kWave < n && i < steps) {
+                if (t >= end) {
+                    do {
+                        begin = end;
+                        end = s_voff[++x + 1];
+                    } while (t >= end);
+                    delta = s_delta[x];
+                }
+                if (t == begin) begins |= 1u << i;
+                p = t + delta;
+            }
+            u[i] = (uint32_t)a.col_idx[p];
+            w[i] = SCALED ? a.edge_w[p] : 1.f;
+        }
+    };
+    if (n_edges > 0) fetch(0);
+    for (int t0 = 0, turn = 0; t0 < n_edges; t0 += piece, turn ^= 1) {
+        const int n = n_edges - t0 < piece ? n_edges - t0 : piece;
+        const int per = ((n + NG - 1) / NG + 7) / 8 * 8;    // edges of a group's stretch
+        {
+            const int steps = (n + 255) / 256;
+            const int k = wave * steps * kWave + lane;
+#pragma unroll
+            for (int i = 0; i < kIds; ++i) {
+                if (i < steps) {        // uniform
+                    const int q = k + i * kWave;
+                    if (q < n) {
+                        s_ent[q] = u[i] * row_units;
+                        if (SCALED) s_w[q] = w[i];
+                    }
+                    const uint64_t b = __ballot((begins >> i) & 1u);
+                    if (lane < 2) s_flag[((q - lane) >> 5) + lane] = (uint32_t)(b >> (32 * lane));
                 }
             }
-        } else {  // a piece: head (the row began in an earlier stretch) or tail (it goes on in the next one)
-            const int slot = gi * 2 + (b0 < lo ? 0 : 1);
-#pragma unroll
-            for (int c = 0; c < NCH; ++c)
-#pragma unroll
-                for (int k = 0; k < VE; ++k) s_carry[slot][(sl + c * LPR) * VE + k] = acc[c][k];
-            if (sl == 0) s_ctag[slot] = cur;
+            for (int q = n + tid; q < n + per; q += 256) s_ent[q] = 0;   // a valid row, never added
         }
+        __syncthreads();     // (also: the cut rows of the piece before have been read)
+        if (t0 + piece < n_edges) fetch(t0 + piece);
+        const int lo = gi * per < n ? gi * per : n;
+        const int cnt = n - lo < per ? n - lo : per;        // this group's stretch: edges lo .. lo + cnt of the piece
+        const int at = cnt > 0 ? lo : 0;
+        int cur = 0, head_row = -1;
+        bool cut = false;          // the accumulators' row began in an earlier stretch
+        float acc[VE];
 #pragma unroll
-        for (int c = 0; c < NCH; ++c)
-#pragma unroll
-            for (int k = 0; k < VE; ++k) acc[c][k] = 0.f;
-    };
-
-    // ---- phase 1: ids (and their scale factors, stored per edge by the prepare pass) are fetched two tiles ahead,
-    // coalesced, each lane for its own edge, so the gather loop below touches global memory for feature rows only
-    int t_c = lo;
-    int r_c, r_n;
-    int32_t p_c, p_n;
-    // (a lane without an edge reads position 0 / vertex 0: the prefetches stay unconditional, see below)
-    bool v_c = locate(t_c, r_c, p_c);
-    bool v_n = locate(t_c + LPR, r_n, p_n);
-    int32_t u_c = a.col_idx[p_c];
-    int32_t u_n = a.col_idx[p_n];
-    if (!v_c) u_c = 0;
-    if (!v_n) u_n = 0;
-    float w_c = 1.f, w_n = 1.f;
-    if (SCALED) {
-        w_c = a.edge_w[p_c];
-        w_n = a.edge_w[p_n];
-    }
-    while (__ballot(t_c < hi) != 0ull) {  // uniform over the wave
-        wave_lds_sync();  // the previous tile has been consumed
-        // what is staged is the neighbour's row offset in 16-byte units (one multiply per lane and tile instead of
-        // a 64-bit multiply per edge in the gather loop); 0 where the lane has no edge: a valid row all the same
-        s_u[lane] = (int32_t)((uint32_t)u_c * row16);
-        s_r[lane] = r_c;
-        if (SCALED) s_w[lane] = w_c;
-        int cnt = hi - t_c;
-        cnt = cnt < 0 ? 0 : (cnt < LPR ? cnt : LPR);
-        int cnt_max = cnt, cnt_min = cnt;
-#pragma unroll
-        for (int d = LPR; d < kWave; d <<= 1) {
-            cnt_max = max(cnt_max, __shfl_xor(cnt_max, d, kWave));
-            cnt_min = min(cnt_min, __shfl_xor(cnt_min, d, kWave));
+        for (int k = 0; k < VE; ++k) acc[k] = 0.f;
+        if (cnt > 0) {
+            cur = row_of(t0 + lo);
+            cut = s_voff[cur] < t0 + lo;
         }
-        // bit k of `starts`: edge k of this group's tile belongs to another row than the edge before it
-        // (edge 0: than the accumulators); the gather loop reads one dword per edge (the id) and looks up
-        // the row slot only where a row starts
-        const int r_before = __shfl_up(r_c, 1, kWave);
-        const bool start = v_c && r_c != (sl == 0 ? cur : r_before);
-        const uint64_t starts = (__ballot(start) >> (sub * LPR)) & (LPR == 64 ? ~0ull : (1ull << (LPR & 63)) - 1ull);
-        wave_lds_sync();
-        // the prefetches go out right before this tile's gathers (everything older has been waited for by now)
-        int r_nn;
-        int32_t p_nn;
-        const bool v_nn = locate(t_c + 2 * LPR, r_nn, p_nn);
-        int32_t u_nn = a.col_idx[p_nn];
-        float w_nn = 1.f;
-        if (SCALED) w_nn = a.edge_w[p_nn];
-
+        auto end_row = [&]() {     // the accumulators' row has ended inside this stretch
+            if (cut) {
+                head_row = cur;
 #pragma unroll
-        for (int k0 = 0; k0 < LPR; k0 += U) {
-            if (k0 >= cnt_max) break;  // uniform over the wave
-            // The loads are unconditional (a slot past the group's count holds row 0, a column past F reads
-            // column 0: both valid addresses, the values are never used): with branches around them the compiler
-            // waits for every load before issuing the next one.
-            typename E::Raw x[U][NCH];
-            float w[U];
-#pragma unroll
-            for (int j = 0; j < U; ++j) {
-                const uint64_t row_bytes = (uint64_t)(uint32_t)s_u[sub * LPR + k0 + j] << 4;
-                w[j] = SCALED ? s_w[sub * LPR + k0 + j] : 1.f;
-#pragma unroll
-                for (int c = 0; c < NCH; ++c) x[j][c] = *(const typename E::Raw*)(x_lane[c] + row_bytes);
-            }
-            // common case, decided for the whole wave: every group has a full tile and no row starts inside this
-            // round -> plain multiply-adds; else each edge checks its count and its row-start bit
-            const bool round_has_start = ((starts >> k0) & ((1ull << U) - 1ull)) != 0ull;
-            if (cnt_min == LPR && __ballot(round_has_start) == 0ull) {
-#pragma unroll
-                for (int j = 0; j < U; ++j)
-#pragma unroll
-                    for (int c = 0; c < NCH; ++c) E::fma(acc[c], w[j], x[j][c]);
+                for (int k = 0; k < VE; ++k) s_head[gi][sl * VE + k] = acc[k];
             } else {
+                store_row(cur, acc);
+            }
+        };
+        for (int k1 = 0; k1 < per; k1 += 32) {
+            // bit k of `starts`: edge k1 + k of this group's stretch begins a row; `any`: of some group of the wave
+            const int q = at + k1;
+            uint32_t starts = __builtin_amdgcn_alignbit(s_flag[(q >> 5) + 1], s_flag[q >> 5], (uint32_t)q & 31u);
+            if (k1 == 0) starts &= ~1u;                     // the stretch's first edge continues the accumulators' row
+            const int left = per - k1 < 32 ? per - k1 : 32;
+            uint32_t any = starts;
+#pragma unroll
+            for (int d = LPR; d < kWave; d <<= 1) any |= __shfl_xor(any, d, kWave);
+            any = __builtin_amdgcn_readfirstlane(any);
+#pragma unroll 1
+            for (int k0 = 0; k0 < left; k0 += U) {
+                // The loads are unconditional (past the group's count lies row 0 or another group's edge, a column past F
+                // reads the slab's first column: valid addresses, the values are never used): with branches around them
+                // the compiler waits for every load before issuing the next one.
+                typename E::Raw x[U];
+                float wt[U];
 #pragma unroll
                 for (int j = 0; j < U; ++j) {
-                    if (k0 + j < cnt) {
-                        if ((starts >> (k0 + j)) & 1ull) {
-                            if (cur >= 0) flush();
-                            cur = s_r[sub * LPR + k0 + j];
-                        }
+                    const uint32_t off = s_ent[q + k0 + j];
+                    wt[j] = SCALED ? s_w[q + k0 + j] : 1.f;
+                    if (OFF32) x[j] = *(const typename E::Raw*)(x_slab + (off + lane_off));
+                    else x[j] = *(const typename E::Raw*)(x_slab + (((uint64_t)off << 4) + lane_off));
+                }
+                // the common round: all groups have its edges and none of them begins a row (scalar test)
+                const bool full = __ballot(cnt < k1 + k0 + U) == 0ull;
+                if (full && ((any >> k0) & ((1u << U) - 1u)) == 0u) {
 #pragma unroll
-                        for (int c = 0; c < NCH; ++c) E::fma(acc[c], w[j], x[j][c]);
+                    for (int j = 0; j < U; ++j) E::fma(acc, wt[j], x[j]);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < U; ++j) {
+                        if (k1 + k0 + j < cnt) {
+                            if ((starts >> (k0 + j)) & 1u) {
+                                end_row();
+                                cut = false;
+                                ++cur;
+#pragma unroll
+                                for (int k = 0; k < VE; ++k) acc[k] = 0.f;
+                            }
+                            E::fma(acc, wt[j], x[j]);
+                        }
                     }
                 }
             }
         }
-        t_c += LPR;
-        r_c = r_n; p_c = p_n; v_c = v_n; u_c = u_n; w_c = w_n;
-        r_n = r_nn; p_n = p_nn; v_n = v_nn; u_n = v_nn ? u_nn : 0; w_n = w_nn;
-    }
-    if (cur >= 0) flush();
-    __syncthreads();
-
-    // ---- phase 2: rows cut by stretch boundaries - their pieces sit in consecutive carry slots
-    for (int col = tid; col < W; col += 256) {
-        const int64_t gcol = (int64_t)blockIdx.y * W + col;
-        if (gcol >= a.F) continue;
-        int tag = -1;
-        float sum = 0.f;
-        for (int q = 0; q <= NG * 2; ++q) {
-            const int tq = q < NG * 2 ? s_ctag[q] : -2;
-            if (tq == -1) continue;
-            if (tq != tag) {
-                if (tag >= 0) {
-                    float o[1] = {sum};
-                    const int64_t off = (int64_t)s_v[tag] * a.ldy + gcol;
-                    store_part<1>(part, off, o, 1, a.accumulate != 0);
-                }
-                tag = tq;
-                sum = 0.f;
-            }
-            if (tq >= 0) sum += s_carry[q][col];
+        bool tail = false;         // the accumulators' row goes on in the next stretch
+        if (cnt > 0) {
+            tail = !cut && s_voff[cur + 1] > t0 + lo + cnt;
+            if (!tail) end_row();
         }
-    }
-    // ---- phase 3: rows without any edge are zero (they never show up in the stream)
-    if (!a.accumulate) {
-        for (int r = gi; r < n_chunk; r += NG) {
-            if (s_voff[r + 1] != s_voff[r]) continue;
-            const int32_t v = s_v[r];
+        if (sl == 0) s_head_row[gi] = head_row;
+        __syncthreads();
+        // ---- rows cut by stretch boundaries: the group where the row began (group 0 for the row that came out of the piece
+        // before) adds the heads of the groups behind it, in stream order
+        int row = tail ? cur : -1, g = gi + 1;
+        for (int pass = 0; pass < 2; ++pass) {
+            if (pass == 1) {
+                if (gi != 0) break;
+                row = s_run_row[turn];
+                g = 0;
 #pragma unroll
-            for (int c = 0; c < NCH; ++c) {
-                if (col_ok[c]) {
-                    float o[VE];
-#pragma unroll
-                    for (int k = 0; k < VE; ++k) o[k] = 0.f;
-                    const int64_t rest = (int64_t)a.F - col_off[c];
-                    const int n_valid = rest >= VE ? VE : (int)rest;
-                    store_part<VE>(part, (int64_t)v * a.ldy + col_off[c], o, n_valid, false);
-                }
+                for (int k = 0; k < VE; ++k) acc[k] = s_run[turn][sl * VE + k];
             }
+            if (row < 0) continue;
+            for (; g < NG && s_head_row[g] == row; ++g)
+#pragma unroll
+                for (int k = 0; k < VE; ++k) acc[k] += s_head[g][sl * VE + k];
+            if (s_voff[row + 1] > t0 + n) {      // goes on in the next piece
+#pragma unroll
+                for (int k = 0; k < VE; ++k) s_run[turn ^ 1][sl * VE + k] = acc[k];
+                if (sl == 0) s_run_row[turn ^ 1] = row;
+            } else {
+                store_row(row, acc);
+            }
+        }
+        if (gi == 0 && sl == 0) s_run_row[turn] = -1;
+    }
+    // ---- rows without any edge are zero (they never show up in the stream)
+    if (!a.accumulate) {
+        float zero[VE];
+#pragma unroll
+        for (int k = 0; k < VE; ++k) zero[k] = 0.f;
+        for (int r = gi; r < n_chunk; r += NG) {
+            if (!((s_empty[r >> 5] >> (r & 31)) & 1u) || !col_ok) continue;
+            store_part<VE>(part, (int64_t)r * a.ldy + col_off, zero, n_valid, false);
         }
     }
 }
 
-template <int DT, int VE, int LPR, int NCH>
-static int32_t launch_stream(const SpmmArgs& a, int64_t avg_row, hipStream_t stream) {
-    constexpr int U = NCH == 1 ? GNN_SPMM_STREAM_U : (NCH == 2 ? 4 : (NCH == 3 ? 3 : 2));
-    constexpr int W = LPR * NCH * VE;
-    // rows per workgroup: about GNN_SPMM_WG_EDGES edges, while the launch keeps a few thousand workgroups
+template <int DT, int VE, int LPR>
+static int32_t launch_stream(const SpmmArgs& a, int64_t avg_row, bool off32, hipStream_t stream) {
+    constexpr int U = kStreamLoads;
+    constexpr int W = LPR * VE;
+    // rows per workgroup: about kStreamWgEdges edges, while the launch keeps a few thousand workgroups
     SpmmArgs b = a;
-    int64_t rows = (int64_t)GNN_SPMM_WG_EDGES / (avg_row < 1 ? 1 : avg_row);
+    int64_t rows = (int64_t)kStreamWgEdges / (avg_row < 1 ? 1 : avg_row);
     const int64_t cap = (int64_t)a.n_active * kDies / 4096;
     if (rows > cap) rows = cap;
     b.rows_per_group = (int32_t)(rows < 16 ? 16 : (rows > kStreamMaxRows ? kStreamMaxRows : rows));
     const int64_t n_chunks = ((int64_t)a.n_active + b.rows_per_group - 1) / b.rows_per_group;
     dim3 grid((unsigned)(n_chunks * kDies), (unsigned)((a.F + W - 1) / W));
-    if (a.edge_w) spmm_stream_kernel<DT, VE, LPR, NCH, U, true><<<grid, 256, 0, stream>>>(b);
-    else spmm_stream_kernel<DT, VE, LPR, NCH, U, false><<<grid, 256, 0, stream>>>(b);
+    if (off32) {
+        if (a.edge_w) spmm_stream_kernel<DT, VE, LPR, U, true, true><<<grid, 256, 0, stream>>>(b);
+        else spmm_stream_kernel<DT, VE, LPR, U, false, true><<<grid, 256, 0, stream>>>(b);
+    } else {
+        if (a.edge_w) spmm_stream_kernel<DT, VE, LPR, U, true, false><<<grid, 256, 0, stream>>>(b);
+        else spmm_stream_kernel<DT, VE, LPR, U, false, false><<<grid, 256, 0, stream>>>(b);
+    }
     GNN_LAUNCH_CHECK("spmm_stream_kernel");
     return GNN_OK;
 }
@@ -1174,6 +1185,7 @@ struct BlockedPlan {
     size_t xs_bytes = 0;                   // fp32 with a neighbour scale: the gathered matrix with its rows scaled
     size_t w_bytes = 0;                    // bf16 with a neighbour scale: the factor of every copied id
     int64_t avg_seg = 0;      // average neighbours of a row inside one column block
+    bool off32 = false;       // the gathered matrix spans less than 4 GB
     int32_t n_cols = 0;
     int32_t limit = 0;        // neighbour ids >= limit are never gathered (n_cols without a source prefix)
     size_t bounds_bytes = 0;  // with a filter: the column-block boundaries (balanced over the active vertices)
@@ -1199,6 +1211,7 @@ static BlockedPlan plan_blocked(const gnn_csr* g, int32_t n_active, int32_t F, i
     p.passes = passes;
     p.n_blocks = n_blocks;
     p.avg_seg = avg_row / n_blocks;
+    p.off32 = (int64_t)g->n_cols * row_bytes < ((int64_t)1 << 32);
     p.block_size = (int32_t)(((int64_t)n_src + n_blocks - 1) / n_blocks);
     p.limit = n_src;
     p.ldp = ((int64_t)F + 7) / 8 * 8;
@@ -1265,7 +1278,7 @@ static int32_t run_blocked(const SpmmArgs& a, const BlockedPlan& p, void* ws, hi
     for (int pass = 0; pass < p.passes; ++pass) {
         b.block0 = pass * kDies;
         b.accumulate = pass > 0;
-        GNN_CHECK((launch_stream<DT, VE, 16, 1>(b, p.avg_seg, stream)));
+        GNN_CHECK((launch_stream<DT, VE, kSlabBytes / 16>(b, p.avg_seg, p.off32, stream)));
     }
     spmm_sum_parts_kernel<DT><<<grid_for((int64_t)a.n_active * ((a.F + 3) / 4), 256, 1 << 16), 256, 0, stream>>>(
         part, p.ldp, a.rows, a.n_active, a.F, a.Y, a.ldy, a.out_scale, a.accumulate, a.relu_h, a.ldh);

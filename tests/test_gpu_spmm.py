@@ -294,6 +294,45 @@ def test_blocked_route_backward_with_filter(dtype, accumulate):
     _bwd_case(g, 136, 136, dtype, 2, 2, accumulate, 45, ws=ws, relu=True)  # the plane sum undoes the ReLU in front
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("wide", [False, True])
+def test_blocked_route_row_lengths(dtype, wide):
+    """Rows without an edge in a block, of one edge, of a stretch and its neighbours, and over several staged pieces, in
+    runs of like length; with a gathered matrix below and above 4 GB (its rows far apart)."""
+    import paper_2311_06837_amd as P
+    n_rows, n_cols, F = 4999, 70_001, 75
+    rng = np.random.default_rng(8)
+    lens = np.full(n_rows, 130)
+    lens[100:400] = 0
+    lens[400:700] = 1
+    lens[700:1000] = rng.integers(0, 70, 300)
+    lens[1000:1003] = [n_cols, 0, n_cols]
+    lens[1500:1520] = 9000
+    lens[-1] = n_cols
+    cols = [np.sort(rng.choice(n_cols, k, replace=False)).astype(np.int32) for k in lens]
+    cols[2000] = np.arange(130, dtype=np.int32)                      # all in one block
+    lens[2000] = 130
+    rp = np.zeros(n_rows + 1, np.int32)
+    rp[1:] = np.cumsum(lens)
+    G = P.Graph(torch.from_numpy(rp).cuda(), torch.from_numpy(np.concatenate(cols)).cuda(), n_cols=n_cols, sorted_columns=True)
+    ld = (1 << 32) // n_cols // dtype.itemsize // 64 * 64 + 64 if wide else 80
+    X = torch.empty((n_cols, ld), dtype=dtype, device="cuda")
+    assert (X.numel() * dtype.itemsize >= 1 << 32) == wide
+    X[:, :F] = torch.from_numpy(rng.standard_normal((n_cols, F)).astype(np.float32)).cuda()
+    Y = torch.zeros((n_rows, 80), dtype=dtype, device="cuda")
+    ws = P.Workspace()
+    P.gnn_masked_spmm_fwd(G, None, n_rows, X, Y, F, ws=ws)
+    assert _used_blocked_route(ws)
+    x = X[:, :F].double().cpu().numpy()
+    want = np.stack([x[c].sum(0) for c in cols])
+    size = np.stack([np.abs(x[c]).sum(0) for c in cols])
+    got = Y[:, :F].double().cpu().numpy()
+    # fp32 sums in any order: at most (terms + 8 planes) * 2^-24 of the sum of magnitudes; then bf16 rounding, 2^-8 of the value
+    tol = (lens[:, None] + 8) * 2.0 ** -24 * size + (2.0 ** -8 * np.abs(want) if dtype == torch.bfloat16 else 0.0)
+    assert (np.abs(got - want) <= tol).all()
+    assert not Y[:, F:].any()
+
+
 def test_blocked_route_falls_back_without_promise_or_density():
     """Unsorted columns (no GNN_CSR_SORTED_COLUMNS promise) or a sparse graph: the size query reports 0 and the
     call gathers whole rows."""
