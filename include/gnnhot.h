@@ -24,8 +24,7 @@
  *   - `stream` is a hipStream_t (NULL = the default stream).  All work is enqueued on it and
  *     nothing synchronises, except where a *_host output is requested (documented below).
  *   - Matrices are row-major with an explicit leading dimension in ELEMENTS (int64).
- *     dtype GNN_F32: float storage and arithmetic (a product may run as sums of bfloat16 products that
- *     add up to the float product; infinities, NaN and overflow as in float).  dtype GNN_BF16: bfloat16 storage,
+ *     dtype GNN_F32: float storage and arithmetic.  dtype GNN_BF16: bfloat16 storage,
  *     float accumulation; weight and bias gradients are float in both cases.
  *   - Rows that a call is not asked to produce are neither read nor written.
  *   - Every function returns a gnn_status.  Nothing throws, aborts or prints.
@@ -225,7 +224,7 @@ int32_t gnn_fused_layer_fwd(const gnn_csr *g, const int32_t *rows, int32_t n_act
  * gnn_linear_fwd for callers that cannot allocate device memory and so have no workspace to hand over: code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments without
  * (ws, ws_bytes), same kernels, same bits.  The two transposed weight copies go to an array that the library
- * holds in device memory on every GPU it runs on until the process ends (16 MiB); no hipMalloc / hipFree or other
+ * holds in device memory on every GPU it runs on until the process ends (8 MiB); no hipMalloc / hipFree or other
  * allocating call is made.
  *   limit      N * round_up(K, 16 bytes) * element size <= 4 MiB per weight matrix (1024 x 1024 floats,
  *              2048 x 1024 bf16); beyond it GNN_ERR_UNSUPPORTED - use gnn_linear_fwd

@@ -1029,399 +1029,6 @@ __global__ __launch_bounds__(256, NTW == 4 ? 2 : 3) void gemm_nt_line_kernel(Gem
 #undef GNN_QUARTERS
 }
 
-// ------------------------------------------------------------------------------------------
-// gemm_nt, fp32 on the bf16 matrix cores.  The fp32 MFMAs set the time of the wide variant (116 of the
-// 153 TFLOP/s that a large library product reaches here), and bf16 MFMAs are sixteen times as fast.
-// A float is the exact sum of three bf16 numbers (each the rounding of what the ones before it leave:
-// 8 + 8 + 8 significant bits), so a product of two floats is nine bf16 products; the three smallest,
-// below 2^-25 of it, are left out.  The six others of a slice of sixteen reduction elements meet in a sum
-// of their own, which is added to the accumulator: the error against 64 bits
-// is half of that with fp32 MFMAs.  Measured, 600 001 rows, 2 x 256 -> 256: 1.40 -> 0.91 ms, error 2.5e-7
-// -> 1.1e-7 (all six products straight into the accumulator: 0.81 ms, but 2.7e-7); 602 -> 256, 233 000
-// rows: 0.72 -> 0.44 ms; 200 rows: 80 -> 64 us.
-//
-// The weights are split once per call into slices of sixteen reduction elements, [slice][row][part][16],
-// zero-padded: the slab of a tile is one contiguous copy, moved into LDS without passing through
-// registers.  The other operand is split on its way from registers to LDS, once per workgroup.  A row
-// of a slice is 96 bytes in LDS, so sixteen consecutive 16-byte reads fall into different banks.  A step
-// is: all fragments of the slice to registers; barrier; the next slab and the next rows on their way to
-// LDS while the 12 * NTW MFMAs run; barrier.  Two workgroups per CU: one reads while the other multiplies.
-//
-// Both operands are multiplied by 2^32 before they are split, so that the parts of the smallest floats
-// are within the range of bf16 too (without it the error grew below 1e-33), and the sum by 2^-64 in the
-// end.  A value without a split (infinite, NaN, from 2^95) leaves a NaN among its parts, which reaches every
-// sum it takes part in, and a sum from 2^64 overflows: a tile with such a sum is computed again with fp32
-// MFMAs straight from memory before anything is stored.
-// ------------------------------------------------------------------------------------------
-constexpr int kSplitK = 16;                                 // reduction elements per slice
-constexpr int kSplitRow = 3 * kSplitK * 2;                  // bytes of one row of a slice
-constexpr size_t kSplitMaxBytes = (size_t)8 << 20;          // largest split weight matrix (what the static entry point holds)
-constexpr int kSplitPrepRows = 128;                         // (slice, row) pairs per workgroup of the preparation
-
-struct GemmSplit : GemmNT {
-    const char* Bp[2];         // split weights
-    int32_t n_pad;             // rows of a slice of them
-    const float* W[2];         // the weights themselves: element (k, n) at k * w_k + n * w_n
-    int64_t w_k, w_n;
-};
-
-constexpr float kSplitScale = 4294967296.f;               // 2^32
-constexpr float kSplitUnscale = 1.f / (kSplitScale * kSplitScale);
-
-// the three parts of eight floats times 2^32
-__device__ __forceinline__ void split8(const u32x4& lo, const u32x4& hi, u32x4 (&part)[3]) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const uint32_t b0 = q < 2 ? lo[2 * q] : hi[2 * q - 4], b1 = q < 2 ? lo[2 * q + 1] : hi[2 * q - 3];
-        float x0 = __uint_as_float(b0) * kSplitScale, x1 = __uint_as_float(b1) * kSplitScale;
-        const uint32_t w0 = pack_bf16(x0, x1);
-        x0 -= bf16lo(w0);
-        x1 -= bf16hi(w0);
-        const uint32_t w1 = pack_bf16(x0, x1);
-        x0 -= bf16lo(w1);
-        x1 -= bf16hi(w1);
-        part[0][q] = w0;
-        part[1][q] = w1;
-        part[2][q] = pack_bf16(x0, x1);
-    }
-}
-
-// One thread per half row of a slice.  The element (k, n) of source blockIdx.y lies at k * w_k + n * w_n.
-__global__ __launch_bounds__(256) void split_weights_kernel(const float* __restrict__ W0, const float* __restrict__ W1, int64_t w_k, int64_t w_n,
-                                                            int32_t K, int32_t N, int32_t n_pad, char* __restrict__ out0, char* __restrict__ out1) {
-    const float* W = blockIdx.y ? W1 : W0;
-    char* out = blockIdx.y ? out1 : out0;
-    const int64_t rows = (int64_t)((K + kSplitK - 1) / kSplitK) * n_pad;
-    const int half = (int)threadIdx.x / kSplitPrepRows;           // consecutive threads: consecutive rows
-    const int64_t r = (int64_t)blockIdx.x * kSplitPrepRows + threadIdx.x % kSplitPrepRows;
-    if (r < rows) {
-        const int32_t n = (int32_t)(r % n_pad), k0 = (int32_t)(r / n_pad) * kSplitK + half * 8;
-        u32x4 x[2], part[3];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[e >> 2][e & 3] = (n < N && k0 + e < K) ? __float_as_uint(W[(int64_t)(k0 + e) * w_k + (int64_t)n * w_n]) : 0u;
-        split8(x[0], x[1], part);
-#pragma unroll
-        for (int p = 0; p < 3; ++p) *(u32x4*)(out + r * kSplitRow + p * (kSplitK * 2) + half * 16) = part[p];
-    }
-}
-
-template <int NTW, bool KTAIL>
-__global__ __launch_bounds__(256, 2) void gemm_nt_split_kernel(GemmSplit a) {
-    constexpr int BM = 128, BN = 64 * NTW, MT = 2, NT = NTW, WTN = 32 * NTW;
-    constexpr int ROW = kSplitRow / 4;                       // words per row of a slice in LDS
-    constexpr int B_CH = BN * kSplitRow / (256 * 16);        // 16-byte chunks of the slab per thread
-    constexpr int CW = 64;                                   // columns of one staged output piece (256 bytes)
-    constexpr int CROW = CW + 4;                             // words per staged row
-    constexpr int STAGE = 32 * CROW;                         // words per wave
-    constexpr int SMEM = (BM + BN) * ROW > 4 * STAGE ? (BM + BN) * ROW : 4 * STAGE;
-    __shared__ __attribute__((aligned(16))) uint32_t smem[SMEM];
-    __shared__ float s_bias[BN];
-    __shared__ int32_t s_crow[BM];
-    uint32_t* sA = smem;
-    uint32_t* sB = smem + BM * ROW;
-
-    const int tiles_n = (a.N + BN - 1) / BN;
-    const int m0 = (int)(blockIdx.x / tiles_n) * BM, n0 = (int)(blockIdx.x % tiles_n) * BN;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int li = lane & 31, g = lane >> 5;
-    const int ld_row = tid >> 1, ld_h = tid & 1;             // loader: row of the tile, half of the slice
-
-    auto row_of = [&](int r) -> int64_t {                    // operand row r of the tile (past M: an addressable one)
-        const int m = m0 + r;
-        return m < a.M ? (a.a_rows ? (int64_t)a.a_rows[m] : (int64_t)m) : (a.a_rows ? (int64_t)a.a_rows[0] : 0);
-    };
-    const int64_t ao = row_of(ld_row) * a.lda;
-    const int k_slices = (a.K + kSplitK - 1) / kSplitK;
-    const int n_steps = k_slices * ((a.n_src == 2 && m0 >= a.M1) ? 1 : a.n_src);   // a tile past M1 has one source only
-    const bool z = m0 + ld_row >= a.M1;                      // this row has no second source
-
-    v16f acc[MT][NT];
-    u32x4 ra0, ra1;
-// rows of slice step_ (beyond the last one: the last one again)
-#define GNN_LOAD_A(step_)                                                                   \
-    {                                                                                       \
-        const int st_ = (step_) < n_steps ? (step_) : n_steps - 1;                          \
-        const int src_ = st_ >= k_slices ? 1 : 0;                                           \
-        const int k_ = (st_ - src_ * k_slices) * kSplitK + ld_h * 8;                        \
-        const float* p_ = (const float*)(src_ ? a.A[1] : a.A[0]) + ao;                      \
-        ra0 = *(const u32x4*)(p_ + (!KTAIL || k_ < a.K ? k_ : 0));                          \
-        ra1 = *(const u32x4*)(p_ + (!KTAIL || k_ + 4 < a.K ? k_ + 4 : 0));                  \
-    }
-#define GNN_STASH_A(step_)                                                                  \
-    {                                                                                       \
-        const int st_ = (step_) < n_steps ? (step_) : n_steps - 1;                          \
-        if (KTAIL) {                                                                        \
-            const int nv_ = a.K - ((st_ - (st_ >= k_slices ? k_slices : 0)) * kSplitK + ld_h * 8); \
-            ra0 = mask_chunk<GNN_F32>(ra0, nv_);                                            \
-            ra1 = mask_chunk<GNN_F32>(ra1, nv_ - 4);                                        \
-        }                                                                                   \
-        if (st_ >= k_slices && z) ra0 = ra1 = (u32x4){0u, 0u, 0u, 0u};                      \
-        u32x4 part_[3];                                                                     \
-        split8(ra0, ra1, part_);                                                            \
-        _Pragma("unroll") for (int p_ = 0; p_ < 3; ++p_) *(u32x4*)&sA[ld_row * ROW + p_ * 8 + ld_h * 4] = part_[p_]; \
-    }
-// the tile's slab of the split weights, straight to LDS: lane l of a wavefront writes 16 bytes at the wavefront's base + 16 l
-#define GNN_LOAD_B(step_)                                                                   \
-    {                                                                                       \
-        const int st_ = (step_) < n_steps ? (step_) : n_steps - 1;                          \
-        const int src_ = st_ >= k_slices ? 1 : 0;                                           \
-        const char* p_ = (src_ ? a.Bp[1] : a.Bp[0]) + ((int64_t)(st_ - src_ * k_slices) * a.n_pad + n0) * kSplitRow + tid * 16; \
-        _Pragma("unroll") for (int c_ = 0; c_ < B_CH; ++c_)                                 \
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(p_ + c_ * 4096),  \
-                                             (__attribute__((address_space(3))) void*)(sB + c_ * 1024 + wave * 256), 16, 0, 0); \
-    }
-// Everything but the two row loads issued last has landed, in this wavefront; then in all of them.
-#define GNN_LANDED                                                     \
-    {                                                                  \
-        __builtin_amdgcn_sched_barrier(0);                             \
-        asm volatile("s_waitcnt vmcnt(2) lgkmcnt(0)" ::: "memory");    \
-        __builtin_amdgcn_s_barrier();                                  \
-        asm volatile("" ::: "memory");                                 \
-        __builtin_amdgcn_sched_barrier(0);                             \
-    }
-    GNN_LOAD_A(0)
-    s_bias[tid & (BN - 1)] = (a.bias && n0 + (tid & (BN - 1)) < a.N) ? a.bias[n0 + (tid & (BN - 1))] : 0.f;
-    {
-        const int m = m0 + (tid & (BM - 1));
-        s_crow[tid & (BM - 1)] = m < a.M ? (a.c_rows ? a.c_rows[m] : m) : -1;   // -1: a row past M, never stored
-    }
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-    GNN_STASH_A(0)
-    GNN_LOAD_B(0)
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("" ::: "memory");
-    GNN_LOAD_A(1)
-    GNN_LANDED
-    const int fa = (wm * 64 + li) * ROW + g * 4, fb = (wn * WTN + li) * ROW + g * 4;
-    for (int s = 0; s < n_steps; ++s) {
-        u32x4 va[MT][3], vb[NT][3];
-#pragma unroll
-        for (int p = 0; p < 3; ++p) {
-#pragma unroll
-            for (int i = 0; i < MT; ++i) va[i][p] = *(const u32x4*)&sA[fa + i * 32 * ROW + p * 8];
-#pragma unroll
-            for (int j = 0; j < NT; ++j) vb[j][p] = *(const u32x4*)&sB[fb + j * 32 * ROW + p * 8];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        __builtin_amdgcn_s_barrier();              // every wave has its fragments: the buffers are free
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
-        GNN_STASH_A(s + 1)                         // waits for the rows; the slab's loads go out after it, so they are not waited for here
-        GNN_LOAD_B(s + 1)
-        __builtin_amdgcn_sched_barrier(0);
-        asm volatile("" ::: "memory");
-        GNN_LOAD_A(s + 2)
-        __builtin_amdgcn_sched_barrier(0);
-        // The six products of a slice meet in a sum of their own, small ones first, which is then added to the accumulator:
-        // that is rounded once per slice, not six times.  Two such sums take turns, so that one is added while the matrix
-        // cores work on the other - in the wide tile only from block kLag on, when fragments have been used up: before, the
-        // registers are full.
-        constexpr int kLag = NTW == 4 ? 4 : 0;
-        constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
-        v16f t[2];
-        const v16f zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int b = 0; b < NT * MT; ++b) {
-            const int i = b % MT, j = b / MT;
-#pragma unroll
-            for (int q = 0; q < 6; ++q) {
-                t[b & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, vb[j][PB[q]]), __builtin_bit_cast(v8bf, va[i][PA[q]]),
-                                                                    q ? t[b & 1] : zero, 0, 0, 0);
-                if (q == 1 && b > kLag) {
-                    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[(b - 1) % MT][(b - 1) / MT][r] += t[(b - 1) & 1][r];
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-            if (b < kLag || b == NT * MT - 1) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][j][r] += t[b & 1][r];
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        GNN_LANDED
-    }
-#undef GNN_LOAD_A
-#undef GNN_STASH_A
-#undef GNN_LOAD_B
-#undef GNN_LANDED
-    int bad = 0;
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) bad |= !(fabsf(acc[i][j][r]) < INFINITY);
-    float unscale = kSplitUnscale;
-    if (__syncthreads_or(bad)) {   // uniform over the workgroup: the tile again, with fp32 MFMAs
-        unscale = 1.f;
-#pragma unroll
-        for (int i = 0; i < MT; ++i)
-#pragma unroll
-            for (int j = 0; j < NT; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-        const int n_src = (a.n_src == 2 && m0 >= a.M1) ? 1 : a.n_src;
-        for (int src = 0; src < n_src; ++src) {
-            const float* A = (const float*)a.A[src];
-            const float* W = a.W[src];
-            for (int k0 = 0; k0 < a.K; k0 += 2) {
-                const int k = k0 + g;
-                float x[MT], w[NT];
-#pragma unroll
-                for (int i = 0; i < MT; ++i) {
-                    const int r = wm * 64 + i * 32 + li;
-                    x[i] = (k < a.K && (src == 0 || m0 + r < a.M1)) ? A[row_of(r) * a.lda + k] : 0.f;
-                }
-#pragma unroll
-                for (int j = 0; j < NT; ++j) {
-                    const int n = n0 + wn * WTN + j * 32 + li;
-                    w[j] = (k < a.K && n < a.N) ? W[(int64_t)k * a.w_k + (int64_t)n * a.w_n] : 0.f;
-                }
-#pragma unroll
-                for (int i = 0; i < MT; ++i)
-#pragma unroll
-                    for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[j], x[i], acc[i][j], 0, 0, 0);
-            }
-        }
-    }
-
-    // Epilogue as in the line variant: acc[i][j][r] is C[row li][column (r/4)*8 + g*4 + r%4] of its 32x32 block.
-    uint32_t* stg = smem + wave * STAGE;
-    constexpr int JP = CW / 32, NP = 8;    // 32-column blocks per piece; passes of four rows over it
-    const bool vec_out = a.c_vec && (!a.mask || a.m_vec);   // uniform over the grid
-#pragma unroll
-    for (int i = 0; i < MT; ++i) {
-#pragma unroll
-        for (int p = 0; p < NT / JP; ++p) {
-#pragma unroll
-            for (int jj = 0; jj < JP; ++jj) {
-                const int j = p * JP + jj;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int c = q * 8 + g * 4;     // first of this lane's four consecutive columns of the block
-                    const float4 bv = *(const float4*)&s_bias[wn * WTN + j * 32 + c];
-                    float v0 = fmaf(acc[i][j][q * 4 + 0], unscale, bv.x), v1 = fmaf(acc[i][j][q * 4 + 1], unscale, bv.y);
-                    float v2 = fmaf(acc[i][j][q * 4 + 2], unscale, bv.z), v3 = fmaf(acc[i][j][q * 4 + 3], unscale, bv.w);
-                    if (a.relu) {
-                        v0 = v0 > 0.f ? v0 : 0.f; v1 = v1 > 0.f ? v1 : 0.f; v2 = v2 > 0.f ? v2 : 0.f; v3 = v3 > 0.f ? v3 : 0.f;
-                    }
-                    *(uint4*)&stg[li * CROW + jj * 32 + c] = make_uint4(__float_as_uint(v0), __float_as_uint(v1), __float_as_uint(v2), __float_as_uint(v3));
-                }
-            }
-            __syncthreads();
-            const int n = n0 + wn * WTN + p * CW + (lane & 15) * 4;
-            int32_t crs[NP];
-            uint4 vs[NP];
-#pragma unroll
-            for (int pass = 0; pass < NP; ++pass) {
-                const int row = pass * 4 + (lane >> 4);
-                crs[pass] = s_crow[wm * 64 + i * 32 + row];
-                vs[pass] = *(const uint4*)&stg[row * CROW + (lane & 15) * 4];
-            }
-            if (vec_out && n + 4 <= a.N) {
-                if (a.mask) {   // all loads before the first store (see the line variant)
-                    uint4 hs[NP], os[NP];
-#pragma unroll
-                    for (int pass = 0; pass < NP; ++pass) {
-                        const int64_t crow = crs[pass] >= 0 ? crs[pass] : 0;
-                        const int m = m0 + wm * 64 + i * 32 + pass * 4 + (lane >> 4);
-                        hs[pass] = *(const uint4*)((const float*)a.mask + crow * a.ldm + n);
-                        os[pass] = make_uint4(0u, 0u, 0u, 0u);
-                        if (m < a.n_acc) os[pass] = *(const uint4*)((const float*)a.C + crow * a.ldc + n);
-                    }
-#pragma unroll
-                    for (int pass = 0; pass < NP; ++pass) {
-                        const int m = m0 + wm * 64 + i * 32 + pass * 4 + (lane >> 4);
-                        vs[pass] = post_apply<GNN_F32>(vs[pass], os[pass], m < a.n_acc, hs[pass]);
-                    }
-                }
-#pragma unroll
-                for (int pass = 0; pass < NP; ++pass)
-                    if (crs[pass] >= 0) *(uint4*)((float*)a.C + (int64_t)crs[pass] * a.ldc + n) = vs[pass];
-            } else {
-#pragma unroll
-                for (int pass = 0; pass < NP; ++pass) {
-                    const int m = m0 + wm * 64 + i * 32 + pass * 4 + (lane >> 4);
-                    const int64_t crow = crs[pass];
-                    const uint32_t w[4] = {vs[pass].x, vs[pass].y, vs[pass].z, vs[pass].w};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        if (crow >= 0 && n + e < a.N) {
-                            float o = __uint_as_float(w[e]);
-                            if (a.mask) o = post_elem<GNN_F32>(o, a.C, crow * a.ldc + n + e, m < a.n_acc, a.mask, crow * a.ldm + n + e);
-                            ((float*)a.C)[crow * a.ldc + n + e] = o;
-                        }
-                    }
-                }
-            }
-            __syncthreads();
-        }
-    }
-}
-
-// Tile width (in 64 columns) of an output width: the one that pads least, 256 on a tie.
-static inline int nt_tile_width(int32_t N) {
-    const int64_t p256 = ((int64_t)N + 255) / 256 * 256, p128 = ((int64_t)N + 127) / 128 * 128, p64 = ((int64_t)N + 63) / 64 * 64;
-    return (p256 <= p128 && p256 <= p64) ? 4 : (p128 <= p64 ? 2 : 1);
-}
-
-// What a call needs to run its fp32 product of n_src sources, K -> N, on the bf16 matrix cores (bytes 0: it does not).
-struct SplitPlan {
-    int ntw = 0;
-    int32_t n_pad = 0, blocks = 0;
-    size_t bytes = 0;   // per source
-};
-
-
-// Any row count (200 rows: 80 -> 64 us, the wide variant's steps wait for memory just the same).  Not for widths up to 64,
-// whose tile would be half padding (256 -> 47, 300 000 rows: 0.12 ms with fp32 MFMAs, bound by its operands) nor for reductions
-// shorter than four slices, which are all prologue and epilogue.
-static inline SplitPlan split_plan(int32_t dtype, int32_t K, int32_t N, int n_src) {
-    SplitPlan p;
-    const int ntw = nt_tile_width(N) == 1 ? 2 : nt_tile_width(N);
-    const int64_t n_pad = ((int64_t)N + 64 * ntw - 1) / (64 * ntw) * (64 * ntw);
-    const int64_t rows = (int64_t)((K + kSplitK - 1) / kSplitK) * n_pad;
-    if (dtype != GNN_F32 || N <= 64 || (int64_t)K * n_src < 64 || (size_t)rows * kSplitRow > kSplitMaxBytes) return p;
-    p.ntw = ntw;
-    p.n_pad = (int32_t)n_pad;
-    p.bytes = (size_t)rows * kSplitRow;
-    p.blocks = (int32_t)((rows + kSplitPrepRows - 1) / kSplitPrepRows);
-    return p;
-}
-
-// W[s]: element (k, n) at k * w_k + n * w_n; split[s]: workspace of the plan.  Operand rows are 16-byte aligned.
-static int32_t launch_gemm_split(const GemmNT& g, const SplitPlan& p, const void* W0, const void* W1, int64_t w_k, int64_t w_n, void* split0,
-                                 void* split1, hipStream_t stream) {
-    GemmSplit a;
-    static_cast<GemmNT&>(a) = g;
-    a.Bp[0] = (const char*)split0; a.Bp[1] = (const char*)split1;
-    a.n_pad = p.n_pad;
-    a.W[0] = (const float*)W0; a.W[1] = (const float*)W1; a.w_k = w_k; a.w_n = w_n;
-    split_weights_kernel<<<dim3((unsigned)p.blocks, (unsigned)g.n_src), 256, 0, stream>>>(a.W[0], a.W[1], w_k, w_n, g.K, g.N, p.n_pad,
-                                                                                        (char*)split0, (char*)split1);
-    GNN_LAUNCH_CHECK("split_weights_kernel");
-    const unsigned grid = (unsigned)(((int64_t)g.M + 127) / 128 * (p.n_pad / (64 * p.ntw)));
-    const bool ktail = g.K % kSplitK != 0;
-    if (p.ntw == 4) {
-        if (ktail) gemm_nt_split_kernel<4, true><<<grid, 256, 0, stream>>>(a);
-        else gemm_nt_split_kernel<4, false><<<grid, 256, 0, stream>>>(a);
-    } else {
-        if (ktail) gemm_nt_split_kernel<2, true><<<grid, 256, 0, stream>>>(a);
-        else gemm_nt_split_kernel<2, false><<<grid, 256, 0, stream>>>(a);
-    }
-    GNN_LAUNCH_CHECK("gemm_nt_split_kernel");
-    return GNN_OK;
-}
-
 template <int DT>
 static int32_t launch_gemm_nt(const GemmNT& a, hipStream_t stream) {
     if (a.M <= 0 || a.N <= 0) return GNN_OK;
@@ -1429,7 +1036,8 @@ static int32_t launch_gemm_nt(const GemmNT& a, hipStream_t stream) {
     const bool vec = a.a_vec && a.b_vec;  // both operands aligned: the branch-free loader
     if (vec && a.N > 32 && a.K > 0) {
         // wide tile: the tile width that pads the output width least (256 on a tie)
-        int ntw = nt_tile_width(a.N);
+        const int64_t p256 = ((int64_t)a.N + 255) / 256 * 256, p128 = ((int64_t)a.N + 127) / 128 * 128, p64 = ((int64_t)a.N + 63) / 64 * 64;
+        int ntw = (p256 <= p128 && p256 <= p64) ? 4 : (p128 <= p64 ? 2 : 1);
         // a reduction of one or two slices (an input gradient from 32 or 41 class scores) is all prologue and epilogue:
         // narrow tiles keep more workgroups on a CU to hide those latencies, and re-reading the short rows costs little
         if ((int64_t)a.K * a.n_src * DTy<DT>::ES <= 128) ntw = 1;
@@ -1450,7 +1058,7 @@ static int32_t launch_gemm_nt(const GemmNT& a, hipStream_t stream) {
             GNN_LAUNCH_CHECK("gemm_nt_line_kernel");
             return GNN_OK;
         }
-        const unsigned grid = (unsigned)(tiles_m * (((int64_t)a.N + 64 * ntw - 1) / (64 * ntw)));
+        const unsigned grid = (unsigned)(tiles_m * (ntw == 4 ? p256 / 256 : (ntw == 2 ? p128 / 128 : p64 / 64)));
         const bool ktail = a.K % (64 / DTy<DT>::ES) != 0;
 #define GNN_WIDE(NTW_)                                                                                  \
     {                                                                                                   \
@@ -1863,8 +1471,15 @@ static inline bool vec_ok(const void* p, int64_t ld, int es) { return ((uintptr_
 template <int DT>
 static int32_t linear_fwd_impl(const int32_t* rows, int32_t n_active, const void* A, const void* Xs, int64_t ld_in, int32_t K,
                                const void* Wn, const void* Ws, const float* bias, int32_t N, void* H, int64_t ld_out,
-                               int32_t relu, void* Wt0, void* Wt1, int64_t ldt, const SplitPlan& split, hipStream_t stream) {
+                               int32_t relu, void* Wt0, void* Wt1, int64_t ldt, hipStream_t stream) {
     constexpr int ES = DTy<DT>::ES;
+    dim3 tg((K + 31) / 32, (N + 31) / 32);
+    transpose_kernel<DT><<<tg, 256, 0, stream>>>(Wn, K, N, Wt0, ldt);
+    GNN_LAUNCH_CHECK("transpose_kernel");
+    if (Xs) {
+        transpose_kernel<DT><<<tg, 256, 0, stream>>>(Ws, K, N, Wt1, ldt);
+        GNN_LAUNCH_CHECK("transpose_kernel");
+    }
     GemmNT g;
     g.A[0] = A; g.A[1] = Xs; g.Bt[0] = Wt0; g.Bt[1] = Wt1; g.n_src = Xs ? 2 : 1;
     g.lda = ld_in; g.ldb = ldt;
@@ -1873,14 +1488,6 @@ static int32_t linear_fwd_impl(const int32_t* rows, int32_t n_active, const void
     g.a_rows = rows; g.c_rows = rows; g.M = n_active; g.N = N; g.K = K;
     g.bias = bias; g.relu = relu; g.C = H; g.ldc = ld_out; g.c_vec = vec_ok(H, ld_out, ES);
     g.mask = nullptr; g.ldm = 0; g.m_vec = 0; g.n_acc = 0; g.M1 = INT32_MAX;
-    if (split.bytes && g.a_vec) return launch_gemm_split(g, split, Wn, Ws, N, 1, Wt0, Wt1, stream);
-    dim3 tg((K + 31) / 32, (N + 31) / 32);
-    transpose_kernel<DT><<<tg, 256, 0, stream>>>(Wn, K, N, Wt0, ldt);
-    GNN_LAUNCH_CHECK("transpose_kernel");
-    if (Xs) {
-        transpose_kernel<DT><<<tg, 256, 0, stream>>>(Ws, K, N, Wt1, ldt);
-        GNN_LAUNCH_CHECK("transpose_kernel");
-    }
     return launch_gemm_nt<DT>(g, stream);
 }
 
@@ -1889,7 +1496,7 @@ static int32_t linear_bwd_impl(const int32_t* rows, int32_t M, const void* dH, c
                                const void* A, const void* Xs, int64_t ld_in, int32_t K, const void* Wn, const void* Ws, int32_t N,
                                float* dWn, float* dWs, float* dbias, void* dA, void* dXs, int64_t ld_din, void* dZ, int64_t ldz,
                                float* part, int32_t n_part, float* P, float* Pb, int32_t splits, int32_t rows_per_split,
-                               void* Wpad0, void* Wpad1, int32_t ldwp, const SplitPlan& split, void* Wsplit, hipStream_t stream) {
+                               void* Wpad0, void* Wpad1, int32_t ldwp, hipStream_t stream) {
     constexpr int ES = DTy<DT>::ES;
     // Without an activation to undo and without a row list, dH IS the compact dZ: no copy is made, the products read
     // dH in place and the weight-gradient kernel adds up the bias gradient on its way.
@@ -1947,25 +1554,21 @@ static int32_t linear_bwd_impl(const int32_t* rows, int32_t M, const void* dH, c
         void* out = which == 0 ? dA : dXs;
         const void* W = which == 0 ? Wn : Ws;
         if (!out) continue;
+        int64_t ldw = N;
         void* Wpad = which == 0 ? Wpad0 : Wpad1;
-        GemmNT g;
-        g.A[0] = dZ; g.A[1] = nullptr; g.Bt[0] = W; g.Bt[1] = nullptr; g.n_src = 1;
-        g.lda = ldz; g.ldb = N; g.a_vec = vec_ok(dZ, ldz, ES); g.b_vec = vec_ok(W, N, ES);
-        g.a_rows = nullptr; g.c_rows = rows; g.M = M; g.N = K; g.K = N;
-        g.bias = nullptr; g.relu = 0; g.C = out; g.ldc = ld_din; g.c_vec = vec_ok(out, ld_din, ES);
-        g.mask = nullptr; g.ldm = 0; g.m_vec = 0; g.n_acc = 0; g.M1 = INT32_MAX;
-        if (split.bytes && g.a_vec) {   // the two products run after each other: one split copy serves both
-            GNN_CHECK(launch_gemm_split(g, split, W, nullptr, 1, N, Wsplit, nullptr, stream));
-            continue;
-        }
         if (Wpad != nullptr) {
             // rows of N elements are not 16-byte aligned (41 or 47 classes): the product reads a padded copy with vector loads
             pad_rows_kernel<DT><<<grid_for((int64_t)K * ldwp, 256, 1024), 256, 0, stream>>>(W, K, N, Wpad, ldwp);
             GNN_LAUNCH_CHECK("pad_rows_kernel");
-            g.Bt[0] = Wpad;
-            g.ldb = ldwp;
-            g.b_vec = vec_ok(Wpad, ldwp, ES);
+            W = Wpad;
+            ldw = ldwp;
         }
+        GemmNT g;
+        g.A[0] = dZ; g.A[1] = nullptr; g.Bt[0] = W; g.Bt[1] = nullptr; g.n_src = 1;
+        g.lda = ldz; g.ldb = ldw; g.a_vec = vec_ok(dZ, ldz, ES); g.b_vec = vec_ok(W, ldw, ES);
+        g.a_rows = nullptr; g.c_rows = rows; g.M = M; g.N = K; g.K = N;
+        g.bias = nullptr; g.relu = 0; g.C = out; g.ldc = ld_din; g.c_vec = vec_ok(out, ld_din, ES);
+        g.mask = nullptr; g.ldm = 0; g.m_vec = 0; g.n_acc = 0; g.M1 = INT32_MAX;
         GNN_CHECK(launch_gemm_nt<DT>(g, stream));
     }
     return GNN_OK;
@@ -1993,10 +1596,8 @@ extern "C" int32_t gnn_linear_fwd(const int32_t* rows, int32_t n_active, const v
     const int es = dtype == GNN_F32 ? 4 : 2;
     const int64_t ldt = (int64_t)align_up((size_t)K, 16 / es);
     WsCarver carve(ws);
-    const SplitPlan split = split_plan(dtype, K, N, X_self ? 2 : 1);
-    const size_t wt_bytes = (size_t)N * ldt * es > split.bytes ? (size_t)N * ldt * es : split.bytes;
-    char* Wt0 = carve.take<char>(wt_bytes);
-    char* Wt1 = carve.take<char>(wt_bytes);
+    char* Wt0 = carve.take<char>((size_t)N * ldt * es);
+    char* Wt1 = carve.take<char>((size_t)N * ldt * es);
     bool query;
     GNN_CHECK(ws_protocol(ws, ws_bytes, carve.used, &query));
     if (query) return GNN_OK;
@@ -2004,18 +1605,17 @@ extern "C" int32_t gnn_linear_fwd(const int32_t* rows, int32_t n_active, const v
     GNN_REQUIRE(A_neigh && W_neigh && H_out, GNN_ERR_INVALID_ARG, "A_neigh, W_neigh or H_out is NULL");
     if (dtype == GNN_F32)
         return linear_fwd_impl<GNN_F32>(rows, n_active, A_neigh, X_self, ld_in, K, W_neigh, W_self, bias, N, H_out, ld_out, relu, Wt0,
-                                        Wt1, ldt, split, stream);
+                                        Wt1, ldt, stream);
     return linear_fwd_impl<GNN_BF16>(rows, n_active, A_neigh, X_self, ld_in, K, W_neigh, W_self, bias, N, H_out, ld_out, relu, Wt0,
-                                     Wt1, ldt, split, stream);
+                                     Wt1, ldt, stream);
 }
 
 // ---- the forward transform for callers that cannot allocate ---------------------------------
 // Same kernels as gnn_linear_fwd; the two transposed weight copies live in a file-scope device array instead of a
 // caller's workspace.  Every GPU holds its own copy of the array at its own address: the address is looked up once
 // per device (with that device current) and only that pointer is ever handed to kernels.
-constexpr size_t kStaticWtBytes = (size_t)4 << 20;   // largest transposed weight matrix: N * round_up(K) elements
-// ... and room for its split form (fp32 on the bf16 matrix cores), which takes at most kSplitMaxBytes
-static __device__ __align__(256) unsigned char scratch[2 * kSplitMaxBytes];
+constexpr size_t kStaticWtBytes = (size_t)4 << 20;   // one transposed weight matrix: N * round_up(K) elements
+static __device__ __align__(256) unsigned char scratch[2 * kStaticWtBytes];
 constexpr int kMaxDevices = 64;
 static void* g_scratch_ptr[kMaxDevices];
 static std::mutex g_scratch_mutex;
@@ -2053,13 +1653,12 @@ extern "C" int32_t gnn_linear_fwd_static(const int32_t* rows, int32_t n_active, 
     if (n_active == 0) return GNN_OK;
     GNN_REQUIRE(A_neigh && W_neigh && H_out, GNN_ERR_INVALID_ARG, "A_neigh, W_neigh or H_out is NULL");
     char* Wt0 = (char*)base;
-    char* Wt1 = (char*)base + kSplitMaxBytes;
-    const SplitPlan split = split_plan(dtype, K, N, X_self ? 2 : 1);
+    char* Wt1 = (char*)base + kStaticWtBytes;
     if (dtype == GNN_F32)
         return linear_fwd_impl<GNN_F32>(rows, n_active, A_neigh, X_self, ld_in, K, W_neigh, W_self, bias, N, H_out, ld_out, relu, Wt0,
-                                        Wt1, ldt, split, stream);
+                                        Wt1, ldt, stream);
     return linear_fwd_impl<GNN_BF16>(rows, n_active, A_neigh, X_self, ld_in, K, W_neigh, W_self, bias, N, H_out, ld_out, relu, Wt0,
-                                     Wt1, ldt, split, stream);
+                                     Wt1, ldt, stream);
 }
 
 extern "C" int32_t gnn_linear_bwd(const int32_t* rows, int32_t n_active, const void* dH_out, const void* H_out, int64_t ld_out,
@@ -2105,8 +1704,6 @@ extern "C" int32_t gnn_linear_bwd(const int32_t* rows, int32_t n_active, const v
     const int32_t ldwp = (int32_t)ldz;
     char* Wpad0 = carve.take<char>(pad_w ? (size_t)K * ldwp * es : 0);
     char* Wpad1 = carve.take<char>(pad_w ? (size_t)K * ldwp * es : 0);
-    const SplitPlan split = (dA_neigh || dX_self) ? split_plan(dtype, N, K, 1) : SplitPlan();
-    char* Wsplit = carve.take<char>(split.bytes);
     if (!pad_w || ws == nullptr) Wpad0 = Wpad1 = nullptr;
     bool query;
     GNN_CHECK(ws_protocol(ws, ws_bytes, carve.used, &query));
@@ -2124,10 +1721,10 @@ extern "C" int32_t gnn_linear_bwd(const int32_t* rows, int32_t n_active, const v
     if (dtype == GNN_F32)
         return linear_bwd_impl<GNN_F32>(rows, n_active, dH_out, H_out, ld_out, relu, A_neigh, X_self, ld_in, K, W_neigh, W_self, N,
                                         dW_neigh, dW_self, dbias, dA_neigh, dX_self, ld_din, dZ, ldz, part, n_part, P, Pb, splits,
-                                        rows_per_split, Wpad0, Wpad1, ldwp, split, Wsplit, stream);
+                                        rows_per_split, Wpad0, Wpad1, ldwp, stream);
     return linear_bwd_impl<GNN_BF16>(rows, n_active, dH_out, H_out, ld_out, relu, A_neigh, X_self, ld_in, K, W_neigh, W_self, N,
                                      dW_neigh, dW_self, dbias, dA_neigh, dX_self, ld_din, dZ, ldz, part, n_part, P, Pb, splits,
-                                     rows_per_split, Wpad0, Wpad1, ldwp, split, Wsplit, stream);
+                                     rows_per_split, Wpad0, Wpad1, ldwp, stream);
 }
 
 extern "C" int32_t gnn_bias_grad(const int32_t* rows, int32_t n_active, const void* dZ, int64_t ldz, int32_t N, int32_t dtype,
@@ -2176,30 +1773,27 @@ extern "C" int32_t gnn_linear_bwd_input(const int32_t* rows, int32_t n_active, c
     const int es = dtype == GNN_F32 ? 4 : 2;
     const bool pad_w = ((int64_t)N * es) % 16 != 0;
     const int32_t ldwp = (int32_t)align_up((size_t)N, 16 / es);
-    const SplitPlan split = split_plan(dtype, N, K, 1);
     WsCarver carve(ws);
     char* Wpad = carve.take<char>(pad_w ? (size_t)K * ldwp * es : 0);
-    char* Wsplit = carve.take<char>(split.bytes);
     bool query;
     GNN_CHECK(ws_protocol(ws, ws_bytes, carve.used, &query));
     if (query) return GNN_OK;
     if (n_active == 0) return GNN_OK;
     GNN_REQUIRE(dZ && W && dX, GNN_ERR_INVALID_ARG, "dZ, W or dX is NULL");
-    GemmNT g;
-    g.A[0] = dZ; g.A[1] = nullptr; g.Bt[0] = W; g.Bt[1] = nullptr; g.n_src = 1;
-    g.lda = lddz; g.ldb = N; g.a_vec = vec_ok(dZ, lddz, es); g.b_vec = vec_ok(W, N, es);
-    g.a_rows = rows; g.c_rows = rows; g.M = n_active; g.N = K; g.K = N;
-    g.bias = nullptr; g.relu = 0; g.C = dX; g.ldc = lddx; g.c_vec = vec_ok(dX, lddx, es);
-    g.mask = relu_H; g.ldm = ld_relu; g.m_vec = relu_H ? vec_ok(relu_H, ld_relu, es) : 0; g.n_acc = n_accumulate; g.M1 = INT32_MAX;
-    if (split.bytes && g.a_vec) return launch_gemm_split(g, split, W, nullptr, 1, N, Wsplit, nullptr, stream);
+    int64_t ldw = N;
     if (pad_w) {
         if (dtype == GNN_F32) pad_rows_kernel<GNN_F32><<<grid_for((int64_t)K * ldwp, 256, 1024), 256, 0, stream>>>(W, K, N, Wpad, ldwp);
         else pad_rows_kernel<GNN_BF16><<<grid_for((int64_t)K * ldwp, 256, 1024), 256, 0, stream>>>(W, K, N, Wpad, ldwp);
         GNN_LAUNCH_CHECK("pad_rows_kernel");
-        g.Bt[0] = Wpad;
-        g.ldb = ldwp;
-        g.b_vec = vec_ok(Wpad, ldwp, es);
+        W = Wpad;
+        ldw = ldwp;
     }
+    GemmNT g;
+    g.A[0] = dZ; g.A[1] = nullptr; g.Bt[0] = W; g.Bt[1] = nullptr; g.n_src = 1;
+    g.lda = lddz; g.ldb = ldw; g.a_vec = vec_ok(dZ, lddz, es); g.b_vec = vec_ok(W, ldw, es);
+    g.a_rows = rows; g.c_rows = rows; g.M = n_active; g.N = K; g.K = N;
+    g.bias = nullptr; g.relu = 0; g.C = dX; g.ldc = lddx; g.c_vec = vec_ok(dX, lddx, es);
+    g.mask = relu_H; g.ldm = ld_relu; g.m_vec = relu_H ? vec_ok(relu_H, ld_relu, es) : 0; g.n_acc = n_accumulate; g.M1 = INT32_MAX;
     return dtype == GNN_F32 ? launch_gemm_nt<GNN_F32>(g, stream) : launch_gemm_nt<GNN_BF16>(g, stream);
 }
 
@@ -2218,26 +1812,14 @@ extern "C" int32_t gnn_linear_bwd_input2(const int32_t* rows, int32_t n_active, 
     WsCarver carve(ws);
     char* Wpad0 = carve.take<char>(pad_w ? (size_t)K * ldwp * es : 0);
     char* Wpad1 = carve.take<char>(pad_w ? (size_t)K * ldwp * es : 0);
-    const bool two = n_self > 0;
-    const SplitPlan split = split_plan(dtype, N, K, two ? 2 : 1);
-    char* Wsplit0 = carve.take<char>(split.bytes);
-    char* Wsplit1 = carve.take<char>(two ? split.bytes : 0);
     bool query;
     GNN_CHECK(ws_protocol(ws, ws_bytes, carve.used, &query));
     if (query) return GNN_OK;
     if (n_active == 0) return GNN_OK;
     GNN_REQUIRE(dG && W_neigh && dX, GNN_ERR_INVALID_ARG, "dG, W_neigh or dX is NULL");
     GNN_REQUIRE(n_self == 0 || (dZ && W_self), GNN_ERR_INVALID_ARG, "dZ or W_self is NULL with n_self > 0");
-    GemmNT g;
-    g.A[0] = dG; g.A[1] = two ? dZ : nullptr; g.Bt[0] = W_neigh; g.Bt[1] = two ? W_self : nullptr; g.n_src = two ? 2 : 1;
-    g.lda = ldd; g.ldb = N;
-    g.a_vec = vec_ok(dG, ldd, es) && (!two || vec_ok(dZ, ldd, es));
-    g.b_vec = vec_ok(W_neigh, N, es) && (!two || vec_ok(W_self, N, es));
-    g.a_rows = rows; g.c_rows = rows; g.M = n_active; g.N = K; g.K = N;
-    g.bias = nullptr; g.relu = 0; g.C = dX; g.ldc = lddx; g.c_vec = vec_ok(dX, lddx, es);
-    g.mask = relu_H; g.ldm = ld_relu; g.m_vec = relu_H ? vec_ok(relu_H, ld_relu, es) : 0; g.n_acc = 0;
-    g.M1 = two ? n_self : INT32_MAX;
-    if (split.bytes && g.a_vec) return launch_gemm_split(g, split, W_neigh, W_self, 1, N, Wsplit0, Wsplit1, stream);
+    const bool two = n_self > 0;
+    int64_t ldw = N;
     if (pad_w) {   // weight rows of an unaligned width (41 or 47 classes): the product reads padded copies with vector loads
         for (int which = 0; which < (two ? 2 : 1); ++which) {
             const void* W = which == 0 ? W_neigh : W_self;
@@ -2245,10 +1827,19 @@ extern "C" int32_t gnn_linear_bwd_input2(const int32_t* rows, int32_t n_active, 
             if (dtype == GNN_F32) pad_rows_kernel<GNN_F32><<<grid_for((int64_t)K * ldwp, 256, 1024), 256, 0, stream>>>(W, K, N, Wp, ldwp);
             else pad_rows_kernel<GNN_BF16><<<grid_for((int64_t)K * ldwp, 256, 1024), 256, 0, stream>>>(W, K, N, Wp, ldwp);
             GNN_LAUNCH_CHECK("pad_rows_kernel");
-            g.Bt[which] = Wp;
         }
-        g.ldb = ldwp;
-        g.b_vec = 1;
+        W_neigh = Wpad0;
+        W_self = Wpad1;
+        ldw = ldwp;
     }
+    GemmNT g;
+    g.A[0] = dG; g.A[1] = two ? dZ : nullptr; g.Bt[0] = W_neigh; g.Bt[1] = two ? W_self : nullptr; g.n_src = two ? 2 : 1;
+    g.lda = ldd; g.ldb = ldw;
+    g.a_vec = vec_ok(dG, ldd, es) && (!two || vec_ok(dZ, ldd, es));
+    g.b_vec = vec_ok(W_neigh, ldw, es) && (!two || vec_ok(W_self, ldw, es));
+    g.a_rows = rows; g.c_rows = rows; g.M = n_active; g.N = K; g.K = N;
+    g.bias = nullptr; g.relu = 0; g.C = dX; g.ldc = lddx; g.c_vec = vec_ok(dX, lddx, es);
+    g.mask = relu_H; g.ldm = ld_relu; g.m_vec = relu_H ? vec_ok(relu_H, ld_relu, es) : 0; g.n_acc = 0;
+    g.M1 = two ? n_self : INT32_MAX;
     return dtype == GNN_F32 ? launch_gemm_nt<GNN_F32>(g, stream) : launch_gemm_nt<GNN_BF16>(g, stream);
 }
