@@ -473,12 +473,13 @@ int32_t gnn_expand_row_ptr(int32_t n, const int32_t *ids, int32_t n_ids, const i
  * Extraction after boundary sampling (section 5.3.1: the local graph is built on what the sampler's
  * traversal reached, and no edge between two inner vertices is dropped).
  *   gs   the kept rows as an n-row CSR (rows of non-targets empty, columns ascending)
- *   gT   the transposed unpartitioned graph (the same arrays as the graph itself if it is symmetric)
+ *   gT   the transposed unpartitioned graph (the same arrays as the graph itself if it is symmetric): it holds the
+ *        reverse of every kept entry, repeated entries one after the other
  *   ring_ids, dist   gnn_build_active_sets(gs, targets, L = 1): targets (distance 0), then every
  *        outside vertex some target kept (distance 1), each group ascending
  * Local vertices = ring order (targets first).  Local rows: a target keeps its kept row; an outside
  * vertex u gets the reverse of the kept edges that reach it, { v target : u in kept row of v } (so the
- * local graph is symmetric); there are no edges between two outside vertices.  Rows ascending in
+ * local graph is symmetric), v as often as its kept row holds u; there are no edges between two outside vertices.  Rows ascending in
  * local id.  new_id and the two passes are as for gnn_extract_partition.  Bit-exact.
  */
 int32_t gnn_extract_sampled_partition(const gnn_csr *gT, const gnn_csr *gs, const int32_t *ring_ids,

@@ -22,9 +22,10 @@
 // reverse of the kept edges that reach it.  The kernels above run over the targets' kept rows; an entry that leads
 // outside also takes part in the transposition: the count pass adds it to the outside vertex's length, the fill pass
 // puts the target into the next free place of its row (integer atomics, so in any order), and a last launch orders every
-// such row - it holds distinct ids, so each entry's place is the number of smaller ones.  A reverse row of more than
-// kExSortMax entries (or one that the output's capacity cuts) is instead collected in order by a workgroup that scans the
-// vertex's row of the transposed graph and keeps the targets whose kept row contains it (binary search).  That scan for
+// such row: each entry's place is the number of smaller ones, and of equal ones (a repeated column of a kept row) before it.
+// A reverse row of more than kExSortMax entries (or one that the output's capacity cuts) is instead collected in order by a
+// workgroup that scans the vertex's row of the transposed graph and keeps the targets whose kept row contains it (binary
+// search), as often as it does.  That scan for
 // EVERY outside vertex, sixteen lanes each, took 11.7 of the 12.8 ms of sampling and extraction on a 5M-vertex / 75M-entry
 // graph with 625 000 targets and fanout 5; now extraction is 0.8 of 1.8 ms.
 #include "common.h"
@@ -434,7 +435,7 @@ __global__ __launch_bounds__(256) void ex_order_kernel(ExArgs a) {
                 for (int t = 0; t < kRowLanes && r * kRowLanes + t < len_max; ++t) {   // uniform over the wavefront
                     const int32_t y = __shfl(x[r], sub * kRowLanes + t, kWave);
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) place[q] += y < x[q];
+                    for (int q = 0; q < 4; ++q) place[q] += y < x[q] + (r < q || (r == q && t < sl));   // equal ids: the earlier first
                 }
             }
 #pragma unroll
@@ -466,7 +467,10 @@ __device__ __forceinline__ void ex_order_medium(const ExArgs& a) {
         for (int t = 0; t < len; t += 4) {   // the filling is larger than every id
             const int4 y = *(const int4*)&s_x[t];
 #pragma unroll
-            for (int r = 0; r < kExSortMax / 256; ++r) place[r] += (y.x < x[r]) + (y.y < x[r]) + (y.z < x[r]) + (y.w < x[r]);
+            for (int r = 0; r < kExSortMax / 256; ++r) {
+                const int before = (int)threadIdx.x + 256 * r - t;   // equal ids: the earlier first
+                place[r] += (y.x < x[r] + (before > 0)) + (y.y < x[r] + (before > 1)) + (y.z < x[r] + (before > 2)) + (y.w < x[r] + (before > 3));
+            }
         }
 #pragma unroll
         for (int r = 0; r < kExSortMax / 256; ++r)
@@ -474,17 +478,16 @@ __device__ __forceinline__ void ex_order_medium(const ExArgs& a) {
     }
 }
 
-// is v in the kept row of target u?  (kept rows are ascending)
-__device__ __forceinline__ bool ex_kept(const ExArgs& a, int32_t u, int32_t v) {
-    int32_t lo = a.rp[u], hi = a.rp[u + 1];
+// does the kept row of target u hold v more than `nth` times?  (kept rows are ascending)
+__device__ __forceinline__ bool ex_kept(const ExArgs& a, int32_t u, int32_t v, int64_t nth) {
+    const int32_t e = a.rp[u + 1];
+    int32_t lo = a.rp[u], hi = e;
     while (lo < hi) {
         const int32_t mid = lo + ((hi - lo) >> 1);
-        const int32_t c = a.ci[mid];
-        if (c == v) return true;
-        if (c < v) lo = mid + 1;
+        if (a.ci[mid] < v) lo = mid + 1;
         else hi = mid;
     }
-    return false;
+    return lo + nth < e && a.ci[lo + nth] == v;
 }
 
 // the remaining reverse rows, collected in order from the transposed graph
@@ -500,16 +503,23 @@ __device__ __forceinline__ void ex_reverse_scan(const ExArgs& a) {
             e = a.t_rp[v + 1];
         }
         int64_t out = a.out_rp[j];
+        const int64_t end = a.out_rp[j + 1] < a.capacity ? a.out_rp[j + 1] : a.capacity;
         for (int64_t base = s; base < e; base += 256) {
             int32_t id = -1;
-            if (base + threadIdx.x < e) {
-                const int32_t u = a.t_ci[base + threadIdx.x];
+            const int64_t p = base + threadIdx.x;
+            if (p < e) {
+                const int32_t u = a.t_ci[p];
                 id = a.new_id[u];
-                if (id >= n_targets || (id >= 0 && !ex_kept(a, u, v))) id = -1;
+                if (id >= n_targets) id = -1;
+                if (id >= 0) {
+                    int64_t first = p;      // a repeated entry stays as often as the kept row holds it
+                    while (first > s && a.t_ci[first - 1] == u) --first;
+                    if (!ex_kept(a, u, v, p - first)) id = -1;
+                }
             }
             int total;
             const int64_t q = out + block_exclusive_scan<256>(id >= 0 ? 1 : 0, s_part, &total);
-            if (id >= 0 && q < a.capacity) a.out_ci[q] = id;
+            if (id >= 0 && q < end) a.out_ci[q] = id;
             out += total;
         }
     }

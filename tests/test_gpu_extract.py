@@ -259,3 +259,59 @@ def test_reverse_rows_at_the_edges_of_the_length_classes_and_cut_by_the_capacity
         B._with_ws(B.lib().gnn_extract_sampled_partition, common + (B._ptr(out), C.c_int64(cap), B._ptr(nnz_dev), None), (B._stream(),), None)
         got = out.cpu().numpy()
         assert np.array_equal(got[:cap], ci[:cap]) and (got[cap:] == -7).all(), cap
+
+
+def _multigraph(n, a, b, times):
+    """Symmetric CSR whose edges (a[i], b[i]) appear times[i] times in both directions, columns ascending."""
+    a, b = np.repeat(a, times), np.repeat(b, times)
+    r, c = np.concatenate([a, b]).astype(np.int64), np.concatenate([b, a]).astype(np.int64)
+    order = np.lexsort((c, r))
+    rp = np.zeros(n + 1, dtype=np.int32)
+    rp[1:] = np.cumsum(np.bincount(r, minlength=n))
+    return gg.CSR(n, n, rp, c[order].astype(np.int32))
+
+
+@pytest.mark.parametrize("whole", [True, False])
+def test_reverse_rows_of_kept_rows_that_repeat_a_column(whole):
+    """Kept rows of the caller's own, in which columns repeat (a repeated column counts as often as it appears): reverse rows of
+    every length class, ascending, with every target as often as its kept row holds the vertex; `whole` False: some copies
+    of an edge are kept and others not.  Then the same into outputs that are too small."""
+    import ctypes as C
+    import paper_2311_06837_amd as P
+    from paper_2311_06837_amd import binding as B
+    n, nt = 9000, 4000
+    rng = np.random.default_rng(17 + whole)
+    a, b = [], []
+    for k, ln in enumerate([1, 2, 3, 10, 30, 33, 400, 600, 1500, 3900]):    # outside vertex nt + 5 k next to ln targets
+        a.append(rng.choice(nt, ln, replace=False)), b.append(np.full(ln, nt + 5 * k))
+    a, b = np.concatenate(a), np.concatenate(b)
+    g = _multigraph(n, a, b, rng.integers(1, 4, a.size))
+    T = np.arange(nt, dtype=np.int32)
+    keep = np.ones(g.nnz, dtype=bool) if whole else rng.random(g.nnz) < 0.7
+    row = np.repeat(np.arange(n), np.diff(g.row_ptr))
+    keep &= row < nt
+    srp = np.zeros(nt + 1, dtype=np.int32)
+    srp[1:] = np.cumsum(np.bincount(row[keep], minlength=nt)[:nt])
+    sci = g.col_idx[keep]
+    rp, ci, l2g, off, dl = oracle.extract_sampled(n, T, srp, sci)
+    lens = np.diff(rp)[nt:]
+    assert lens.min() < 10 and ((lens > 64) & (lens <= 1024)).any() and (lens > 1024).sum() >= 2
+    G, Td = P.Graph.from_numpy(g.row_ptr, g.col_idx), dev(T)
+    local, l2g_d, hop = P.gnn_extract_sampled_partition(G, Td, dev(srp), dev(sci))
+    assert list(hop) == list(off) and np.array_equal(l2g_d.cpu().numpy(), l2g)
+    assert np.array_equal(local.row_ptr.cpu().numpy(), rp)
+    assert np.array_equal(local.col_idx.cpu().numpy(), ci)
+    gs = B.Graph(P.gnn_expand_row_ptr(n, Td, dev(srp)), dev(sci), n_cols=n, sorted_columns=True)
+    dist, ring, _, hop = P.gnn_build_active_sets(gs, Td, 1)
+    new_id = torch.empty(n, dtype=torch.int32, device="cuda")
+    out_rp = torch.empty(len(l2g) + 1, dtype=torch.int32, device="cuda")
+    nnz_dev = torch.empty(1, dtype=torch.int64, device="cuda")
+    common = (C.byref(G.c), C.byref(gs.c), B._ptr(ring), len(l2g), B._ptr(dist), B._ptr(new_id), B._ptr(out_rp))
+    B._with_ws(B.lib().gnn_extract_sampled_partition, common + (None, 0, B._ptr(nnz_dev), None), (B._stream(),), None)
+    for cap in sorted({int(rp[j]) + d for j in range(nt, len(l2g)) for d in (1, 2, 37)}):
+        if cap > ci.size:
+            continue
+        out = torch.full((ci.size,), -7, dtype=torch.int32, device="cuda")
+        B._with_ws(B.lib().gnn_extract_sampled_partition, common + (B._ptr(out), cap, B._ptr(nnz_dev), None), (B._stream(),), None)
+        got = out.cpu().numpy()
+        assert np.array_equal(got[:cap], ci[:cap]) and (got[cap:] == -7).all(), cap
