@@ -193,16 +193,16 @@ __device__ __forceinline__ void as_push_hubs(const int32_t* __restrict__ row_ptr
         const int32_t part = (int32_t)(job % parts);
         const int64_t s0 = row_ptr[v], len = row_ptr[v + 1] - s0;
         const int32_t s = (int32_t)(s0 + len * part / parts), e = (int32_t)(s0 + len * (part + 1) / parts);
-        for (int32_t base = s + (int32_t)threadIdx.x; base < e; base += 256 * kAsU) {
+        for (uint32_t base = s + threadIdx.x; base < (uint32_t)e; base += 256 * kAsU) {   // (past the end, a position may not fit an int32_t)
             int32_t u[kAsU];
             uint8_t w[kAsU];
 #pragma unroll
-            for (int j = 0; j < kAsU; ++j) u[j] = base + j * 256 < e ? col_idx[base + j * 256] : 0;
+            for (int j = 0; j < kAsU; ++j) u[j] = base + j * 256 < (uint32_t)e ? col_idx[base + j * 256] : 0;
 #pragma unroll
             for (int j = 0; j < kAsU; ++j) w[j] = seen[u[j]];
 #pragma unroll
             for (int j = 0; j < kAsU; ++j)
-                if (base + j * 256 < e && !w[j]) seen[u[j]] = 1;
+                if (base + j * 256 < (uint32_t)e && !w[j]) seen[u[j]] = 1;
         }
     }
 }
@@ -236,10 +236,10 @@ __device__ __forceinline__ void as_pull(const int32_t* __restrict__ row_ptr_t, c
                 continue;
             }
             bool found = false;
-            for (int32_t p = s; p < e && !found; p += 64) {
+            for (uint32_t p = s; p < (uint32_t)e && !found; p += 64) {
                 int32_t u[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) u[j] = p + j * 16 + sl < e ? col_idx_t[p + j * 16 + sl] : -1;
+                for (int j = 0; j < 4; ++j) u[j] = p + j * 16 + sl < (uint32_t)e ? col_idx_t[p + j * 16 + sl] : -1;
                 bool hit = false;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) hit |= u[j] >= 0 && in_set(frontier, u[j]);
@@ -257,9 +257,9 @@ __device__ __forceinline__ void as_pull_hubs(const int32_t* __restrict__ row_ptr
     for (int32_t h = blockIdx.x; h < n_hubs; h += gridDim.x) {   // uniform over the workgroup
         const int32_t v = hubq[h];
         const int32_t s = row_ptr_t[v], e = row_ptr_t[v + 1];
-        for (int32_t base = s; base < e; base += 256) {
-            const int32_t p = base + (int32_t)threadIdx.x;
-            const int hit = p < e && in_set(frontier, col_idx_t[p]);
+        for (uint32_t base = s; base < (uint32_t)e; base += 256) {
+            const uint32_t p = base + threadIdx.x;
+            const int hit = p < (uint32_t)e && in_set(frontier, col_idx_t[p]);
             if (__syncthreads_or(hit)) {
                 if (threadIdx.x == 0) seen[v] = 1;
                 break;
@@ -425,8 +425,8 @@ __global__ __launch_bounds__(256) void eas_connections_kernel(const int32_t* __r
     for (int64_t u = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / 16; u < n; u += groups) {
         const int32_t s = row_ptr[u], e = row_ptr[u + 1];
         int32_t c = 0;
-        for (int32_t p = s; p < e; p += 16) {
-            const bool open = p + sl < e && !in_set(visited, col_idx[p + sl]);
+        for (uint32_t p = s; p < (uint32_t)e; p += 16) {
+            const bool open = p + sl < (uint32_t)e && !in_set(visited, col_idx[p + sl]);
             c += __popcll((__ballot(open) >> (sub * 16)) & 0xffffull);
         }
         if (sl == 0) conn[u] = c;
@@ -467,7 +467,7 @@ __global__ __launch_bounds__(256) void eas_expand_kernel(const int32_t* __restri
         bool cand[kPerLane];
         uint64_t key[kPerLane];
 #pragma unroll
-        for (int j = 0; j < kPerLane; ++j) u[j] = s + j * 16 + sl < e ? col_idx[s + j * 16 + sl] : -1;
+        for (int j = 0; j < kPerLane; ++j) u[j] = (uint32_t)s + j * 16 + sl < (uint32_t)e ? col_idx[(uint32_t)s + j * 16 + sl] : -1;
 #pragma unroll
         for (int j = 0; j < kPerLane; ++j) cand[j] = u[j] >= 0 && !in_set(visited, u[j]);
         int32_t n_cand = 0;
@@ -548,10 +548,10 @@ __global__ __launch_bounds__(256) void eas_expand_long_kernel(const int32_t* __r
         int32_t thr_u = 0x7fffffff;
         int32_t n_list = 0;       // pairs in the list
         int32_t n_cand = 0;       // candidates of the row (only needed when not streaming)
-        for (int32_t p = s; p < e; p += kWave) {
-            const int32_t q = p + lane;
-            const int32_t u = q < e ? col_idx[q] : 0;
-            const bool cand = q < e && !in_set(visited, u);
+        for (uint32_t p = s; p < (uint32_t)e; p += kWave) {
+            const uint32_t q = p + lane;
+            const int32_t u = q < (uint32_t)e ? col_idx[q] : 0;
+            const bool cand = q < (uint32_t)e && !in_set(visited, u);
             const uint64_t k = cand ? eas_key(rule, seed_hop_mixed, conn, v, u) : 0ull;
             bool take = cand && !pair_less(thr_k, thr_u, k, u);
             uint64_t mask = __ballot(take);
@@ -585,7 +585,7 @@ __global__ __launch_bounds__(256) void eas_expand_long_kernel(const int32_t* __r
                 for (int32_t round = 0; round < fanout; ++round) {
                     uint64_t best_k = ~0ull;
                     int32_t best_u = 0x7fffffff;
-                    for (int32_t p = s + lane; p < e; p += kWave) {
+                    for (uint32_t p = (uint32_t)s + lane; p < (uint32_t)e; p += kWave) {
                         const int32_t u = col_idx[p];
                         if (in_set(visited, u)) continue;
                         const uint64_t k = eas_key(rule, seed_hop_mixed, conn, v, u);
@@ -609,7 +609,7 @@ __global__ __launch_bounds__(256) void eas_expand_long_kernel(const int32_t* __r
                 thr_k = prev_k;
                 thr_u = prev_u;
             }
-            for (int32_t p = s + lane; p < e; p += kWave) {
+            for (uint32_t p = (uint32_t)s + lane; p < (uint32_t)e; p += kWave) {
                 const int32_t u = col_idx[p];
                 if (in_set(visited, u)) continue;
                 if (!pair_less(thr_k, thr_u, eas_key(rule, seed_hop_mixed, conn, v, u), u) && !seen[u]) seen[u] = 1;

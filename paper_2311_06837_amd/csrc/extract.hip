@@ -148,7 +148,10 @@ __global__ __launch_bounds__(256) void ex_count_kernel(ExArgs a) {
         }
         int32_t u[4], cnt = 0;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) u[r] = s + r * kRowLanes + sl < e ? a.ci[s + r * kRowLanes + sl] : -1;
+        for (int r = 0; r < 4; ++r) {
+            const uint32_t p = (uint32_t)s + r * kRowLanes + sl;   // (past the row's end, a position may not fit an int32_t)
+            u[r] = p < (uint32_t)e ? a.ci[p] : -1;
+        }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             int32_t id = -1;
@@ -241,7 +244,10 @@ __global__ __launch_bounds__(256) void ex_fill_kernel(ExArgs a) {
         int32_t u[4], id[4], cls[4];
         uint32_t classes = 0u;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) u[r] = s + r * kRowLanes + sl < e ? a.ci[s + r * kRowLanes + sl] : -1;
+        for (int r = 0; r < 4; ++r) {
+            const uint32_t p = (uint32_t)s + r * kRowLanes + sl;   // (past the row's end, a position may not fit an int32_t)
+            u[r] = p < (uint32_t)e ? a.ci[p] : -1;
+        }
 #pragma unroll
         for (int r = 0; r < 4; ++r) id[r] = u[r] >= 0 ? a.new_id[u[r]] : -1;
 #pragma unroll
@@ -282,7 +288,10 @@ __device__ __forceinline__ void ex_fill_medium(const ExArgs& a, int32_t first) {
         int32_t id[EPL], cls[EPL];
         uint32_t classes = 0u;
 #pragma unroll
-        for (int r = 0; r < EPL; ++r) id[r] = s + r * kWave + lane < e ? a.ci[s + r * kWave + lane] : -1;
+        for (int r = 0; r < EPL; ++r) {
+            const uint32_t p = (uint32_t)s + r * kWave + lane;
+            id[r] = p < (uint32_t)e ? a.ci[p] : -1;
+        }
 #pragma unroll
         for (int r = 0; r < EPL; ++r) id[r] = id[r] >= 0 ? a.new_id[id[r]] : -1;
 #pragma unroll

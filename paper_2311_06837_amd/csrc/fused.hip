@@ -178,11 +178,10 @@ __global__ __launch_bounds__(256) void fused_agg_linear_kernel(FusedArgs a) {
 #pragma unroll
         for (int d = LPR; d < kWave; d <<= 1) len_max = max(len_max, __shfl_xor(len_max, d, kWave));
         for (int off = 0; off < len_max; off += LPR) {   // uniform over the wavefront
-            const int32_t p = s + off + sl;
-            const bool in = p < e;
-            const int32_t u_mine = in ? a.col_idx[p] : 0;
-            const float w_mine = (in && a.nbr_scale) ? a.nbr_scale[u_mine] : 1.f;
             int cnt = e - s - off;
+            const bool in = sl < cnt;
+            const int32_t u_mine = in ? a.col_idx[s + off + sl] : 0;
+            const float w_mine = (in && a.nbr_scale) ? a.nbr_scale[u_mine] : 1.f;
             cnt = cnt < 0 ? 0 : (cnt < LPR ? cnt : LPR);
             int cnt_max = cnt;
 #pragma unroll
@@ -201,13 +200,11 @@ __global__ __launch_bounds__(256) void fused_agg_linear_kernel(FusedArgs a) {
         float acc[VE];
 #pragma unroll
         for (int t = 0; t < VE; ++t) acc[t] = 0.f;
-        for (int32_t base = s; base < e; base += NG * LPR) {   // uniform over the workgroup
-            const int32_t p0 = base + gi * LPR;
-            const int32_t p = p0 + sl;
-            const bool in = p < e;
-            const int32_t u_mine = in ? a.col_idx[p] : 0;
+        for (int32_t left = e - s; left > 0; left -= NG * LPR) {   // uniform over the workgroup
+            int cnt = left - gi * LPR;
+            const bool in = sl < cnt;
+            const int32_t u_mine = in ? a.col_idx[e - cnt + sl] : 0;   // (a position past the row's end may not fit 32 bits)
             const float w_mine = (in && a.nbr_scale) ? a.nbr_scale[u_mine] : 1.f;
-            int cnt = e - p0;
             cnt = cnt < 0 ? 0 : (cnt < LPR ? cnt : LPR);
             int cnt_max = cnt;
 #pragma unroll

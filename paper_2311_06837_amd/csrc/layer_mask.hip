@@ -70,8 +70,8 @@ __global__ __launch_bounds__(256) void lm_mask_kernel(const int32_t* __restrict_
         uint32_t cand = 0u;
 #pragma unroll
         for (int j = 0; j < kPerLane; ++j) {
-            const int32_t p = s + j * kLmLanes + sl;
-            u[j] = p < e ? col_idx[p] : -1;
+            const uint32_t p = (uint32_t)s + j * kLmLanes + sl;   // (past the row's end, a position may not fit an int32_t)
+            u[j] = p < (uint32_t)e ? col_idx[p] : -1;
         }
 #pragma unroll
         for (int j = 0; j < kPerLane; ++j) {
@@ -167,7 +167,7 @@ __device__ __forceinline__ void lm_pair_of_hub(const int32_t* __restrict__ col_i
     for (int32_t round = 0; round < fanout; ++round) {
         uint64_t best_k = ~0ull;
         int32_t best_u = 0x7fffffff;
-        for (int32_t p = s + lane; p < e; p += kWave) {
+        for (uint32_t p = (uint32_t)s + lane; p < (uint32_t)e; p += kWave) {
             const int32_t u = col_idx[p];
             const uint64_t k = edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)u);
             if (pair_less(prev_k, prev_u, k, u) && pair_less(k, u, best_k, best_u)) {
@@ -229,11 +229,14 @@ __global__ __launch_bounds__(256) void lm_mask_long_kernel(const int32_t* __rest
                 int32_t u[NP];
                 uint32_t cand = 0u;
 #pragma unroll
-                for (int j = 0; j < NP; ++j) u[j] = s + j * kWave + lane < e ? col_idx[s + j * kWave + lane] : -1;
+                for (int j = 0; j < NP; ++j) {
+                    const uint32_t p = (uint32_t)s + j * kWave + lane;
+                    u[j] = p < (uint32_t)e ? col_idx[p] : -1;
+                }
 #pragma unroll
                 for (int j = 0; j < NP; ++j) {
                     key[j] = ~0ull;
-                    if (s + j * kWave < e) {   // uniform over the wavefront
+                    if ((uint32_t)s + j * kWave < (uint32_t)e) {   // uniform over the wavefront
                         key[j] = edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)(u[j] >= 0 ? u[j] : 0));
                         cand |= u[j] >= 0 ? 1u << j : 0u;
                     }
@@ -241,7 +244,7 @@ __global__ __launch_bounds__(256) void lm_mask_long_kernel(const int32_t* __rest
                 if (fanout > 0 && e - s > fanout) group_kth<NP, kWave>(key, u, cand, fanout, true, thr_k, thr_u);
 #pragma unroll
                 for (int j = 0; j < NP; ++j) {
-                    if (s + j * kWave < e) {   // uniform over the wavefront
+                    if ((uint32_t)s + j * kWave < (uint32_t)e) {   // uniform over the wavefront
                         const uint64_t m = __ballot(u[j] >= 0 && !pair_less(thr_k, thr_u, key[j], u[j]));
                         kept += __popcll(m);
                         lm_or_tile(bits, (int64_t)s + j * kWave, m);
@@ -375,9 +378,9 @@ __global__ __launch_bounds__(256) void lm_transpose_kernel(const int32_t* __rest
         len_max = max(len_max, __shfl_xor(len_max, 16, kWave));
         len_max = max(len_max, __shfl_xor(len_max, 32, kWave));
         for (int32_t off = 0; off < len_max; off += kLmLanes) {
-            const int32_t q = s + off + sl;
+            const uint32_t q = (uint32_t)s + off + sl;
             bool bit = false;
-            if (q < e) {
+            if (q < (uint32_t)e) {
                 const int32_t v = ciT[q];
                 int32_t lo = row_ptr[v], hi = row_ptr[v + 1];  // first position of row v whose column is >= u
                 while (lo < hi) {

@@ -54,12 +54,12 @@ __global__ __launch_bounds__(256) void sb_count_kernel(const int32_t* __restrict
         int32_t ru[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {  // all four loads of a lane in flight together
-            const int32_t p = s + r * kRowLanes + sl;
-            ru[r] = p < e ? col_idx[p] : 0;
+            const uint32_t p = (uint32_t)s + r * kRowLanes + sl;   // (past the row's end, a position may not fit an int32_t)
+            ru[r] = p < (uint32_t)e ? col_idx[p] : 0;
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const bool valid = s + r * kRowLanes + sl < e;
+            const bool valid = (uint32_t)s + r * kRowLanes + sl < (uint32_t)e;
             const bool inner = valid && in_set(tbits, ru[r]);
             n_in += __popc(group_ballot(inner, sub));
             n_ext += __popc(group_ballot(valid && !inner, sub));
@@ -101,13 +101,13 @@ __global__ __launch_bounds__(256) void sb_fill_kernel(const int32_t* __restrict_
     int32_t n_out = 0;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int32_t p = s + r * kRowLanes + sl;
-        ru[r] = p < e ? col_idx[p] : 0;
+        const uint32_t p = (uint32_t)s + r * kRowLanes + sl;
+        ru[r] = p < (uint32_t)e ? col_idx[p] : 0;
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int32_t p = s + r * kRowLanes + sl;
-        rf[r] = p < e ? (in_set(tbits, ru[r]) ? 1 : 2) : 0;
+        const uint32_t p = (uint32_t)s + r * kRowLanes + sl;
+        rf[r] = p < (uint32_t)e ? (in_set(tbits, ru[r]) ? 1 : 2) : 0;
         rk[r] = rf[r] == 2 ? edge_key(seed_hop_mixed, (uint64_t)v, (uint64_t)ru[r]) : ~0ull;
         n_out += __popc(group_ballot(rf[r] == 2, sub));
     }
@@ -159,14 +159,14 @@ __global__ __launch_bounds__(256) void sb_medium_rows_kernel(const int32_t* __re
         int rf[EPL];  // 0: no entry, 1: neighbour inside the target set, 2: outside
 #pragma unroll
         for (int r = 0; r < EPL; ++r) {
-            const int32_t p = s + r * kWave + lane;
-            ru[r] = p < e ? col_idx[p] : 0;
+            const uint32_t p = (uint32_t)s + r * kWave + lane;
+            ru[r] = p < (uint32_t)e ? col_idx[p] : 0;
         }
         int32_t n_in = 0, n_ext = 0;
 #pragma unroll
         for (int r = 0; r < EPL; ++r) {
-            const int32_t p = s + r * kWave + lane;
-            rf[r] = p < e ? (in_set(tbits, ru[r]) ? 1 : 2) : 0;
+            const uint32_t p = (uint32_t)s + r * kWave + lane;
+            rf[r] = p < (uint32_t)e ? (in_set(tbits, ru[r]) ? 1 : 2) : 0;
             n_in += __popcll(__ballot(rf[r] == 1));
             n_ext += __popcll(__ballot(rf[r] == 2));
         }
@@ -275,13 +275,13 @@ __global__ __launch_bounds__(256) void sb_long_rows_kernel(const int32_t* __rest
         const int32_t v = targets[i];
         const int32_t s = row_ptr[v], e = row_ptr[v + 1];
         int n_in = 0, n_ext = 0;
-        for (int32_t base = s; base < e; base += 1024) {
+        for (uint32_t base = s; base < (uint32_t)e; base += 1024) {
             int32_t u[4];
             bool ok[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int32_t p = base + r * 256 + tid;
-                ok[r] = p < e;
+                const uint32_t p = base + r * 256 + tid;
+                ok[r] = p < (uint32_t)e;
                 u[r] = ok[r] ? col_idx[p] : 0;
             }
 #pragma unroll
@@ -365,13 +365,13 @@ __global__ __launch_bounds__(256) void sb_long_rows_kernel(const int32_t* __rest
             for (int32_t round = 0; round < fanout; ++round) {
                 uint64_t best_k = ~0ull;
                 int32_t best_u = 0x7fffffff;
-                for (int32_t base = s; base < e; base += 1024) {
+                for (uint32_t base = s; base < (uint32_t)e; base += 1024) {
                     int32_t u[4];
                     bool ok[4];
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        const int32_t p = base + r * 256 + tid;
-                        ok[r] = p < e;
+                        const uint32_t p = base + r * 256 + tid;
+                        ok[r] = p < (uint32_t)e;
                         u[r] = ok[r] ? col_idx[p] : 0;
                     }
 #pragma unroll
@@ -393,11 +393,11 @@ __global__ __launch_bounds__(256) void sb_long_rows_kernel(const int32_t* __rest
             thr_u = prev_u;
         }
         int64_t pos = out_row_ptr[i];
-        for (int32_t base = s; base < e; base += 256) {
-            const int32_t p = base + tid;
+        for (uint32_t base = s; base < (uint32_t)e; base += 256) {
+            const uint32_t p = base + tid;
             bool keep = false;
             int32_t u = 0;
-            if (p < e) {
+            if (p < (uint32_t)e) {
                 u = col_idx[p];
                 if (in_set(tbits, u)) keep = true;
                 else keep = !pair_less(thr_k, thr_u, edge_key(seed_hop_mixed, (uint64_t)v, (uint64_t)u), u);

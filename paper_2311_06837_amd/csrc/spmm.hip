@@ -488,7 +488,7 @@ __global__ __launch_bounds__(256, NCH == 1 ? (LPR == 64 ? GNN_SPMM_MINB_WIDE : G
     // Tile descriptors (row slot j, position p, row end e, valid flag) of the current tile and of the
     // two tiles after it: ids are fetched two tiles ahead and their dist values (backward filter) one
     // tile ahead, so neither latency is paid between two gathers.
-    auto advance = [&](int j, int32_t p, int32_t e, bool hv, int& jo, int32_t& po, int32_t& eo, bool& ho) {
+    auto advance = [&](int j, uint32_t p, uint32_t e, bool hv, int& jo, uint32_t& po, uint32_t& eo, bool& ho) {   // (past a row's end, a position may not fit an int32_t)
         const bool done = hv && p + LPR >= e;
         int got = 0;
         if (done && sl == 0) got = atomicAdd(&s_next, 1);
@@ -503,13 +503,13 @@ __global__ __launch_bounds__(256, NCH == 1 ? (LPR == 64 ? GNN_SPMM_MINB_WIDE : G
     };
     int jc = gi;
     bool have = jc < n_chunk;
-    int32_t pc = 0, ec = 0;
+    uint32_t pc = 0, ec = 0;
     if (have) {
         pc = s_row_s[jc];
         ec = s_row_e[jc];
     }
     int jn;
-    int32_t pn, en;
+    uint32_t pn, en;
     bool have_n;
     advance(jc, pc, ec, have, jn, pn, en, have_n);
     int32_t u_c = (have && pc + sl < ec) ? a.col_idx[pc + sl] : 0;
@@ -519,14 +519,14 @@ __global__ __launch_bounds__(256, NCH == 1 ? (LPR == 64 ? GNN_SPMM_MINB_WIDE : G
     while (__ballot(have) != 0ull) {  // uniform over the wave
         const bool row_done = have && pc + LPR >= ec;
         int jnn;
-        int32_t pnn, enn;
+        uint32_t pnn, enn;
         bool have_nn;
         advance(jn, pn, en, have_n, jnn, pnn, enn, have_nn);
         const int32_t u_nn = (have_nn && pnn + sl < enn) ? a.col_idx[pnn + sl] : 0;  // two tiles ahead
         int32_t d_n = 0;
         if (FILTER) d_n = (have_n && pn + sl < en) ? filter_probe(a, u_n, pn + sl) : -1;  // one tile ahead
 
-        int left = have ? ec - pc : 0;
+        int left = have ? (int)(ec - pc) : 0;
         left = left < 0 ? 0 : (left < LPR ? left : LPR);
         wave_lds_sync();  // the previous tile has been consumed
         const int cnt = commit_tile<LPR, FILTER>(a, sl < left, u_c, d_c, left, sub, sl, s_idx);
@@ -1009,13 +1009,13 @@ __global__ __launch_bounds__(256) void spmm_prepare_kernel(const int32_t* __rest
         // kT tiles of 16 entries per step: all their id loads go out together, then all dist / scale loads, so a
         // typical segment (a few tiles) pays each memory latency once instead of once per tile
         constexpr int kT = 4;
-        for (int32_t p = lo; p < hi; p += kT * LPG) {
+        for (uint32_t p = lo; p < (uint32_t)hi; p += kT * LPG) {
             int32_t u[kT], d[kT];
             float f[kT];
             bool valid[kT];
 #pragma unroll
             for (int t = 0; t < kT; ++t) {
-                valid[t] = p + t * LPG + sl < hi;
+                valid[t] = p + t * LPG + sl < (uint32_t)hi;
                 u[t] = valid[t] ? col_idx[p + t * LPG + sl] : 0;
             }
 #pragma unroll
