@@ -126,10 +126,12 @@ __device__ __forceinline__ uint64_t key_guess(int32_t want, int32_t n) {
     return want >= n ? ~0ull : (~0ull / (uint64_t)n) * (uint64_t)want;
 }
 
-// How many keys to aim for when the k smallest are wanted: fewer than k come out of it in one of a few million rows.
-__device__ __forceinline__ int32_t guess_count(int32_t k) { return k + 6 * (int32_t)ceilf(sqrtf((float)k)) + 10; }
+// How far from k to aim when the k-th smallest key is wanted: aimed at k + spread keys, fewer than k lie at or below the
+// guess in one of a few million rows; aimed at k - spread, k or more do about as rarely.
+__host__ __device__ __forceinline__ int32_t guess_spread(int32_t k) { return 6 * (int32_t)ceilf(sqrtf((float)k)) + 10; }
+__device__ __forceinline__ int32_t guess_count(int32_t k) { return k + guess_spread(k); }
 
-// ---- a wavefront's list of (key, id) pairs in LDS: the selection step shared by the traversal and the layer masks ----
+// ---- a wavefront's list of (key, id) pairs in LDS: the selection step of the traversal ----
 
 // The k-th smallest of the n (> k >= 1) distinct pairs of the list: k rounds of "smallest pair above the previous
 // one".  Every lane returns the same pair.

@@ -8,10 +8,10 @@
 //                        on which group runs first.  The threshold rule has a fixed pair; the fanout rule selects its
 //                        pair in registers (group_kth).
 //   lm_mask_long_kernel  the longer rows, a wavefront each.  Up to 1024 entries the fanout rule holds the row's keys in
-//                        registers; beyond, one sweep lists the entries below a guessed key in LDS (the keys are uniform:
-//                        the guess holds a few more than `fanout` of them), the pair is selected from that list and a
-//                        second sweep writes the bits.  Where the guess fails, or the fanout is too large for the list,
-//                        `fanout` rounds over the row itself find the pair.
+//                        registers; beyond, one sweep lists the entries between two guessed keys in LDS (the keys are uniform:
+//                        the pair lies between them, and they hold some 12 * sqrt(fanout) entries) and counts those below;
+//                        the pair is selected from that list and a second sweep writes the bits.  Where the guess fails, or
+//                        the fanout is too large for the list (above 4624), `fanout` rounds over the row itself find the pair.
 //   lm_transpose_kernel  the same mask in the positions of the transposed graph (backward aggregation): entry q =
 //                        (row u, column v) of the transposed graph looks up u in row v of the graph by binary search.
 //   lm_mask_t_kernel     the fast way to the same transposed mask: both rules are "(key, id) <= the row's threshold
@@ -41,7 +41,14 @@ __device__ __forceinline__ void lm_or_bits(uint32_t* __restrict__ bits, int64_t 
 
 constexpr int kLmShortRow = 64;              // rows up to this length: sixteen lanes, longer ones: a wavefront
 constexpr int kLmRegRow = 16 * kWave;        // fanout rule: rows up to this length stay in a wavefront's registers
-constexpr int kLmListCap = 256;              // pairs a wavefront lists in LDS
+constexpr int kLmListCap = 256;              // pairs a wavefront lists in LDS for fanouts up to 144
+constexpr int kLmListCapWide = 1024;         // ... and above (48 KB a workgroup instead of 12)
+
+// Entries a row's list holds, with room for six standard deviations.
+static inline int32_t lm_list_need(int32_t fanout) {
+    const int32_t aim = fanout < guess_spread(fanout) ? fanout + guess_spread(fanout) : 2 * guess_spread(fanout);
+    return aim + 6 * (int32_t)ceilf(sqrtf((float)aim));
+}
 
 __global__ __launch_bounds__(256) void lm_mask_kernel(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
                                                       const int32_t* __restrict__ rows, int32_t n_active, int32_t rule, int32_t fanout,
@@ -118,15 +125,16 @@ __device__ __forceinline__ void lm_or_tile(uint32_t* __restrict__ bits, int64_t 
 }
 
 // The fanout rule's pair of a row of more than kLmRegRow (> fanout) entries; see the head of the file.
+template <int CAP>
 __device__ __forceinline__ void lm_pair_of_hub(const int32_t* __restrict__ col_idx, int32_t v, int32_t s, int32_t e, int32_t fanout,
                                                uint64_t seed_layer_mixed, uint64_t* key, int32_t* id, uint64_t& thr_k, int32_t& thr_u) {
     constexpr int kU = 4;
     const int lane = lane_id();
     const uint64_t lanes_below = (1ull << lane) - 1ull;
-    const int32_t want = fanout <= kLmListCap / 2 ? guess_count(fanout) : kLmListCap + 1;
-    int32_t n_list = 0;
-    if (want <= kLmListCap / 2) {
-        const uint64_t guess = key_guess(want, e - s);
+    const int32_t spread = guess_spread(fanout);
+    int32_t n_list = 0, n_below = 0;
+    if (fanout <= CAP * 8) {   // (the list may hold it: see lm_list_need)
+        const uint64_t low = fanout > spread ? key_guess(fanout - spread, e - s) : 0ull, high = key_guess(fanout + spread, e - s);
         for (int64_t p = s; p < e; p += kU * kWave) {
             int32_t u[kU];
 #pragma unroll
@@ -134,10 +142,11 @@ __device__ __forceinline__ void lm_pair_of_hub(const int32_t* __restrict__ col_i
 #pragma unroll
             for (int j = 0; j < kU; ++j) {
                 const uint64_t k = edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)(u[j] >= 0 ? u[j] : 0));
-                const bool take = u[j] >= 0 && k <= guess;
+                const bool take = u[j] >= 0 && k >= low && k <= high;
+                n_below += __popcll(__ballot(u[j] >= 0 && k < low));
                 const uint64_t m = __ballot(take);
                 const int32_t pos = n_list + __popcll(m & lanes_below);
-                if (take && pos < kLmListCap) {
+                if (take && pos < CAP) {
                     key[pos] = k;
                     id[pos] = u[j];
                 }
@@ -146,8 +155,8 @@ __device__ __forceinline__ void lm_pair_of_hub(const int32_t* __restrict__ col_i
         }
         wave_lds_sync();
     }
-    if (n_list >= fanout && n_list <= kLmListCap) {   // uniform over the wavefront
-        constexpr int NP = kLmListCap / kWave;
+    if (n_below < fanout && n_below + n_list >= fanout && n_list <= CAP) {   // uniform over the wavefront
+        constexpr int NP = CAP / kWave;
         uint64_t k[NP];
         int32_t u[NP];
         uint32_t cand = 0u;
@@ -158,7 +167,7 @@ __device__ __forceinline__ void lm_pair_of_hub(const int32_t* __restrict__ col_i
             u[j] = in ? id[j * kWave + lane] : 0x7fffffff;
             cand |= in ? 1u << j : 0u;
         }
-        group_kth<NP, kWave>(k, u, cand, fanout, true, thr_k, thr_u);
+        group_kth<NP, kWave>(k, u, cand, fanout - n_below, true, thr_k, thr_u);
         wave_lds_sync();   // the list is read before the next row overwrites it
         return;
     }
@@ -194,13 +203,14 @@ __device__ __forceinline__ void lm_pair_of_hub(const int32_t* __restrict__ col_i
 // Rows longer than kLmShortRow: a wavefront looks at kLmLook rows of the list at a time and takes the long ones one by one.
 constexpr int kLmLook = 16;
 
+template <int CAP>
 __global__ __launch_bounds__(256) void lm_mask_long_kernel(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
                                                            const int32_t* __restrict__ rows, int32_t n_active, int32_t rule, int32_t fanout,
                                                            uint64_t threshold, uint64_t seed_layer_mixed, uint32_t* __restrict__ bits,
                                                            int32_t* __restrict__ kept_len, uint64_t* __restrict__ row_thr_key,
                                                            int32_t* __restrict__ row_thr_id) {
-    __shared__ uint64_t s_key[4][kLmListCap];
-    __shared__ int32_t s_id[4][kLmListCap];
+    __shared__ uint64_t s_key[4][CAP];
+    __shared__ int32_t s_id[4][CAP];
     const int lane = lane_id(), wave = (int)(threadIdx.x >> 6);
     const int64_t waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
     for (int64_t base = (((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6) * kLmLook; base < n_active; base += waves * kLmLook) {
@@ -252,7 +262,7 @@ __global__ __launch_bounds__(256) void lm_mask_long_kernel(const int32_t* __rest
                 }
             } else {
                 if (by_fanout && fanout > 0 && e - s > fanout)
-                    lm_pair_of_hub(col_idx, v, s, e, fanout, seed_layer_mixed, s_key[wave], s_id[wave], thr_k, thr_u);
+                    lm_pair_of_hub<CAP>(col_idx, v, s, e, fanout, seed_layer_mixed, s_key[wave], s_id[wave], thr_k, thr_u);
                 constexpr int kU = 4;
                 for (int64_t p = s; p < e; p += kU * kWave) {
                     int32_t u[kU];
@@ -428,9 +438,15 @@ extern "C" int32_t gnn_layer_edge_mask(const gnn_csr* g, const int32_t* rows, in
             row_thr_id);
         GNN_LAUNCH_CHECK("lm_mask_kernel");
         if (g->nnz > kLmShortRow) {   // else no row is longer
-            lm_mask_long_kernel<<<grid_for(((int64_t)n_active + kLmLook - 1) / kLmLook, 4, 8192), 256, 0, stream>>>(
-                g->row_ptr, g->col_idx, rows, n_active, rule, fanout, threshold, mix64(seed + (uint64_t)layer), edge_keep, kept_len,
-                row_thr_key, row_thr_id);
+            const bool wide = rule == GNN_LAYER_MASK_FANOUT && lm_list_need(fanout) > kLmListCap && lm_list_need(fanout) <= kLmListCapWide;
+            const int grid = grid_for(((int64_t)n_active + kLmLook - 1) / kLmLook, 4, 8192);
+            const uint64_t mixed = mix64(seed + (uint64_t)layer);
+            if (wide)
+                lm_mask_long_kernel<kLmListCapWide><<<grid, 256, 0, stream>>>(g->row_ptr, g->col_idx, rows, n_active, rule, fanout, threshold,
+                                                                              mixed, edge_keep, kept_len, row_thr_key, row_thr_id);
+            else
+                lm_mask_long_kernel<kLmListCap><<<grid, 256, 0, stream>>>(g->row_ptr, g->col_idx, rows, n_active, rule, fanout, threshold,
+                                                                          mixed, edge_keep, kept_len, row_thr_key, row_thr_id);
             GNN_LAUNCH_CHECK("lm_mask_long_kernel");
         }
     }

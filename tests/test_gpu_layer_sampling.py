@@ -61,14 +61,67 @@ def test_masks_hub_rows_empty_rows_and_nothing_listed():
     assert big.degrees().max() > 4096
     _mask_case(big, None, "fanout", 30, 1, 2)
     _mask_case(big, np.arange(0, 20000, 7), "fanout", 1, 2, 3)
-    _mask_case(big, np.arange(0, 20000, 3), "fanout", 990, 1, 4)     # too large a fanout for the bounded list: rounds over the row
-    _mask_case(big, np.arange(0, 20000, 3), "fanout", 960, 1, 5)     # the largest fanout the bounded list takes
+    _mask_case(big, np.arange(0, 20000, 3), "fanout", 990, 1, 4)     # rows of up to 1024 entries: rounds over registers, longer ones:
+    _mask_case(big, np.arange(0, 20000, 3), "fanout", 960, 1, 5)     # the wide list
     d = gg.random_directed(5000, 1.5, 13)
     assert (d.degrees() == 0).any()
     _mask_case(d, None, "fanout", 2, 1, 9)
     _mask_case(d, [], "fanout", 2, 1, 9)
     empty = gg.CSR(40, 40, np.zeros(41, dtype=np.int32), np.zeros(0, dtype=np.int32))
     _mask_case(empty, None, "threshold", M64, 1, 0)
+
+
+def _rows_of(lengths, n_cols, seed):
+    rng = np.random.default_rng(seed)
+    cols = [np.sort(rng.choice(n_cols, ln, replace=False)).astype(np.int32) for ln in lengths]
+    rp = np.zeros(len(lengths) + 1, dtype=np.int32)
+    rp[1:] = np.cumsum(lengths)
+    return gg.CSR(len(lengths), n_cols, rp, np.concatenate(cols))
+
+
+@pytest.mark.parametrize("fanout", [1, 45, 46, 64, 65, 100, 144, 145, 500, 1023, 1024, 1025, 2999, 4624, 4625, 9000])
+def test_fanouts_around_the_limits_of_the_lists(fanout):
+    """Rows on both sides of what sixteen lanes (64) and registers (1024) hold, and longer ones, at fanouts on both sides of
+    where the list of a long row starts above nothing (46), gets wide (145) and is given up (4625): bits, kept lengths and
+    threshold pairs."""
+    import paper_2311_06837_amd as P
+    g = _rows_of([20, 64, 65, 900, 1024, 1025, 1300, 3000, 5000, 12000, 40000] * 2, 50000, fanout)
+    G, keep, okeep = _mask_case(g, None, "fanout", fanout, 1, 77)
+    _, kept_len, tk, tu = P.gnn_layer_edge_mask(G, None, g.n_rows, "fanout", 1, 77, fanout=fanout, with_thresholds=True)
+    for r in range(g.n_rows):                       # the pair is the last kept entry's, or keeps everything
+        cols = g.col_idx[g.row_ptr[r]: g.row_ptr[r + 1]]
+        key, u = int(tk[r]) & M64, int(tu[r])
+        if cols.size <= fanout:
+            assert (key, u) == (M64, 0x7fffffff)
+        else:
+            kept = cols[okeep[g.row_ptr[r]: g.row_ptr[r + 1]] == 1]
+            assert (key, u) == max((oracle.edge_key(77, r, int(c), 1), int(c)) for c in kept)
+
+
+def _time_us(f):
+    f()
+    times = []
+    for _ in range(3):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record(), f(), b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b) * 1e3)
+    return min(times)
+
+
+def test_cost_of_long_rows():
+    """A long row is read a fixed number of times whatever the fanout (once per kept entry would be 100 times as much here)."""
+    import paper_2311_06837_amd as P
+    ln, n_cols = 60000, 200000
+    def mask(rows_of_it, fanout):
+        lens = torch.tensor([ln] * rows_of_it + [5] * (400 - rows_of_it), device="cuda")
+        rp = torch.zeros(401, dtype=torch.int32, device="cuda")
+        rp[1:] = torch.cumsum(lens, 0)
+        at = torch.arange(int(rp[-1]), device="cuda") - torch.repeat_interleave(rp[:-1], lens)
+        G = P.Graph(rp, (at * 3).int(), n_cols=n_cols, sorted_columns=True)
+        return _time_us(lambda: P.gnn_layer_edge_mask(G, None, 400, "fanout", 1, 5, fanout=fanout))
+    one = mask(1, 10)
+    assert mask(1, 100) < 6 * one and mask(1, 960) < 6 * one, "the cost grows with the fanout"
 
 
 def _mix64(x):
