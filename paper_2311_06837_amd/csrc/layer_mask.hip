@@ -200,89 +200,98 @@ __device__ __forceinline__ void lm_pair_of_hub(const int32_t* __restrict__ col_i
     thr_u = prev_u;
 }
 
-// Rows longer than kLmShortRow: a wavefront looks at kLmLook rows of the list at a time and takes the long ones one by one.
-constexpr int kLmLook = 16;
+// Rows longer than kLmShortRow: a wavefront looks at up to kLmLook rows of the list and takes the long ones one by one.
+// 64 wavefronts share a stretch of the list and take its rows in turn, one row of every 64: long rows that follow each other
+// (a graph numbered by degree, a list of hubs) go to different wavefronts, a list of fewer rows than the chip holds wavefronts
+// gives each of its rows one, and what runs at a time still lies close together.  From one group of 64 rows to the next the
+// wavefronts move by 37 places, so that long rows at regular distances do not meet in one of them.
+// Measured (fanout 10): 64 rows of 100 000 entries at the head of a list 10.5 ms with sixteen consecutive rows for a wavefront,
+// now 0.74; 2000 rows of 490 entries 121 us, now 39; 1.2M rows of 50 (with the short ones) 541 us, now 533 - 595 with
+// rows as far apart as there are wavefronts, which then run all over the graph at a time.
+constexpr int kLmLook = 32;
+constexpr int kLmShare = 64;
+constexpr int kLmWaves = 8192;    // fewer rows than this (twice what the chip holds at a time): one for a wavefront
 
 template <int CAP>
 __global__ __launch_bounds__(256) void lm_mask_long_kernel(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
                                                            const int32_t* __restrict__ rows, int32_t n_active, int32_t rule, int32_t fanout,
                                                            uint64_t threshold, uint64_t seed_layer_mixed, uint32_t* __restrict__ bits,
                                                            int32_t* __restrict__ kept_len, uint64_t* __restrict__ row_thr_key,
-                                                           int32_t* __restrict__ row_thr_id) {
+                                                           int32_t* __restrict__ row_thr_id, int32_t look) {
     __shared__ uint64_t s_key[4][CAP];
     __shared__ int32_t s_id[4][CAP];
     const int lane = lane_id(), wave = (int)(threadIdx.x >> 6);
-    const int64_t waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    for (int64_t base = (((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6) * kLmLook; base < n_active; base += waves * kLmLook) {
-        int32_t v_l = 0, s_l = 0, e_l = 0;
-        if (lane < kLmLook && base + lane < n_active) {
-            v_l = rows ? rows[base + lane] : (int32_t)(base + lane);
-            s_l = row_ptr[v_l];
-            e_l = row_ptr[v_l + 1];
+    const int64_t wave_g = (int64_t)blockIdx.x * 4 + wave;
+    const int64_t group = wave_g / kLmShare * look + lane;       // of 64 rows; lanes 0 .. look - 1
+    const int64_t i = group * kLmShare + ((wave_g + 37 * group) & (kLmShare - 1));
+    int32_t v_l = 0, s_l = 0, e_l = 0;
+    if (lane < look && i < n_active) {
+        v_l = rows ? rows[i] : (int32_t)i;
+        s_l = row_ptr[v_l];
+        e_l = row_ptr[v_l + 1];
+    }
+    uint64_t todo = __ballot(e_l - s_l > kLmShortRow);
+    while (todo) {   // uniform over the wavefront
+        const int from = __ffsll((unsigned long long)todo) - 1;
+        todo &= todo - 1ull;
+        const int32_t v = __builtin_amdgcn_readlane(v_l, from), s = __builtin_amdgcn_readlane(s_l, from),
+                      e = __builtin_amdgcn_readlane(e_l, from);
+        uint64_t thr_k = threshold;   // pairs above (thr_k, thr_u) are out
+        int32_t thr_u = 0x7fffffff, kept = 0;
+        const bool by_fanout = rule == GNN_LAYER_MASK_FANOUT;
+        if (by_fanout) {
+            thr_k = fanout == 0 ? 0ull : ~0ull;
+            thr_u = fanout == 0 ? -1 : 0x7fffffff;
         }
-        uint64_t todo = __ballot(e_l - s_l > kLmShortRow);
-        while (todo) {   // uniform over the wavefront
-            const int from = __ffsll((unsigned long long)todo) - 1;
-            todo &= todo - 1ull;
-            const int32_t v = __builtin_amdgcn_readlane(v_l, from), s = __builtin_amdgcn_readlane(s_l, from),
-                          e = __builtin_amdgcn_readlane(e_l, from);
-            uint64_t thr_k = threshold;   // pairs above (thr_k, thr_u) are out
-            int32_t thr_u = 0x7fffffff, kept = 0;
-            const bool by_fanout = rule == GNN_LAYER_MASK_FANOUT;
-            if (by_fanout) {
-                thr_k = fanout == 0 ? 0ull : ~0ull;
-                thr_u = fanout == 0 ? -1 : 0x7fffffff;
+        if (by_fanout && e - s <= kLmRegRow) {
+            constexpr int NP = kLmRegRow / kWave;
+            uint64_t key[NP];
+            int32_t u[NP];
+            uint32_t cand = 0u;
+#pragma unroll
+            for (int j = 0; j < NP; ++j) {
+                const uint32_t p = (uint32_t)s + j * kWave + lane;
+                u[j] = p < (uint32_t)e ? col_idx[p] : -1;
             }
-            if (by_fanout && e - s <= kLmRegRow) {
-                constexpr int NP = kLmRegRow / kWave;
-                uint64_t key[NP];
-                int32_t u[NP];
-                uint32_t cand = 0u;
 #pragma unroll
-                for (int j = 0; j < NP; ++j) {
-                    const uint32_t p = (uint32_t)s + j * kWave + lane;
-                    u[j] = p < (uint32_t)e ? col_idx[p] : -1;
-                }
-#pragma unroll
-                for (int j = 0; j < NP; ++j) {
-                    key[j] = ~0ull;
-                    if ((uint32_t)s + j * kWave < (uint32_t)e) {   // uniform over the wavefront
-                        key[j] = edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)(u[j] >= 0 ? u[j] : 0));
-                        cand |= u[j] >= 0 ? 1u << j : 0u;
-                    }
-                }
-                if (fanout > 0 && e - s > fanout) group_kth<NP, kWave>(key, u, cand, fanout, true, thr_k, thr_u);
-#pragma unroll
-                for (int j = 0; j < NP; ++j) {
-                    if ((uint32_t)s + j * kWave < (uint32_t)e) {   // uniform over the wavefront
-                        const uint64_t m = __ballot(u[j] >= 0 && !pair_less(thr_k, thr_u, key[j], u[j]));
-                        kept += __popcll(m);
-                        lm_or_tile(bits, (int64_t)s + j * kWave, m);
-                    }
-                }
-            } else {
-                if (by_fanout && fanout > 0 && e - s > fanout)
-                    lm_pair_of_hub<CAP>(col_idx, v, s, e, fanout, seed_layer_mixed, s_key[wave], s_id[wave], thr_k, thr_u);
-                constexpr int kU = 4;
-                for (int64_t p = s; p < e; p += kU * kWave) {
-                    int32_t u[kU];
-#pragma unroll
-                    for (int j = 0; j < kU; ++j) u[j] = p + j * kWave + lane < e ? col_idx[p + j * kWave + lane] : -1;
-#pragma unroll
-                    for (int j = 0; j < kU; ++j) {
-                        const uint64_t k = edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)(u[j] >= 0 ? u[j] : 0));
-                        const uint64_t m = __ballot(u[j] >= 0 && !pair_less(thr_k, thr_u, k, u[j]));
-                        kept += __popcll(m);
-                        if (m != 0ull) lm_or_tile(bits, p + j * kWave, m);   // uniform over the wavefront
-                    }
+            for (int j = 0; j < NP; ++j) {
+                key[j] = ~0ull;
+                if ((uint32_t)s + j * kWave < (uint32_t)e) {   // uniform over the wavefront
+                    key[j] = edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)(u[j] >= 0 ? u[j] : 0));
+                    cand |= u[j] >= 0 ? 1u << j : 0u;
                 }
             }
-            if (lane == 0) {
-                kept_len[v] = kept;
-                if (row_thr_key) {
-                    row_thr_key[v] = thr_k;
-                    row_thr_id[v] = thr_u;
+            if (fanout > 0 && e - s > fanout) group_kth<NP, kWave>(key, u, cand, fanout, true, thr_k, thr_u);
+#pragma unroll
+            for (int j = 0; j < NP; ++j) {
+                if ((uint32_t)s + j * kWave < (uint32_t)e) {   // uniform over the wavefront
+                    const uint64_t m = __ballot(u[j] >= 0 && !pair_less(thr_k, thr_u, key[j], u[j]));
+                    kept += __popcll(m);
+                    lm_or_tile(bits, (int64_t)s + j * kWave, m);
                 }
+            }
+        } else {
+            if (by_fanout && fanout > 0 && e - s > fanout)
+                lm_pair_of_hub<CAP>(col_idx, v, s, e, fanout, seed_layer_mixed, s_key[wave], s_id[wave], thr_k, thr_u);
+            constexpr int kU = 4;
+            for (int64_t p = s; p < e; p += kU * kWave) {
+                int32_t u[kU];
+#pragma unroll
+                for (int j = 0; j < kU; ++j) u[j] = p + j * kWave + lane < e ? col_idx[p + j * kWave + lane] : -1;
+#pragma unroll
+                for (int j = 0; j < kU; ++j) {
+                    const uint64_t k = edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)(u[j] >= 0 ? u[j] : 0));
+                    const uint64_t m = __ballot(u[j] >= 0 && !pair_less(thr_k, thr_u, k, u[j]));
+                    kept += __popcll(m);
+                    if (m != 0ull) lm_or_tile(bits, p + j * kWave, m);   // uniform over the wavefront
+                }
+            }
+        }
+        if (lane == 0) {
+            kept_len[v] = kept;
+            if (row_thr_key) {
+                row_thr_key[v] = thr_k;
+                row_thr_id[v] = thr_u;
             }
         }
     }
@@ -439,14 +448,18 @@ extern "C" int32_t gnn_layer_edge_mask(const gnn_csr* g, const int32_t* rows, in
         GNN_LAUNCH_CHECK("lm_mask_kernel");
         if (g->nnz > kLmShortRow) {   // else no row is longer
             const bool wide = rule == GNN_LAYER_MASK_FANOUT && lm_list_need(fanout) > kLmListCap && lm_list_need(fanout) <= kLmListCapWide;
-            const int grid = grid_for(((int64_t)n_active + kLmLook - 1) / kLmLook, 4, 8192);
+            const int32_t look = n_active > kLmLook * kLmWaves ? kLmLook : (n_active + kLmWaves - 1) / kLmWaves;
+            const int64_t groups = ((int64_t)n_active + kLmShare - 1) / kLmShare, stretches = (groups + look - 1) / look;
+            const uint32_t grid = (uint32_t)(stretches * (kLmShare / 4));
             const uint64_t mixed = mix64(seed + (uint64_t)layer);
             if (wide)
-                lm_mask_long_kernel<kLmListCapWide><<<grid, 256, 0, stream>>>(g->row_ptr, g->col_idx, rows, n_active, rule, fanout, threshold,
-                                                                              mixed, edge_keep, kept_len, row_thr_key, row_thr_id);
+                lm_mask_long_kernel<kLmListCapWide><<<grid, 256, 0, stream>>>(g->row_ptr, g->col_idx, rows, n_active, rule, fanout,
+                                                                                           threshold, mixed, edge_keep, kept_len, row_thr_key,
+                                                                                           row_thr_id, look);
             else
-                lm_mask_long_kernel<kLmListCap><<<grid, 256, 0, stream>>>(g->row_ptr, g->col_idx, rows, n_active, rule, fanout, threshold,
-                                                                          mixed, edge_keep, kept_len, row_thr_key, row_thr_id);
+                lm_mask_long_kernel<kLmListCap><<<grid, 256, 0, stream>>>(g->row_ptr, g->col_idx, rows, n_active, rule, fanout,
+                                                                                       threshold, mixed, edge_keep, kept_len, row_thr_key,
+                                                                                       row_thr_id, look);
             GNN_LAUNCH_CHECK("lm_mask_long_kernel");
         }
     }

@@ -110,7 +110,8 @@ def _time_us(f):
 
 
 def test_cost_of_long_rows():
-    """A long row is read a fixed number of times whatever the fanout (once per kept entry would be 100 times as much here)."""
+    """A long row is read a fixed number of times whatever the fanout (once per kept entry would be 100 times as much here), and
+    long rows that follow each other in the list are not taken one after the other by one wavefront (16 times as much)."""
     import paper_2311_06837_amd as P
     ln, n_cols = 60000, 200000
     def mask(rows_of_it, fanout):
@@ -122,6 +123,7 @@ def test_cost_of_long_rows():
         return _time_us(lambda: P.gnn_layer_edge_mask(G, None, 400, "fanout", 1, 5, fanout=fanout))
     one = mask(1, 10)
     assert mask(1, 100) < 6 * one and mask(1, 960) < 6 * one, "the cost grows with the fanout"
+    assert mask(32, 10) < 4 * one, "consecutive long rows wait for each other"
 
 
 def _mix64(x):
