@@ -301,6 +301,11 @@ __global__ __launch_bounds__(256) void lm_mask_long_kernel(const int32_t* __rest
 // left: entry q = (row u, column v) of the transposed graph is the forward entry (v <- u), kept iff
 // (key(v, u), u) <= (row_thr_key[v], row_thr_id[v]).
 constexpr int kLmChunk = 4096;   // entries per workgroup
+// A chunk whose rows (the empty ones between its first and its last entry among them) are more than this searches the row of
+// every entry, four entries of a thread side by side, instead of walking the rows one for each thread: 128 dependent loads
+// against four times the depth of the search.  The call with 1M / 8M empty rows in one place of the graph: walked 1.16 /
+// 8.9 ms, searched 31 / 38 us (without any 23 us).
+constexpr int kLmWalk = 8 * kLmChunk;
 
 __global__ __launch_bounds__(256) void lm_mask_t_kernel(int32_t n_t, int64_t nnz, const int32_t* __restrict__ rpT,
                                                         const int32_t* __restrict__ ciT, const uint64_t* __restrict__ row_thr_key,
@@ -308,28 +313,51 @@ __global__ __launch_bounds__(256) void lm_mask_t_kernel(int32_t n_t, int64_t nnz
                                                         uint32_t* __restrict__ keep_t) {
     constexpr int kTiles = kLmChunk / 256;          // 64-entry tiles per wavefront
     __shared__ int32_t s_start[kLmChunk];           // at the first entry of a row: its number relative to the chunk's first row
-    __shared__ int32_t s_last[4], s_row0;
+    __shared__ int32_t s_last[4], s_row[2];
     const int lane = lane_id(), wave = (int)(threadIdx.x >> 6);
     const int64_t q0 = (int64_t)blockIdx.x * kLmChunk;
     const int64_t q1 = q0 + kLmChunk < nnz ? q0 + kLmChunk : nnz;
     for (int t = threadIdx.x; t < kLmChunk; t += 256) s_start[t] = 0;
-    if (wave == 0) {   // the row that holds entry q0: a search with 64 probes a step; rpT[lo] <= q0 < rpT[hi]
+    if (wave < 2) {   // the rows that hold the first and the last entry: a search with 64 probes a step; rpT[lo] <= q < rpT[hi]
+        const int64_t q = wave == 0 ? q0 : q1 - 1;
         int64_t lo = 0, hi = n_t;
         while (hi - lo > 1) {
             const int64_t step = (hi - lo + 63) / 64;
             const int64_t at = lo + step * (lane + 1);
-            const int n_below = __popcll(__ballot(at < hi && (int64_t)rpT[at < hi ? at : lo] <= q0));
+            const int n_below = __popcll(__ballot(at < hi && (int64_t)rpT[at < hi ? at : lo] <= q));
             lo += step * n_below;
             hi = lo + step < hi ? lo + step : hi;
         }
-        if (lane == 0) s_row0 = (int32_t)lo;
+        if (lane == 0) s_row[wave] = (int32_t)lo;
     }
     __syncthreads();
-    const int32_t row0 = s_row0;
-    for (int64_t r = (int64_t)row0 + 1 + threadIdx.x; r < n_t; r += 256) {
-        const int64_t at = rpT[r];
-        if (at >= q1) break;
-        atomicMax(&s_start[at - q0], (int32_t)(r - row0));   // of several rows that start here all but the last are empty
+    const int32_t row0 = s_row[0], row1 = s_row[1];
+    if (row1 - row0 <= kLmWalk) {   // uniform over the workgroup
+        for (int64_t r = (int64_t)row0 + 1 + threadIdx.x; r <= row1; r += 256)
+            atomicMax(&s_start[rpT[r] - q0], (int32_t)(r - row0));   // of several rows that start here all but the last are empty
+    } else {
+        constexpr int kQ = 4;   // searches side by side
+        for (int t0 = (int)threadIdx.x; t0 < kLmChunk; t0 += 256 * kQ) {
+            int32_t lo[kQ], hi[kQ];
+#pragma unroll
+            for (int j = 0; j < kQ; ++j) {
+                lo[j] = row0;
+                hi[j] = row1 + 1;
+            }
+            for (int64_t width = (int64_t)row1 + 1 - row0; width > 1; width = (width + 1) / 2) {   // uniform over the workgroup
+#pragma unroll
+                for (int j = 0; j < kQ; ++j) {
+                    const int32_t mid = lo[j] + (hi[j] - lo[j]) / 2;   // (lo itself once the search has ended)
+                    if (rpT[mid] <= q0 + t0 + j * 256) lo[j] = mid;
+                    else hi[j] = mid;
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < kQ; ++j) {
+                const int t = t0 + j * 256;
+                if (q0 + t < q1 && lo[j] > row0 && rpT[lo[j]] == q0 + t) s_start[t] = lo[j] - row0;
+            }
+        }
     }
     __syncthreads();
     // the last row that starts in each wavefront's part

@@ -184,6 +184,44 @@ def test_transposed_mask_rows_across_chunks():
         assert tail == 0, "bits past the last entry are set"
 
 
+@pytest.mark.parametrize("run", [32700, 32800, 400_000])
+def test_transposed_mask_across_long_runs_of_empty_rows(run):
+    """Chunks whose entries lie on both sides of more empty rows than a workgroup walks (8 * 4096): in the middle of a chunk, at
+    its first and at its last entry."""
+    import paper_2311_06837_amd as P
+    lengths = [0] * run + [4090, 5] + [0] * run + [1, 4096] + [0] * run + [4096, 3, 0, 0, 9] + [0] * run + [700] + [0] * run
+    n, m = len(lengths), 6000
+    rng = np.random.default_rng(run)
+    rp = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    cols = np.concatenate([np.sort(rng.choice(m, ln, replace=False)) for ln in lengths if ln]).astype(np.int32)
+    gt = gg.CSR(n, m, rp, cols)
+    g = gg.transpose(gt)
+    G = P.Graph.from_numpy(g.row_ptr, g.col_idx, n_cols=n)
+    GT = P.Graph.from_numpy(gt.row_ptr, gt.col_idx, n_cols=m)
+    keep, _, tk, tu = P.gnn_layer_edge_mask(G, None, m, "fanout", 2, 13, fanout=2, with_thresholds=True)
+    kt = P.gnn_layer_edge_mask_transposed(GT, tk, tu, 2, 13)
+    ok, _ = oracle.layer_edge_mask(g.row_ptr, g.col_idx, None, "fanout", 2, 13, fanout=2)
+    assert np.array_equal(_bits(keep, g.nnz), ok)
+    assert np.array_equal(_bits(kt, gt.nnz), oracle.transpose_mask(g.row_ptr, g.col_idx, ok, gt.row_ptr, gt.col_idx))
+
+
+def test_cost_of_empty_rows_in_the_transposed_mask():
+    """Four million empty rows between two entries are not walked by the one workgroup that meets them (200 times the cost of
+    the same rows behind the last entry)."""
+    import paper_2311_06837_amd as P
+    def mask(before, between, after):
+        lens = torch.tensor([0] * before + [20] * 5000 + [0] * between + [20] * 5000 + [0] * after, device="cuda")
+        rp = torch.zeros(lens.numel() + 1, dtype=torch.int32, device="cuda")
+        rp[1:] = torch.cumsum(lens, 0)
+        at = torch.arange(int(rp[-1]), device="cuda") % 20
+        G = P.Graph(rp, at.int(), n_cols=20, sorted_columns=True)
+        k, u = torch.zeros(20, dtype=torch.int64, device="cuda"), torch.zeros(20, dtype=torch.int32, device="cuda")
+        return _time_us(lambda: P.gnn_layer_edge_mask_transposed(G, k, u, 1, 3))
+    many = 4_000_000
+    behind = mask(0, 0, many)
+    assert mask(0, many, 0) < 12 * behind and mask(many, 0, 0) < 12 * behind
+
+
 def test_transposed_mask():
     import paper_2311_06837_amd as P
     for g in (gg.random_directed(20000, 6.0, 4), gg.chung_lu(9000, 40.0, 2.1, 5)):
