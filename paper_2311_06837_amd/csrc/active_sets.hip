@@ -3,11 +3,11 @@
 // vertices, step 4 generates the per-layer mask).
 //
 // Data layout.  In the workspace: bitmaps of n bits, `visited` (everything reached by the
-// levels before the one being expanded, read-only while it expands; two copies that the levels
-// use in turn) and `frontier` (the ring the last level found), and `seen`, ONE BYTE per vertex (`visited` plus what the level has
-// found so far).  `seen` is bytes because every lane that finds a vertex marks it: a byte takes
-// a plain store of 1 - whoever comes first, the byte ends up the same - where a bit needs an
-// atomic OR, and a ring of a few million new vertices packs those atomics onto a few thousand
+// levels before the one being expanded, read-only while it expands; in a small graph, whose emit
+// blocks read each other's words, two copies that the levels use in turn) and `frontier` (the ring
+// the last level found), and `seen`, ONE BYTE per vertex (`visited` plus what the level has found
+// so far).  `seen` is bytes because every lane that finds a vertex marks it: a byte takes
+// a plain store of 1 - whoever comes first, the byte ends up the same - where a bit needs an atomic OR, and a ring of a few million new vertices packs those atomics onto a few thousand
 // cache lines (measured: 0.60 ms of atomics for 24 M edges that discover 2.2 M vertices).
 // The byte accesses are ordinary loads and stores on purpose: a stale 0 from the vector cache
 // only means one more store of the same 1 (relaxed atomic loads, which bypass that cache, were
@@ -20,7 +20,8 @@
 // With few vertices or many rings a construction is as long as its launches (about 5 us each,
 // the gap included), so a level is four of them: expansion in whichever direction, its long
 // rows, count, emit (which adds up the counts before its own and, for the direction switch, the
-// row lengths of the ring it writes) - three where emit counts for itself (kAsSelfCount).  With a
+// row lengths of the ring it writes) - three where emit counts for itself (kAsSelfCount), five
+// above 16M vertices, where the counts are scanned by a launch of their own (kAsSumCounts).  With a
 // launch per direction, per scan and per plan it was eight: eight rings of a 1M-vertex graph
 // 342 -> 269 us, two of a 10 000-vertex graph 119 -> 95 us, three of a 5M-vertex graph 688 -> 650 us
 // (with the call's own host work and its copy of the ring sizes).
@@ -44,6 +45,7 @@
 // Bound: a push level reads each edge of the frontier once (4 B, streaming) and makes one
 // 1-byte probe per edge into n bytes that stay in L2: the probes, not the bytes, are what
 // limits it (the L2s serve a fixed number of requests per clock).
+#include <type_traits>
 #include "common.h"
 #include "hashkey.h"
 #include "scan.h"
@@ -56,27 +58,51 @@ constexpr int kAsHubDegree = 2048;      // longer rows are queued and expanded b
 // A graph of up to this many blocks: emit counts the blocks before its own itself instead of reading what a count launch
 // left (a block reads 9 KB per block before it: cheaper than the launch up to about 16).
 constexpr int64_t kAsSelfCount = 16;
+// Above this many blocks a launch turns the counts into positions: blocks that add up all counts before their own read
+// half of nb^2 of them.  Three rings of a graph of 1e9 vertices took 10.1 ms that way and take 4.0 (100M: 437 -> 349 us; 10M,
+// below the limit: 82, with the launch 96).
+constexpr int64_t kAsSumCounts = 2048;
+
+// Sums that every workgroup of emit adds to, dealt out to cache lines of their own above kAsOneSlot workgroups: on one address
+// 12 000 of them (100M vertices) wait 0.2 ms a level for each other.  (Adding the slots up takes 4 us a level: with few
+// workgroups there is one place.)  Three rings of 100M vertices with the transposed graph: 1290 -> 412 us.
+constexpr int kAsSlots = 32;
+constexpr int64_t kAsOneSlot = 256;
+struct AsSlot {
+    unsigned long long v;
+    unsigned long long pad[15];
+};
 
 struct AsLevel {
-    unsigned long long frontier_edges;   // entries of the ring's rows
+    AsSlot frontier_edges[kAsSlots];     // entries of the ring's rows
     int32_t n_hubs;                      // rows queued while the ring is expanded
-    int32_t pad;
+    int32_t pad[31];
 };
 
 struct AsCtrl {
-    unsigned long long reached_edges_t;  // entries of the transposed rows of everything reached so far
-    unsigned long long pad;
+    AsSlot reached_edges_t[kAsSlots];    // entries of the transposed rows of everything reached so far
     AsLevel level[1];                    // one per ring (L + 1 of them)
 };
 
-inline size_t as_ctrl_words(int32_t L) { return (sizeof(AsCtrl) + (size_t)(L + 1) * sizeof(AsLevel)) / sizeof(int64_t); }
+inline size_t as_ctrl_words(int32_t L) { return (sizeof(AsCtrl) + (size_t)L * sizeof(AsLevel)) / sizeof(int64_t); }
+
+// The slots' sum; all lanes of the wavefront call it and get it.
+__device__ __forceinline__ int64_t as_slot_sum(const AsSlot* __restrict__ slots, bool many) {
+    static_assert(kAsSlots == 32, "half a wavefront");
+    if (!many) return (int64_t)slots[0].v;
+    unsigned long long x = lane_id() < kAsSlots ? slots[lane_id()].v : 0ull;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d, kWave);
+    return (int64_t)x;
+}
 
 // True when ring `ring` is expanded in the pull direction.  A pull touches at most the transposed rows of the unreached
 // vertices, sixteen lanes at a time.
-__device__ __forceinline__ bool as_pull_level(const AsCtrl* ctrl, const int64_t* __restrict__ hop_offsets, int32_t ring, int64_t n, int64_t nnz_t) {
+__device__ __forceinline__ bool as_pull_level(const AsCtrl* ctrl, const int64_t* __restrict__ hop_offsets, int32_t ring, int64_t n, int64_t nnz_t,
+                                              bool many) {
     const int64_t unreached = n - hop_offsets[ring + 1];
-    const int64_t unreached_edges = nnz_t - (int64_t)ctrl->reached_edges_t;
-    return (int64_t)ctrl->level[ring].frontier_edges > unreached_edges + 16 * unreached;
+    const int64_t unreached_edges = nnz_t - as_slot_sum(ctrl->reached_edges_t, many);
+    return __builtin_amdgcn_readfirstlane((int)(as_slot_sum(ctrl->level[ring].frontier_edges, many) > unreached_edges + 16 * unreached)) != 0;
 }
 
 // Bit b of the result = byte b of the 32 bytes at p (each 0 or 1); p is 32-byte aligned.
@@ -273,6 +299,7 @@ struct AsArgs {
     const int32_t *row_ptr_t, *col_idx_t;   // its transpose, or NULL: every level pushes
     int32_t n;
     int64_t nw, nnz_t;
+    bool many;                              // workgroups of emit: the sums are in kAsSlots places
     const int32_t* ring_ids;
     const int64_t* hop_offsets;
     const uint32_t* visited;
@@ -284,7 +311,7 @@ struct AsArgs {
 
 // Expansion of ring `ring`, in the direction that costs less.
 __global__ __launch_bounds__(256) void as_expand_kernel(AsArgs a, int32_t ring) {
-    if (a.row_ptr_t != nullptr && as_pull_level(a.ctrl, a.hop_offsets, ring, a.n, a.nnz_t))   // uniform over the grid
+    if (a.row_ptr_t != nullptr && as_pull_level(a.ctrl, a.hop_offsets, ring, a.n, a.nnz_t, a.many))   // uniform over the grid
         as_pull(a.row_ptr_t, a.col_idx_t, a.n, a.nw, a.visited, a.seen, a.frontier, ring, a.hubq, a.ctrl);
     else
         as_push(a.row_ptr, a.col_idx, a.ring_ids, a.hop_offsets, ring, a.seen, a.hubq, a.ctrl);
@@ -294,7 +321,7 @@ __global__ __launch_bounds__(256) void as_expand_kernel(AsArgs a, int32_t ring) 
 __global__ __launch_bounds__(256) void as_expand_hubs_kernel(AsArgs a, int32_t ring) {
     const int32_t n_hubs = a.ctrl->level[ring].n_hubs;
     if (n_hubs <= 0) return;
-    if (a.row_ptr_t != nullptr && as_pull_level(a.ctrl, a.hop_offsets, ring, a.n, a.nnz_t))
+    if (a.row_ptr_t != nullptr && as_pull_level(a.ctrl, a.hop_offsets, ring, a.n, a.nnz_t, a.many))
         as_pull_hubs(a.row_ptr_t, a.col_idx_t, a.seen, a.frontier, a.hubq, n_hubs);
     else
         as_push_hubs(a.row_ptr, a.col_idx, a.seen, a.hubq, n_hubs);
@@ -312,81 +339,87 @@ __global__ __launch_bounds__(kAsWordsPerBlock) void as_count_kernel(const uint8_
     if (threadIdx.x == 0) blk_cnt[blockIdx.x] = total;
 }
 
-// Sum over the workgroup; every thread gets it.  Two barriers.
-__device__ __forceinline__ unsigned long long as_block_sum(unsigned long long x, unsigned long long* s_sum) {
+__global__ __launch_bounds__(1024) void as_scan_kernel(int32_t* __restrict__ blk_cnt, int64_t nb) {
+    __shared__ int s_part[1024 / kWave];
+    single_block_exclusive_scan(blk_cnt, nb, s_part);
+}
+
+// Sums over the workgroup; every thread gets them.  Two barriers.
+template <int N>
+__device__ __forceinline__ void as_block_sum(unsigned long long (&x)[N], unsigned long long (*s_sum)[N]) {
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d, kWave);
-    if (lane_id() == 0) s_sum[threadIdx.x >> 6] = x;
+    for (int k = 0; k < N; ++k)
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) x[k] += __shfl_xor(x[k], d, kWave);
+    if (lane_id() == 0)
+#pragma unroll
+        for (int k = 0; k < N; ++k) s_sum[threadIdx.x >> 6][k] = x[k];
     __syncthreads();
-    x = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
+#pragma unroll
+    for (int k = 0; k < N; ++k) x[k] = s_sum[0][k] + s_sum[1][k] + s_sum[2][k] + s_sum[3][k];
     __syncthreads();
-    return x;
 }
 
 // Lists ring `ring` (seen & ~visited) in ascending id order behind the rings before it and writes the next `visited`.
-// Every block adds up the counts of the blocks before it (blk_cnt NULL: counts them); the last one knows the ring's end.
+// Every block adds up the counts of the blocks before it (blk_cnt NULL: counts them; scanned: finds their sum in its place of
+// blk_cnt); the last one knows the ring's end.
 // With row_ptr_t (a later pull is possible): the ring as a bitmap, and the exact sums the direction switch needs, the
 // entries of the ring's rows and of its transposed rows (integer atomics: the totals do not depend on their order).
-__global__ __launch_bounds__(kAsWordsPerBlock) void as_emit_kernel(const uint8_t* __restrict__ seen, const uint32_t* __restrict__ visited,
-                                                                   uint32_t* __restrict__ visited_next, int64_t nw,
-                                                                   const int32_t* __restrict__ blk_cnt, int64_t* __restrict__ hop_offsets,
+__global__ __launch_bounds__(kAsWordsPerBlock) void as_emit_kernel(const uint8_t* __restrict__ seen, const uint32_t* visited,
+                                                                   uint32_t* visited_next, int64_t nw,
+                                                                   const int32_t* __restrict__ blk_cnt, bool scanned, bool many,
+                                                                   int64_t* __restrict__ hop_offsets,
                                                                    int32_t ring, int32_t* __restrict__ ring_ids, int32_t* __restrict__ dist,
                                                                    uint32_t* __restrict__ frontier, const int32_t* __restrict__ row_ptr,
                                                                    const int32_t* __restrict__ row_ptr_t, AsCtrl* ctrl) {
     static_assert(kAsWordsPerBlock == 256, "as_block_sum adds four wavefronts");
     __shared__ int s_part[kAsWordsPerBlock / kWave];
-    __shared__ unsigned long long s_sum[kAsWordsPerBlock / kWave];
+    __shared__ unsigned long long s_base[kAsWordsPerBlock / kWave][1], s_edges[kAsWordsPerBlock / kWave][2];
     __shared__ uint32_t s_fresh[kAsWordsPerBlock];
     __shared__ int s_before[kAsWordsPerBlock];
-    unsigned long long base = 0ull;
-    if (blk_cnt != nullptr) {
-        for (int64_t b = threadIdx.x; b < blockIdx.x; b += kAsWordsPerBlock) base += (unsigned long long)blk_cnt[b];
+    unsigned long long base[1] = {0ull};
+    if (scanned) {   // uniform over the grid
+        base[0] = (unsigned long long)blk_cnt[blockIdx.x];
     } else {
-        for (int64_t w = threadIdx.x; w < (int64_t)blockIdx.x * kAsWordsPerBlock; w += kAsWordsPerBlock)
-            base += (unsigned long long)__popc(as_mask_of_bytes(seen + 32 * w) & ~visited[w]);
+        if (blk_cnt != nullptr) {
+            for (int64_t b = threadIdx.x; b < blockIdx.x; b += kAsWordsPerBlock) base[0] += (unsigned long long)blk_cnt[b];
+        } else {
+            for (int64_t w = threadIdx.x; w < (int64_t)blockIdx.x * kAsWordsPerBlock; w += kAsWordsPerBlock)
+                base[0] += (unsigned long long)__popc(as_mask_of_bytes(seen + 32 * w) & ~visited[w]);
+        }
+        as_block_sum(base, s_base);
     }
-    base = as_block_sum(base, s_sum);
     const int64_t w = (int64_t)blockIdx.x * kAsWordsPerBlock + threadIdx.x;
     uint32_t fresh = 0u;
     if (w < nw) {
         const uint32_t sn = as_mask_of_bytes(seen + 32 * w), vis = visited[w];
         fresh = sn & ~vis;
-        visited_next[w] = vis | sn;
+        if (fresh || visited_next != visited) visited_next[w] = vis | sn;
         if (row_ptr_t != nullptr) frontier[w] = fresh;   // the ring a pull level looks for
     }
     int total;
     const int before = block_exclusive_scan<kAsWordsPerBlock>(__popc(fresh), s_part, &total);
-    const int64_t begin = hop_offsets[ring] + (int64_t)base;
+    const int64_t begin = hop_offsets[ring] + (int64_t)base[0];
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) hop_offsets[ring + 1] = begin + total;
     if (total == 0) return;   // uniform over the workgroup
-    // a lane per vertex, not per word (32 vertices after each other, each with its loads, took 17 us whatever the size),
-    // eight vertices at a time with all their loads in flight (a lane without a vertex of the ring reads the first row)
-    s_fresh[threadIdx.x] = fresh;
-    s_before[threadIdx.x] = before;
-    __syncthreads();
-    unsigned long long edges = 0ull, edges_t = 0ull;
-    const int bit = (int)(threadIdx.x & 31);
-    const uint32_t below = (1u << bit) - 1u;
-    constexpr int kBatch = 8;
-    for (int r0 = 0; r0 < 32; r0 += kBatch) {
-        bool in[kBatch];
-        int32_t v[kBatch], lo[kBatch], hi[kBatch], lo_t[kBatch], hi_t[kBatch];
+    unsigned long long edges[2] = {0ull, 0ull};   // of the ring's rows and of its transposed rows
+    // vertices v[r] where in[r]: into the list at pos[r], and their rows' lengths; all loads in flight (a lane without a vertex
+    // of the ring reads the first row)
+    auto take = [&](auto n_const, const bool* in, const int32_t* v, const int64_t* pos) {
+        constexpr int N = decltype(n_const)::value;
         bool any = false;
 #pragma unroll
-        for (int r = 0; r < kBatch; ++r) {
-            const int k = (r0 + r) * (kAsWordsPerBlock / 32) + (int)(threadIdx.x >> 5);
-            const uint32_t word = s_fresh[k];
-            in[r] = (word >> bit) & 1u;
+        for (int r = 0; r < N; ++r) {
             any |= in[r];
-            v[r] = (int32_t)(((int64_t)blockIdx.x * kAsWordsPerBlock + k) * 32 + bit);
             if (in[r]) {
-                ring_ids[begin + s_before[k] + __popc(word & below)] = v[r];
+                ring_ids[pos[r]] = v[r];
                 dist[v[r]] = ring;
             }
         }
-        if (row_ptr_t == nullptr || __ballot(any) == 0ull) continue;   // uniform over the wavefront
+        if (row_ptr_t == nullptr || __ballot(any) == 0ull) return;   // uniform over the wavefront
+        int32_t lo[N], hi[N], lo_t[N], hi_t[N];
 #pragma unroll
-        for (int r = 0; r < kBatch; ++r) {
+        for (int r = 0; r < N; ++r) {
             const int32_t u = in[r] ? v[r] : 0;
             lo[r] = row_ptr[u];
             hi[r] = row_ptr[u + 1];
@@ -394,17 +427,51 @@ __global__ __launch_bounds__(kAsWordsPerBlock) void as_emit_kernel(const uint8_t
             hi_t[r] = row_ptr_t[u + 1];
         }
 #pragma unroll
-        for (int r = 0; r < kBatch; ++r) {
-            edges += in[r] ? (unsigned long long)(hi[r] - lo[r]) : 0ull;
-            edges_t += in[r] ? (unsigned long long)(hi_t[r] - lo_t[r]) : 0ull;
+        for (int r = 0; r < N; ++r) {
+            edges[0] += in[r] ? (unsigned long long)(hi[r] - lo[r]) : 0ull;
+            edges[1] += in[r] ? (unsigned long long)(hi_t[r] - lo_t[r]) : 0ull;
+        }
+    };
+    constexpr int kSparse = 4, kBatch = 8;
+    bool in[kBatch];
+    int32_t v[kBatch];
+    int64_t pos[kBatch];
+    if (many && !__syncthreads_or(__popc(fresh) > kSparse)) {
+        // few vertices in every word: a lane takes those of its own word (looking through all of a block's vertices for them,
+        // as below, costs 20 us a level where 100M vertices have rings of a thousandth)
+        uint32_t rest = fresh;
+        for (int r = 0; r < kSparse && __ballot(rest != 0u) != 0ull; ++r) {   // uniform over the wavefront
+            in[0] = rest != 0u;
+            v[0] = (int32_t)(w * 32 + (in[0] ? __ffs(rest) - 1 : 0));
+            pos[0] = begin + before + r;
+            rest &= rest - 1u;
+            take(std::integral_constant<int, 1>(), in, v, pos);
+        }
+    } else {
+        // a lane per vertex, not per word (32 vertices after each other, each with its loads, took 17 us whatever the size),
+        // eight vertices at a time
+        s_fresh[threadIdx.x] = fresh;
+        s_before[threadIdx.x] = before;
+        __syncthreads();
+        const int bit = (int)(threadIdx.x & 31);
+        const uint32_t below = (1u << bit) - 1u;
+        for (int r0 = 0; r0 < 32; r0 += kBatch) {
+#pragma unroll
+            for (int r = 0; r < kBatch; ++r) {
+                const int k = (r0 + r) * (kAsWordsPerBlock / 32) + (int)(threadIdx.x >> 5);
+                const uint32_t word = s_fresh[k];
+                in[r] = (word >> bit) & 1u;
+                v[r] = (int32_t)(((int64_t)blockIdx.x * kAsWordsPerBlock + k) * 32 + bit);
+                pos[r] = begin + s_before[k] + __popc(word & below);
+            }
+            take(std::integral_constant<int, kBatch>(), in, v, pos);
         }
     }
     if (row_ptr_t != nullptr) {   // uniform over the grid
-        edges = as_block_sum(edges, s_sum);
-        edges_t = as_block_sum(edges_t, s_sum);
+        as_block_sum(edges, s_edges);
         if (threadIdx.x == 0) {
-            atomicAdd(&ctrl->level[ring].frontier_edges, edges);
-            atomicAdd(&ctrl->reached_edges_t, edges_t);
+            atomicAdd(&ctrl->level[ring].frontier_edges[many ? blockIdx.x % kAsSlots : 0].v, edges[0]);
+            atomicAdd(&ctrl->reached_edges_t[many ? blockIdx.x % kAsSlots : 0].v, edges[1]);
         }
     }
 }
@@ -619,7 +686,7 @@ __global__ __launch_bounds__(256) void eas_expand_long_kernel(const int32_t* __r
     }
 }
 
-// count (unless the blocks are few) and emit
+// count (unless the blocks are few), scan (if they are many) and emit
 static int32_t as_emit(const uint8_t* seen, const uint32_t* visited, uint32_t* visited_next, int64_t nw, int64_t nb, int32_t* blk_cnt,
                        int64_t* hop_offsets, int32_t ring, int32_t* ring_ids, int32_t* dist, uint32_t* frontier, const int32_t* row_ptr,
                        const int32_t* row_ptr_t, AsCtrl* ctrl, hipStream_t stream) {
@@ -627,8 +694,12 @@ static int32_t as_emit(const uint8_t* seen, const uint32_t* visited, uint32_t* v
         as_count_kernel<<<(int)nb, kAsWordsPerBlock, 0, stream>>>(seen, visited, nw, blk_cnt);
         GNN_LAUNCH_CHECK("as_count_kernel");
     }
+    if (nb > kAsSumCounts) {
+        as_scan_kernel<<<1, 1024, 0, stream>>>(blk_cnt, nb);
+        GNN_LAUNCH_CHECK("as_scan_kernel");
+    }
     as_emit_kernel<<<(int)nb, kAsWordsPerBlock, 0, stream>>>(seen, visited, visited_next, nw, nb > kAsSelfCount ? blk_cnt : nullptr,
-                                                             hop_offsets, ring, ring_ids, dist, frontier, row_ptr, row_ptr_t, ctrl);
+                                                             nb > kAsSumCounts, nb > kAsOneSlot, hop_offsets, ring, ring_ids, dist, frontier, row_ptr, row_ptr_t, ctrl);
     GNN_LAUNCH_CHECK("as_emit_kernel");
     return GNN_OK;
 }
@@ -657,7 +728,8 @@ extern "C" int32_t gnn_build_active_sets(const gnn_csr* g, const gnn_csr* gt, co
 
     WsCarver carve(ws);
     uint32_t* visited[2];
-    for (int k = 0; k < 2; ++k) visited[k] = carve.take<uint32_t>((size_t)nw + 1);
+    visited[0] = carve.take<uint32_t>((size_t)nw + 1);
+    visited[1] = nb > kAsSelfCount ? visited[0] : carve.take<uint32_t>((size_t)nw + 1);
     uint8_t* seen = carve.take<uint8_t>((size_t)nw * 32 + 32);
     uint32_t* frontier = carve.take<uint32_t>((size_t)nw + 1);
     int32_t* blk_cnt = carve.take<int32_t>((size_t)nb + 1);
@@ -683,7 +755,7 @@ extern "C" int32_t gnn_build_active_sets(const gnn_csr* g, const gnn_csr* gt, co
         AsArgs a;
         a.row_ptr = g->row_ptr; a.col_idx = g->col_idx;
         a.row_ptr_t = gt != nullptr ? gt->row_ptr : nullptr; a.col_idx_t = gt != nullptr ? gt->col_idx : nullptr;
-        a.n = n; a.nw = nw; a.nnz_t = gt != nullptr ? gt->nnz : 0;
+        a.n = n; a.nw = nw; a.nnz_t = gt != nullptr ? gt->nnz : 0; a.many = nb > kAsOneSlot;
         a.ring_ids = ring_ids; a.hop_offsets = hop_offsets; a.seen = seen; a.frontier = frontier; a.hubq = hubq; a.ctrl = (AsCtrl*)ctrl;
         const int pull_grid = gt != nullptr ? grid_for(nw * kWave, 256, 8192) : 1;   // a wavefront per 32 vertices
         const int grid = pull_grid > (int)kAsPushBlocks ? pull_grid : (int)kAsPushBlocks;
@@ -724,7 +796,8 @@ extern "C" int32_t gnn_eas_traverse(const gnn_csr* g, const int32_t* targets, in
 
     WsCarver carve(ws);
     uint32_t* visited2[2];
-    for (int k = 0; k < 2; ++k) visited2[k] = carve.take<uint32_t>((size_t)nw + 1);
+    visited2[0] = carve.take<uint32_t>((size_t)nw + 1);
+    visited2[1] = nb > kAsSelfCount ? visited2[0] : carve.take<uint32_t>((size_t)nw + 1);
     uint8_t* seen = carve.take<uint8_t>((size_t)nw * 32 + 32);
     int32_t* blk_cnt = carve.take<int32_t>((size_t)nb + 1);
     int32_t* conn = carve.take<int32_t>(rule == GNN_EAS_DEGREE ? (size_t)n + 1 : 1);

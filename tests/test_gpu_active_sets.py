@@ -110,3 +110,62 @@ def test_levels_that_run_from_the_unreached_vertices():
     iso = gg.csr_from_edges(n, n, np.repeat(np.arange(n // 2), 60),
                             np.random.default_rng(0).integers(0, n // 2, 60 * (n // 2)))   # half the graph is unreachable
     _compare(iso, np.arange(0, n // 2, 5), 3)
+
+
+# ---- graphs of many compaction blocks (8192 vertices each) ---------------------------------------------------------
+
+def _chain(n):
+    """v -> v + 1, and its transpose; the last vertex has no neighbour."""
+    import paper_2311_06837_amd as P
+    at = torch.arange(n + 1, dtype=torch.int64, device="cuda")
+    g = P.Graph(at.clamp(max=n - 1).int(), torch.arange(1, n, dtype=torch.int32, device="cuda"))
+    gt = P.Graph((at - 1).clamp(min=0).int(), torch.arange(n - 1, dtype=torch.int32, device="cuda"))
+    return g, gt
+
+
+@pytest.mark.parametrize("n", [8192 * 256, 8192 * 256 + 1, 8192 * 2048, 8192 * 2048 + 1, 20_000_003])
+def test_sets_of_graphs_with_many_blocks(n):
+    """On both sides of 256 and of 2048 blocks: rings of a thousandth of the vertices, a dense stretch beside them, and nearly
+    all vertices (a level from the unreached ones), with and without the transposed graph."""
+    import paper_2311_06837_amd as P
+    g, gt = _chain(n)
+    sparse = torch.arange(7, n, 1000, device="cuda")
+    dense = torch.unique(torch.cat([sparse, torch.arange(n // 2, n // 2 + 20_000, device="cuda"), torch.arange(n - 40, n - 3, 5, device="cuda")]))
+    most = torch.arange(n, device="cuda")
+    most = most[(most % 100 < 96) | (most < n // 2)]
+    for name, T in (("sparse", sparse), ("dense", dense), ("most", most)):
+        L = 2
+        want = torch.full((n,), -1, dtype=torch.int32, device="cuda")
+        for d in range(L, -1, -1):
+            want[T[T < n - d] + d] = d
+        for t in (None, gt):
+            print(f"sets: chain of {n}, {name}, {'with' if t else 'without'} transpose", flush=True)
+            dist, ring, _, hop = P.gnn_build_active_sets(g, T.int(), L, gt=t)
+            assert torch.equal(dist, want)
+            order = torch.cat([torch.nonzero(want == d).reshape(-1) for d in range(L + 1)]).int()
+            assert hop == [0] + torch.cumsum(torch.stack([(want == d).sum() for d in range(L + 1)]), 0).tolist()
+            assert torch.equal(ring[: int(hop[-1])], order)
+        d, r, _, hop = P.gnn_eas_traverse(g, T.int(), 1, 1, "hash", 3)      # a vertex has one neighbour: the same sets
+        assert torch.equal(d, torch.where(want > 1, -1, want))
+
+
+def test_cost_of_the_direction_switch_in_large_graphs():
+    """What the transposed graph adds to a construction (the sums that choose the direction) stays below the construction
+    itself: sums that all workgroups add to one address were twice that at this size."""
+    import paper_2311_06837_amd as P
+    n = 100_000_000
+    g, gt = _chain(n)
+    T = torch.arange(0, n, 1000, dtype=torch.int32, device="cuda")
+    ws = P.Workspace()
+
+    def time_us(t):
+        times = []
+        for _ in range(4):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            P.gnn_build_active_sets(g, T, 3, sync=False, ws=ws, gt=t)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b) * 1e3)
+        return min(times)
+    assert time_us(gt) < 2 * time_us(None)
