@@ -566,17 +566,20 @@ using namespace gnnhot;
 // through it: a 1M-vertex / 20M-entry graph counts in 0.11 + 0.005 ms instead of 0.15, below the limit nothing is gained.
 constexpr int32_t kExBitsMin = 1 << 19;
 
+// a thread per item, whatever their number (these kernels do not stride)
+static inline int ex_grid(int32_t items) { return grid_for(items, 256, INT32_MAX); }
+
 template <bool SAMPLED>
 static int32_t ex_count_pass(ExArgs a, const int32_t* dist, int32_t* new_id, uint64_t* bits, int row_grid, int long_grid,
                              hipStream_t stream) {
     fill_kernel<int32_t><<<grid_for(a.n, 256, 1 << 16), 256, 0, stream>>>(new_id, a.n, -1);
     GNN_LAUNCH_CHECK("fill_kernel");
     if (a.n_local == 0) return GNN_OK;
-    ex_number_kernel<<<grid_for(a.n_local, 256), 256, 0, stream>>>(a.ring_ids, a.n_local, a.n, dist, new_id, SAMPLED ? a.counts : nullptr,
+    ex_number_kernel<<<ex_grid(a.n_local), 256, 0, stream>>>(a.ring_ids, a.n_local, a.n, dist, new_id, SAMPLED ? a.counts : nullptr,
                                                                    nullptr, a.ctrl);
     GNN_LAUNCH_CHECK("ex_number_kernel");
     if (!SAMPLED && a.n >= kExBitsMin) {
-        ex_bits_kernel<<<grid_for(a.n, 256), 256, 0, stream>>>(new_id, a.n, bits);
+        ex_bits_kernel<<<ex_grid(a.n), 256, 0, stream>>>(new_id, a.n, bits);
         GNN_LAUNCH_CHECK("ex_bits_kernel");
         a.bits = (const uint32_t*)bits;
     }
@@ -589,7 +592,7 @@ static int32_t ex_count_pass(ExArgs a, const int32_t* dist, int32_t* new_id, uin
 
 template <bool SAMPLED>
 static int32_t ex_fill_pass(const ExArgs& a, const int32_t* dist, int row_grid, int long_grid, hipStream_t stream) {
-    ex_number_kernel<<<grid_for(a.n_local, 256), 256, 0, stream>>>(a.ring_ids, a.n_local, a.n, dist, nullptr, SAMPLED ? a.counts : nullptr,
+    ex_number_kernel<<<ex_grid(a.n_local), 256, 0, stream>>>(a.ring_ids, a.n_local, a.n, dist, nullptr, SAMPLED ? a.counts : nullptr,
                                                                    a.out_rp, a.ctrl);
     GNN_LAUNCH_CHECK("ex_number_kernel");
     ex_fill_kernel<SAMPLED><<<row_grid, 256, 0, stream>>>(a);
@@ -705,7 +708,7 @@ extern "C" int32_t gnn_expand_row_ptr(int32_t n, const int32_t* ids, int32_t n_i
         GNN_LAUNCH_CHECK("fill_kernel");
     }
     if (n_ids > 0) {
-        expand_lengths_kernel<<<grid_for(n_ids, 256), 256, 0, stream>>>(ids, n_ids, list_row_ptr, n, counts);
+        expand_lengths_kernel<<<ex_grid(n_ids), 256, 0, stream>>>(ids, n_ids, list_row_ptr, n, counts);
         GNN_LAUNCH_CHECK("expand_lengths_kernel");
     }
     return counts_to_offsets(counts, n, sums, out_row_ptr, total, stream);

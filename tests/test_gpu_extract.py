@@ -315,3 +315,28 @@ def test_reverse_rows_of_kept_rows_that_repeat_a_column(whole):
         B._with_ws(B.lib().gnn_extract_sampled_partition, common + (B._ptr(out), cap, B._ptr(nnz_dev), None), (B._stream(),), None)
         got = out.cpu().numpy()
         assert np.array_equal(got[:cap], ci[:cap]) and (got[cap:] == -7).all(), cap
+
+
+@pytest.mark.parametrize("all_reached", [False, True])
+def test_more_vertices_than_a_limited_grid_has_threads(all_reached):
+    """2^28 + 5000 vertices, edges between the last 4000: extraction of the last vertices, and of everything."""
+    import paper_2311_06837_amd as P
+    n, m = 2 ** 28 + 5000, 4000
+    rp = torch.zeros(n + 1, dtype=torch.int32, device="cuda")
+    rp[n - m + 1:] = torch.arange(1, m + 1, dtype=torch.int32, device="cuda")
+    ci = torch.arange(n - m + 1, n + 1, dtype=torch.int32, device="cuda")
+    ci[-1] = n - m                                               # a cycle through the last m vertices
+    g = P.Graph(rp, ci, sorted_columns=True)
+    T = torch.arange(0 if all_reached else n - 3000, n, dtype=torch.int32, device="cuda")
+    dist, ring, _, hop = P.gnn_build_active_sets(g, T, 1)
+    n_local = n if all_reached else 3001
+    assert hop[-1] == n_local
+    local, new_id = P.gnn_extract_partition(g, ring, n_local, dist, 1)
+    if all_reached:
+        assert torch.equal(local.row_ptr, rp) and torch.equal(local.col_idx, ci)
+        assert torch.equal(new_id, torch.arange(n, dtype=torch.int32, device="cuda"))
+        del local, new_id, dist, ring
+        assert torch.equal(P.gnn_expand_row_ptr(n, T, rp), rp)
+    else:       # the targets in order, then vertex n - m, the last target's neighbour, whose own neighbour is out of reach
+        assert torch.equal(local.row_ptr, torch.arange(3002, dtype=torch.int32, device="cuda").clamp(max=3000))
+        assert torch.equal(local.col_idx, torch.arange(1, 3001, dtype=torch.int32, device="cuda"))
