@@ -137,3 +137,24 @@ def test_recomputation_changes_nothing_and_saves_memory():
         for k in ga:
             assert torch.equal(ga[k], gb[k]), k
     assert b.activation_bytes() < a.activation_bytes()
+
+
+@pytest.mark.parametrize("n,F", [(20000, 256), (100000, 1000)])
+def test_column_sums_of_the_layer_norm_gradients_do_not_lose_precision(n, F):
+    """dbeta is a plain column sum, dgamma one of products: relative error against 64 bits, mean of four draws.  A final chain of
+    64 lane sums gives 1.9e-7 to 2.0e-7, one of 32 gives 1.67e-7 to 1.9e-7, sums in pairs 1.33e-7 to 1.52e-7."""
+    import paper_2311_06837_amd as P
+    off = []
+    for seed in range(4):
+        gen = torch.Generator(device="cuda").manual_seed(seed)
+        x, dy = (torch.randn(n, F, generator=gen, device="cuda") for _ in range(2))
+        gamma, beta = 1.0 + 0.1 * torch.randn(F, generator=gen, device="cuda"), 0.1 * torch.randn(F, generator=gen, device="cuda")
+        t = torch.relu(torch.nn.functional.layer_norm(x, (F,), gamma, beta, 1e-5))
+        dx, dg, db = torch.empty_like(x), torch.empty(F, device="cuda"), torch.empty(F, device="cuda")
+        P.gnn_layer_norm_relu_bwd(None, n, dy, t, x, F, gamma, None, 0, dx, dg, db)
+        g, x = torch.where(t > 0, dy, torch.zeros_like(dy)).double(), x.double()
+        dev_ = x - x.mean(1, keepdim=True)
+        xh = dev_ * torch.rsqrt((dev_ * dev_).mean(1, keepdim=True) + 1e-5)
+        off.append([float((got.double() - want).norm() / want.norm()) for got, want in ((db, g.sum(0)), (dg, (g * xh).sum(0)))])
+    dbeta, dgamma = np.mean(off, axis=0)
+    assert dbeta < 1.6e-7 and dgamma < 1.7e-7, (dbeta, dgamma)
