@@ -4,18 +4,19 @@
 A step is one pass of the whole hot path over one synthetic partition: active-set construction
 (frontier expansion), then per layer masked aggregation + feature transform, the loss, and the
 matching backward pass.  Inputs are resident in HBM before the timed region.  One JSON line on
-stdout:
+stdout with the headline figures (line_of), and the full record on stderr after "[bench] record: ":
   value     aggregated edges per second = (edges visited by all forward and backward aggregations
             of a step, counted for the paper's order of a layer's halves) / (wall time of a step)
   roofline  the dominant kernel (the forward aggregation that gathers the most bytes), against the HBM
             peak; `frac` is never above 1 by construction, see roofline_of_call()
-  roofline_gemm / roofline_sets / roofline_sampling / roofline_extract   the other steps of the path
+  roofline_gemm / roofline_sets / roofline_sampling / roofline_extract   the other steps of the path (full record)
   call_ms   every C-ABI call between two events on the stream it is enqueued on; the weight-gradient
             products run on a second stream beside the backward aggregations, so the sum of the entries
             exceeds the step (ms_per_step is the wall time)
   cpu_baseline  the CPU oracle timed on this machine's host cores on a bounded sample (reported for
             context; it is not the target)
-  others    the same record for the other single-GPU workloads (configs[2], [3], [4]), fewer steps
+  others    the other single-GPU workloads (cfg2, cfg3, cfg4), fewer steps: value, step time and the fraction of the
+            roofline; in the full record all that the headline workload has
 
 python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload cfg1] [--others cfg2,cfg3,cfg4 | --no-others]
 
@@ -643,9 +644,34 @@ def main():
         for o in others:
             assert o in CONFIG_INDEX and o != args.workload
             r = run_workload(args, o, min(args.steps, 5), min(args.warmup, 2), 0.0 if args.no_cpu_baseline else 5.0e10)
-            r.pop("call_ms", None)
             out["others"][o] = r
-    print(json.dumps(out))
+    log("[bench] record: " + json.dumps(out))
+    print(json.dumps(line_of(out)))
+
+
+LINE_KEYS = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling", "vs_baseline", "dtype",
+             "data", "config", "does_not_fit", "epoch_ms", "partition_built_on", "roofline", "cpu_baseline", "call_ms")
+LINE_ROOFLINE = ("kernel", "bound", "achieved", "peak", "unit", "frac", "frac_basis", "traffic", "bytes_per_launch", "launch_ms", "gather_GBs")
+
+
+def line_of(out):
+    """What goes to stdout: the headline figures, the roofline of the dominant call, the time of every call, and one figure with its
+    roofline for each of the other workloads.  A few thousand characters, so that a reader that keeps the end of the output
+    keeps the line whole; the full record (every layer, every product, all of the other workloads) goes to stderr."""
+    def short(r, keys):
+        d = {k: r[k] for k in keys if k in r}
+        if d.get("roofline"):
+            d["roofline"] = {k: d["roofline"][k] for k in LINE_ROOFLINE if k in d["roofline"]}
+        return d
+    line = short(out, LINE_KEYS)
+    if "others" in out:
+        line["others"] = {}
+        for name, r in out["others"].items():
+            d = short(r, ("value", "unit", "ms_per_step", "dtype", "roofline"))
+            d["workload"] = r["config"]["workload"]
+            d["roofline"] = {k: d["roofline"][k] for k in ("bound", "achieved", "peak", "unit", "frac")} if d.get("roofline") else None
+            line["others"][name] = d
+    return line
 
 
 def bench_res_model(args, w, part, sampled_graph, dtype, steps, warmup):

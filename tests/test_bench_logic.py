@@ -87,6 +87,40 @@ def test_committed_sidecar_matches_the_committed_sources():
     assert d["source_sha"] == bench.source_sha()
 
 
+def _record(workload, calls=24):
+    roofline = {"kernel": "k" * 160, "bound": "hbm", "achieved": 5234.123456789012, "peak": 8000.0, "unit": "GB/s", "frac": 0.654265432098626,
+                "frac_basis": "b" * 100, "traffic": 37255404544.0, "bytes_per_launch": 117301264696, "launch_ms": 6.878890252113342,
+                "gather_GBs": 17052.352980913245, "note": "n" * 400, "compulsory_GBs": 135.85585664968127}
+    return {"metric": "aggregated_edges_per_sec", "value": 10637520440.158422, "unit": "edges/s", "n_gpus": 1, "steps": 20, "warmup": 5,
+            "ms_per_step": 34.785383500000044, "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f32",
+            "data": "synthetic", "config": {"workload": f"{workload}: " + "w" * 150, "scale": 1.0, "n_local": 233000, "nnz_local": 113872382,
+                                            "targets": 29125, "hop_offsets": [0, 29125, 232000, 233000, 233000], "layers": 3},
+            "epoch_ms": 34.1, "partition_built_on": "gpu ((distance, id) numbering)",
+            "per_layer": {str(l): {f"x{i}": 1.2345678901234567 for i in range(40)} for l in range(8)},
+            "roofline": roofline, "roofline_gemm": {f"p{i}": dict(roofline) for i in range(12)},
+            "cpu_baseline": {"value": 22344563.20096871, "unit": "edges/s", "cores": 16, "kind": "oracle", "sample": "s" * 200, "seconds": 5.1},
+            "call_ms": {f"linear_bwd_{i}_input_self": 0.1234 for i in range(calls)}}
+
+
+def test_stdout_line_is_short_and_whole():
+    """The line has every headline figure, the roofline, the CPU baseline and a figure of every other workload, and fits
+    into 6000 characters (9500 of the full record's were not enough for a reader that keeps the end of the output)."""
+    out = _record("headline")
+    out["others"] = {o: _record(o) for o in ("cfg2", "cfg3", "cfg4")}
+    text = json.dumps(bench.line_of(out))
+    assert len(json.dumps(out)) > 20000 and len(text) < 6000, len(text)
+    line = json.loads(text)
+    for k in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling", "vs_baseline", "dtype", "data",
+              "config", "cpu_baseline", "call_ms"):
+        assert line[k] == out[k], k
+    for k in ("kernel", "bound", "achieved", "peak", "unit", "frac", "launch_ms"):
+        assert line["roofline"][k] == out["roofline"][k]
+    for o, r in out["others"].items():
+        assert line["others"][o]["value"] == r["value"] and line["others"][o]["ms_per_step"] == r["ms_per_step"]
+        assert line["others"][o]["roofline"]["frac"] == r["roofline"]["frac"] and line["others"][o]["workload"] == r["config"]["workload"]
+    assert "others" not in bench.line_of(_record("alone"))
+
+
 def test_more_than_one_gpu_is_refused():
     import subprocess
     import sys
