@@ -85,7 +85,7 @@ def build_partition(name, scale):
 
 
 def sampled_partition_cfg4(w):
-    """configs[4], steps a0 and a-1 on the GPU: boundary sampling, then extraction of the local one-hop graph with
+    """The sampled-partition workload, steps a0 and a-1 on the GPU: boundary sampling, then extraction of the local one-hop graph with
     (distance, id) numbering.  Returns a host-side Partition (for the CPU baseline), the device graph and the two times
     (best of three passes each; the first pass also warms the allocator)."""
     import torch
@@ -505,7 +505,7 @@ def pmc_probe(args, name, manifest_path, repeats=3):
                                                              model.H[dom - 1] if sage else None, K, p["W_neigh"], p.get("W_self"),
                                                              gr["dW_neigh"], gr.get("dW_self"), gr["dbias"], model.dA[dom],
                                                              model.dH[dom - 1] if sage else None, ws=model.ws))
-    if w.partition is None:        # configs[4]: the sampler
+    if w.partition is None:        # the sampled-partition workload: the sampler
         g = w.global_graph
         Gg = P.Graph.from_numpy(g.row_ptr, g.col_idx)
         Td = torch.from_numpy(w.targets_global.astype(np.int32)).cuda()
@@ -685,7 +685,7 @@ def bench_res_model(args, w, part, sampled_graph, dtype, steps, warmup):
     dims = [w.dims[0]] + [hid] * (L - 1) + [w.dims[-1]]
     dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
     # the partition's halo was cut for the workload's own depth: deeper models see the same vertices (the late active
-    # sets are the whole partition, as in configs[3])
+    # sets are the whole partition, as in the 8-layer workload)
     es = 4 if dtype == torch.float32 else 2
     need = part.graph.n_rows * P.row_stride(hid, dtype) * es * (L * (1 if args.recompute else 3) + 8)
     have = torch.cuda.get_device_properties(0).total_memory

@@ -27,7 +27,7 @@
 // workgroup that scans the vertex's row of the transposed graph and keeps the targets whose kept row contains it (binary
 // search), as often as it does.  That scan for
 // EVERY outside vertex, sixteen lanes each, took 11.7 of the 12.8 ms of sampling and extraction on a 5M-vertex / 75M-entry
-// graph with 625 000 targets and fanout 5; now extraction is 0.8 of 1.8 ms.
+// graph with 625 000 targets and fanout 5; now extraction is 0.8 of 1.6 ms.
 #include "common.h"
 #include "rowlists.h"
 #include "scan.h"

@@ -20,8 +20,9 @@
 //                        keys are equal.  A workgroup takes 4096 consecutive entries whatever rows they belong to, so
 //                        every word of the bitmap has one writer: no atomics, nothing to clear, no long rows.
 // Bound: the random reads (transposed), the hash (two 64-bit multiplications a mix) and the selection.  Measured on a
-// 1.2M-vertex / 60M-entry power-law graph, fanout 10: forward and transposed mask 2.61 -> 1.02 ms (short rows
-// 0.40 -> 0.20, long rows 1.11 -> 0.40, transposed 1.09 -> 0.43, its random reads into a 9.6 MB table).
+// 1.2M-vertex / 60M-entry power-law graph, fanout 10: forward and transposed mask 2.61 -> 0.95 ms (forward 1.5 -> 0.53,
+// transposed 1.09 -> 0.42, its random reads into a 9.6 MB table), against `fanout` rounds over 64-bit pairs and a lane group
+// per row of the transposed graph.
 #include "common.h"
 #include "hashkey.h"
 

@@ -168,7 +168,7 @@ def test_sampled_extraction_hub_outside_vertex_and_tiny_sets():
 
 
 def test_training_step_after_sampling_and_extraction():
-    """configs[4]'s chain at small size, all on the GPU: sample, extract, gather features, one bf16 training step."""
+    """The sampled-partition chain at small size, all on the GPU: sample, extract, gather features, one bf16 training step."""
     import paper_2311_06837_amd as P
     n, dims, dtype = 40000, [64, 48, 48, 5], torch.bfloat16
     g = gg.chung_lu(n, 15.0, 2.1, 83)

@@ -259,7 +259,7 @@ def _linear_sampled(w, rows_all, K, N, dtype, sage, seed, n_sample=2000, n_cols=
 
 
 def test_cfg1_full_size(cfg1):
-    """configs[1] (the benchmark workload): fp32, 3-layer GraphSAGE-mean, 602-256-256-41."""
+    """The benchmark workload: fp32, 3-layer GraphSAGE-mean, 602-256-256-41."""
     w = cfg1
     G, dist, ring, off = _active_sets_full(w)
     L = w.n_layers
@@ -296,7 +296,7 @@ def test_cfg1_sum_of_ones_is_degree_at_full_size(cfg1):
 
 
 def test_cfg3_full_size_bf16(cfg3):
-    """configs[3]: bf16 storage, 8-layer GraphSAGE-mean, hidden 128; active sets shrink layer by layer."""
+    """bf16 storage, 8-layer GraphSAGE-mean, hidden 128; active sets shrink layer by layer."""
     w = cfg3
     G, dist, ring, off = _active_sets_full(w)
     L = w.n_layers
@@ -316,7 +316,7 @@ def test_cfg3_full_size_bf16(cfg3):
 
 @pytest.fixture(scope="module")
 def cfg4_sampled():
-    """configs[4] through sampling and extraction on the GPU and in the oracle, once for the tests below (the 10M-vertex
+    """The sampled-partition workload through sampling and extraction on the GPU and in the oracle, once for the tests below (the 10M-vertex
     graph takes a minute to generate).  Everything the later tests use on the host side is the ORACLE's."""
     import paper_2311_06837_amd as P
     print("generating cfg4 at full size", flush=True)
@@ -341,7 +341,7 @@ def cfg4_sampled():
 
 
 def test_cfg4_sampling_and_extraction_full_size(cfg4_sampled):
-    """configs[4]: boundary sampling over the 10M-vertex graph and the extraction of the sampled partition, both
+    """Boundary sampling over the 10M-vertex graph and the extraction of the sampled partition, both
     bit-exact in full; then the active sets of the sampled partition."""
     c = cfg4_sampled
     rp, ci, hop, l2g_gpu, lrp, lci = c["gpu"]
@@ -369,7 +369,7 @@ def _cfg4_local_partition(c):
 
 
 def test_cfg4_aggregations_full_size(cfg4_sampled):
-    """The aggregation calls of the step on the extracted partition of configs[4], in the forms bench.py's model issues
+    """The aggregation calls of the step on the extracted sampled partition, in the forms bench.py's model issues
     them: bf16, rows as id prefixes (no lists), the backward filter as a source prefix, 128 / 256 / 32 columns."""
     w, n_loc, nt = _cfg4_local_partition(cfg4_sampled)
     local = cfg4_sampled["local"]
@@ -386,7 +386,7 @@ def test_cfg4_aggregations_full_size(cfg4_sampled):
 
 
 def test_cfg4_feature_transforms_full_size(cfg4_sampled):
-    """The feature transforms of configs[4] on the extracted partition: bf16, 128 -> 256, 256 -> 256, 256 -> 32."""
+    """The feature transforms of the sampled-partition workload on the extracted partition: bf16, 128 -> 256, 256 -> 256, 256 -> 32."""
     w, n_loc, nt = _cfg4_local_partition(cfg4_sampled)
     cfg4_sampled["local"] = None        # the device copy of the graph is not needed any more
     allrows, trows = np.arange(n_loc, dtype=np.int32), np.arange(nt, dtype=np.int32)
@@ -403,7 +403,7 @@ def cfg2():
 
 
 def test_cfg2_full_size_gcn(cfg2):
-    """configs[2]: fp32, 3-layer GCN 100-256-256-47 with the symmetric normalisation over the GLOBAL degrees, 2.45M
+    """fp32, 3-layer GCN 100-256-256-47 with the symmetric normalisation over the GLOBAL degrees, 2.45M
     vertices; the last layer in the exchanged order (47 columns gathered, the rows start from the bias)."""
     w = cfg2
     G, dist, ring, off = _active_sets_full(w)
