@@ -128,8 +128,12 @@ int32_t gnn_norm_scales(int32_t norm, const int32_t *len, const int32_t *row_ptr
  * GNN_CSR_SORTED_COLUMNS, 16-byte aligned operands): the neighbour-id range is cut into 8 blocks
  * per pass, workgroup i works on block i mod 8 (the compute die it runs on), so each die's L2
  * only ever holds one eighth of a 256-byte-wide feature slab; the per-block partial sums (float)
- * go to ws and are added in block order.  The size query (ws == NULL) reports 0 when the route
- * does not apply; the sums of the two routes differ by float rounding only.
+ * go to ws and are added in block order.
+ * Or it may take the split route (float, rows == NULL and no filter but a source prefix, more than 96 columns, on
+ * average at least 40 entries a row, a matrix of 48 MB or more): the entries that name one of up to 65 535 frequent
+ * neighbours are added up from a table in ws, the others as without a workspace.  Whether a graph has such
+ * neighbours is decided on the GPU.  A ws too small for this route is no error: the call runs as without one.
+ * The size query (ws == NULL) reports 0 when neither route applies; their sums differ by float rounding only.
  */
 int32_t gnn_masked_spmm_fwd(const gnn_csr *g, const int32_t *rows, int32_t n_active,
                             const void *X, int64_t ldx, void *Y, int64_t ldy, int32_t F, int32_t dtype,

@@ -272,8 +272,17 @@ def gnn_norm_scales(norm: int, n: int, length: torch.Tensor | None = None, row_p
     return out
 
 
-def _with_optional_ws(fn, args_before, args_after, ws: Workspace | None):
-    """ws None: the call runs without a workspace (ws_bytes = NULL); else the usual size query + call."""
+def _with_optional_ws(fn, args_before, args_after, ws: Workspace | None, gathered: int):
+    """ws None: the call runs without a workspace (ws_bytes = NULL); else the usual size query + call.  gathered: bytes the call
+    gathers; from 1 GB on a route may use a workspace that it does not insist on, so the size is asked for first, and a card
+    without that much left runs the call as without a workspace."""
+    if ws is not None and gathered >= 1 << 30:
+        need = C.c_size_t(0)
+        _check(fn(*args_before, None, C.byref(need), *args_after))
+        try:
+            ws.get(need.value)
+        except torch.cuda.OutOfMemoryError:
+            ws = None
     if ws is None:
         _check(fn(*args_before, None, None, *args_after))
     else:
@@ -287,7 +296,7 @@ def gnn_masked_spmm_fwd(g: Graph, rows, n_active: int, X: torch.Tensor, Y: torch
     assert rows is None or rows.numel() >= n_active
     _with_optional_ws(lib().gnn_masked_spmm_fwd, (
         C.byref(g.c), _ptr(_i32(rows, "rows")), C.c_int32(n_active), _ptr(X), C.c_int64(X.stride(0)), _ptr(Y),
-        C.c_int64(Y.stride(0)), C.c_int32(F), C.c_int32(_dtype_code(X)), _ptr(row_scale), _ptr(col_scale)), (_stream(),), ws)
+        C.c_int64(Y.stride(0)), C.c_int32(F), C.c_int32(_dtype_code(X)), _ptr(row_scale), _ptr(col_scale)), (_stream(),), ws, g.nnz * X.stride(0) * X.element_size())
 
 
 def gnn_masked_spmm_fwd_add(g: Graph, rows, n_active: int, X: torch.Tensor, Y: torch.Tensor, F: int,
@@ -300,12 +309,12 @@ def gnn_masked_spmm_fwd_add(g: Graph, rows, n_active: int, X: torch.Tensor, Y: t
     _with_optional_ws(lib().gnn_masked_spmm_fwd_add, (
         C.byref(g.c), _ptr(_i32(rows, "rows")), C.c_int32(n_active), _ptr(X), C.c_int64(X.stride(0)), _ptr(Y),
         C.c_int64(Y.stride(0)), C.c_int32(F), C.c_int32(_dtype_code(X)), _ptr(row_scale), _ptr(col_scale), _ptr(bias),
-        C.c_int32(1 if relu else 0)), (_stream(),), ws)
+        C.c_int32(1 if relu else 0)), (_stream(),), ws, g.nnz * X.stride(0) * X.element_size())
 
 
 def spmm_workspace_bytes(g: Graph, n_active: int, X: torch.Tensor, Y: torch.Tensor, F: int) -> int:
     """Size query of gnn_masked_spmm_fwd: what a workspace would have to hold; 0 = the call gathers whole rows
-    in one launch, > 0 = it takes the column-blocked route."""
+    in one launch, > 0 = it takes the column-blocked or the split route."""
     need = C.c_size_t(0)
     _check(lib().gnn_masked_spmm_fwd(
         C.byref(g.c), None, C.c_int32(n_active), _ptr(X), C.c_int64(X.stride(0)), _ptr(Y), C.c_int64(Y.stride(0)), C.c_int32(F),
@@ -329,7 +338,7 @@ def gnn_masked_spmm_bwd(gT: Graph, out_rows, n_out: int, dist, max_active_dist: 
         C.byref(gT.c), _ptr(_i32(out_rows, "out_rows")), C.c_int32(n_out), _ptr(_i32(dist, "dist")),
         C.c_int32(max_active_dist), C.c_int32(src_prefix), _ptr(dY), C.c_int64(dY.stride(0)), _ptr(dX), C.c_int64(dX.stride(0)), C.c_int32(F),
         C.c_int32(_dtype_code(dY)), _ptr(row_scale), _ptr(col_scale), C.c_int32(1 if accumulate else 0), _ptr(relu_H),
-        C.c_int64(relu_H.stride(0) if relu_H is not None else 0)), (_stream(),), ws)
+        C.c_int64(relu_H.stride(0) if relu_H is not None else 0)), (_stream(),), ws, gT.nnz * dY.stride(0) * dY.element_size())
 
 
 def gnn_linear_fwd(rows, n_active: int, A_neigh: torch.Tensor, X_self, K: int, W_neigh: torch.Tensor, W_self, bias,

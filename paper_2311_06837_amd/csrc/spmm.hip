@@ -19,6 +19,7 @@
 // reduced through LDS in a fixed order, inside the same launch.
 #include "common.h"
 #include "scan.h"
+#include "spmm_split.h"
 #include <mutex>
 
 namespace gnnhot {
@@ -111,6 +112,13 @@ struct SpmmArgs {
     const float* edge_w;      // with a neighbour scale: the factor of every entry of col_idx, at the same position
     int32_t n_blocks;
     int32_t block0;           // first column block of this pass
+    // split route only (spmm_split.h)
+    const int32_t* split_on;       // 1: the rows' other entries lie in split_cold, their hot ones are summed in split_plane
+    const int32_t* split_cold;
+    const SplitRow* split_rows;
+    const SplitChunk* split_chunks;
+    const float* split_plane;      // a row of split_ld floats per part
+    int64_t split_ld;
 };
 
 // ---- element access: VE elements per lane-chunk ------------------------------------------
@@ -433,7 +441,8 @@ __device__ __forceinline__ void consume_tile(const SpmmArgs& a, int cnt, int cnt
 //            tiles q, q+NG, ...); the partial sums meet in LDS and are added in group order.
 // Which group handles a row does not change the order of its additions: results are bit-reproducible.
 // Workgroups per CU: see the tuning constants at the head of the file.
-template <int DT, int VE, int LPR, int NCH, int U, bool FILTER>
+// SPLIT: the split route's last launch - a row's entries are those the route left over, and its sum starts from its parts.
+template <int DT, int VE, int LPR, int NCH, int U, bool FILTER, bool SPLIT>
 __global__ __launch_bounds__(256, NCH == 1 ? (LPR == 64 ? GNN_SPMM_MINB_WIDE : GNN_SPMM_MINB_NARROW) : 4) void spmm_rows_kernel(SpmmArgs a) {
     using E = Elem<DT, VE>;
     constexpr int RPW = kWave / LPR;
@@ -443,12 +452,15 @@ __global__ __launch_bounds__(256, NCH == 1 ? (LPR == 64 ? GNN_SPMM_MINB_WIDE : G
     __shared__ int32_t s_idx_all[4][kWave];
     __shared__ int32_t s_row_v[RPB], s_row_s[RPB], s_row_e[RPB], s_row_hub[RPB], s_row_he[RPB];
     __shared__ float s_row_sc[RPB];
+    __shared__ int32_t s_row_part[SPLIT ? RPB : 1], s_row_np[SPLIT ? RPB : 1], s_row_nc[SPLIT ? RPB : 1];
     __shared__ int32_t s_next;
     __shared__ float s_red[NG][W];
     const int lane = lane_id(), wave = (int)(threadIdx.x >> 6);
     const int sub = lane / LPR, sl = lane % LPR;
     const int gi = wave * RPW + sub;
     int32_t* s_idx = s_idx_all[wave];
+    const bool split = SPLIT && *a.split_on != 0;     // uniform
+    const int32_t* const ids = split ? a.split_cold : a.col_idx;
 
     // ---- phase 0
     const int rpb = NG * a.rows_per_group;
@@ -459,11 +471,22 @@ __global__ __launch_bounds__(256, NCH == 1 ? (LPR == 64 ? GNN_SPMM_MINB_WIDE : G
         const int32_t v = a.rows ? a.rows[chunk0 + r] : (int32_t)(chunk0 + r);
         const int32_t s = a.row_ptr[v];
         int32_t e = a.row_ptr[v + 1];
-        if (a.cut_id >= 0) e = row_lower_bound(a.col_idx, s, e, a.cut_id);   // the entries past it can never pass the filter
-        const bool hub = e - s > kHubTiles * LPR;
+        if (a.cut_id >= 0 && !split) e = row_lower_bound(a.col_idx, s, e, a.cut_id);   // the entries past it can never pass the filter
+        int32_t own = e - s;
+        bool hub = own > kHubTiles * LPR;
+        if (split) {
+            // a row that reaches into another chunk of entries is taken by the whole workgroup, whatever its length
+            SplitRow d = {0, 0, 0};
+            if (e > s) d = a.split_rows[v];
+            own = d.n_cold;
+            hub = own > kHubTiles * LPR || (e > s && (uint32_t)s / kSplitChunk != (uint32_t)(e - 1) / kSplitChunk);
+            s_row_part[r] = d.part;
+            s_row_np[r] = d.n_parts;
+            s_row_nc[r] = own;
+        }
         s_row_v[r] = v;
         s_row_s[r] = s;
-        s_row_e[r] = hub ? s : e;
+        s_row_e[r] = hub ? s : s + own;
         s_row_he[r] = e;
         s_row_hub[r] = hub ? 1 : 0;
         s_row_sc[r] = a.out_scale ? a.out_scale[v] : 1.f;
@@ -483,6 +506,31 @@ __global__ __launch_bounds__(256, NCH == 1 ? (LPR == 64 ? GNN_SPMM_MINB_WIDE : G
     for (int c = 0; c < NCH; ++c)
 #pragma unroll
         for (int k = 0; k < VE; ++k) acc[c][k] = 0.f;
+    float parts[SPLIT ? NCH : 1][SPLIT ? VE : 1];     // sum of the row's parts: fetched when the row begins, added when it ends
+    auto add_part = [&](float (&to)[NCH][VE], int64_t part) {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            if (!col_ok[c]) continue;
+            const float* q = a.split_plane + part * a.split_ld + col_off[c];
+#pragma unroll
+            for (int k = 0; k < VE; k += 4) {
+                const float4 t = *(const float4*)(q + k);
+                to[c][k] += t.x; to[c][k + 1] += t.y; to[c][k + 2] += t.z; to[c][k + 3] += t.w;
+            }
+        }
+    };
+    auto begin_row = [&](int j, bool valid) {
+        if constexpr (SPLIT) {
+#pragma unroll
+            for (int c = 0; c < NCH; ++c)
+#pragma unroll
+                for (int k = 0; k < VE; ++k) parts[c][k] = 0.f;
+            if (split && valid && !s_row_hub[j]) {
+                const int np = s_row_np[j];
+                for (int k = 0; k < np; ++k) add_part(parts, (int64_t)s_row_part[j] + k);
+            }
+        }
+    };
 
     // ---- phase 1
     // Tile descriptors (row slot j, position p, row end e, valid flag) of the current tile and of the
@@ -508,12 +556,13 @@ __global__ __launch_bounds__(256, NCH == 1 ? (LPR == 64 ? GNN_SPMM_MINB_WIDE : G
         pc = s_row_s[jc];
         ec = s_row_e[jc];
     }
+    begin_row(jc, have);
     int jn;
     uint32_t pn, en;
     bool have_n;
     advance(jc, pc, ec, have, jn, pn, en, have_n);
-    int32_t u_c = (have && pc + sl < ec) ? a.col_idx[pc + sl] : 0;
-    int32_t u_n = (have_n && pn + sl < en) ? a.col_idx[pn + sl] : 0;
+    int32_t u_c = (have && pc + sl < ec) ? ids[pc + sl] : 0;
+    int32_t u_n = (have_n && pn + sl < en) ? ids[pn + sl] : 0;
     int32_t d_c = 0;
     if (FILTER) d_c = (have && pc + sl < ec) ? filter_probe(a, u_c, pc + sl) : -1;
     while (__ballot(have) != 0ull) {  // uniform over the wave
@@ -522,7 +571,7 @@ __global__ __launch_bounds__(256, NCH == 1 ? (LPR == 64 ? GNN_SPMM_MINB_WIDE : G
         uint32_t pnn, enn;
         bool have_nn;
         advance(jn, pn, en, have_n, jnn, pnn, enn, have_nn);
-        const int32_t u_nn = (have_nn && pnn + sl < enn) ? a.col_idx[pnn + sl] : 0;  // two tiles ahead
+        const int32_t u_nn = (have_nn && pnn + sl < enn) ? ids[pnn + sl] : 0;  // two tiles ahead
         int32_t d_n = 0;
         if (FILTER) d_n = (have_n && pn + sl < en) ? filter_probe(a, u_n, pn + sl) : -1;  // one tile ahead
 
@@ -545,7 +594,10 @@ __global__ __launch_bounds__(256, NCH == 1 ? (LPR == 64 ? GNN_SPMM_MINB_WIDE : G
                     if (col_ok[c]) {
                         float o[VE];
 #pragma unroll
-                        for (int k = 0; k < VE; ++k) o[k] = acc[c][k] * sc;
+                        for (int k = 0; k < VE; ++k) {
+                            if constexpr (SPLIT) acc[c][k] += parts[c][k];
+                            o[k] = acc[c][k] * sc;
+                        }
                         const int64_t rest = (int64_t)a.F - col_off[c];
                         E::store(a.Y, (int64_t)v * a.ldy + col_off[c], o, rest >= VE ? VE : (int)rest, a.accumulate != 0, a.relu_h,
                                  (int64_t)v * a.ldh + col_off[c]);
@@ -557,6 +609,7 @@ __global__ __launch_bounds__(256, NCH == 1 ? (LPR == 64 ? GNN_SPMM_MINB_WIDE : G
 #pragma unroll
                 for (int k = 0; k < VE; ++k) acc[c][k] = 0.f;
         }
+        if (row_done) begin_row(jn, have_n);
         jc = jn; pc = pn; ec = en; have = have_n;
         jn = jnn; pn = pnn; en = enn; have_n = have_nn;
         u_c = u_n; u_n = u_nn; d_c = d_n;
@@ -572,21 +625,39 @@ __global__ __launch_bounds__(256, NCH == 1 ? (LPR == 64 ? GNN_SPMM_MINB_WIDE : G
         for (int c = 0; c < NCH; ++c)
 #pragma unroll
             for (int k = 0; k < VE; ++k) acc[c][k] = 0.f;
-        for (int64_t base = (int64_t)hs + (int64_t)wave * kWave; base < he; base += 4 * kWave) {
-            // the wave's RPW groups take consecutive LPR-wide tiles of this 64-entry stretch
-            const int64_t p0 = base + sub * LPR;
-            int left = (int)((int64_t)he - p0 < 0 ? 0 : ((int64_t)he - p0 < LPR ? (int64_t)he - p0 : LPR));
-            const int32_t u = sl < left ? a.col_idx[p0 + sl] : 0;
-            int32_t d = 0;
-            if (FILTER) d = sl < left ? filter_probe(a, u, (int32_t)(p0 + sl)) : -1;
-            wave_lds_sync();
-            const int cnt = commit_tile<LPR, FILTER>(a, sl < left, u, d, left, sub, sl, s_idx);
-            int cnt_max = cnt;
-#pragma unroll
-            for (int d = LPR; d < kWave; d <<= 1) cnt_max = max(cnt_max, __shfl_xor(cnt_max, d, kWave));
-            wave_lds_sync();
-            consume_tile<E, LPR, NCH, U>(a, cnt, cnt_max, sub, col_off, col_ok, s_idx, acc);
+        // a row of the split route: chunk by chunk, its parts (one of every NG to a group) and its other entries there
+        int64_t lo = hs, hi = he, chunk = 0;
+        bool more = true;
+        if constexpr (SPLIT) if (split) {
+            chunk = (uint32_t)hs / kSplitChunk;
+            hi = lo + s_row_nc[q];
+            for (int k = gi; k < s_row_np[q]; k += NG) add_part(acc, (int64_t)s_row_part[q] + k);
         }
+        do {
+            for (int64_t base = lo + (int64_t)wave * kWave; base < hi; base += 4 * kWave) {
+                // the wave's RPW groups take consecutive LPR-wide tiles of this 64-entry stretch
+                const int64_t p0 = base + sub * LPR;
+                int left = (int)(hi - p0 < 0 ? 0 : (hi - p0 < LPR ? hi - p0 : LPR));
+                const int32_t u = sl < left ? ids[p0 + sl] : 0;
+                int32_t d = 0;
+                if (FILTER) d = sl < left ? filter_probe(a, u, (int32_t)(p0 + sl)) : -1;
+                wave_lds_sync();
+                const int cnt = commit_tile<LPR, FILTER>(a, sl < left, u, d, left, sub, sl, s_idx);
+                int cnt_max = cnt;
+#pragma unroll
+                for (int d = LPR; d < kWave; d <<= 1) cnt_max = max(cnt_max, __shfl_xor(cnt_max, d, kWave));
+                wave_lds_sync();
+                consume_tile<E, LPR, NCH, U>(a, cnt, cnt_max, sub, col_off, col_ok, s_idx, acc);
+            }
+            ++chunk;
+            more = split && chunk * kSplitChunk < he;      // uniform
+            if constexpr (SPLIT) if (more) {
+                const SplitChunk d = a.split_chunks[chunk];
+                lo = chunk * kSplitChunk;
+                hi = lo + d.head_cold;
+                for (int k = gi; k < d.head_parts; k += NG) add_part(acc, (int64_t)d.part0 + k);
+            }
+        } while (more);
 #pragma unroll
         for (int c = 0; c < NCH; ++c)
 #pragma unroll
@@ -903,7 +974,7 @@ static int32_t launch_stream(const SpmmArgs& a, int64_t avg_row, bool off32, hip
     return GNN_OK;
 }
 
-template <int DT, int VE, int LPR, int NCH, bool FILTER>
+template <int DT, int VE, int LPR, int NCH, bool FILTER, bool SPLIT = false>
 static int32_t launch_rows(const SpmmArgs& a, hipStream_t stream) {
     constexpr int U = NCH == 1 ? (LPR < 16 ? 4 : (LPR < 64 ? GNN_SPMM_U_NARROW : GNN_SPMM_U_WIDE)) : (NCH == 2 ? 4 : (NCH == 3 ? 3 : 2));
     constexpr int NG = 4 * (kWave / LPR);
@@ -916,7 +987,7 @@ static int32_t launch_rows(const SpmmArgs& a, hipStream_t stream) {
     b.rows_per_group = rpg < 1 ? 1 : (rpg > kMaxRpg ? kMaxRpg : rpg);
     const int rpb = NG * b.rows_per_group;
     dim3 grid((unsigned)(((int64_t)a.n_active + rpb - 1) / rpb), (unsigned)((a.F + W - 1) / W));
-    spmm_rows_kernel<DT, VE, LPR, NCH, U, FILTER><<<grid, 256, 0, stream>>>(b);
+    spmm_rows_kernel<DT, VE, LPR, NCH, U, FILTER, SPLIT><<<grid, 256, 0, stream>>>(b);
     GNN_LAUNCH_CHECK("spmm_rows_kernel");
     return GNN_OK;
 }
@@ -1160,13 +1231,18 @@ static bool die_ids_round_robin(const int32_t* ids) {
     return true;
 }
 
-// 1: the mapping holds on the current device, 0: it does not (or could not be probed); probed at the first question
-static int die_mapping_holds() {
+// 1: the mapping holds on the current device, 0: it does not (or could not be probed); probed at the first question.  `capturing`
+// (nullable): a stream whose capture the probe would end - not probed then, and asked again next time.
+static int die_mapping_holds(const hipStream_t* capturing = nullptr) {
     static std::mutex mu;
     static int state[64];   // per device: 0 unknown, 1 holds, 2 does not
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
     std::lock_guard<std::mutex> lock(mu);
+    if (state[dev] == 0 && capturing != nullptr) {
+        hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(*capturing, &status) != hipSuccess || status != hipStreamCaptureStatusNone) return 0;
+    }
     if (state[dev] == 0) {
         int32_t ids[kProbeX * kProbeY];
         state[dev] = (probe_die_ids(ids) == GNN_OK && die_ids_round_robin(ids)) ? 1 : 2;
@@ -1286,6 +1362,83 @@ static int32_t run_blocked(const SpmmArgs& a, const BlockedPlan& p, void* ws, hi
     return GNN_OK;
 }
 
+// The split route's shape for one call; n_chunks == 0: the route does not apply.
+struct SplitPlan {
+    int64_t n_chunks = 0, n_parts = 0;
+    int32_t n_slabs = 0, n_nbr = 0;
+};
+
+// Where the line lies (power-law graphs, call with / without the route, us): what the route costs - moving the entries once, a
+// part written and read once per row - has to be made up for by the rows' hot entries, so it takes long rows
+//   256 columns: 2.4 M rows of 12 4385 / 4232, of 25 8190 / 8158; 1 M of 24 2796 / 3118, of 50 5311 / 6492; 400 k of 120 4277 / 6243
+// of several cache lines
+//   1 M rows of 50: 48 columns 1591 / 1403, 64 1890 / 2045, 100 2730 / 3124, 128 3100 / 3927, 602 14129 / 16556
+//   300 k rows of 50: 48 465 / 374, 64 492 / 449, 100 759 / 847, 128 807 / 981, 602 3201 / 4796
+// in fp32 (bf16 parts are floats all the same: 1 M rows of 50, 256 columns 3565 / 3052, 512 columns 6752 / 6687), out of a matrix
+// that the L2s of all dies (32 MB) do not hold
+//   100 k rows of 60: 100 columns 285 / 298, 256 494 / 671.
+static SplitPlan plan_split(const gnn_csr* g, const int32_t* rows, int32_t n_active, int32_t F, int32_t dtype, int64_t row_bytes, bool vec_ok,
+                            bool filter, int32_t cut_id, hipStream_t stream) {
+    SplitPlan p;
+    if (dtype != GNN_F32 || rows != nullptr || !vec_ok || filter || n_active < 4096 || F <= 3 * kSplitCols) return p;
+    const int32_t n_src = cut_id >= 0 ? cut_id : g->n_cols;
+    if (g->nnz / g->n_rows < 40 || n_src * row_bytes < (48ll << 20) || g->nnz * row_bytes < (1ll << 30)) return p;
+    p.n_nbr = n_src < g->n_rows ? n_src : g->n_rows;
+    p.n_chunks = (g->nnz + kSplitChunk - 1) / kSplitChunk;
+    p.n_slabs = (F + kSplitCols - 1) / kSplitCols;
+    p.n_parts = (int64_t)n_active + p.n_chunks * (kSplitGroups + 1);
+    if (p.n_parts > INT32_MAX || !die_mapping_holds(&stream)) p.n_chunks = 0;
+    return p;
+}
+
+// Lays the route's arrays out; with base == nullptr it only measures.
+static SplitArgs carve_split(const SplitPlan& p, int32_t n_active, WsCarver& carve) {
+    SplitArgs s = {};
+    s.hist = carve.take<int32_t>((size_t)kSplitBlocks * kSplitBins);
+    s.hits = carve.take<int32_t>(kSplitSampleBlocks);
+    s.ctrl = carve.take<int32_t>(2);
+    s.first_row = carve.take<int32_t>(p.n_chunks + 1);
+    s.slot = carve.take<uint2>(((size_t)p.n_nbr + 31) / 32);
+    s.hot = carve.take<int32_t>(kSplitSlots + 1);
+    s.table = carve.take<float>((size_t)p.n_slabs * (kSplitSlots + 1) * kSplitCols);
+    s.stream = carve.take<uint16_t>((size_t)p.n_chunks * kSplitStage);
+    s.ends = carve.take<uint64_t>((size_t)p.n_chunks * kSplitQuadWords);
+    s.before = carve.take<uint16_t>((size_t)p.n_chunks * kSplitGroups);
+    s.cold = carve.take<int32_t>((size_t)p.n_chunks * kSplitChunk);
+    s.rows = carve.take<SplitRow>(n_active);
+    s.chunks = carve.take<SplitChunk>(p.n_chunks);
+    s.plane = carve.take<float>((size_t)p.n_slabs * p.n_parts * kSplitCols);
+    return s;
+}
+
+static int32_t run_split(const SpmmArgs& a, const SplitPlan& p, void* ws, hipStream_t stream) {
+    WsCarver carve(ws);
+    SplitArgs s = carve_split(p, a.n_active, carve);
+    s.row_ptr = a.row_ptr; s.col_idx = a.col_idx; s.n_active = a.n_active;
+    s.n_nbr = p.n_nbr; s.limit = a.cut_id >= 0 ? a.cut_id : INT32_MAX;
+    s.n_chunks = p.n_chunks; s.n_parts = p.n_parts; s.n_slabs = p.n_slabs;
+    s.X = a.X; s.ldx = a.ldx; s.F = a.F; s.nbr_scale = a.nbr_scale;
+    split_degrees_kernel<<<kSplitBlocks, 1024, 0, stream>>>(s);
+    GNN_LAUNCH_CHECK("split_degrees_kernel");
+    split_assign_kernel<<<kSplitBlocks, 1024, 0, stream>>>(s);
+    GNN_LAUNCH_CHECK("split_assign_kernel");
+    split_table_kernel<<<kSplitTableBlocks + kSplitSampleBlocks, 256, 0, stream>>>(s);
+    GNN_LAUNCH_CHECK("split_table_kernel");
+    if (a.cut_id >= 0) split_entries_kernel<true><<<(unsigned)p.n_chunks, 1024, 0, stream>>>(s);
+    else split_entries_kernel<false><<<(unsigned)p.n_chunks, 1024, 0, stream>>>(s);
+    GNN_LAUNCH_CHECK("split_entries_kernel");
+    const int64_t per_die = (p.n_chunks * p.n_slabs + kDies - 1) / kDies;
+    split_sum_kernel<<<(unsigned)(per_die * kDies), 256, 0, stream>>>(s, per_die);
+    GNN_LAUNCH_CHECK("split_sum_kernel");
+    SpmmArgs b = a;
+    b.split_on = s.ctrl + 1; b.split_cold = s.cold; b.split_rows = s.rows; b.split_chunks = s.chunks;
+    b.split_plane = s.plane; b.split_ld = (int64_t)p.n_slabs * kSplitCols;
+    if (a.F <= 128) return launch_rows<GNN_F32, 4, 32, 1, false, true>(b, stream);
+    if (a.F <= 256) return launch_rows<GNN_F32, 4, 64, 1, false, true>(b, stream);
+    if (a.F <= 512) return launch_rows<GNN_F32, 4, 64, 2, false, true>(b, stream);
+    return launch_rows<GNN_F32, 4, 64, 3, false, true>(b, stream);
+}
+
 template <int DT, bool FILTER>
 static int32_t dispatch(const SpmmArgs& a, bool vec_ok, hipStream_t stream) {
     constexpr int VE = DT == GNN_F32 ? 4 : 8;
@@ -1333,6 +1486,7 @@ static int32_t spmm_common(const gnn_csr* g, const char* gname, const int32_t* r
     const int32_t cut_id = (use_prefix && sorted) ? src_prefix : -1, id_limit = (use_prefix && !sorted) ? src_prefix : -1;
     const bool filter = dist != nullptr || g->edge_keep != nullptr || id_limit >= 0;
     BlockedPlan plan;
+    SplitPlan split;
     if (ws_bytes != nullptr) {
         if (n_active > 0 && F > 0) plan = plan_blocked(g, n_active, F, ldx * (dtype == GNN_F32 ? 4 : 2), vec_ok, filter, nbr_scale != nullptr,
                                                             dtype == GNN_F32, cut_id);
@@ -1347,6 +1501,15 @@ static int32_t spmm_common(const gnn_csr* g, const char* gname, const int32_t* r
             if (plan.xs_bytes) measure.take<char>(plan.xs_bytes);
             if (plan.w_bytes) measure.take<char>(plan.w_bytes);
             if (plan.bounds_bytes) measure.take<char>(plan.bounds_bytes);
+        }
+        if (plan.passes == 0 && n_active > 0 && F > 0) {
+            split = plan_split(g, rows, n_active, F, dtype, ldx * (dtype == GNN_F32 ? 4 : 2), vec_ok, filter, cut_id, stream);
+            if (split.n_chunks > 0) {
+                WsCarver wanted(nullptr);
+                carve_split(split, n_active, wanted);
+                if (ws == nullptr) measure.used = wanted.used;              // asked for
+                else if (*ws_bytes < wanted.used) split.n_chunks = 0;       // the row kernel needs none
+            }
         }
         bool query_only = false;
         GNN_CHECK(ws_protocol(ws, ws_bytes, measure.used, &query_only));
@@ -1377,11 +1540,13 @@ static int32_t spmm_common(const gnn_csr* g, const char* gname, const int32_t* r
         a.x_row_bytes = small ? (uint32_t)row_bytes : 0u;
     }
     a.seg = nullptr; a.seg_end = nullptr; a.edge_w = nullptr; a.n_blocks = 0; a.block0 = 0;
+    a.split_on = nullptr; a.split_cold = nullptr; a.split_rows = nullptr; a.split_chunks = nullptr; a.split_plane = nullptr; a.split_ld = 0;
 
     if (plan.passes > 0) {
         if (dtype == GNN_F32) return filter ? run_blocked<GNN_F32, true>(a, plan, ws, stream) : run_blocked<GNN_F32, false>(a, plan, ws, stream);
         return filter ? run_blocked<GNN_BF16, true>(a, plan, ws, stream) : run_blocked<GNN_BF16, false>(a, plan, ws, stream);
     }
+    if (split.n_chunks > 0) return run_split(a, split, ws, stream);
     if (dtype == GNN_F32) return filter ? dispatch<GNN_F32, true>(a, vec_ok, stream) : dispatch<GNN_F32, false>(a, vec_ok, stream);
     return filter ? dispatch<GNN_BF16, true>(a, vec_ok, stream) : dispatch<GNN_BF16, false>(a, vec_ok, stream);
 }

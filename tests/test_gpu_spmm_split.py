@@ -1,0 +1,138 @@
+"""The split route of the aggregation (hot neighbours summed from a table, the others by the row kernel), against plain torch
+sums in 64 bits, at the places where its pieces meet: chunks of 8192 entries, fours of slots, rows that cross chunks, runs of
+rows without entries, a cut at a source prefix, slabs of 32 columns."""
+import numpy as np
+import pytest
+import torch
+
+import graphgen as gg
+
+pytestmark = pytest.mark.gpu
+CTRL = 256 * 256 * 4 + 256 * 4      # byte offset in the workspace of (hot neighbours, 1: the route went on)
+
+
+def _graph(n, deg, seed, empty=(), hubs=0):
+    """Skewed, symmetric but for the rows of `empty` (ranges), whose entries are dropped, and the first `hubs` rows, which hold
+    30 000 entries more."""
+    g = gg.chung_lu(n, deg, 2.1, seed)
+    rng = np.random.default_rng(seed)
+    rows = np.repeat(np.arange(n, dtype=np.int64), g.degrees())
+    keys = rows * n + g.col_idx
+    keep = np.ones(len(keys), bool)
+    for a, b in empty:
+        keep &= (rows < a) | (rows >= b)
+    keys = keys[keep]
+    for r in range(hubs):
+        keys = np.concatenate([keys, r * n + rng.integers(0, n, 30_000)])
+    keys = np.unique(keys)
+    row_ptr = np.zeros(n + 1, np.int64)
+    row_ptr[1:] = np.cumsum(np.bincount(keys // n, minlength=n))
+    return row_ptr.astype(np.int32), (keys % n).astype(np.int32)
+
+
+def _want(row_ptr, ci, n_active, X, rs, cs, limit):
+    """-> the sums in 64 bits, and the sums of the magnitudes."""
+    F = X.shape[1]
+    out, size = (torch.zeros(n_active, F, dtype=torch.float64, device="cuda") for _ in range(2))
+    m = int(row_ptr[n_active])
+    lens = torch.from_numpy(np.diff(row_ptr[: n_active + 1]).astype(np.int64)).cuda()
+    row = torch.repeat_interleave(torch.arange(n_active, device="cuda"), lens)
+    for a in range(int(row_ptr[0]), m, 400_000):
+        b = min(m, a + 400_000)
+        r, c = row[a - int(row_ptr[0]): b - int(row_ptr[0])], ci[a:b].long()
+        ok = c < limit
+        r, c = r[ok], c[ok]
+        t = X[c].double() * (cs[c].double()[:, None] if cs is not None else 1.0)
+        out.index_add_(0, r, t)
+        size.index_add_(0, r, t.abs())
+    s = rs[:n_active].double()[:, None] if rs is not None else 1.0
+    return out * s, size * s, lens[:, None].double()
+
+
+CASES = {
+    # name: graph arguments, F, ld, scales, rows (share), source prefix (share), accumulate and ReLU
+    "256": (dict(n=60_000, deg=46, seed=1), 256, 256, True, 1.0, None, False),
+    "100_crossing_rows": (dict(n=140_001, deg=60, seed=2, hubs=3, empty=((40, 7000), (100_000, 101_500))), 100, 128, False, 0.83, None, False),
+    "301_prefix": (dict(n=50_000, deg=50, seed=3, hubs=2, empty=((30_000, 34_000),)), 301, 304, True, 1.0, 0.9, True),
+    "97_prefix": (dict(n=400_000, deg=45, seed=4, empty=((0, 2500),)), 97, 100, True, 0.999, 0.97, False),
+    "640": (dict(n=24_000, deg=50, seed=5, hubs=1), 640, 640, True, 1.0, None, True),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_split_route(name):
+    import paper_2311_06837_amd as P
+    kw, F, ld, scales, share, prefix, extra = CASES[name]
+    dtype = torch.float32
+    row_ptr, col = _graph(**kw)
+    n, n_active = kw["n"], int(kw["n"] * share)
+    G = P.Graph(torch.from_numpy(row_ptr).cuda(), torch.from_numpy(col).cuda(), sorted_columns=True)
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    X = torch.full((n, ld), float("nan"), dtype=dtype, device="cuda")                 # pad columns must never matter
+    X[:, :F] = torch.randn(n, F, generator=gen, device="cuda").to(dtype)
+    limit = n if prefix is None else int(n * prefix)
+    rs, cs = ((torch.rand(n, generator=gen, device="cuda") + 0.5) if scales else None for _ in range(2))
+    Y = torch.full((n, ld), 12345.0, dtype=dtype, device="cuda")
+    H = None
+    if extra:
+        Y[:, :F] = torch.randn(n, F, generator=gen, device="cuda").to(dtype)
+        H = torch.randn(n, ld, generator=gen, device="cuda").to(dtype)
+    start = Y.clone()
+    ws = P.Workspace()
+
+    def call(w):
+        Y.copy_(start)
+        if prefix is None and not extra:
+            P.gnn_masked_spmm_fwd(G, None, n_active, X, Y, F, rs, cs, ws=w)
+        else:
+            P.gnn_masked_spmm_bwd(G, None, n_active, None, 0, X, Y, F, cs, rs, accumulate=extra, ws=w, relu_H=H, src_prefix=-1 if prefix is None else limit)
+        return Y.clone()
+
+    got = call(ws)
+    n_hot, on = ws.buf[CTRL: CTRL + 8].view(torch.int32).tolist()
+    print(f"{name}: {len(col)} entries, {n_hot} hot neighbours", flush=True)
+    assert on == 1 and 0 < n_hot <= 65535
+    want, size, lens = _want(row_ptr, torch.from_numpy(col).cuda(), n_active, X[:, :F], rs, cs, limit)
+    if extra:
+        want = torch.where(H[:n_active, :F] > 0, want + start[:n_active, :F].double(), 0.0)
+        size = size + start[:n_active, :F].double().abs()
+    # fp32 sums in any order with two roundings more a term: at most (terms + 8) * 2^-24 of the sum of magnitudes
+    tol = (lens + 8) * 2.0 ** -24 * size + 1e-30
+    worst = ((got[:n_active, :F].double() - want).abs() / tol).max().item()
+    assert worst <= 1.0, worst
+    assert torch.equal(got[n_active:], start[n_active:]) and torch.equal(got[:, F:], start[:, F:]), "written outside"
+    assert torch.equal(call(ws), got), "not the same bits twice"
+    small = P.Workspace()
+    small.buf = torch.empty(4096, dtype=torch.uint8, device="cuda")
+    plain = call(None)
+    lib, C = P.binding.lib(), P.binding.C          # a workspace too small for the route: as without one
+    Y.copy_(start)
+    P.binding._check(lib.gnn_masked_spmm_bwd(C.byref(G.c), None, n_active, None, 0, -1 if prefix is None else limit, X.data_ptr(), ld, Y.data_ptr(), ld, F,
+                                             0, cs.data_ptr() if scales else None, rs.data_ptr() if scales else None,
+                                             1 if extra else 0, H.data_ptr() if extra else None, ld if extra else 0,
+                                             small.buf.data_ptr(), C.byref(C.c_size_t(4096)), P.binding._stream()))
+    assert torch.equal(Y, plain)
+
+
+@pytest.mark.parametrize("skewed_rows", [False, True])
+def test_a_graph_without_hot_neighbours_runs_as_before(skewed_rows):
+    """Every neighbour equally frequent: seen from the row lengths, or, where those are skewed, from the samples."""
+    import paper_2311_06837_amd as P
+    n, deg, F = 400_000, 42, 128
+    rng = np.random.default_rng(3)
+    lens = np.minimum(rng.pareto(1.1, n) * 12 + 1, 20_000).astype(np.int64) if skewed_rows else np.full(n, deg)
+    lens = np.maximum(1, lens * deg * n // lens.sum())
+    rows = np.repeat(np.arange(n, dtype=np.int64), lens)
+    keys = np.unique(rows * n + rng.integers(0, n, len(rows)))
+    row_ptr = np.zeros(n + 1, np.int64)
+    row_ptr[1:] = np.cumsum(np.bincount(keys // n, minlength=n))
+    assert len(keys) // n >= 40
+    G = P.Graph(torch.from_numpy(row_ptr.astype(np.int32)).cuda(), torch.from_numpy((keys % n).astype(np.int32)).cuda(), sorted_columns=True)
+    X = torch.randn(n, F, device="cuda")
+    ws = P.Workspace()
+    Y, Z = torch.zeros_like(X), torch.zeros_like(X)
+    P.gnn_masked_spmm_fwd(G, None, n, X, Y, F, ws=ws)
+    P.gnn_masked_spmm_fwd(G, None, n, X, Z, F)
+    n_hot, on = ws.buf[CTRL: CTRL + 8].view(torch.int32).tolist()
+    assert on == 0 and (n_hot > 0) == skewed_rows
+    assert torch.equal(Y, Z)
