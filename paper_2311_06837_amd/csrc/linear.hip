@@ -496,7 +496,7 @@ __device__ __forceinline__ u32x4 mask_chunk(u32x4 r, int n_valid) {
 // that start at or beyond K are read from the start of their row instead (always addressable) and every chunk is
 // masked to its valid elements when it is moved to LDS, so neither padding nor a neighbouring row reaches the MFMAs.
 template <int DT, int NTW, bool KTAIL>
-__global__ __launch_bounds__(256, 2) void gemm_nt_wide_kernel(GemmNT a) {
+__global__ __launch_bounds__(256, NTW == 4 ? 2 : NTW == 2 ? 3 : 4) void gemm_nt_wide_kernel(GemmNT a) {
     constexpr int BM = 128, BN = 64 * NTW, MT = 2, NT = NTW, WTN = 32 * NTW;
     constexpr int ES = DTy<DT>::ES, EPV = DTy<DT>::EPV;
     constexpr int EPS = 64 / ES;                  // reduction elements per slice
@@ -513,7 +513,9 @@ __global__ __launch_bounds__(256, 2) void gemm_nt_wide_kernel(GemmNT a) {
     __shared__ int32_t s_crow[BM];
 
     const int tiles_n = (a.N + BN - 1) / BN;
-    const int m0 = (int)(blockIdx.x / tiles_n) * BM, n0 = (int)(blockIdx.x % tiles_n) * BN;
+    // the tiles of a band of rows follow each other on one die (workgroup i runs on die i mod 8): its rows leave memory once
+    const int turn = (int)(blockIdx.x >> 3), m0 = ((turn / tiles_n) * 8 + (int)(blockIdx.x & 7)) * BM, n0 = (turn % tiles_n) * BN;
+    if (m0 >= a.M) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int li = lane & 31, g = lane >> 5;
@@ -1038,6 +1040,22 @@ static int32_t launch_gemm_nt(const GemmNT& a, hipStream_t stream) {
         // wide tile: the tile width that pads the output width least (256 on a tie)
         const int64_t p256 = ((int64_t)a.N + 255) / 256 * 256, p128 = ((int64_t)a.N + 127) / 128 * 128, p64 = ((int64_t)a.N + 63) / 64 * 64;
         int ntw = (p256 <= p128 && p256 <= p64) ? 4 : (p128 <= p64 ? 2 : 1);
+        if (DT == GNN_F32) {
+            // fp32 products are bound by the matrix instructions, so what counts is how many tiles the busiest CU gets: n tiles of
+            // 256, 128, 64 columns take about 5 + 74 n, 15 + 35 n and 13 + 19.2 n (us at 512 reduction elements; two, three and
+            // four workgroups of a CU run side by side).  256 columns from 512 (us, tile of 256 / 128 / 64): 1000 to 7000 rows 84 /
+            // 49 / 33, 20 000 87 / 81 / 72, 32 000 87 / 83 / 91, 45 000 146 / 124 / 125, 60 000 148 / 185 / 161, 75 000 220 / 190 /
+            // 195, 600 001 1357 / 1284 / 1411.
+            auto cost = [&](int width, double once, double each) {
+                return once + each * (double)(((tiles_m + 7) / 8 * (((int64_t)a.N + width - 1) / width) + 31) / 32);     // 32 CUs a die
+            };
+            const double c256 = cost(256, 5, 74), c128 = cost(128, 15, 35), c64 = cost(64, 13, 19.2);
+            ntw = c64 < c128 && c64 < c256 ? 1 : (c128 < c256 ? 2 : 4);
+        } else if (ntw == 4 && tiles_m * (p256 / 256) <= 384) {
+            // too few tiles of 256 columns to give every CU two (256 columns from 512, us, 256 / 128 wide: 1000 rows 22.6 / 17.3,
+            // 12 000 23.6 / 19.4, 45 000 31.8 / 30.5; 60 000, 469 tiles, 33.6 / 36.6)
+            ntw = 2;
+        }
         // a reduction of one or two slices (an input gradient from 32 or 41 class scores) is all prologue and epilogue:
         // narrow tiles keep more workgroups on a CU to hide those latencies, and re-reading the short rows costs little
         if ((int64_t)a.K * a.n_src * DTy<DT>::ES <= 128) ntw = 1;
@@ -1058,7 +1076,7 @@ static int32_t launch_gemm_nt(const GemmNT& a, hipStream_t stream) {
             GNN_LAUNCH_CHECK("gemm_nt_line_kernel");
             return GNN_OK;
         }
-        const unsigned grid = (unsigned)(tiles_m * (ntw == 4 ? p256 / 256 : (ntw == 2 ? p128 / 128 : p64 / 64)));
+        const unsigned grid = (unsigned)((tiles_m + 7) / 8 * 8 * (ntw == 4 ? p256 / 256 : (ntw == 2 ? p128 / 128 : p64 / 64)));
         const bool ktail = a.K % (64 / DTy<DT>::ES) != 0;
 #define GNN_WIDE(NTW_)                                                                                  \
     {                                                                                                   \

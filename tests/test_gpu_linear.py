@@ -355,3 +355,20 @@ def test_f32_products_with_infinities_nan_and_overflow():
         assert bool((torch.isinf(got) == torch.isinf(want)).all()) and bool((got[torch.isinf(want)] == want[torch.isinf(want)]).all())
         assert bool(torch.isnan(got[140, 11])) and bool(torch.isinf(got[520, 9])) and bool(torch.isnan(got[300]).all())
         assert torch.equal(got[rest], before[rest])
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("M,K,N", [(1025, 72, 256), (12_167, 64, 300), (45_001, 40, 256), (60_001, 64, 256), (49_153, 64, 512)])
+def test_tile_widths_of_the_forward_product(dtype, M, K, N):
+    """Row counts on either side of where the tile width changes (64, 128, 256 columns), last band of rows ragged, bands not a
+    multiple of the eight dies.  Every partial sum is an exact small integer, so any tiling gives the same bits."""
+    import paper_2311_06837_amd as P
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    a, x = (torch.randint(-2, 3, (M, K), generator=gen, device="cuda").to(dtype) for _ in range(2))
+    Wn, Ws = (torch.randint(-1, 2, (K, N), generator=gen, device="cuda").to(dtype) for _ in range(2))
+    b = torch.randint(-3, 4, (N,), generator=gen, device="cuda").float()
+    out = torch.full((M + 3, N), SENT, dtype=dtype, device="cuda")
+    P.gnn_linear_fwd(None, M, a, x, K, Wn, Ws, b, out, False)
+    want = a.float() @ Wn.float() + x.float() @ Ws.float() + b
+    assert torch.equal(out[:M].float(), want.to(dtype).float())
+    assert (out[M:] == torch.tensor(SENT, dtype=dtype)).all()
