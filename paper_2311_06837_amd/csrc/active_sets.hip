@@ -686,6 +686,117 @@ __global__ __launch_bounds__(256) void eas_expand_long_kernel(const int32_t* __r
     }
 }
 
+// ---- small graphs: all levels in one launch, by one workgroup -------------------------------------------------------
+// A construction of a small graph is as long as its launches, so here one workgroup keeps the bitmaps in LDS (a word a thread)
+// and walks the frontier's rows edge-parallel, 8192 edges a step; the row of an edge is a rank among the bits of rows'
+// beginnings (a search over the rows' prefix sums is ten dependent LDS reads an edge: 65 us of kernel where this takes 41).
+// The whole call (us, a launch per part of a level / this one): 2000 vertices of degree 5, two levels 86 / 39, 10 000 of 10
+// 92 / 57, five levels 132 / 77; 240 000 entries: 20 000 vertices, three levels 108 / 105, 30 000 109 / 117, eight levels 172 /
+// 144 - one compute unit walks what it takes the others to hide, so the line lies at half of that.
+constexpr int32_t kAsSmallRows = 32 * 1024;
+constexpr int64_t kAsSmallEntries = (int64_t)1 << 17;
+
+__global__ __launch_bounds__(1024) void as_small_kernel(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int32_t n,
+                                                        const int32_t* __restrict__ targets, int32_t n_targets, int32_t L,
+                                                        int32_t* __restrict__ dist, int32_t* ring_ids, int64_t* __restrict__ hop_offsets) {
+    constexpr int kRows = 4096, kPer = kRows / 1024, kWords = (int)(kAsSmallEntries / 32), kU = 8;
+    __shared__ uint32_t s_seen[1024], s_new[1024];
+    __shared__ int32_t s_at[1024];
+    __shared__ int32_t s_first[kRows];        // of the rows with entries: position of the first, less the edges before it
+    __shared__ uint32_t s_begin[kWords];      // bit: the edge begins a row
+    __shared__ uint16_t s_rank[kWords];       // rows that begin before the word's edges
+    __shared__ int s_part[16];
+    const int tid = (int)threadIdx.x;
+    s_seen[tid] = 0u;
+    for (int32_t v = tid; v < n; v += 1024) dist[v] = -1;
+    if (tid == 0) hop_offsets[0] = 0;
+    __syncthreads();
+    for (int32_t i = tid; i < n_targets; i += 1024) {
+        const int32_t v = targets[i];
+        if (v >= 0 && v < n) atomicOr(&s_seen[v >> 5], 1u << (v & 31));
+    }
+    __syncthreads();
+    uint32_t visited = 0u;      // of the thread's 32 vertices
+    int32_t total = 0;
+    for (int32_t ring = 0;; ++ring) {
+        const uint32_t found = s_seen[tid] & ~visited;
+        visited |= found;
+        int count;
+        const int before = block_exclusive_scan<1024>(__popc(found), s_part, &count);
+        const int32_t begin = total;
+        total += count;
+        s_new[tid] = found;
+        s_at[tid] = begin + before;
+        if (tid == 0) hop_offsets[ring + 1] = total;
+        __syncthreads();
+        for (int32_t v = tid; v < n; v += 1024) {
+            const uint32_t w = s_new[v >> 5], bit = 1u << (v & 31);
+            if ((w & bit) == 0u) continue;
+            ring_ids[s_at[v >> 5] + __popc(w & (bit - 1u))] = v;
+            dist[v] = ring;
+        }
+        if (ring == L) break;
+        if (count == 0) {      // nothing more is reached
+            for (int32_t r = ring + 1 + tid; r <= L; r += 1024) hop_offsets[r + 1] = total;
+            break;
+        }
+        __syncthreads();       // the ring's ids are there
+        for (int32_t c0 = begin; c0 < total; c0 += kRows) {
+            int32_t s[kPer], len[kPer], v[kPer], sum = 0;
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) v[k] = ring_ids[c0 + tid * kPer + k < total ? c0 + tid * kPer + k : begin];
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) {
+                s[k] = row_ptr[v[k]];
+                len[k] = row_ptr[v[k] + 1] - s[k];
+            }
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) {
+                if (c0 + tid * kPer + k >= total) len[k] = 0;
+                sum += len[k] | (len[k] > 0 ? 1 << 19 : 0);      // edges (2^17 at most) and rows with some, in one sum
+            }
+            int all;
+            int at = block_exclusive_scan<1024>(sum, s_part, &all);
+            const int edges = all & ((1 << 19) - 1), words = (edges + 31) / 32;
+            for (int w = tid; w < words; w += 1024) s_begin[w] = 0u;
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) {
+                if (len[k] == 0) continue;
+                const int off = at & ((1 << 19) - 1);
+                s_first[at >> 19] = s[k] - off;
+                atomicOr(&s_begin[off >> 5], 1u << (off & 31));
+                at += len[k] | 1 << 19;
+            }
+            __syncthreads();
+            const int each = (words + 1023) / 1024;              // words a thread, one after the other
+            int mine = 0, rank_all;
+            for (int w = tid * each; w < (tid + 1) * each && w < words; ++w) mine += __popc(s_begin[w]);
+            int rank = block_exclusive_scan<1024>(mine, s_part, &rank_all);
+            for (int w = tid * each; w < (tid + 1) * each && w < words; ++w) {
+                s_rank[w] = (uint16_t)rank;
+                rank += __popc(s_begin[w]);
+            }
+            __syncthreads();
+            for (int32_t e0 = tid; e0 < edges; e0 += kU * 1024) {
+                int32_t u[kU];
+#pragma unroll
+                for (int j = 0; j < kU; ++j) {
+                    const int32_t e = e0 + j * 1024 < edges ? e0 + j * 1024 : edges - 1;
+                    const int row = s_rank[e >> 5] + __popc(s_begin[e >> 5] & (~0u >> (31 - (e & 31)))) - 1;
+                    u[j] = col_idx[s_first[row] + e];
+                }
+#pragma unroll
+                for (int j = 0; j < kU; ++j) {
+                    const uint32_t bit = 1u << (u[j] & 31);
+                    if ((s_seen[u[j] >> 5] & bit) == 0u) atomicOr(&s_seen[u[j] >> 5], bit);
+                }
+            }
+            __syncthreads();
+        }
+    }
+}
+
 // count (unless the blocks are few), scan (if they are many) and emit
 static int32_t as_emit(const uint8_t* seen, const uint32_t* visited, uint32_t* visited_next, int64_t nw, int64_t nb, int32_t* blk_cnt,
                        int64_t* hop_offsets, int32_t ring, int32_t* ring_ids, int32_t* dist, uint32_t* frontier, const int32_t* row_ptr,
@@ -744,10 +855,16 @@ extern "C" int32_t gnn_build_active_sets(const gnn_csr* g, const gnn_csr* gt, co
     GNN_REQUIRE(n == 0 || (dist != nullptr && ring_ids != nullptr), GNN_ERR_INVALID_ARG, "dist / ring_ids is NULL");
     GNN_REQUIRE(n_targets == 0 || targets != nullptr, GNN_ERR_INVALID_ARG, "targets is NULL");
 
-    as_init_kernel<<<grid_for(n > L + 2 ? n : L + 2, 256, 2048), 256, 0, stream>>>(dist, n, visited[0], seen, nw, ctrl, (int32_t)ctrl_words,
-                                                                                   hop_offsets, L);
-    GNN_LAUNCH_CHECK("as_init_kernel");
-    if (n > 0) {
+    const bool small = n > 0 && n <= kAsSmallRows && g->nnz <= kAsSmallEntries;
+    if (small) {
+        as_small_kernel<<<1, 1024, 0, stream>>>(g->row_ptr, g->col_idx, n, targets, n_targets, L, dist, ring_ids, hop_offsets);
+        GNN_LAUNCH_CHECK("as_small_kernel");
+    } else {
+        as_init_kernel<<<grid_for(n > L + 2 ? n : L + 2, 256, 2048), 256, 0, stream>>>(dist, n, visited[0], seen, nw, ctrl, (int32_t)ctrl_words,
+                                                                                       hop_offsets, L);
+        GNN_LAUNCH_CHECK("as_init_kernel");
+    }
+    if (n > 0 && !small) {
         if (n_targets > 0) {
             as_seed_kernel<<<grid_for(n_targets, 256, 2048), 256, 0, stream>>>(targets, n_targets, n, seen);
             GNN_LAUNCH_CHECK("as_seed_kernel");

@@ -169,3 +169,24 @@ def test_cost_of_the_direction_switch_in_large_graphs():
             times.append(a.elapsed_time(b) * 1e3)
         return min(times)
     assert time_us(gt) < 2 * time_us(None)
+
+
+@pytest.mark.parametrize("n,nnz", [(32768, 131072), (32768, 131073), (32769, 100_000), (31, 40), (1025, 131072), (4097, 60_000)])
+def test_sets_of_small_graphs_around_the_one_launch_limit(n, nnz):
+    """One workgroup builds the sets of graphs of up to 32 768 vertices and 131 072 entries: rows without entries, a hub,
+    repeated entries, targets out of range, more levels than rings, more than 4096 vertices in a ring."""
+    rng = np.random.default_rng(nnz)
+    rows = np.sort(np.where(rng.random(nnz) < 0.2, 3 % n, rng.integers(0, max(1, n * 3 // 4), nnz)))
+    cols = rng.integers(0, n, nnz)
+    row_ptr = np.zeros(n + 1, np.int32)
+    row_ptr[1:] = np.cumsum(np.bincount(rows, minlength=n))
+    import paper_2311_06837_amd as P
+    G = P.Graph(dev(row_ptr), dev(cols.astype(np.int32)))
+    for targets in ([n - 1, 0, 0, -1, n], rng.integers(0, n, max(1, n // 3)), []):
+        for L in (1, 3, 12):
+            targets = np.asarray(targets, dtype=np.int32)
+            valid = targets[(targets >= 0) & (targets < n)]
+            od, oring, ooff = oracle.active_sets(row_ptr, cols.astype(np.int32), valid, L)
+            dist, ring, off, hop = P.gnn_build_active_sets(G, dev(targets), L)
+            assert list(hop) == list(ooff) and np.array_equal(off.cpu().numpy(), ooff)
+            assert np.array_equal(dist.cpu().numpy(), od) and np.array_equal(ring.cpu().numpy()[: ooff[-1]], oring)
