@@ -1336,11 +1336,35 @@ __global__ __launch_bounds__(256, BN == 256 ? 2 : 3) void gemm_tn_kernel(GemmTN 
 // order and the four sums are added in lane order - a fixed tree (bit-reproducible) with four times the loads in flight
 // of one chain over all splits (which took 72 us for 256 splits of a 128 x 256 gradient: as long as half the product).
 __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __restrict__ P, int32_t splits, int32_t n_src,
-                                                              int64_t kn, float* __restrict__ out0, float* __restrict__ out1) {
+                                                              int64_t kn, float* __restrict__ out0, float* __restrict__ out1,
+                                                              const float* __restrict__ Pb, int32_t N, float* __restrict__ dbias,
+                                                              int32_t bias_blocks) {
+    if ((int)blockIdx.x >= (int)gridDim.x - bias_blocks) {
+        // the bias gradient's partial sums ride along: 32 columns a workgroup, 32 chains each, as in reduce_rows_kernel
+        __shared__ float s_b[32][33];
+        const int tx = (int)(threadIdx.x & 31), ty = (int)(threadIdx.x >> 5);
+        const int n = ((int)blockIdx.x - ((int)gridDim.x - bias_blocks)) * 32 + tx;
+        float b[4] = {0.f, 0.f, 0.f, 0.f};
+        if (n < N)
+            for (int32_t r = ty; r < splits; r += 32)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (r + 8 * j < splits) b[j] += Pb[(int64_t)(r + 8 * j) * N + n];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) s_b[ty + 8 * j][tx] = b[j];
+        __syncthreads();
+        if (ty == 0 && n < N) {
+            float t = 0.f;
+#pragma unroll
+            for (int y = 0; y < 32; ++y) t += s_b[y][tx];
+            dbias[n] = t;
+        }
+        return;
+    }
     __shared__ float s_sum[4][64];
     const int x = (int)(threadIdx.x & 63), y = (int)(threadIdx.x >> 6);
     const int64_t total = (int64_t)n_src * kn;
-    for (int64_t base = (int64_t)blockIdx.x * 64; base < total; base += (int64_t)gridDim.x * 64) {   // uniform over the workgroup
+    for (int64_t base = (int64_t)blockIdx.x * 64; base < total; base += (int64_t)((int)gridDim.x - bias_blocks) * 64) {   // uniform over the workgroup
         const int64_t i = base + x;
         float s = 0.f;
         if (i < total) {
@@ -1559,13 +1583,10 @@ static int32_t linear_bwd_impl(const int32_t* rows, int32_t M, const void* dH, c
         else gemm_tn_kernel<DT, 32, false><<<(unsigned)((total + 7) / 8 * 8), 256, 0, stream>>>(t);
     }
     GNN_LAUNCH_CHECK("gemm_tn_kernel");
-    reduce_partials_kernel<<<grid_for((int64_t)t.n_src * K * N, 64, 8192), 256, 0, stream>>>(P, splits, t.n_src, (int64_t)K * N, dWn,
-                                                                                           dWs);
+    const int bias_blocks = in_place ? (N + 31) / 32 : 0;
+    reduce_partials_kernel<<<grid_for((int64_t)t.n_src * K * N, 64, 8192) + bias_blocks, 256, 0, stream>>>(P, splits, t.n_src, (int64_t)K * N, dWn,
+                                                                                                         dWs, Pb, N, dbias, bias_blocks);
     GNN_LAUNCH_CHECK("reduce_partials_kernel");
-    if (in_place) {
-        reduce_rows_kernel<<<(N + 31) / 32, 1024, 0, stream>>>(Pb, splits, N, dbias);
-        GNN_LAUNCH_CHECK("reduce_rows_kernel");
-    }
 
     // input gradients: dA = dZ W_neigh^T, dX_self = dZ W_self^T   (Bt = W as stored: [K][N])
     for (int which = 0; which < 2; ++which) {
@@ -1697,12 +1718,16 @@ extern "C" int32_t gnn_linear_bwd(const int32_t* rows, int32_t n_active, const v
     const int32_t n_part = n_active > 0 ? (n_active + kDzRows - 1) / kDzRows : 1;
     // Row splits of the weight-gradient reduction: as many as give every CU the three workgroups it can hold at once
     // and no more (256 CUs: 768 workgroups; the splits are equally long, so a second, partly filled round of workgroups
-    // would cost a whole round: 1024 workgroups took 2 rounds where 768 take 1.33 of the old round's length), at least
-    // 256 rows each, at most 256 splits and 128 MB of partial tiles
+    // would cost a whole round: 1024 workgroups took 2 rounds where 768 take 1.33 of the old round's length), at most 256
+    // splits and 128 MB of partial tiles
     const bool wide_n = tn_wide_columns(dtype, N) && vec_ok(A_neigh, ld_in, es) && (!X_self || vec_ok(X_self, ld_in, es));
     const int tiles = n_src * ((K + 127) / 128) * (wide_n ? N / 256 : (N > 32 ? (N + 127) / 128 : 1));
     int32_t splits = (wide_n ? 512 : 768) / tiles;   // two workgroups of the 256-column tile fit a CU, three of the others
-    const int32_t max_splits = n_active > 0 ? (n_active + 255) / 256 : 1;
+    // rows a split has at least: few rows go to many short splits while the chip has room for them (us at 256 / 128 / 64 rows at
+    // least, fp32: 1000 rows 256 x 256, two sources 56.8 / 48.7 / 46.6, 10 000 rows 64 x 64 33.1 / 26.5 / 24.2, 20 000 35.6 / 30.3 / 30.8;
+    // bf16: 1000 rows 256 x 256 33.6 / 30.0 / 29.7, 10 000 rows 40.8 / 41.0 / 44.0, 20 000 49.8 / 53.6 / 53.8)
+    const int32_t min_rows = (dtype == GNN_F32 ? 64 : 128) * (n_active <= 16384 ? 1 : 2);
+    const int32_t max_splits = n_active > 0 ? (n_active + min_rows - 1) / min_rows : 1;
     const int64_t split_bytes = (int64_t)n_src * K * N * 4;
     if (splits > max_splits) splits = max_splits;
     if (splits > 256) splits = 256;
