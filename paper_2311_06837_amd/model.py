@@ -19,6 +19,12 @@ def row_stride(width: int, dtype) -> int:
     return (width + mult - 1) // mult * mult
 
 
+# A second stream costs a small step more than it hides: two waits of 15 us and the change of streams, on the host, which is
+# what bounds such a step (10 000 vertices, 64-64-8, fp32: 250 us with the second stream, 205 without).  Weight gradients of all layers
+# of fewer operations than this take less than that on the GPU.
+SIDE_STREAM_FLOPS = {torch.float32: 5e9, torch.bfloat16: 2.5e10}
+
+
 class MaskedGNN:
     """L-layer GCN ("gcn") or GraphSAGE-mean ("sage") over one partition under one-hop masking.
 
@@ -57,7 +63,8 @@ class MaskedGNN:
     side_stream      True (default): the weight-gradient products of the backward pass - nothing in the step waits for
                      them - are enqueued on a second HIP stream (default priority, a workspace of its own), so they
                      run beside the backward aggregations, which leave the matrix cores idle; the step's stream
-                     waits for that stream when the backward pass ends.  False: everything on the caller's stream.
+                     waits for that stream when the backward pass ends.  False, or too little work in the products
+                     (SIDE_STREAM_FLOPS): everything on the caller's stream.
     """
 
     def __init__(self, graph: B.Graph, graph_t: B.Graph, targets: torch.Tensor, kind: str, params: list,
@@ -72,10 +79,12 @@ class MaskedGNN:
         self.n = graph.n_rows
         self.L = len(params)
         self.ws = B.Workspace()
+        self.dims = [params[0]["W_neigh"].shape[0]] + [p["W_neigh"].shape[1] for p in params]
+        products = sum(2.0 * self.n * K * N * (2 if kind == "sage" else 1) for K, N in zip(self.dims[:-1], self.dims[1:]))
+        side_stream = side_stream and products >= SIDE_STREAM_FLOPS[dtype]
         self.side = torch.cuda.Stream(device=targets.device) if side_stream else None
         self._ready = torch.cuda.Event() if side_stream else None     # recorded on the step's stream before each call on the side
         self.ws_side = B.Workspace()
-        self.dims = [params[0]["W_neigh"].shape[0]] + [p["W_neigh"].shape[1] for p in params]
         self.params = []
         for p in params:
             q = {"W_neigh": p["W_neigh"].to(dtype).contiguous(), "bias": p["bias"].float().contiguous()}

@@ -225,6 +225,17 @@ def test_side_stream_changes_nothing(kind, dims):
             assert torch.equal(ga[k], gb[k]), k
 
 
+@pytest.mark.parametrize("kind,dims", [("sage", [96, 64, 64, 7]), ("gcn", [64, 48, 24, 6]), ("sage", [16, 32, 32, 8])])
+def test_side_stream_at_any_size(kind, dims, monkeypatch):
+    """The same with the second stream taken however little the products are (small models leave it out by themselves)."""
+    import paper_2311_06837_amd.model as M
+    seen, join = [], M.MaskedGNN._join_side
+    monkeypatch.setattr(M, "SIDE_STREAM_FLOPS", {d: 0.0 for d in M.SIDE_STREAM_FLOPS})
+    monkeypatch.setattr(M.MaskedGNN, "_join_side", lambda self: seen.append(self.side is not None) or join(self))
+    test_side_stream_changes_nothing(kind, dims)
+    assert seen == [True, True, False, False]
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("transform_first", [False, True])
 def test_backward_in_the_chain_rules_order(dtype, transform_first):
