@@ -470,8 +470,8 @@ __global__ __launch_bounds__(256, BN == 128 ? GNN_NT_MINB : GNN_NT_MINB_NARROW) 
 // gemm_nt, wide tile.  The layer widths of the paper's models (128 .. 602) make these products
 // "skinny": the reduction and the output width are both a few hundred, the row count is millions,
 // so at bf16 the operand rows come from HBM faster than a small tile can turn them over.  This
-// variant gives one workgroup 128 rows x the WHOLE output width (up to 256 columns: each operand
-// row is read once), a wave 64 x 32*NTW, and moves 64-byte row slices through a double-buffered LDS
+// variant gives one workgroup 128 rows x 64, 128 or 256 columns (launch_gemm_nt picks the width),
+// a wave 64 x 32*NTW, and moves 64-byte row slices through a double-buffered LDS
 // ring with ONE barrier per slice: while slice s feeds the MFMAs, slice s+1 waits in registers and
 // slice s+2 is in flight.  LDS rows are 64 bytes without padding; the 16-byte chunk c of row r sits
 // at slot c ^ ((r >> 1) & 3), so that eight consecutive rows read with the same c touch eight
