@@ -974,10 +974,6 @@ static int32_t launch_stream(const SpmmArgs& a, int64_t avg_row, bool off32, hip
     return GNN_OK;
 }
 
-}  // namespace gnnhot
-#include "spmm_wave.h"
-namespace gnnhot {
-
 template <int DT, int VE, int LPR, int NCH, bool FILTER, bool SPLIT = false>
 static int32_t launch_rows(const SpmmArgs& a, hipStream_t stream) {
     constexpr int U = NCH == 1 ? (LPR < 16 ? 4 : (LPR < 64 ? GNN_SPMM_U_NARROW : GNN_SPMM_U_WIDE)) : (NCH == 2 ? 4 : (NCH == 3 ? 3 : 2));
@@ -1551,8 +1547,6 @@ static int32_t spmm_common(const gnn_csr* g, const char* gname, const int32_t* r
         return filter ? run_blocked<GNN_BF16, true>(a, plan, ws, stream) : run_blocked<GNN_BF16, false>(a, plan, ws, stream);
     }
     if (split.n_chunks > 0) return run_split(a, split, ws, stream);
-    if (wave_rows_apply(g, n_active, F, dtype, vec_ok, filter, accumulate == 0 && relu_h == nullptr))
-        return dtype == GNN_F32 ? launch_wave_rows<GNN_F32>(a, stream) : launch_wave_rows<GNN_BF16>(a, stream);
     if (dtype == GNN_F32) return filter ? dispatch<GNN_F32, true>(a, vec_ok, stream) : dispatch<GNN_F32, false>(a, vec_ok, stream);
     return filter ? dispatch<GNN_BF16, true>(a, vec_ok, stream) : dispatch<GNN_BF16, false>(a, vec_ok, stream);
 }
