@@ -348,7 +348,7 @@ def run_workload(args, name, steps, warmup, cpu_flops):
         blocked = P.binding.spmm_workspace_bytes(G, nd, src_dom, dst_dom, Fd) > 0     # a route whose point is reuse in the L2s
         slab = G.n_cols * 256
         by_columns = slab >= 16 << 20 and G.nnz / G.n_rows >= 64 * -(-slab // (64 << 20))
-        kernels = ("spmm_rows_kernel or, for short rows, spmm_wave_kernel" if not blocked else
+        kernels = ("spmm_rows_kernel" if not blocked else
                    "spmm_stream_kernel (+ spmm_seg_kernel before and spmm_sum_parts_kernel after it: column-blocked route)" if by_columns else
                    "split_sum_kernel (frequent neighbours, from a table) and spmm_rows_kernel (the others; + split_degrees, _assign, "
                    "_table, _entries before them: split route)")
