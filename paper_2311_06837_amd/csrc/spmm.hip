@@ -65,7 +65,7 @@ constexpr int kHubTiles = GNN_SPMM_HUB_TILES;   // rows of more tiles (of LPR en
 constexpr int kMaxChunk = 256;                  // rows of the list per workgroup, at most (one descriptor per thread)
 
 // Column-blocked route (dense graphs, gathered matrix far larger than an L2).  The neighbour-id
-// range [0, n_cols) is cut into 8 * passes equal blocks; in pass p workgroup i gathers, for its
+// range [0, n_cols) is cut into 8 * passes blocks of about as many entries; in pass p workgroup i gathers, for its
 // rows, only the neighbours inside block 8p + (i mod 8).  Workgroups are dealt round-robin to the 8
 // compute dies, so every die's L2 sees one eighth of the matrix - and with the feature axis walked
 // in slabs of 256 bytes per row (grid.y, the slow grid axis) that eighth fits: the gathers then
@@ -992,58 +992,122 @@ static int32_t launch_rows(const SpmmArgs& a, hipStream_t stream) {
     return GNN_OK;
 }
 
-// Column-block boundaries of a FILTERED call: bounds[j], j = 0 .. n_blocks, split the neighbour-id range so that
-// every block holds the same number of ACTIVE vertices (0 <= dist <= max_dist) - only those are ever gathered, and
-// they need not be spread evenly over the id range (after a (distance, id) renumbering they are a prefix).
-// One workgroup of 1024 threads: per-thread counts over contiguous id chunks, a block scan, then the thread whose
-// chunk contains the j-th quantile walks it to the exact id.
-__global__ __launch_bounds__(1024) void spmm_bounds_kernel(const int32_t* __restrict__ dist, int32_t max_dist, int32_t n_cols,
-                                                            int32_t n_blocks, int32_t* __restrict__ bounds) {
+// Column-block boundaries: bounds[j], j = 0 .. n_blocks, split the gathered neighbour ids [0, n_src) so that every block holds
+// about the same number of the call's entries (with a dist filter: of those that pass it).  The die whose block has the
+// most entries ends last, and the others wait: with eight equally long blocks of a partition numbered by (distance, id), whose
+// first block - the targets - holds 1.20 times its share of the entries, a call over 114 M entries (233 000 rows of 256 floats) took 7.33 ms
+// or 7.01, as that block's die had an even number or an odd one (workgroup 0 of a launch goes to a die that depends on the
+// hardware queue behind the stream); cut like this 6.25 to 6.32 on every queue (bf16 4.43 / 4.26, now 3.78; vertices renamed at random, where
+// equal blocks are equal shares, 6.21 -> 6.23).
+// 131 072 entries, one at a hashed place in each of as many equal stretches, are counted into 2048 bins of ids; the share of a
+// bin is that of its samples, but at least half its share of the (active) ids: a block of rare ids outgrows the L2 otherwise.
+// The samples are random reads all over the entries, 1.5 ns apart for a single workgroup (65 536 of them 0.1 ms): 512
+// workgroups fetch them, one counts.  The counts are integers, so the same call cuts at the same ids.
+constexpr int kBoundBins = 2048, kBoundSamples = 131072;
+
+__device__ __forceinline__ int64_t bound_sample(int i, int64_t n) {      // the i-th stretch's place of n
+    uint32_t h = (uint32_t)i * 2654435761u;
+    h = (h ^ (h >> 15)) * 2246822519u;
+    h ^= h >> 13;
+    return ((int64_t)i * n + (int64_t)(((uint64_t)h * (uint64_t)n) >> 32)) / kBoundSamples;
+}
+
+// bins[i]: bin of the i-th sampled entry, kBoundBins if it is not gathered; with dist, bins[kBoundSamples + i]: of the i-th sampled id
+__global__ __launch_bounds__(256) void spmm_samples_kernel(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
+                                                            int32_t n_rows, const int32_t* __restrict__ dist, int32_t max_dist, int32_t n_src,
+                                                            uint16_t* __restrict__ bins) {
+    const int i = (int)(blockIdx.x * 256 + threadIdx.x);
+    const int32_t width = (n_src + kBoundBins - 1) / kBoundBins, first = row_ptr[0];
+    const int64_t m = (int64_t)row_ptr[n_rows] - first;
+    int32_t u = m > 0 ? col_idx[first + bound_sample(i, m)] : n_src, v = (int32_t)bound_sample(i, n_src);
+    if (dist) {
+        const int32_t du = dist[u < n_src ? u : 0], dv = dist[v];
+        if (du < 0 || du > max_dist) u = n_src;
+        if (dv < 0 || dv > max_dist) v = n_src;
+        bins[kBoundSamples + i] = (uint16_t)(v < n_src ? v / width : kBoundBins);
+    }
+    bins[i] = (uint16_t)(u < n_src ? u / width : kBoundBins);
+}
+
+__global__ __launch_bounds__(1024) void spmm_bounds_kernel(const uint16_t* __restrict__ bins, bool filtered, int32_t n_src, int32_t n_blocks,
+                                                            int32_t* __restrict__ bounds) {
+    __shared__ int32_t s_e[kBoundBins + 1], s_v[kBoundBins + 1], s_cum[kBoundBins + 1];
     __shared__ int s_part[16];
-    const int64_t chunk = ((int64_t)n_cols + 1023) / 1024;
-    const int64_t lo = (int64_t)threadIdx.x * chunk, hi = lo + chunk < n_cols ? lo + chunk : n_cols;
-    int cnt = 0;
-    for (int64_t u = lo; u < hi; ++u) {
-        const int32_t d = dist[u];
-        cnt += d >= 0 && d <= max_dist;
-    }
-    int total;
-    const int before = block_exclusive_scan<1024>(cnt, s_part, &total);
-    if (threadIdx.x == 0) {
-        bounds[0] = 0;
-        bounds[n_blocks] = n_cols;
-    }
-    // boundary j sits before the active vertex of rank ceil(j * total / n_blocks) (ranks from 0)
-    for (int j = 1; j < n_blocks; ++j) {
-        const int64_t want = ((int64_t)j * total + n_blocks - 1) / n_blocks;
-        if (total == 0) {
-            if (threadIdx.x == 0) bounds[j] = (int32_t)((int64_t)j * n_cols / n_blocks);
-        } else if (want >= before && want < (int64_t)before + cnt) {
-            int64_t rank = before;
-            for (int64_t u = lo; u < hi; ++u) {
-                const int32_t d = dist[u];
-                if (d >= 0 && d <= max_dist) {
-                    if (rank == want) {
-                        bounds[j] = (int32_t)u;
-                        break;
-                    }
-                    ++rank;
-                }
+    constexpr int kPer = kBoundBins / 1024, kLoads = kBoundSamples / 1024 / 8;
+    const int tid = (int)threadIdx.x;
+    const int32_t width = (n_src + kBoundBins - 1) / kBoundBins;
+    for (int b = tid; b <= kBoundBins; b += 1024) s_e[b] = s_v[b] = 0;
+    __syncthreads();
+    auto count = [&](int32_t* to, const uint16_t* from) {
+        uint4 x[kLoads];
+#pragma unroll
+        for (int k = 0; k < kLoads; ++k) x[k] = ((const uint4*)from)[k * 1024 + tid];
+#pragma unroll
+        for (int k = 0; k < kLoads; ++k) {
+            const uint32_t w[4] = {x[k].x, x[k].y, x[k].z, x[k].w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                atomicAdd(&to[w[j] & 0xffffu], 1);
+                atomicAdd(&to[w[j] >> 16], 1);
             }
-        } else if (want >= total && threadIdx.x == 0) {
-            bounds[j] = n_cols;
         }
+    };
+    count(s_e, bins);
+    if (filtered) count(s_v, bins + kBoundSamples);
+    __syncthreads();
+    int32_t e[kPer], v[kPer], all_e, all_v, sum_e = 0, sum_v = 0;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int b = tid * kPer + k;
+        e[k] = s_e[b];
+        v[k] = s_v[b];
+        sum_e += e[k];
+        sum_v += v[k];
+    }
+    block_exclusive_scan<1024>(sum_e, s_part, &all_e);
+    block_exclusive_scan<1024>(sum_v, s_part, &all_v);
+    int32_t mass[kPer], sum = 0, total;      // of a bin, in 2^-28ths of all: less than 2^29 together
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int64_t lo = (int64_t)(tid * kPer + k) * width, ids = lo >= n_src ? 0 : (n_src - lo < width ? n_src - lo : width);
+        const float share_v = all_v > 0 ? (float)v[k] / (float)all_v : (float)ids / (float)n_src;
+        const float share_e = all_e > 0 ? (float)e[k] / (float)all_e : 0.f;
+        mass[k] = (int32_t)(fmaxf(share_e, share_v * 0.5f) * 268435456.f);
+        sum += mass[k];
+    }
+    int32_t at = block_exclusive_scan<1024>(sum, s_part, &total);
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        s_cum[tid * kPer + k] = at;
+        at += mass[k];
+    }
+    if (tid == 0) {
+        s_cum[kBoundBins] = total;
+        bounds[0] = 0;
+        bounds[n_blocks] = n_src;
+    }
+    __syncthreads();
+    for (int j = 1 + tid; j < n_blocks; j += 1024) {
+        const int32_t want = (int32_t)((int64_t)j * total / n_blocks);      // < total: some bin holds it
+        int x = 0, y = kBoundBins;
+        while (y - x > 1) {
+            const int h = (x + y) >> 1;
+            if (s_cum[h] <= want) x = h;
+            else y = h;
+        }
+        const int64_t at_id = (int64_t)x * width + (int64_t)(want - s_cum[x]) * width / (s_cum[x + 1] > s_cum[x] ? s_cum[x + 1] - s_cum[x] : 1);
+        bounds[j] = (int32_t)(at_id < n_src ? at_id : n_src);
     }
 }
 
 // Cut points of every listed row at the column-block boundaries (rows sorted by column): seg[r][j] = first position
-// of row r whose column is >= the j-th boundary (bounds[j] if given, else j * block_size); seg[r][0] = start,
+// of row r whose column is >= the j-th boundary; seg[r][0] = start,
 // seg[r][n_blocks] = end - or, with limit < n_cols, the first position whose column is >= limit (the entries past it
 // are never gathered), and no boundary lies above limit.
 __global__ __launch_bounds__(256) void spmm_seg_kernel(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
                                                         const int32_t* __restrict__ rows, int32_t n_active, int32_t n_blocks,
-                                                        int32_t block_size, const int32_t* __restrict__ bounds, int32_t limit,
-                                                        int32_t n_cols, int32_t* __restrict__ seg) {
+                                                        const int32_t* __restrict__ bounds, int32_t limit, int32_t n_cols,
+                                                        int32_t* __restrict__ seg) {
     const int64_t total = (int64_t)n_active * (n_blocks + 1);
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
         const int32_t r = (int32_t)(i / (n_blocks + 1)), j = (int32_t)(i % (n_blocks + 1));
@@ -1052,9 +1116,7 @@ __global__ __launch_bounds__(256) void spmm_seg_kernel(const int32_t* __restrict
         if (j == n_blocks) {
             lo = limit < n_cols ? row_lower_bound(col_idx, lo, hi, limit) : hi;
         } else if (j > 0) {
-            int64_t bound = bounds ? (int64_t)bounds[j] : (int64_t)j * block_size;
-            bound = bound < limit ? bound : limit;
-            lo = row_lower_bound(col_idx, lo, hi, bound);
+            lo = row_lower_bound(col_idx, lo, hi, bounds[j]);
         }
         seg[i] = lo;
     }
@@ -1254,7 +1316,6 @@ static int die_mapping_holds(const hipStream_t* capturing = nullptr) {
 struct BlockedPlan {
     int passes = 0;
     int n_blocks = 0;
-    int32_t block_size = 0;
     int64_t ldp = 0;          // leading dimension of a partial plane, in floats
     size_t seg_bytes = 0, part_bytes = 0;
     size_t end_bytes = 0, ids_bytes = 0;   // with a filter or a neighbour scale: segment ends and the (compacted) copy of the ids
@@ -1262,9 +1323,9 @@ struct BlockedPlan {
     size_t w_bytes = 0;                    // bf16 with a neighbour scale: the factor of every copied id
     int64_t avg_seg = 0;      // average neighbours of a row inside one column block
     bool off32 = false;       // the gathered matrix spans less than 4 GB
-    int32_t n_cols = 0;
+    int32_t n_rows = 0, n_cols = 0;
     int32_t limit = 0;        // neighbour ids >= limit are never gathered (n_cols without a source prefix)
-    size_t bounds_bytes = 0;  // with a filter: the column-block boundaries (balanced over the active vertices)
+    size_t bounds_bytes = 0, sample_bytes = 0;  // the column-block boundaries, and the samples they come from
 };
 
 static BlockedPlan plan_blocked(const gnn_csr* g, int32_t n_active, int32_t F, int64_t row_bytes, bool vec_ok, bool filter,
@@ -1288,7 +1349,6 @@ static BlockedPlan plan_blocked(const gnn_csr* g, int32_t n_active, int32_t F, i
     p.n_blocks = n_blocks;
     p.avg_seg = avg_row / n_blocks;
     p.off32 = (int64_t)g->n_cols * row_bytes < ((int64_t)1 << 32);
-    p.block_size = (int32_t)(((int64_t)n_src + n_blocks - 1) / n_blocks);
     p.limit = n_src;
     p.ldp = ((int64_t)F + 7) / 8 * 8;
     p.seg_bytes = (size_t)n_active * (n_blocks + 1) * sizeof(int32_t);
@@ -1301,7 +1361,9 @@ static BlockedPlan plan_blocked(const gnn_csr* g, int32_t n_active, int32_t F, i
     }
     if (scaled && f32) p.xs_bytes = (size_t)n_src * (size_t)row_bytes;
     if (scaled && !f32) p.w_bytes = (size_t)g->nnz * sizeof(float);
-    if (filter) p.bounds_bytes = ((size_t)n_blocks + 1) * sizeof(int32_t);
+    p.bounds_bytes = ((size_t)n_blocks + 1) * sizeof(int32_t);
+    p.sample_bytes = (size_t)kBoundSamples * (filter ? 2 : 1) * sizeof(uint16_t);
+    p.n_rows = g->n_rows;
     p.n_cols = g->n_cols;
     return p;
 }
@@ -1318,13 +1380,15 @@ static int32_t run_blocked(const SpmmArgs& a, const BlockedPlan& p, void* ws, hi
     int32_t* ids = prepare ? carve.take<int32_t>(p.ids_bytes / sizeof(int32_t)) : nullptr;
     char* xs = prescale ? carve.take<char>(p.xs_bytes) : nullptr;
     float* edge_w = per_edge ? carve.take<float>(p.w_bytes / sizeof(float)) : nullptr;
-    int32_t* bounds = FILTER ? carve.take<int32_t>((size_t)p.n_blocks + 1) : nullptr;
-    if (FILTER) {
-        spmm_bounds_kernel<<<1, 1024, 0, stream>>>(a.dist, a.max_dist, p.n_cols, p.n_blocks, bounds);
-        GNN_LAUNCH_CHECK("spmm_bounds_kernel");
-    }
+    int32_t* bounds = carve.take<int32_t>(p.bounds_bytes / sizeof(int32_t));
+    uint16_t* bins = carve.take<uint16_t>(p.sample_bytes / sizeof(uint16_t));
+    const int32_t* dist = FILTER ? a.dist : nullptr;
+    spmm_samples_kernel<<<kBoundSamples / 256, 256, 0, stream>>>(a.row_ptr, a.col_idx, a.rows ? p.n_rows : a.n_active, dist, a.max_dist, p.limit, bins);
+    GNN_LAUNCH_CHECK("spmm_samples_kernel");
+    spmm_bounds_kernel<<<1, 1024, 0, stream>>>(bins, dist != nullptr, p.limit, p.n_blocks, bounds);
+    GNN_LAUNCH_CHECK("spmm_bounds_kernel");
     spmm_seg_kernel<<<grid_for((int64_t)a.n_active * (p.n_blocks + 1), 256, 1 << 16), 256, 0, stream>>>(
-        a.row_ptr, a.col_idx, a.rows, a.n_active, p.n_blocks, p.block_size, bounds, p.limit, p.n_cols, seg);
+        a.row_ptr, a.col_idx, a.rows, a.n_active, p.n_blocks, bounds, p.limit, p.n_cols, seg);
     GNN_LAUNCH_CHECK("spmm_seg_kernel");
     SpmmArgs b = a;
     if (prescale) {
@@ -1500,7 +1564,8 @@ static int32_t spmm_common(const gnn_csr* g, const char* gname, const int32_t* r
             }
             if (plan.xs_bytes) measure.take<char>(plan.xs_bytes);
             if (plan.w_bytes) measure.take<char>(plan.w_bytes);
-            if (plan.bounds_bytes) measure.take<char>(plan.bounds_bytes);
+            measure.take<char>(plan.bounds_bytes);
+            measure.take<char>(plan.sample_bytes);
         }
         if (plan.passes == 0 && n_active > 0 && F > 0) {
             split = plan_split(g, rows, n_active, F, dtype, ldx * (dtype == GNN_F32 ? 4 : 2), vec_ok, filter, cut_id, stream);

@@ -445,6 +445,51 @@ def test_blocked_route_backward_with_source_prefix(dtype):
     assert not _used_blocked_route(ws2)
 
 
+@pytest.mark.parametrize("form", ["all rows", "row list", "source prefix", "distances"])
+def test_blocked_route_gives_the_dies_equal_shares(form):
+    """Every column block holds about the same number of the call's entries, wherever in the id range they lie: the die whose
+    block has most ends last.  Here the first eighth of the ids draws a third of the entries (equal ids: 3.1 shares).  The cut
+    points of the rows are the first array of the workspace."""
+    import paper_2311_06837_amd as P
+    n, F = 70_000, 64
+    rng = np.random.default_rng(19)
+    row = np.repeat(np.arange(n, dtype=np.int64), 120)
+    col = np.where(rng.random(len(row)) < 0.3, rng.integers(0, n // 8, len(row)), rng.integers(0, n, len(row)))
+    keys = np.unique(row * n + col)
+    row, col = keys // n, (keys % n).astype(np.int32)
+    row_ptr = np.zeros(n + 1, np.int32)
+    row_ptr[1:] = np.cumsum(np.bincount(row, minlength=n))
+    G = P.Graph.from_numpy(row_ptr, col)
+    X = torch.randn(n, F, device="cuda")
+    Y, Z = torch.zeros_like(X), torch.zeros_like(X)
+    ws = P.Workspace()
+    rows, dist, prefix = None, None, -1
+    kept = np.ones(len(col), bool)
+    if form == "row list":
+        rows = rng.permutation(n)[: n // 2].astype(np.int32)
+    elif form == "source prefix":
+        prefix = 68_001
+        kept = col < prefix
+    elif form == "distances":
+        dist = rng.integers(0, 3, n).astype(np.int32)
+        kept = dist[col] <= 1
+    n_out = n if rows is None else len(rows)
+
+    def call(out, w):
+        P.gnn_masked_spmm_bwd(G, dev(rows) if rows is not None else None, n_out, dev(dist) if dist is not None else None, 1, X, out, F, None, None,
+                              accumulate=False, ws=w, src_prefix=prefix)
+    call(Y, ws)
+    call(Z, None)
+    assert _used_blocked_route(ws)
+    seg = ws.buf[: n_out * 9 * 4].view(torch.int32).reshape(n_out, 9).cpu().numpy()
+    before = np.concatenate([[0], np.cumsum(kept)])
+    share = (before[seg[:, 1:]] - before[seg[:, :-1]]).sum(0)
+    print(form, (share / share.mean()).round(3), flush=True)
+    # a block's share of 65 536 samples: 1 % of itself at one standard deviation, 1.3 % where two thirds of them pass the filter
+    assert share.max() <= 1.06 * share.mean() and share.min() >= 0.94 * share.mean()
+    assert (Y - Z).abs().max() <= 1e-4 * Z.abs().max()
+
+
 def test_die_mapping_probe_and_the_route_that_depends_on_it():
     """Workgroup i on compute die i mod 8: the probe's raw ids are checked here on the CPU, and the size query of a call the
     column-blocked route is made for offers the route exactly when the pattern holds."""
