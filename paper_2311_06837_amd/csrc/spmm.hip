@@ -1492,7 +1492,7 @@ static int32_t run_split(const SpmmArgs& a, const SplitPlan& p, void* ws, hipStr
     else split_entries_kernel<false><<<(unsigned)p.n_chunks, 1024, 0, stream>>>(s);
     GNN_LAUNCH_CHECK("split_entries_kernel");
     const int64_t per_die = (p.n_chunks * p.n_slabs + kDies - 1) / kDies;
-    split_sum_kernel<<<(unsigned)(per_die * kDies), 256, 0, stream>>>(s, per_die);
+    split_sum_kernel<<<(unsigned)(per_die * kDies), 256, 0, stream>>>(s);
     GNN_LAUNCH_CHECK("split_sum_kernel");
     SpmmArgs b = a;
     b.split_on = s.ctrl + 1; b.split_cold = s.cold; b.split_rows = s.rows; b.split_chunks = s.chunks;

@@ -424,16 +424,18 @@ __device__ __forceinline__ void split_add(float4& s, const float4 (&x)[4]) {
     s.w += (x[0].w + x[1].w) + (x[2].w + x[3].w);
 }
 
-// Workgroup b runs on die b mod 8 and takes unit b / 8 of the die's: the units (slab, chunk) are dealt to the dies in eight
-// stretches, slab by slab, so a die meets few slabs, one after the other, at any width.  A lane of eight holds every eighth
+// Workgroup b runs on die b mod 8 and takes unit b / 8 of the die's: the units (slab, chunk) of the chunks in use are dealt to the
+// dies in eight stretches, slab by slab, so a die meets few slabs, one after the other, at any width.  A lane of eight holds every eighth
 // four of its group's stretch and hands it round; a load of 1 KB (eight table rows) costs about seven vector instructions
 // where the vector cache takes as long as sixteen.
-static __global__ __launch_bounds__(256, 6) void split_sum_kernel(SplitArgs a, int64_t per_die) {
+static __global__ __launch_bounds__(256, 6) void split_sum_kernel(SplitArgs a) {
     if (a.ctrl[1] == 0) return;
+    const int64_t used = ((int64_t)a.row_ptr[a.n_active] + kSplitChunk - 1) / kSplitChunk;
+    const int64_t units = used * a.n_slabs, per_die = (units + 7) / 8;
     const int64_t unit = (int64_t)(blockIdx.x & 7) * per_die + (blockIdx.x >> 3);
-    if (unit >= a.n_chunks * a.n_slabs) return;
-    const int slab = (int)(unit / a.n_chunks);
-    const int64_t chunk = unit - (int64_t)slab * a.n_chunks;
+    if ((blockIdx.x >> 3) >= per_die || unit >= units) return;
+    const int slab = (int)(unit / used);
+    const int64_t chunk = unit - (int64_t)slab * used;
     const SplitChunk info = a.chunks[chunk];
     if (info.n_quads == 0) return;
     const int lane = lane_id(), sl = lane & 7, g = (int)(threadIdx.x >> 3);
