@@ -130,7 +130,7 @@ int32_t gnn_norm_scales(int32_t norm, const int32_t *len, const int32_t *row_ptr
  * only ever holds one eighth of a 256-byte-wide feature slab; the per-block partial sums (float)
  * go to ws and are added in block order.
  * Or it may take the split route (float, rows == NULL and no filter but a source prefix, more than 96 columns, on
- * average at least 40 entries a row, a matrix of 48 MB or more): the entries that name one of up to 65 535 frequent
+ * average at least 40 entries a row, a matrix of 48 MB or more, and enough rows and neighbours in the call): the entries that name one of up to 65 535 frequent
  * neighbours are added up from a table in ws, the others as without a workspace.  Whether a graph has such
  * neighbours is decided on the GPU.  A ws too small for this route is no error: the call runs as without one.
  * The size query (ws == NULL) reports 0 when neither route applies; their sums differ by float rounding only.

@@ -1441,12 +1441,24 @@ struct SplitPlan {
 // in fp32 (bf16 parts are floats all the same: 1 M rows of 50, 256 columns 3565 / 3052, 512 columns 6752 / 6687), out of a matrix
 // that the L2s of all dies (32 MB) do not hold
 //   100 k rows of 60: 100 columns 285 / 298, 256 494 / 671.
+// The neighbours are looked through and the table is copied however few rows a call asks for, and a source prefix shortens the rows, so
+// the call's own share counts (1.2 M rows of 51; a call over the first rows, in random order / numbered by distance, where they are the longer ones)
+//   256 columns: 0.4 % of the rows (0.25 GB) 222 / 221, 331 / 378; 1 % 283 / 332, 477 / 579; 10 % 938 / 1177, 2766 / 3740
+//   100 columns: 1 % (0.25 GB) 172 / 163, 301 / 340; 2 % (0.5 GB) 214 / 207, 438 / 536; 5 % 320 / 344, 843 / 1058
+//   300 k rows of 51, 128 columns: 5 % (0.39 GB) 120 / 109, 210 / 245; 10 % 154 / 160, 333 / 405
+// and of the neighbours (a source prefix; it stands for rows of the forward call, so the numbering by distance decides)
+//   256 columns: 5 % 1146 / 1077, 1630 / 1558; 12.5 % (6 entries a row) 1514 / 1435, 3051 / 3567; 25 % (13) 2218 / 2142, 3494 / 4408; 50 % 3660 / 4343, 4479 / 5984
+//   100 columns: 25 % 1195 / 1131, 2061 / 2052; 50 % (26) 2162 / 2245, 2573 / 2857
+//   300 k rows of 51, 256 columns: 12.5 % 356 / 357, 681 / 681; 25 % 543 / 492, 802 / 860; with 10 % of the rows and 50 % 178 / 156, 372 / 517.
 static SplitPlan plan_split(const gnn_csr* g, const int32_t* rows, int32_t n_active, int32_t F, int32_t dtype, int64_t row_bytes, bool vec_ok,
                             bool filter, int32_t cut_id, hipStream_t stream) {
     SplitPlan p;
     if (dtype != GNN_F32 || rows != nullptr || !vec_ok || filter || n_active < 4096 || F <= 3 * kSplitCols) return p;
     const int32_t n_src = cut_id >= 0 ? cut_id : g->n_cols;
     if (g->nnz / g->n_rows < 40 || n_src * row_bytes < (48ll << 20) || g->nnz * row_bytes < (1ll << 30)) return p;
+    const double row_share = (double)n_active / g->n_rows, src_share = (double)n_src / g->n_cols;
+    if ((double)g->nnz / g->n_rows * src_share < (F > 4 * kSplitCols ? 6 : 20)) return p;
+    if ((double)g->nnz * row_bytes * row_share * src_share * src_share < 4e8) return p;
     p.n_nbr = n_src < g->n_rows ? n_src : g->n_rows;
     p.n_chunks = (g->nnz + kSplitChunk - 1) / kSplitChunk;
     p.n_slabs = (F + kSplitCols - 1) / kSplitCols;

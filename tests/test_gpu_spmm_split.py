@@ -163,3 +163,21 @@ def test_dies_share_the_chunks_in_use():
     assert ws.buf[CTRL: CTRL + 8].view(torch.int32).tolist()[1] == 1
     print(f"split route {split:.0f} us, row kernel {plain:.0f} us", flush=True)
     assert split < 1.08 * plain      # between the two
+
+
+@pytest.mark.parametrize("n,deg,F,rows,prefix,takes", [
+    (1_200_000, 51, 256, 1.0, 1.0, True), (1_200_000, 51, 256, 0.05, 1.0, True), (1_200_000, 51, 256, 0.004, 1.0, False),
+    (1_200_000, 51, 100, 0.05, 1.0, True), (1_200_000, 51, 100, 0.01, 1.0, False), (300_000, 51, 128, 0.05, 1.0, False),
+    (1_200_000, 51, 256, 1.0, 0.5, True), (1_200_000, 51, 256, 1.0, 0.125, True), (1_200_000, 51, 256, 1.0, 0.1, False), (1_200_000, 51, 100, 1.0, 0.25, False),
+    (300_000, 51, 256, 0.1, 0.5, False), (300_000, 51, 256, 1.0, 0.5, True), (1_200_000, 39, 256, 1.0, 1.0, False)])
+def test_the_route_is_asked_for_by_the_work_of_the_call(n, deg, F, rows, prefix, takes):
+    """Few rows, or a source prefix that leaves little of them, are not worth the route's look at all neighbours.  A size query reads
+    no array, so none is made."""
+    import paper_2311_06837_amd as P
+    C, some = P.binding.C, torch.zeros(64, device="cuda")
+    g = P.binding.gnn_csr(n, n, n * deg, some.data_ptr(), some.data_ptr(), P.binding.GNN_CSR_SORTED_COLUMNS, None)
+    need = C.c_size_t(0)
+    P.binding._check(P.binding.lib().gnn_masked_spmm_bwd(
+        C.byref(g), None, int(n * rows), None, 0, -1 if prefix == 1.0 else int(n * prefix), some.data_ptr(), F, some.data_ptr(), F, F, 0, None, None, 0,
+        None, 0, None, C.byref(need), P.binding._stream()))
+    assert (need.value > 0) == takes
