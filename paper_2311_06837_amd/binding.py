@@ -163,11 +163,31 @@ class Workspace:
 
     def __init__(self):
         self.buf = None
+        self.calls_without = 0      # calls left that do not ask for more for a route that can do without
 
     def get(self, nbytes: int) -> torch.Tensor:
         if self.buf is None or self.buf.numel() < nbytes:
+            self.buf = None         # given back first: the card need not hold both
             self.buf = torch.empty(max(nbytes, 256), dtype=torch.uint8, device="cuda")
         return self.buf
+
+    def offer(self, nbytes: int):
+        """Grow to nbytes if that leaves other allocations room: at most half of what the card has left, and never while the
+        stream captures.  If not, the buffer stays as it is and is offered more again 256 calls later."""
+        if self.buf is None or self.buf.numel() < nbytes:
+            if not torch.cuda.is_current_stream_capturing() and 2 * nbytes <= _memory_left():
+                try:
+                    self.get(nbytes)
+                    return
+                except torch.cuda.OutOfMemoryError:     # in pieces too small
+                    pass
+            self.calls_without = 256
+            self.get(256)
+
+
+def _memory_left() -> int:
+    """Bytes that torch's allocator could still hand out: free on the card, or held by it unused."""
+    return torch.cuda.mem_get_info()[0] + torch.cuda.memory_reserved() - torch.cuda.memory_allocated()
 
 
 _default_ws = Workspace()
@@ -274,19 +294,18 @@ def gnn_norm_scales(norm: int, n: int, length: torch.Tensor | None = None, row_p
 
 def _with_optional_ws(fn, args_before, args_after, ws: Workspace | None, gathered: int):
     """ws None: the call runs without a workspace (ws_bytes = NULL); else the usual size query + call.  gathered: bytes the call
-    gathers; from 1 GB on a route may use a workspace that it does not insist on, so the size is asked for first, and a card
-    without that much left runs the call as without a workspace."""
-    if ws is not None and gathered >= 1 << 30:
-        need = C.c_size_t(0)
-        _check(fn(*args_before, None, C.byref(need), *args_after))
-        try:
-            ws.get(need.value)
-        except torch.cuda.OutOfMemoryError:
-            ws = None
+    gathers; from 1 GB on it may use a workspace without insisting on it (a smaller one is no error then), so the size is asked
+    for first and the workspace grows if there is room."""
     if ws is None:
-        _check(fn(*args_before, None, None, *args_after))
-    else:
-        _with_ws(fn, args_before, args_after, ws)
+        return _check(fn(*args_before, None, None, *args_after))
+    if gathered >= 1 << 30:
+        if ws.calls_without > 0:
+            ws.calls_without -= 1
+        else:
+            need = C.c_size_t(0)
+            _check(fn(*args_before, None, C.byref(need), *args_after))
+            ws.offer(need.value)
+    _with_ws(fn, args_before, args_after, ws)
 
 
 def gnn_masked_spmm_fwd(g: Graph, rows, n_active: int, X: torch.Tensor, Y: torch.Tensor, F: int,

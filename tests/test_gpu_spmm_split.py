@@ -181,3 +181,86 @@ def test_the_route_is_asked_for_by_the_work_of_the_call(n, deg, F, rows, prefix,
         C.byref(g), None, int(n * rows), None, 0, -1 if prefix == 1.0 else int(n * prefix), some.data_ptr(), F, some.data_ptr(), F, F, 0, None, None, 0,
         None, 0, None, C.byref(need), P.binding._stream()))
     assert (need.value > 0) == takes
+
+
+def _full_card(monkeypatch, limit):
+    """An allocator that has nothing of more than `limit` bytes; -> the sizes it was asked for."""
+    import paper_2311_06837_amd.binding as B
+    asked, empty = [], torch.empty
+
+    def few(*size, **kw):
+        if kw.get("dtype") == torch.uint8:
+            asked.append(size[0])
+            if size[0] > limit:
+                raise torch.cuda.OutOfMemoryError("none left")
+        return empty(*size, **kw)
+    monkeypatch.setattr(B.torch, "empty", few)
+    return asked
+
+
+@pytest.mark.parametrize("why", ["no room", "in pieces", "capture"])
+def test_without_memory_for_the_route(why, monkeypatch):
+    """The route's workspace is one the call can do without: it is not taken from a card where half of what is left would not hold it,
+    not while a stream captures, and a card that has none is not asked at every call."""
+    import paper_2311_06837_amd as P
+    import paper_2311_06837_amd.binding as B
+    n, F = 60_000, 256
+    row_ptr, col = _graph(n, 46, 1)
+    G = P.Graph(torch.from_numpy(row_ptr).cuda(), torch.from_numpy(col).cuda(), sorted_columns=True)
+    X = torch.randn(n, F, device="cuda")
+    Y, Z = torch.zeros_like(X), torch.zeros_like(X)
+    need = B.spmm_workspace_bytes(G, n, X, Y, F)
+    assert need > 1 << 20
+    P.gnn_masked_spmm_fwd(G, None, n, X, Z, F)
+    ws = P.Workspace()
+    call = lambda: P.gnn_masked_spmm_fwd(G, None, n, X, Y, F, ws=ws)
+    if why == "capture":
+        graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        with torch.cuda.graph(graph, stream=side):
+            call()
+        assert ws.buf.numel() == 256
+        for _ in range(3):
+            Y.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(Y, Z)
+        return
+    asked = _full_card(monkeypatch, 1 << 20 if why == "in pieces" else 1 << 40)
+    if why == "no room":
+        monkeypatch.setattr(B, "_memory_left", lambda: 2 * need - 1)
+    for _ in range(100):
+        call()
+    assert asked == ([256] if why == "no room" else [need, 256])
+    assert torch.equal(Y, Z)
+    monkeypatch.undo()
+    for _ in range(200):        # memory is there again
+        call()
+    assert ws.buf.numel() >= need
+
+
+def test_a_route_that_insists_on_its_workspace_still_does(monkeypatch):
+    """The column-blocked route raises where there is no memory for it."""
+    import paper_2311_06837_amd as P
+    n, F = 70_000, 256
+    rng = np.random.default_rng(2)
+    keys = np.unique(np.repeat(np.arange(n, dtype=np.int64), 80) * n + rng.integers(0, n, 80 * n))
+    row_ptr = np.zeros(n + 1, np.int32)
+    row_ptr[1:] = np.cumsum(np.bincount(keys // n, minlength=n))
+    G = P.Graph.from_numpy(row_ptr, (keys % n).astype(np.int32))
+    X = torch.randn(n, F, device="cuda")
+    assert P.binding.spmm_workspace_bytes(G, n, X, X.clone(), F) >= 8 * n * F * 4
+    ws, Y = P.Workspace(), torch.zeros_like(X)
+    _full_card(monkeypatch, 1 << 20)
+    with pytest.raises(torch.cuda.OutOfMemoryError):
+        P.gnn_masked_spmm_fwd(G, None, n, X, Y, F, ws=ws)
+
+
+def test_a_workspace_gives_its_buffer_back_before_it_grows():
+    import paper_2311_06837_amd as P
+    ws = P.Workspace()
+    ws.get(64 << 20)
+    torch.cuda.empty_cache()
+    torch.cuda.reset_peak_memory_stats()
+    before = torch.cuda.memory_allocated()
+    ws.get(96 << 20)
+    assert torch.cuda.max_memory_allocated() <= before + (40 << 20)
