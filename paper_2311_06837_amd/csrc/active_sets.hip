@@ -699,7 +699,8 @@ constexpr int64_t kAsSmallEntries = (int64_t)1 << 17;
 __global__ __launch_bounds__(1024) void as_small_kernel(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int32_t n,
                                                         const int32_t* __restrict__ targets, int32_t n_targets, int32_t L,
                                                         int32_t* __restrict__ dist, int32_t* ring_ids, int64_t* __restrict__ hop_offsets) {
-    constexpr int kRows = 4096, kPer = kRows / 1024, kWords = (int)(kAsSmallEntries / 32), kU = 8;
+    constexpr int kRows = 4096, kPer = kRows / 1024, kWords = (int)(kAsSmallEntries / 32), kU = 8, kRowBit = 18, kRow = 1 << kRowBit;
+    static_assert(kAsSmallEntries < kRow && (int64_t)kRows << kRowBit <= INT32_MAX, "edges and rows share an int");
     __shared__ uint32_t s_seen[1024], s_new[1024];
     __shared__ int32_t s_at[1024];
     __shared__ int32_t s_first[kRows];        // of the rows with entries: position of the first, less the edges before it
@@ -753,20 +754,20 @@ __global__ __launch_bounds__(1024) void as_small_kernel(const int32_t* __restric
 #pragma unroll
             for (int k = 0; k < kPer; ++k) {
                 if (c0 + tid * kPer + k >= total) len[k] = 0;
-                sum += len[k] | (len[k] > 0 ? 1 << 19 : 0);      // edges (2^17 at most) and rows with some, in one sum
+                sum += len[k] | (len[k] > 0 ? kRow : 0);      // edges (2^17 at most) and rows with some (4096: 2^30), in one sum
             }
             int all;
             int at = block_exclusive_scan<1024>(sum, s_part, &all);
-            const int edges = all & ((1 << 19) - 1), words = (edges + 31) / 32;
+            const int edges = all & (kRow - 1), words = (edges + 31) / 32;
             for (int w = tid; w < words; w += 1024) s_begin[w] = 0u;
             __syncthreads();
 #pragma unroll
             for (int k = 0; k < kPer; ++k) {
                 if (len[k] == 0) continue;
-                const int off = at & ((1 << 19) - 1);
-                s_first[at >> 19] = s[k] - off;
+                const int off = at & (kRow - 1);
+                s_first[at >> kRowBit] = s[k] - off;
                 atomicOr(&s_begin[off >> 5], 1u << (off & 31));
-                at += len[k] | 1 << 19;
+                at += len[k] | kRow;
             }
             __syncthreads();
             const int each = (words + 1023) / 1024;              // words a thread, one after the other

@@ -190,3 +190,19 @@ def test_sets_of_small_graphs_around_the_one_launch_limit(n, nnz):
             dist, ring, off, hop = P.gnn_build_active_sets(G, dev(targets), L)
             assert list(hop) == list(ooff) and np.array_equal(off.cpu().numpy(), ooff)
             assert np.array_equal(dist.cpu().numpy(), od) and np.array_equal(ring.cpu().numpy()[: ooff[-1]], oring)
+
+
+@pytest.mark.parametrize("deg", [1, 4])
+def test_sets_of_a_small_graph_whose_every_vertex_has_entries(deg):
+    """Whole steps of 4096 rows with entries, at both limits of the one-launch form: the two counts that share an integer."""
+    import paper_2311_06837_amd as P
+    n = 32_768
+    cols = ((np.arange(n)[:, None] + 1 + np.arange(deg) * 5000) % n).astype(np.int32)
+    cols.sort(axis=1)
+    row_ptr = (np.arange(n + 1) * deg).astype(np.int32)
+    G = P.Graph(dev(row_ptr), dev(cols.reshape(-1)))
+    for targets in (np.arange(n, dtype=np.int32), np.arange(0, n, 3, dtype=np.int32), np.arange(4096, dtype=np.int32)):
+        od, oring, ooff = oracle.active_sets(row_ptr, cols.reshape(-1), targets, 3)
+        dist, ring, off, hop = P.gnn_build_active_sets(G, dev(targets), 3)
+        assert list(hop) == list(ooff) and np.array_equal(dist.cpu().numpy(), od)
+        assert np.array_equal(ring.cpu().numpy()[: ooff[-1]], oring)
