@@ -19,10 +19,14 @@ def row_stride(width: int, dtype) -> int:
     return (width + mult - 1) // mult * mult
 
 
-# A second stream costs a small step more than it hides: two waits of 15 us and the change of streams, on the host, which is
-# what bounds such a step (10 000 vertices, 64-64-8, fp32: 250 us with the second stream, 205 without).  Weight gradients of all layers
-# of fewer operations than this take less than that on the GPU.
-SIDE_STREAM_FLOPS = {torch.float32: 5e9, torch.bfloat16: 2.5e10}
+# Weight gradients of all layers of fewer operations than this stay on the step's stream: a second stream costs a small step two
+# waits and the change of streams on the host, which is what bounds such a step.  us of a step with two streams / with one, by
+# the operations (Chung-Lu, degree 10 unless given):
+#   fp32  1e8 GraphSAGE 64-64-8 199 / 184; 4e8 GraphSAGE 64-128-16 262 / 228; 7e8 GCN 128-128-16 289 / 271, three layers 128-128-128-41 347 / 387;
+#         1.5e9 GCN 128-256-32 291 / 304; GraphSAGE 128-128-128-41 375 / 393; 3e9 GCN 602-256-41, degree 50, 571 / 650; 4e10 2686 / 2767
+#   bf16  1e8 196 / 172; 4e8 216 / 197; 7e8 244 / 236, three layers 286 / 292; 1.4e9 238 / 237; 300 / 309; 3e9 457 / 509; 4e10 1339 / 1376
+# (A stream that shares the hardware queue of the step's stream - the fourth one that a process makes does - hides nothing and costs 2 to 9 %.)
+SIDE_STREAM_FLOPS = {torch.float32: 1.4e9, torch.bfloat16: 1.4e9}
 
 
 class MaskedGNN:

@@ -196,9 +196,20 @@ def test_add_rows_masked(dtype, F, ld):
         P.gnn_add_rows_masked(None, 10, padded(X, ld, dtype), 11, padded(Y, ld, dtype), F, padded(H, ld, dtype))
 
 
+@pytest.fixture
+def two_streams(monkeypatch):
+    """Second stream taken however little the products are (small models leave it out by themselves).  -> for every backward pass
+    whether it had one."""
+    import paper_2311_06837_amd.model as M
+    seen, join = [], M.MaskedGNN._join_side
+    monkeypatch.setattr(M, "SIDE_STREAM_FLOPS", {d: 0.0 for d in M.SIDE_STREAM_FLOPS})
+    monkeypatch.setattr(M.MaskedGNN, "_join_side", lambda self: seen.append(self.side is not None) or join(self))
+    return seen
+
+
 @pytest.mark.parametrize("kind,dims", [("sage", [96, 64, 64, 7]), ("gcn", [64, 48, 24, 6]), ("sage", [16, 32, 32, 8])])
-def test_side_stream_changes_nothing(kind, dims):
-    """The weight-gradient products run on a second stream by default; with everything on one stream the step gives the
+def test_side_stream_changes_nothing(kind, dims, two_streams):
+    """The weight-gradient products run on a second stream; with everything on one stream the step gives the
     same bits (same kernels, same inputs - only the order in time differs)."""
     import paper_2311_06837_amd as P
     g = gg.chung_lu(6000, 9.0, 2.2, 71)
@@ -219,21 +230,74 @@ def test_side_stream_changes_nothing(kind, dims):
             loss = m.step(y)
         torch.cuda.synchronize()
         out.append((loss.item(), [{k: v.clone() for k, v in gr.items()} for gr in m.grads]))
+    assert two_streams == [True, True, False, False]
     assert out[0][0] == out[1][0]
     for ga, gb in zip(out[0][1], out[1][1]):
         for k in ga:
             assert torch.equal(ga[k], gb[k]), k
 
 
-@pytest.mark.parametrize("kind,dims", [("sage", [96, 64, 64, 7]), ("gcn", [64, 48, 24, 6]), ("sage", [16, 32, 32, 8])])
-def test_side_stream_at_any_size(kind, dims, monkeypatch):
-    """The same with the second stream taken however little the products are (small models leave it out by themselves)."""
-    import paper_2311_06837_amd.model as M
-    seen, join = [], M.MaskedGNN._join_side
-    monkeypatch.setattr(M, "SIDE_STREAM_FLOPS", {d: 0.0 for d in M.SIDE_STREAM_FLOPS})
-    monkeypatch.setattr(M.MaskedGNN, "_join_side", lambda self: seen.append(self.side is not None) or join(self))
-    test_side_stream_changes_nothing(kind, dims)
-    assert seen == [True, True, False, False]
+@pytest.mark.parametrize("n,dims,two", [(2000, [64, 64, 8], False), (9000, [64, 128, 128, 16], False), (9000, [64, 256, 256, 16], True)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_side_stream_by_the_work_of_the_products(n, dims, two, dtype):
+    """Below 1.4e9 operations in the weight gradients everything stays on one stream."""
+    import paper_2311_06837_amd as P
+    row_ptr = torch.arange(n + 1, dtype=torch.int32, device="cuda")
+    G = P.Graph(row_ptr, row_ptr[:-1].contiguous())
+    params = [{k: dev(v) for k, v in p.items()} for p in gg.layer_weights(dims, True, 0)]
+    make = lambda **kw: P.MaskedGNN(G, G, row_ptr[:100].contiguous(), "sage", params, dtype=dtype, **kw)
+    assert (make().side is not None) == two and make(side_stream=False).side is None
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_gcn_that_keeps_its_width(dtype, two_streams):
+    """Weight gradients on the second stream, the input gradient of the same layer on the step's."""
+    g = gg.add_self_loops(gg.chung_lu(5000, 9.0, 2.2, 64))
+    T = np.sort(np.random.default_rng(64).choice(5000, 300, replace=False)).astype(np.int64)
+    part = gg.halo_partition(g, T, 3)
+    m, _ = _parity("gcn of one width", part, "gcn", [64, 64, 64, 8], dtype, 64, False)
+    assert m.side is not None and two_streams and all(two_streams)
+
+
+def test_two_streams_through_an_extracted_partition(two_streams):
+    """(distance, id) numbering: row prefixes instead of row lists, source prefixes instead of distances; same bits as one stream."""
+    import paper_2311_06837_amd as P
+    g = gg.chung_lu(6000, 9.0, 2.2, 72)
+    G = P.Graph.from_numpy(g.row_ptr, g.col_idx)
+    T = dev(np.sort(np.random.default_rng(72).choice(6000, 400, replace=False)).astype(np.int32))
+    dist, ring, _, hop = P.gnn_build_active_sets(G, T, 3, gt=G)
+    local, _ = P.gnn_extract_partition(G, ring, int(hop[-1]), dist, 3)
+    dims = [64, 64, 64, 8]
+    params = gg.layer_weights(dims, True, 72)
+    H0 = padded(gg.features(local.n_rows, 64, 72), 64, torch.float32)
+    y = dev(gg.labels(400, 8, 72))
+    out = []
+    for side in (True, False):
+        m = P.MaskedGNN(local, local, torch.arange(400, dtype=torch.int32, device="cuda"), "sage",
+                        [{k: dev(v) for k, v in p.items()} for p in params], prefix_numbered=True, side_stream=side)
+        m.set_input(H0)
+        for _ in range(2):
+            m.step(y)
+        torch.cuda.synchronize()
+        out.append([v.clone() for gr in m.grads for v in gr.values()])
+    assert two_streams == [True, True, False, False]
+    assert all(torch.equal(a, b) for a, b in zip(*out))
+
+
+F32, BF16 = torch.float32, torch.bfloat16
+
+
+@pytest.mark.parametrize("what,dtype", [("chain rule's order", F32), ("chain rule's order", BF16), ("the same, weights first", F32), ("the same, weights first", BF16),
+                                        ("fused", F32), ("fused", BF16), ("masks", F32), ("masks", BF16), ("cfg2", F32), ("cfg3", BF16), ("cfg4", BF16)])
+def test_parity_on_two_streams(what, dtype, two_streams):
+    """Tests of this directory whose models are too small for a second stream, with one."""
+    import test_gpu_layer_sampling as ls
+    {"chain rule's order": lambda: test_backward_in_the_chain_rules_order(dtype, False),
+     "the same, weights first": lambda: test_backward_in_the_chain_rules_order(dtype, True),
+     "fused": lambda: test_fused_forward_layers(dtype),
+     "masks": lambda: ls.test_training_step_with_per_layer_masks("sage", dtype, ("fanout", 4, 11), [32, 64, 48, 8]),
+     "cfg2": lambda: test_cfg2_scaled(False), "cfg3": test_cfg3_scaled_deep_bf16, "cfg4": test_cfg4_scaled_sampled_bf16}[what]()
+    assert two_streams and all(two_streams)
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
