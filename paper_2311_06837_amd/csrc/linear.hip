@@ -495,8 +495,9 @@ __device__ __forceinline__ u32x4 mask_chunk(u32x4 r, int n_valid) {
 // KTAIL: the reduction length is not a multiple of the slice.  The last slice of every source is then cut: chunks
 // that start at or beyond K are read from the start of their row instead (always addressable) and every chunk is
 // masked to its valid elements when it is moved to LDS, so neither padding nor a neighbouring row reaches the MFMAs.
-template <int DT, int NTW, bool KTAIL>
-__global__ __launch_bounds__(256, NTW == 4 ? 2 : NTW == 2 ? 3 : 4) void gemm_nt_wide_kernel(GemmNT a) {
+// MINB: workgroups that share a CU; the registers of a lane follow from it.
+template <int DT, int NTW, bool KTAIL, int MINB = NTW == 4 ? 2 : NTW == 2 ? 3 : 4>
+__global__ __launch_bounds__(256, MINB) void gemm_nt_wide_kernel(GemmNT a) {
     constexpr int BM = 128, BN = 64 * NTW, MT = 2, NT = NTW, WTN = 32 * NTW;
     constexpr int ES = DTy<DT>::ES, EPV = DTy<DT>::EPV;
     constexpr int EPS = 64 / ES;                  // reduction elements per slice
@@ -1041,15 +1042,25 @@ static int32_t launch_gemm_nt(const GemmNT& a, hipStream_t stream) {
         const int64_t p256 = ((int64_t)a.N + 255) / 256 * 256, p128 = ((int64_t)a.N + 127) / 128 * 128, p64 = ((int64_t)a.N + 63) / 64 * 64;
         int ntw = (p256 <= p128 && p256 <= p64) ? 4 : (p128 <= p64 ? 2 : 1);
         if (DT == GNN_F32) {
-            // fp32 products are bound by the matrix instructions, so what counts is how many tiles the busiest CU gets: n tiles of
-            // 256, 128, 64 columns take about 5 + 74 n, 15 + 35 n and 13 + 19.2 n (us at 512 reduction elements; two, three and
-            // four workgroups of a CU run side by side).  256 columns from 512 (us, tile of 256 / 128 / 64): 1000 to 7000 rows 84 /
-            // 49 / 33, 20 000 87 / 81 / 72, 32 000 87 / 83 / 91, 45 000 146 / 124 / 125, 60 000 148 / 185 / 161, 75 000 220 / 190 /
-            // 195, 600 001 1357 / 1284 / 1411.
-            auto cost = [&](int width, double once, double each) {
-                return once + each * (double)(((tiles_m + 7) / 8 * (((int64_t)a.N + width - 1) / width) + 31) / 32);     // 32 CUs a die
+            // fp32 products are bound by the matrix instructions, so what counts is how many tiles the busiest CU gets.  Four, three
+            // and two workgroups of 64, 128 and 256 columns run side by side on it, and a tile that runs alone leaves the matrix units
+            // idle while it loads: tiles of 128 and 256 columns come in rounds of three and two, a begun round costs most of a whole one,
+            // until there are so many (12) that the CUs no longer keep step.
+            // us of 1, 2, .. 8 tiles, at 512 reduction elements: 64 columns 29 46 65 84 103 121 149 157, 128 columns 46 76 118 181 221 229
+            // 287 300, 256 columns 82 142 276 287 412 421 548 559; the steps shrink alike with the reduction (256 elements: 19 28 39 49 64 75
+            // 85 88, 29 45 67 107 122 124 163 178, 50 82 151 159 231 238 306 314).  From 600 on a round's beginning no longer
+            // shows (1204: 65 109 146 190, 103 180 268 356, 183 349 517 679).  256 columns from 512 (us, tile of 256 / 128 / 64): 1000 to 7000
+            // rows 84 / 49 / 33, 20 000 87 / 81 / 72, 60 000 148 / 185 / 161, 75 000 279 / 221 / 194, 120 000 283 / 292 / 290,
+            // 600 001 1357 / 1284 / 1411; 128 columns 120 000 rows - / 184 / 162.
+            const double tail = a.K % 16 != 0 ? 1.06 : 1.0;      // of a slice, which 256 columns feel: 100 + 100 elements 153 / 147 / 144 at 120 000 rows
+            auto cost = [&](int width) {
+                const int64_t n = ((tiles_m + 7) / 8 * (((int64_t)a.N + width - 1) / width) + 31) / 32;     // 32 CUs a die
+                if ((int64_t)a.K * a.n_src >= 600) return width == 64 ? 20 + 44.5 * n : width == 128 ? 18 + 83.5 * n : 20 + 167.0 * n;
+                if (width == 64) return 10 + 18.6 * n;
+                if (width == 128) return n < 3 ? 16 + 30.0 * n : n >= 12 ? 10 + 34.0 * n : 10 + 103.0 * (n / 3) + (n % 3 == 0 ? 0 : n % 3 == 1 ? 57 : 85);
+                return tail * (n == 1 ? 82 : n >= 12 ? 5 + 69.0 * n : 5 + 139.0 * ((n + 1) / 2));
             };
-            const double c256 = cost(256, 5, 74), c128 = cost(128, 15, 35), c64 = cost(64, 13, 19.2);
+            const double c256 = cost(256), c128 = cost(128), c64 = cost(64);
             ntw = c64 < c128 && c64 < c256 ? 1 : (c128 < c256 ? 2 : 4);
         } else if (ntw == 4 && tiles_m * (p256 / 256) <= 384) {
             // too few tiles of 256 columns to give every CU two (256 columns from 512, us, 256 / 128 wide: 1000 rows 22.6 / 17.3,
@@ -1057,8 +1068,12 @@ static int32_t launch_gemm_nt(const GemmNT& a, hipStream_t stream) {
             ntw = 2;
         }
         // a reduction of one or two slices (an input gradient from 32 or 41 class scores) is all prologue and epilogue:
-        // narrow tiles keep more workgroups on a CU to hide those latencies, and re-reading the short rows costs little
-        if ((int64_t)a.K * a.n_src * DTy<DT>::ES <= 128) ntw = 1;
+        // narrow tiles keep more workgroups on a CU to hide those latencies, and re-reading the short rows costs little - but where
+        // the output, far larger, no longer fits the last-level cache it has to leave in whole lines (bf16, narrow / wide, us:
+        // 64 -> 200 columns 300 000 rows 45.9 / 51.5, 600 001 143 / 114; 64 -> 256 600 001 132 / 98.6; 64 -> 128 300 000 29.1 / 31.1, 600 001 47.7 /
+        // 43.0; 64 -> 100, which half fills a tile of 128, 600 001 62.7 / 70.6, 1 200 000 144 / 157)
+        const bool whole_lines = DT == GNN_BF16 && (int64_t)a.M * a.N * DTy<DT>::ES > (128ll << 20) && (ntw == 4 || a.N % 128 == 0);
+        if ((int64_t)a.K * a.n_src * DTy<DT>::ES <= 128 && !whole_lines) ntw = 1;
         // whole cache lines per step where the shapes allow it (see gemm_nt_line_kernel)
 #ifndef GNN_NT_LINE
 #define GNN_NT_LINE 1
@@ -1085,6 +1100,9 @@ static int32_t launch_gemm_nt(const GemmNT& a, hipStream_t stream) {
     }
         if (ntw == 4) GNN_WIDE(4)
         else if (ntw == 2) GNN_WIDE(2)
+        // two tiles a CU at most have no use for room for four, but for the registers (fp32, 602 -> 48 columns, 33 000 to 60 000 rows:
+        // 54.3 to 55.9 us with room for four, 52.5 to 53.6 for two; without a tail both are equal)
+        else if (DT == GNN_F32 && ktail && (int64_t)(grid + 7) / 8 <= 64) gemm_nt_wide_kernel<DT, 1, true, 2><<<grid, 256, 0, stream>>>(a);
         else GNN_WIDE(1)
 #undef GNN_WIDE
         GNN_LAUNCH_CHECK("gemm_nt_wide_kernel");

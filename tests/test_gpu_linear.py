@@ -358,10 +358,11 @@ def test_f32_products_with_infinities_nan_and_overflow():
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
-@pytest.mark.parametrize("M,K,N", [(1025, 72, 256), (12_167, 64, 300), (45_001, 40, 256), (60_001, 64, 256), (49_153, 64, 512)])
+@pytest.mark.parametrize("M,K,N", [(1025, 72, 256), (12_167, 64, 300), (45_001, 40, 256), (60_001, 64, 256), (49_153, 64, 512),
+                                   (33_001, 100, 48), (65_537, 100, 64), (120_001, 100, 128), (120_001, 320, 256), (530_001, 32, 128), (520_001, 32, 130)])
 def test_tile_widths_of_the_forward_product(dtype, M, K, N):
-    """Row counts on either side of where the tile width changes (64, 128, 256 columns), last band of rows ragged, bands not a
-    multiple of the eight dies.  Every partial sum is an exact small integer, so any tiling gives the same bits."""
+    """Row counts on either side of where the tile width changes (64, 128, 256 columns) and of two tiles a CU, last band of rows ragged,
+    bands not a multiple of the eight dies, short reductions into an output above and below 128 MB.  Every partial sum is an exact small integer, so any tiling gives the same bits."""
     import paper_2311_06837_amd as P
     gen = torch.Generator(device="cuda").manual_seed(M)
     a, x = (torch.randint(-2, 3, (M, K), generator=gen, device="cuda").to(dtype) for _ in range(2))
