@@ -227,7 +227,10 @@ def test_without_memory_for_the_route(why, monkeypatch):
         return
     asked = _full_card(monkeypatch, 1 << 20 if why == "in pieces" else 1 << 40)
     if why == "no room":
-        monkeypatch.setattr(B, "_memory_left", lambda: 2 * need - 1)
+        left = 2 * need - 1
+        monkeypatch.setattr(torch.cuda, "mem_get_info", lambda: (left // 2, 1 << 40))
+        monkeypatch.setattr(torch.cuda, "memory_reserved", lambda: left - left // 2 + (1 << 20))
+        monkeypatch.setattr(torch.cuda, "memory_allocated", lambda: 1 << 20)
     for _ in range(100):
         call()
     assert asked == ([256] if why == "no room" else [need, 256])
