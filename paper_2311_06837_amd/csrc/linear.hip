@@ -1734,26 +1734,39 @@ extern "C" int32_t gnn_linear_bwd(const int32_t* rows, int32_t n_active, const v
     const int n_src = X_self ? 2 : 1;
     const int64_t ldz = (int64_t)align_up((size_t)N, 16 / es);
     const int32_t n_part = n_active > 0 ? (n_active + kDzRows - 1) / kDzRows : 1;
-    // Row splits of the weight-gradient reduction: as many as give every CU the three workgroups it can hold at once
-    // and no more (256 CUs: 768 workgroups; the splits are equally long, so a second, partly filled round of workgroups
-    // would cost a whole round: 1024 workgroups took 2 rounds where 768 take 1.33 of the old round's length), at most 256
-    // splits and 128 MB of partial tiles
+    // Row splits of the weight-gradient reduction: at most as many as give every CU the three workgroups it can hold at once (two of
+    // the 256-column tile) and no more (256 CUs: 768 workgroups; the splits are equally long, so a second, partly filled round of
+    // workgroups would cost a whole round: 1024 workgroups took 2 rounds where 768 take 1.33 of the old round's length), 256
+    // splits and 128 MB of partial tiles.  Fewer where that is cheaper: a split's rows are one after the other (0.078 us a row in fp32, 0.018 in bf16,
+    // 0.04 with the wide tile; 1.4 and 1.9 times that where two and three workgroups share a CU in fp32), and its partial tile
+    // is written and read again (1 to 1.4 us a million elements, 0.02 a split).  us of a call at 64 / 128 / 256 rows a split and at the rows taken: fp32, 256 x 256 from
+    // two sources, 1000 rows 18.2 / 20.8 / 29.4, 18.2; 6000 37.5 / 36.2 / 36.6, 32.7 (192 rows); 16 384 60.4 / 59.6 / 53.4, 53.4; 64 x 64, 10 000 rows 15.6 / 16.3 / 22.7,
+    // 15.6; bf16, 256 x 256 from two sources, 1000 rows 17.3 / 16.8 / 19.9, 16.7; 16 384 34.0 / 34.0 / 27.4, 27.4; 64 x 64, 20 000 rows 15.7 / 14.4 / 14.6, 14.1.
+    // Over 234 shapes 1.1 % from the best of 32 to 512 rows (256 always: 14 %; one number of rows a type and side of 16 384: 4 %).
     const bool wide_n = tn_wide_columns(dtype, N) && vec_ok(A_neigh, ld_in, es) && (!X_self || vec_ok(X_self, ld_in, es));
     const int tiles = n_src * ((K + 127) / 128) * (wide_n ? N / 256 : (N > 32 ? (N + 127) / 128 : 1));
-    int32_t splits = (wide_n ? 512 : 768) / tiles;   // two workgroups of the 256-column tile fit a CU, three of the others
-    // rows a split has at least: few rows go to many short splits while the chip has room for them (us at 256 / 128 / 64 rows at
-    // least, fp32: 1000 rows 256 x 256, two sources 56.8 / 48.7 / 46.6, 10 000 rows 64 x 64 33.1 / 26.5 / 24.2, 20 000 35.6 / 30.3 / 30.8;
-    // bf16: 1000 rows 256 x 256 33.6 / 30.0 / 29.7, 10 000 rows 40.8 / 41.0 / 44.0, 20 000 49.8 / 53.6 / 53.8)
-    const int32_t min_rows = (dtype == GNN_F32 ? 64 : 128) * (n_active <= 16384 ? 1 : 2);
-    const int32_t max_splits = n_active > 0 ? (n_active + min_rows - 1) / min_rows : 1;
     const int64_t split_bytes = (int64_t)n_src * K * N * 4;
-    if (splits > max_splits) splits = max_splits;
-    if (splits > 256) splits = 256;
-    if ((int64_t)splits * split_bytes > ((int64_t)128 << 20)) splits = (int32_t)(((int64_t)128 << 20) / split_bytes);
-    if (splits < 1) splits = 1;
-    int32_t rows_per_split = (int32_t)align_up((size_t)((n_active + splits - 1) / splits), 32);
-    if (rows_per_split < 32) rows_per_split = 32;
-    splits = n_active > 0 ? (n_active + rows_per_split - 1) / rows_per_split : 1;
+    int32_t most = (wide_n ? 512 : 768) / tiles;
+    if (most > 256) most = 256;
+    if ((int64_t)most * split_bytes > ((int64_t)128 << 20)) most = (int32_t)(((int64_t)128 << 20) / split_bytes);
+    if (most < 1) most = 1;
+    int32_t rows_per_split = 32, splits = 1;
+    double least = -1;
+    for (int32_t at_least = 256; n_active > 0 && at_least >= 32; at_least -= 32) {
+        int32_t count = (n_active + at_least - 1) / at_least;
+        if (count > most) count = most;
+        const int32_t rows_each = (int32_t)align_up((size_t)((n_active + count - 1) / count), 32);
+        count = (n_active + rows_each - 1) / rows_each;
+        const int64_t per_cu = ((int64_t)tiles * count + 255) / 256;
+        const double shared = per_cu >= 3 ? (dtype == GNN_F32 ? 1.9 : 1.2) * (double)per_cu / 3 : (per_cu == 2 && dtype == GNN_F32 ? 1.4 : 1);
+        const double row = dtype == GNN_F32 ? (N > 64 ? 0.078 : 0.046) : (wide_n ? 0.04 : 0.018);
+        const double cost = shared * row * rows_each + count * ((double)split_bytes / 4e6 * (dtype == GNN_F32 ? 1.4 : 1.0) + 0.02);
+        if (least < 0 || cost < least) {
+            least = cost;
+            rows_per_split = rows_each;
+            splits = count;
+        }
+    }
 
     WsCarver carve(ws);
     char* dZ = carve.take<char>((size_t)(n_active > 0 ? n_active : 1) * ldz * es);

@@ -373,3 +373,23 @@ def test_tile_widths_of_the_forward_product(dtype, M, K, N):
     want = a.float() @ Wn.float() + x.float() @ Ws.float() + b
     assert torch.equal(out[:M].float(), want.to(dtype).float())
     assert (out[M:] == torch.tensor(SENT, dtype=dtype)).all()
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("K,N,two", [(64, 8, False), (72, 48, True), (256, 256, True), (512, 512, True)])
+def test_weight_gradients_at_any_number_of_splits(dtype, K, N, two):
+    """Rows on either side of where the number of splits changes: one split, a last split with few rows, as many as there may be.
+    Small integers: every partial sum is exact, so any split gives the same bits."""
+    import paper_2311_06837_amd as P
+    ws = P.Workspace()
+    for M in (0, 1, 31, 33, 257, 1000, 4097, 16_385, 40_001):
+        gen = torch.Generator(device="cuda").manual_seed(M)
+        a, x = (torch.randint(-2, 3, (M + 1, K), generator=gen, device="cuda").to(dtype) for _ in range(2))     # (the last row is not the call's)
+        dz = torch.randint(-2, 3, (M + 1, N), generator=gen, device="cuda").to(dtype)
+        W = torch.zeros(K, N, dtype=dtype, device="cuda")
+        dWn, dWs = (torch.full((K, N), SENT, device="cuda") for _ in range(2))
+        db = torch.full((N,), SENT, device="cuda")
+        P.gnn_linear_bwd(None, M, dz, None, False, a, x if two else None, K, W, W if two else None, dWn, dWs if two else None, db, None, None, ws=ws)
+        assert torch.equal(dWn, a[:M].float().T @ dz[:M].float()) and torch.equal(db, dz[:M].float().sum(0)), M
+        if two:
+            assert torch.equal(dWs, x[:M].float().T @ dz[:M].float()), M
