@@ -1357,17 +1357,30 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __res
                                                               int64_t kn, float* __restrict__ out0, float* __restrict__ out1,
                                                               const float* __restrict__ Pb, int32_t N, float* __restrict__ dbias,
                                                               int32_t bias_blocks) {
-    if ((int)blockIdx.x >= (int)gridDim.x - bias_blocks) {
-        // the bias gradient's partial sums ride along: 32 columns a workgroup, 32 chains each, as in reduce_rows_kernel
+    if ((int)blockIdx.x < bias_blocks) {
+        // the bias gradient's partial sums ride along: 32 columns a workgroup, 32 chains each, as in reduce_rows_kernel.  Sixteen loads
+        // in flight, and these workgroups first: behind the others and with a wait per step they were the launch's tail (256 splits of two
+        // 256 x 256 gradients 15.3 us, two launches 12.0 + 5.2; of a 64 x 8 gradient 9.9, 5.7 + 3.4)
         __shared__ float s_b[32][33];
         const int tx = (int)(threadIdx.x & 31), ty = (int)(threadIdx.x >> 5);
-        const int n = ((int)blockIdx.x - ((int)gridDim.x - bias_blocks)) * 32 + tx;
+        const int n = (int)blockIdx.x * 32 + tx;
         float b[4] = {0.f, 0.f, 0.f, 0.f};
         if (n < N)
-            for (int32_t r = ty; r < splits; r += 32)
+            for (int32_t r0 = ty; r0 < splits; r0 += 128) {
+                float x[4][4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (r + 8 * j < splits) b[j] += Pb[(int64_t)(r + 8 * j) * N + n];
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const int32_t r = r0 + 32 * i + 8 * j;
+                        x[i][j] = Pb[(int64_t)(r < splits ? r : splits - 1) * N + n];
+                    }
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (r0 + 32 * i + 8 * j < splits) b[j] += x[i][j];
+            }
 #pragma unroll
         for (int j = 0; j < 4; ++j) s_b[ty + 8 * j][tx] = b[j];
         __syncthreads();
@@ -1382,7 +1395,7 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __res
     __shared__ float s_sum[4][64];
     const int x = (int)(threadIdx.x & 63), y = (int)(threadIdx.x >> 6);
     const int64_t total = (int64_t)n_src * kn;
-    for (int64_t base = (int64_t)blockIdx.x * 64; base < total; base += (int64_t)((int)gridDim.x - bias_blocks) * 64) {   // uniform over the workgroup
+    for (int64_t base = (int64_t)((int)blockIdx.x - bias_blocks) * 64; base < total; base += (int64_t)((int)gridDim.x - bias_blocks) * 64) {   // uniform over the workgroup
         const int64_t i = base + x;
         float s = 0.f;
         if (i < total) {
