@@ -496,6 +496,7 @@ __device__ __forceinline__ u32x4 mask_chunk(u32x4 r, int n_valid) {
 // that start at or beyond K are read from the start of their row instead (always addressable) and every chunk is
 // masked to its valid elements when it is moved to LDS, so neither padding nor a neighbouring row reaches the MFMAs.
 // MINB: workgroups that share a CU; the registers of a lane follow from it.
+constexpr int64_t kLargeOutput = 128ll << 20;     // bytes of an output from which a short reduction is bound by writing it
 template <int DT, int NTW, bool KTAIL, int MINB = NTW == 4 ? 2 : NTW == 2 ? 3 : 4>
 __global__ __launch_bounds__(256, MINB) void gemm_nt_wide_kernel(GemmNT a) {
     constexpr int BM = 128, BN = 64 * NTW, MT = 2, NT = NTW, WTN = 32 * NTW;
@@ -515,7 +516,12 @@ __global__ __launch_bounds__(256, MINB) void gemm_nt_wide_kernel(GemmNT a) {
 
     const int tiles_n = (a.N + BN - 1) / BN;
     // the tiles of a band of rows follow each other on one die (workgroup i runs on die i mod 8): its rows leave memory once
-    const int turn = (int)(blockIdx.x >> 3), m0 = ((turn / tiles_n) * 8 + (int)(blockIdx.x & 7)) * BM, n0 = (turn % tiles_n) * BN;
+    // - but for short reductions into a bf16 output that does not fit the last-level cache: there they go to all dies at once, so that
+    // a band's rows are written together (from 41 elements, across / band by band, us: 602 columns 233 000 rows 102 / 132, 100 000 rows
+    // (120 MB) 46 / 44; from 64: 200 columns 300 000 rows (120 MB) 52 / 46)
+    const bool across = DT == GNN_BF16 && NTW == 1 && a.K * a.n_src * ES <= 128 && (int64_t)a.M * a.N * ES > kLargeOutput;
+    const int turn = across ? (int)blockIdx.x : (int)(blockIdx.x >> 3);
+    const int m0 = (across ? turn / tiles_n : (turn / tiles_n) * 8 + (int)(blockIdx.x & 7)) * BM, n0 = (turn % tiles_n) * BN;
     if (m0 >= a.M) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
@@ -1069,10 +1075,11 @@ static int32_t launch_gemm_nt(const GemmNT& a, hipStream_t stream) {
         }
         // a reduction of one or two slices (an input gradient from 32 or 41 class scores) is all prologue and epilogue:
         // narrow tiles keep more workgroups on a CU to hide those latencies, and re-reading the short rows costs little - but where
-        // the output, far larger, no longer fits the last-level cache it has to leave in whole lines (bf16, narrow / wide, us:
+        // the output, far larger, no longer fits the last-level cache and one tile spans it, its rows leave whole (bf16, narrow / wide, us:
         // 64 -> 200 columns 300 000 rows 45.9 / 51.5, 600 001 143 / 114; 64 -> 256 600 001 132 / 98.6; 64 -> 128 300 000 29.1 / 31.1, 600 001 47.7 /
-        // 43.0; 64 -> 100, which half fills a tile of 128, 600 001 62.7 / 70.6, 1 200 000 144 / 157)
-        const bool whole_lines = DT == GNN_BF16 && (int64_t)a.M * a.N * DTy<DT>::ES > (128ll << 20) && (ntw == 4 || a.N % 128 == 0);
+        // 43.0; 64 -> 100, which half fills a tile of 128, 600 001 62.7 / 70.6, 1 200 000 144 / 157; 41 -> 602, five tiles of 128, 233 000
+        // 102 / 122)
+        const bool whole_lines = DT == GNN_BF16 && (int64_t)a.M * a.N * DTy<DT>::ES > kLargeOutput && a.N <= 64 * ntw && (ntw == 4 || a.N == 128);
         if ((int64_t)a.K * a.n_src * DTy<DT>::ES <= 128 && !whole_lines) ntw = 1;
         // whole cache lines per step where the shapes allow it (see gemm_nt_line_kernel)
 #ifndef GNN_NT_LINE
