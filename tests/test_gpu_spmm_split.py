@@ -56,6 +56,9 @@ CASES = {
     "301_prefix": (dict(n=50_000, deg=50, seed=3, hubs=2, empty=((30_000, 34_000),)), 301, 304, True, 1.0, 0.9, True),
     "97_prefix": (dict(n=400_000, deg=45, seed=4, empty=((0, 2500),)), 97, 100, True, 0.999, 0.97, False),
     "640": (dict(n=24_000, deg=50, seed=5, hubs=1), 640, 640, True, 1.0, None, True),
+    "800_two_column_blocks": (dict(n=24_000, deg=50, seed=6, hubs=1), 800, 800, True, 1.0, None, False),
+    "few_rows": (dict(n=140_000, deg=60, seed=7, hubs=1), 256, 256, True, 0.06, None, True),
+    "short_prefix": (dict(n=140_000, deg=60, seed=8, hubs=1), 256, 256, True, 1.0, 0.37, False),
 }
 
 
@@ -112,6 +115,71 @@ def test_split_route(name):
                                              1 if extra else 0, H.data_ptr() if extra else None, ld if extra else 0,
                                              small.buf.data_ptr(), C.byref(C.c_size_t(4096)), P.binding._stream()))
     assert torch.equal(Y, plain)
+
+
+def _sum_and_bound(row_ptr, col, n, X, rs, cs, extra):
+    """64-bit sums plus `extra`, and what fp32 sums in any order may be off by."""
+    want, size, lens = _want(row_ptr, torch.from_numpy(col).cuda(), n, X, rs, cs, X.shape[0])
+    return want + extra.double(), (lens + 8) * 2.0 ** -24 * (size + extra.double().abs()) + 1e-30
+
+
+@pytest.mark.parametrize("bias", [False, True])
+@pytest.mark.parametrize("relu", [False, True])
+def test_split_route_added_onto_the_output(bias, relu):
+    """gnn_masked_spmm_fwd_add: the rows start from what Y holds or from a bias, the ReLU's matrix is Y itself."""
+    import paper_2311_06837_amd as P
+    n, F = 60_000, 252
+    row_ptr, col = _graph(n, 46, 1, hubs=2, empty=((30_000, 31_000),))
+    G = P.Graph(torch.from_numpy(row_ptr).cuda(), torch.from_numpy(col).cuda(), sorted_columns=True)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    X, Y = (torch.randn(n, F, generator=gen, device="cuda") for _ in range(2))
+    rs, cs = (torch.rand(n, generator=gen, device="cuda") + 0.5 for _ in range(2))
+    b = torch.randn(F, generator=gen, device="cuda") if bias else None
+    want, tol = _sum_and_bound(row_ptr, col, n, X, rs, cs, b[None].expand(n, F) if bias else Y)
+    ws = P.Workspace()
+    P.gnn_masked_spmm_fwd_add(G, None, n, X, Y, F, rs, cs, relu=relu, ws=ws, bias=b)
+    assert ws.buf[CTRL: CTRL + 8].view(torch.int32).tolist()[1] == 1
+    want = torch.relu(want) if relu else want
+    assert ((Y.double() - want).abs() / tol).max().item() <= 1.0
+
+
+def test_split_route_with_infinities_and_nan():
+    """In frequent neighbours (the table) and in others: a sum is infinite or NaN where it is without the route, the rest are untouched."""
+    import paper_2311_06837_amd as P
+    n, F = 60_000, 256
+    row_ptr, col = _graph(n, 46, 1)
+    G = P.Graph(torch.from_numpy(row_ptr).cuda(), torch.from_numpy(col).cuda(), sorted_columns=True)
+    lens = np.diff(row_ptr)
+    often, seldom = np.argsort(-lens)[:3], np.flatnonzero(lens == lens[lens > 0].min())[:3]
+    X = torch.randn(n, F, device="cuda")
+    for a, b, c in (often, seldom):
+        X[a, 5], X[b, 7], X[b, 9], X[c, 9] = float("inf"), float("nan"), float("inf"), float("-inf")
+    Y, Z = torch.zeros_like(X), torch.zeros_like(X)
+    ws = P.Workspace()
+    P.gnn_masked_spmm_fwd(G, None, n, X, Y, F, ws=ws)
+    P.gnn_masked_spmm_fwd(G, None, n, X, Z, F)
+    assert ws.buf[CTRL: CTRL + 8].view(torch.int32).tolist()[1] == 1
+    assert torch.equal(torch.isnan(Y), torch.isnan(Z)) and torch.equal(torch.isinf(Y), torch.isinf(Z))
+    assert torch.isnan(Y).any() and torch.isinf(Y).any()
+    ok = torch.isfinite(Z)
+    assert torch.equal(torch.sign(Y[torch.isinf(Y)]), torch.sign(Z[torch.isinf(Z)])) and (Y[ok] - Z[ok]).abs().max() <= 1e-4 * Z[ok].abs().max()
+
+
+def test_split_route_over_the_last_rows_of_a_graph():
+    """A row pointer that does not begin at 0: the rows behind the first of a larger graph."""
+    import paper_2311_06837_amd as P
+    n, F, first = 120_000, 128, 3001
+    row_ptr, col = _graph(n, 60, 9)
+    assert row_ptr[first] > 8192
+    G = P.Graph(torch.from_numpy(row_ptr[first:]).cuda(), torch.from_numpy(col).cuda(), n_cols=n, sorted_columns=True)
+    X = torch.randn(n, F, device="cuda")
+    Y = torch.zeros(n - first, F, device="cuda")
+    ws = P.Workspace()
+    P.gnn_masked_spmm_fwd(G, None, n - first, X, Y, F, ws=ws)
+    on = ws.buf[CTRL: CTRL + 8].view(torch.int32).tolist()[1]
+    want, tol = _sum_and_bound(row_ptr[first:], col, n - first, X, None, None, torch.zeros_like(Y))
+    print("went on:", on, flush=True)
+    assert ((Y.double() - want).abs() / tol).max().item() <= 1.0
 
 
 @pytest.mark.parametrize("skewed_rows", [False, True])
