@@ -345,13 +345,18 @@ def run_workload(args, name, steps, warmup, cpu_flops):
         blocked, kernels = False, "fused_agg_linear_kernel (aggregation and feature transform in one kernel)"
     else:
         src_dom, dst_dom = (model.P[dom], model.H[dom]) if dom in model.tf_layers else (model.H[dom - 1], model.A[dom])
-        blocked = P.binding.spmm_workspace_bytes(G, nd, src_dom, dst_dom, Fd) > 0     # a route whose point is reuse in the L2s
-        slab = G.n_cols * 256
-        by_columns = slab >= 16 << 20 and G.nnz / G.n_rows >= 64 * -(-slab // (64 << 20))
-        kernels = ("spmm_rows_kernel" if not blocked else
-                   "spmm_stream_kernel (+ spmm_seg_kernel before and spmm_sum_parts_kernel after it: column-blocked route)" if by_columns else
-                   "split_sum_kernel (frequent neighbours, from a table) and spmm_rows_kernel (the others; + split_degrees, _assign, "
-                   "_table, _entries before them: split route)")
+        ask = lambda ws=None: P.gnn_spmm_route(G, model.rows, nd, src_dom, dst_dom, Fd, scaled=model.cs is not None, ws=ws)
+        route = ask()
+        if route == "split":        # taken only if the graph has frequent neighbours, which the GPU finds out in the call
+            route_ws = P.Workspace()
+            P.gnn_masked_spmm_fwd(G, model.rows, nd, src_dom, torch.empty_like(dst_dom), Fd, model.rs, model.cs, ws=route_ws)
+            route = ask(route_ws)
+            del route_ws
+        blocked = route != "rows"   # a route whose point is reuse in the L2s
+        kernels = {"rows": "spmm_rows_kernel",
+                   "columns": "spmm_stream_kernel (+ spmm_samples, _bounds, _seg_kernel before and spmm_sum_parts_kernel after it: column-blocked route)",
+                   "split": "split_sum_kernel (frequent neighbours, from a table) and spmm_rows_kernel (the others; + split_degrees, _assign, "
+                            "_table, _entries before them: split route)"}[route]
     c_dom = side.get("spmm_fwd_dom") if side.get("dominant_layer") == dom else None
     roofline = roofline_of_call(kernels, f"gnn_masked_spmm_fwd, layer {dom}, F={Fd}", t_dom, gather_bytes, compulsory, blocked, c_dom)
 

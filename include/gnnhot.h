@@ -144,11 +144,20 @@ int32_t gnn_masked_spmm_fwd(const gnn_csr *g, const int32_t *rows, int32_t n_act
  * (Helper; no passage of the paper.)  The compute die (XCC id, 0..7) that each of the first n_ids <= 64 workgroups of a
  * 16 x 4 probe grid ran on, in dispatch order (x fastest), to xcc_ids_host (HOST memory); *holds_host (nullable, host) = 1
  * if workgroup i ran on the die of workgroup i mod 8 and the first eight dies are all different - the dispatch order the
- * column-blocked route of the aggregation calls is built on.  The library asks the same question once per device before
- * it takes that route for the first time (the size query then reports 0 if the answer is no).  Launches on the null
- * stream and waits.
+ * column-blocked and the split route of the aggregation calls are built on.  The library asks the same question once per device
+ * before it takes one of them for the first time (the size query then reports 0 if the answer is no; for the split route also while
+ * the stream captures, as long as the question has not been asked).  Launches on the null stream and waits.
  */
 int32_t gnn_die_mapping(int32_t *xcc_ids_host, int32_t n_ids, int32_t *holds_host);
+
+/*
+ * (Helper; no passage of the paper.)  The route that gnn_masked_spmm_fwd takes with a workspace for the same arguments, to
+ * *route_host: 0 whole rows in one launch, 1 column blocks, 2 split.  On 2, *decision_host (nullable) is the place in ws, in bytes, of
+ * an int32 that the call leaves 1 if the graph had enough frequent neighbours, 0 if the rows were gathered whole after all.
+ * Reads no array; X and Y are looked at for their alignment.
+ */
+int32_t gnn_spmm_route(const gnn_csr *g, const int32_t *rows, int32_t n_active, const void *X, int64_t ldx, const void *Y,
+                       int64_t ldy, int32_t F, int32_t dtype, int32_t scaled, int32_t *route_host, int64_t *decision_host, void *stream);
 
 /*
  * Masked aggregation added onto the output (section 2.1's layer equation with the neighbour sum and the weight

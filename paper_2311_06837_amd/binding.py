@@ -27,7 +27,7 @@ EXPORTS = ["gnn_version", "gnn_last_error", "gnn_build_active_sets", "gnn_norm_s
            "gnn_sample_boundary", "gnn_extract_partition", "gnn_gather_rows", "gnn_expand_row_ptr",
            "gnn_extract_sampled_partition", "gnn_eas_traverse", "gnn_layer_edge_mask", "gnn_transpose_edge_mask",
            "gnn_layer_edge_mask_transposed", "gnn_layer_norm_relu_fwd", "gnn_layer_norm_relu_bwd", "gnn_add_rows", "gnn_add_rows_masked", "gnn_bias_grad", "gnn_linear_bwd_input",
-           "gnn_linear_fwd_static", "gnn_linear_bwd_input2", "gnn_die_mapping", "gnn_fused_layer_fwd"]
+           "gnn_linear_fwd_static", "gnn_linear_bwd_input2", "gnn_die_mapping", "gnn_fused_layer_fwd", "gnn_spmm_route"]
 
 
 class GnnError(RuntimeError):
@@ -57,6 +57,7 @@ _SIGNATURES = {
     "gnn_add_rows": "piplplii" + "p", "gnn_add_rows_masked": "pipl" + "ipl" + "ipl" + "i" + "p",
     "gnn_extract_partition": "ppi" + "pip" + "pplpp" + "ppp", "gnn_extract_sampled_partition": "pppi" + "pp" + "pplpp" + "ppp",
     "gnn_expand_row_ptr": "ipipp" + "ppp", "gnn_gather_rows": "plipiiipl" + "p", "gnn_die_mapping": "pip",
+    "gnn_spmm_route": "ppi" + "plpl" + "iii" + "ppp",
     "gnn_fused_layer_fwd": "ppi" + "pli" + "pppp" + "pi" + "plii" + "ppp",
 }
 
@@ -613,6 +614,20 @@ def gnn_linear_bwd_input2(rows, n_active: int, dG: torch.Tensor, W_neigh: torch.
               _ptr(W_self) if n_self > 0 else None, C.c_int32(n_self), C.c_int64(dG.stride(0)), C.c_int32(N), C.c_int32(K),
               _ptr(relu_H), C.c_int64(relu_H.stride(0) if relu_H is not None else 0), _ptr(dX), C.c_int64(dX.stride(0)),
               C.c_int32(_dtype_code(dG))), (_stream(),), ws)
+
+
+def gnn_spmm_route(g: Graph, rows, n_active: int, X: torch.Tensor, Y: torch.Tensor, F: int, scaled: bool = False, ws: Workspace | None = None):
+    """The route that gnn_masked_spmm_fwd takes with a workspace: "rows", "columns" or "split".  ws: the workspace of such a call that
+    has been enqueued; waits for it, and says "rows" if a split call found no frequent neighbours or had no room."""
+    route, at = C.c_int32(0), C.c_int64(0)
+    _check(lib().gnn_spmm_route(C.byref(g.c), _ptr(_i32(rows, "rows")), C.c_int32(n_active), _ptr(X), C.c_int64(X.stride(0)), _ptr(Y),
+                                C.c_int64(Y.stride(0)), C.c_int32(F), C.c_int32(_dtype_code(X)), C.c_int32(1 if scaled else 0), C.byref(route),
+                                C.byref(at), _stream()))
+    if route.value == 2 and ws is not None:
+        buf = ws.buf
+        if buf.numel() < spmm_workspace_bytes(g, n_active, X, Y, F) or int(buf[at.value: at.value + 4].view(torch.int32)) != 1:
+            return "rows"
+    return ("rows", "columns", "split")[route.value]
 
 
 def gnn_die_mapping():

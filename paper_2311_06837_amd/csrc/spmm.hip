@@ -1468,10 +1468,11 @@ static SplitPlan plan_split(const gnn_csr* g, const int32_t* rows, int32_t n_act
 }
 
 // Lays the route's arrays out; with base == nullptr it only measures.
-static SplitArgs carve_split(const SplitPlan& p, int32_t n_active, WsCarver& carve) {
+static SplitArgs carve_split(const SplitPlan& p, int32_t n_active, WsCarver& carve, size_t* decision = nullptr) {
     SplitArgs s = {};
     s.hist = carve.take<int32_t>((size_t)kSplitBlocks * kSplitBins);
     s.hits = carve.take<int32_t>(kSplitSampleBlocks);
+    if (decision) *decision = carve.used + sizeof(int32_t);      // ctrl[1]
     s.ctrl = carve.take<int32_t>(2);
     s.first_row = carve.take<int32_t>(p.n_chunks + 1);
     s.slot = carve.take<uint2>(((size_t)p.n_nbr + 31) / 32);
@@ -1631,6 +1632,32 @@ static int32_t spmm_common(const gnn_csr* g, const char* gname, const int32_t* r
 }  // namespace gnnhot
 
 using namespace gnnhot;
+
+extern "C" int32_t gnn_spmm_route(const gnn_csr* g, const int32_t* rows, int32_t n_active, const void* X, int64_t ldx, const void* Y, int64_t ldy,
+                                  int32_t F, int32_t dtype, int32_t scaled, int32_t* route_host, int64_t* decision_host, void* stream) {
+    GNN_CHECK(check_csr(g, "g"));
+    GNN_REQUIRE(route_host != nullptr, GNN_ERR_INVALID_ARG, "route_host is NULL");
+    GNN_REQUIRE(n_active >= 0 && F >= 0 && (rows != nullptr || n_active <= g->n_rows), GNN_ERR_INVALID_ARG, "negative or too many rows, or F < 0");
+    GNN_REQUIRE(dtype == GNN_F32 || dtype == GNN_BF16, GNN_ERR_UNSUPPORTED, "unknown dtype %d", dtype);
+    const int ve = dtype == GNN_F32 ? 4 : 8;
+    const bool vec_ok = (uintptr_t)X % 16 == 0 && (uintptr_t)Y % 16 == 0 && ldx % ve == 0 && ldy % ve == 0, filter = g->edge_keep != nullptr;
+    const int64_t row_bytes = ldx * (16 / ve);
+    *route_host = 0;
+    if (n_active == 0 || F == 0) return GNN_OK;
+    if (plan_blocked(g, n_active, F, row_bytes, vec_ok, filter, scaled != 0, dtype == GNN_F32, -1).passes > 0) {
+        *route_host = 1;
+        return GNN_OK;
+    }
+    const SplitPlan p = plan_split(g, rows, n_active, F, dtype, row_bytes, vec_ok, filter, -1, (hipStream_t)stream);
+    if (p.n_chunks > 0) {
+        WsCarver carve(nullptr);
+        size_t decision = 0;
+        carve_split(p, n_active, carve, &decision);
+        *route_host = 2;
+        if (decision_host) *decision_host = (int64_t)decision;
+    }
+    return GNN_OK;
+}
 
 extern "C" int32_t gnn_die_mapping(int32_t* xcc_ids_host, int32_t n_ids, int32_t* holds_host) {
     GNN_REQUIRE(n_ids >= 0 && (xcc_ids_host != nullptr || n_ids == 0), GNN_ERR_INVALID_ARG, "xcc_ids_host is NULL");

@@ -168,8 +168,7 @@ static __global__ __launch_bounds__(1024) void split_assign_kernel(SplitArgs a) 
     block_exclusive_scan<1024>(kSplitBins - 1 - tid >= least ? len : 0, s_scan, &hot_len);
     if ((int64_t)hot_len * kSplitSamples < (int64_t)all_len * kSplitMinShare) least = kSplitBins;
     const bool taken = tid < kSplitBins && kSplitBins - 1 - tid >= least;
-    const int base_before = block_exclusive_scan<1024>(taken ? m : 0, s_scan, &total);
-    (void)base_before;
+    block_exclusive_scan<1024>(taken ? m : 0, s_scan, &total);
     if (tid == 0) s_base = total;
     block_exclusive_scan<1024>(taken ? n : 0, s_scan, &total);
     if (tid == 0) s_count = total;
@@ -259,7 +258,7 @@ __global__ __launch_bounds__(1024, 8) void split_entries_kernel(SplitArgs a) {
         return;
     }
     const int n = (int)(m - e0 < kSplitChunk ? m - e0 : kSplitChunk), n0 = (int)(m0 > e0 ? m0 - e0 : 0);
-        const int32_t r0 = a.first_row[chunk];
+    const int32_t r0 = a.first_row[chunk];
     const int32_t r_end = split_last_row(a, chunk, m) + 1;      // rows with entries here lie in [r0, r_end)
     const uint32_t n_rows = (uint32_t)(r_end - r0);
     const bool few = n_rows <= 1024;

@@ -335,3 +335,25 @@ def test_a_workspace_gives_its_buffer_back_before_it_grows():
     before = torch.cuda.memory_allocated()
     ws.get(96 << 20)
     assert torch.cuda.max_memory_allocated() <= before + (40 << 20)
+
+
+@pytest.mark.parametrize("graph,dtype,route", [("skewed", torch.float32, "split"), ("even", torch.float32, "rows"), ("skewed", torch.bfloat16, "rows"),
+                                               ("dense", torch.float32, "columns"), ("dense", torch.bfloat16, "columns")])
+def test_the_route_that_a_call_took(graph, dtype, route):
+    """Asked before the call, the route it prepares for; with the call's workspace, the one it went on with."""
+    import paper_2311_06837_amd as P
+    if graph == "skewed":
+        n, (row_ptr, col) = 60_000, _graph(60_000, 46, 1)
+    else:
+        n, deg = (140_000, 46) if graph == "even" else (70_000, 80)
+        rng = np.random.default_rng(2)
+        keys = np.unique(np.repeat(np.arange(n, dtype=np.int64), deg) * n + rng.integers(0, n, deg * n))
+        row_ptr, col = np.searchsorted(keys, np.arange(n + 1, dtype=np.int64) * n).astype(np.int32), (keys % n).astype(np.int32)
+    G = P.Graph(torch.from_numpy(row_ptr).cuda(), torch.from_numpy(col).cuda(), sorted_columns=True)
+    X = torch.randn(n, 256, device="cuda").to(dtype)
+    Y, ws = torch.zeros_like(X), P.Workspace()
+    before = P.gnn_spmm_route(G, None, n, X, Y, 256)
+    assert before == ("split" if graph != "dense" and dtype == torch.float32 else route)
+    P.gnn_masked_spmm_fwd(G, None, n, X, Y, 256, ws=ws)
+    assert P.gnn_spmm_route(G, None, n, X, Y, 256, ws=ws) == route
+    assert P.gnn_spmm_route(G, None, 100, X, Y, 256) == "rows"
