@@ -518,8 +518,9 @@ __global__ __launch_bounds__(256, MINB) void gemm_nt_wide_kernel(GemmNT a) {
     // the tiles of a band of rows follow each other on one die (workgroup i runs on die i mod 8): its rows leave memory once
     // - but for short reductions into a bf16 output that does not fit the last-level cache: there they go to all dies at once, so that
     // a band's rows are written together (from 41 elements, across / band by band, us: 602 columns 233 000 rows 102 / 132, 100 000 rows
-    // (120 MB) 46 / 44; from 64: 200 columns 300 000 rows (120 MB) 52 / 46)
-    const bool across = DT == GNN_BF16 && NTW == 1 && a.K * a.n_src * ES <= 128 && (int64_t)a.M * a.N * ES > kLargeOutput;
+    // (120 MB) 46 / 44; from 64: 200 columns 300 000 rows (120 MB) 52 / 46; with a mask to read beside it 256 from 32 + 32, 300 000 rows 91.7 /
+    // 86.3, 602 from 41 251 / 250)
+    const bool across = DT == GNN_BF16 && NTW == 1 && a.mask == nullptr && a.K * a.n_src * ES <= 128 && (int64_t)a.M * a.N * ES > kLargeOutput;
     const int turn = across ? (int)blockIdx.x : (int)(blockIdx.x >> 3);
     const int m0 = (across ? turn / tiles_n : (turn / tiles_n) * 8 + (int)(blockIdx.x & 7)) * BM, n0 = (turn % tiles_n) * BN;
     if (m0 >= a.M) return;
@@ -1078,8 +1079,8 @@ static int32_t launch_gemm_nt(const GemmNT& a, hipStream_t stream) {
         // the output, far larger, no longer fits the last-level cache and one tile spans it, its rows leave whole (bf16, narrow / wide, us:
         // 64 -> 200 columns 300 000 rows 45.9 / 51.5, 600 001 143 / 114; 64 -> 256 600 001 132 / 98.6; 64 -> 128 300 000 29.1 / 31.1, 600 001 47.7 /
         // 43.0; 64 -> 100, which half fills a tile of 128, 600 001 62.7 / 70.6, 1 200 000 144 / 157; 41 -> 602, five tiles of 128, 233 000
-        // 102 / 122)
-        const bool whole_lines = DT == GNN_BF16 && (int64_t)a.M * a.N * DTy<DT>::ES > kLargeOutput && a.N <= 64 * ntw && (ntw == 4 || a.N == 128);
+        // 102 / 122; with a mask to read beside it, 32 + 32 -> 256, 3 485 000 rows 1340 / 1554)
+        const bool whole_lines = DT == GNN_BF16 && !a.mask && (int64_t)a.M * a.N * DTy<DT>::ES > kLargeOutput && a.N <= 64 * ntw && (ntw == 4 || a.N == 128);
         if ((int64_t)a.K * a.n_src * DTy<DT>::ES <= 128 && !whole_lines) ntw = 1;
         // whole cache lines per step where the shapes allow it (see gemm_nt_line_kernel)
 #ifndef GNN_NT_LINE
