@@ -690,9 +690,12 @@ __global__ __launch_bounds__(256) void eas_expand_long_kernel(const int32_t* __r
 // A construction of a small graph is as long as its launches, so here one workgroup keeps the bitmaps in LDS (a word a thread)
 // and walks the frontier's rows edge-parallel, 8192 edges a step; the row of an edge is a rank among the bits of rows'
 // beginnings (a search over the rows' prefix sums is ten dependent LDS reads an edge: 65 us of kernel where this takes 41).
-// The whole call (us, a launch per part of a level / this one): 2000 vertices of degree 5, two levels 86 / 39, 10 000 of 10
-// 92 / 57, five levels 132 / 77; 240 000 entries: 20 000 vertices, three levels 108 / 105, 30 000 109 / 117, eight levels 172 /
-// 144 - one compute unit walks what it takes the others to hide, so the line lies at half of that.
+// One compute unit walks what it takes the others to hide, so entries and vertices count against it, levels for it.  The whole call, and
+// the GPU's share (us, a launch per part of a level with the transposed graph / this one):
+//   two levels: 2000 vertices of degree 5 71 / 32, 34 / 13; 10 000 of 10 78 / 55, 41 / 36; 15 000 of 8 80 / 63, 43 / 44; 30 000 of 2 81 / 59, 46 / 39,
+//   of 4 83 / 74, 46 / 54; three: 20 000 of 5 94 / 75, 56 / 56; 30 000 of 4 97 / 95, 60 / 75; 32 000 around one hub, 96 000 entries, 83 / 102, 42 / 82
+//   eight: 12 000 of 10 142 / 75, 100 / 55; 32 000 of 4 151 / 118, 112 / 99
+static bool as_takes_small(int32_t n, int64_t nnz, int32_t L) { return nnz + 3 * (int64_t)n <= 168000 || L >= 5; }
 constexpr int32_t kAsSmallRows = 32 * 1024;
 constexpr int64_t kAsSmallEntries = (int64_t)1 << 17;
 
@@ -856,7 +859,7 @@ extern "C" int32_t gnn_build_active_sets(const gnn_csr* g, const gnn_csr* gt, co
     GNN_REQUIRE(n == 0 || (dist != nullptr && ring_ids != nullptr), GNN_ERR_INVALID_ARG, "dist / ring_ids is NULL");
     GNN_REQUIRE(n_targets == 0 || targets != nullptr, GNN_ERR_INVALID_ARG, "targets is NULL");
 
-    const bool small = n > 0 && n <= kAsSmallRows && g->nnz <= kAsSmallEntries;
+    const bool small = n > 0 && n <= kAsSmallRows && g->nnz <= kAsSmallEntries && as_takes_small(n, g->nnz, L);
     if (small) {
         as_small_kernel<<<1, 1024, 0, stream>>>(g->row_ptr, g->col_idx, n, targets, n_targets, L, dist, ring_ids, hop_offsets);
         GNN_LAUNCH_CHECK("as_small_kernel");

@@ -202,7 +202,45 @@ def test_sets_of_a_small_graph_whose_every_vertex_has_entries(deg):
     row_ptr = (np.arange(n + 1) * deg).astype(np.int32)
     G = P.Graph(dev(row_ptr), dev(cols.reshape(-1)))
     for targets in (np.arange(n, dtype=np.int32), np.arange(0, n, 3, dtype=np.int32), np.arange(4096, dtype=np.int32)):
-        od, oring, ooff = oracle.active_sets(row_ptr, cols.reshape(-1), targets, 3)
-        dist, ring, off, hop = P.gnn_build_active_sets(G, dev(targets), 3)
+        od, oring, ooff = oracle.active_sets(row_ptr, cols.reshape(-1), targets, 6)
+        dist, ring, off, hop = P.gnn_build_active_sets(G, dev(targets), 6)
         assert list(hop) == list(ooff) and np.array_equal(dist.cpu().numpy(), od)
         assert np.array_equal(ring.cpu().numpy()[: ooff[-1]], oring)
+
+
+@pytest.mark.parametrize("deg,L", [(1, 2), (2, 2), (3, 4), (3, 5)])
+def test_sets_on_either_side_of_the_small_graphs_rule(deg, L):
+    """nnz + 3 n <= 168 000, or five levels: 32 000 vertices of degree 2 are taken by one launch, of degree 3 from five levels on."""
+    import paper_2311_06837_amd as P
+    n = 32_000
+    cols = np.sort((np.arange(n)[:, None] + 1 + np.arange(deg) * 5000) % n, axis=1).astype(np.int32)
+    row_ptr = (np.arange(n + 1) * deg).astype(np.int32)
+    G = P.Graph(dev(row_ptr), dev(cols.reshape(-1)))
+    targets = np.arange(0, n, 7, dtype=np.int32)
+    od, oring, ooff = oracle.active_sets(row_ptr, cols.reshape(-1), targets, L)
+    dist, ring, off, hop = P.gnn_build_active_sets(G, dev(targets), L, gt=None)
+    assert list(hop) == list(ooff) and np.array_equal(dist.cpu().numpy(), od)
+    assert np.array_equal(ring.cpu().numpy()[: ooff[-1]], oring)
+
+
+def test_a_hub_in_a_small_graph_costs_no_more_than_in_a_larger_one():
+    """32 000 vertices around one hub, 96 000 entries: not for one workgroup (82 us where the form with a launch per part of a level
+    takes 42).  32 800 vertices take that form by their number."""
+    import paper_2311_06837_amd as P
+
+    def time_us(n):
+        i = np.arange(n, dtype=np.int64)
+        keys = np.unique(np.concatenate([i[1:] * n, i[1:], i * n + (i * 7 + 1) % n]))
+        row_ptr = np.searchsorted(keys, np.arange(n + 1, dtype=np.int64) * n).astype(np.int32)
+        G = P.Graph(dev(row_ptr), dev((keys % n).astype(np.int32)))
+        T, ws, times = dev(np.array([0, n // 2], np.int32)), P.Workspace(), []
+        for _ in range(6):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(20):
+                P.gnn_build_active_sets(G, T, 3, sync=False, ws=ws)
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b) * 50)
+        return min(times)
+    assert time_us(32_000) < 1.4 * time_us(32_800)
