@@ -126,8 +126,8 @@ int32_t gnn_norm_scales(int32_t norm, const int32_t *len, const int32_t *row_ptr
  * With a workspace the call may take the column-blocked route for dense graphs whose gathered
  * matrix is far larger than a cache (on average at least 8 entries of a row per column block, columns sorted:
  * GNN_CSR_SORTED_COLUMNS, 16-byte aligned operands): the neighbour-id range is cut into 8 blocks
- * per pass, workgroup i works on block i mod 8 (the compute die it runs on), so each die's L2
- * only ever holds one eighth of a 256-byte-wide feature slab; the per-block partial sums (float)
+ * per pass that hold about as many of the call's entries, workgroup i works on block i mod 8 (the compute die it runs on), so each die's L2
+ * only ever holds a part of a 256-byte-wide feature slab; the per-block partial sums (float)
  * go to ws and are added in block order.
  * Or it may take the split route (float, rows == NULL and no filter but a source prefix, more than 96 columns, on
  * average at least 40 entries a row, a matrix of 48 MB or more, and enough rows and neighbours in the call): the entries that name one of up to 65 535 frequent

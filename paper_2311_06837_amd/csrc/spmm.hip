@@ -697,7 +697,8 @@ __global__ __launch_bounds__(256, NCH == 1 ? (LPR == 64 ? GNN_SPMM_MINB_WIDE : G
 // row ends; the next piece's ids are fetched while this one is gathered), row starts are a bit per edge, tested for the
 // whole wavefront by scalar instructions, and a load's address is one addition to a staged dword.  With a 16-edge tile
 // per group, located by a binary search per edge and tile, 114 M edges of 233 000 rows took (256 columns, the whole call)
-// 8.09 ms in fp32 and 7.67 in bf16 (13.4 backward with a factor per edge), now 7.31, 4.35 and 6.0.  Without
+// 8.09 ms in fp32 and 7.67 in bf16 (13.4 backward with a factor per edge), then 7.31, 4.35 and 6.0, and with blocks of equal shares
+// (spmm_bounds_kernel) 6.25, 3.78 and 5.21.  Without
 // misses, row starts and id loads the loop would take 3.9 ms of fp32: the rest is the fabric's (ids are read once a slab).
 // 128-byte slabs, which fit the L2, read the ids twice as often and meet twice the row ends: 8.07 / 4.87 / 7.0.
 // Pieces of 4096 edges, 8 loads in flight, 5 or 7 workgroups per CU, non-temporal id loads: all within 2 % or slower.
