@@ -1774,10 +1774,10 @@ extern "C" int32_t gnn_linear_bwd(const int32_t* rows, int32_t n_active, const v
     int32_t rows_per_split = 32, splits = 1;
     double least = -1;
     for (int32_t at_least = 256; n_active > 0 && at_least >= 32; at_least -= 32) {
-        int32_t count = (n_active + at_least - 1) / at_least;
+        int32_t count = (int32_t)(((int64_t)n_active + at_least - 1) / at_least);
         if (count > most) count = most;
-        const int32_t rows_each = (int32_t)align_up((size_t)((n_active + count - 1) / count), 32);
-        count = (n_active + rows_each - 1) / rows_each;
+        const int32_t rows_each = (int32_t)align_up((size_t)(((int64_t)n_active + count - 1) / count), 32);
+        count = (int32_t)(((int64_t)n_active + rows_each - 1) / rows_each);
         const int64_t per_cu = ((int64_t)tiles * count + 255) / 256;
         const double shared = per_cu >= 3 ? (dtype == GNN_F32 ? 1.9 : 1.2) * (double)per_cu / 3 : (per_cu == 2 && dtype == GNN_F32 ? 1.4 : 1);
         const double row = dtype == GNN_F32 ? (N > 64 ? 0.078 : 0.046) : (wide_n ? 0.04 : 0.018);

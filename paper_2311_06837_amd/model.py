@@ -25,7 +25,8 @@ def row_stride(width: int, dtype) -> int:
 #   fp32  1e8 GraphSAGE 64-64-8 199 / 184; 4e8 GraphSAGE 64-128-16 262 / 228; 7e8 GCN 128-128-16 289 / 271, three layers 128-128-128-41 347 / 387;
 #         1.5e9 GCN 128-256-32 291 / 304; GraphSAGE 128-128-128-41 375 / 393; 3e9 GCN 602-256-41, degree 50, 571 / 650; 4e10 2686 / 2767
 #   bf16  1e8 196 / 172; 4e8 216 / 197; 7e8 244 / 236, three layers 286 / 292; 1.4e9 238 / 237; 300 / 309; 3e9 457 / 509; 4e10 1339 / 1376
-# (A stream that shares the hardware queue of the step's stream - the fourth one that a process makes does - hides nothing and costs 2 to 9 %.)
+# (Where the second stream shares a hardware queue with the step's - of four, the seventh stream of a process did with the null stream -
+# nothing overlaps: GraphSAGE 128-256-256-41 in bf16 on 33 000 vertices 483 us, 440 on any other, 450 with one stream.)
 SIDE_STREAM_FLOPS = {torch.float32: 1.4e9, torch.bfloat16: 1.4e9}
 
 
