@@ -19,7 +19,9 @@
 // reduced through LDS in a fixed order, inside the same launch.
 #include "common.h"
 #include "scan.h"
+#include "spmm_fours.h"
 #include "spmm_split.h"
+#include <algorithm>
 #include <mutex>
 
 namespace gnnhot {
@@ -68,8 +70,8 @@ constexpr int kMaxChunk = 256;                  // rows of the list per workgrou
 // range [0, n_cols) is cut into 8 * passes blocks of about as many entries; in pass p workgroup i gathers, for its
 // rows, only the neighbours inside block 8p + (i mod 8).  Workgroups are dealt round-robin to the 8
 // compute dies, so every die's L2 sees one eighth of the matrix - and with the feature axis walked
-// in slabs of 256 bytes per row (grid.y, the slow grid axis) that eighth fits: the gathers then
-// run at L2 rather than at fabric speed (measured about 2x).  Each die leaves a plane of float
+// in slabs of 128 bytes per row (row lists: 256; grid.y, the slow grid axis) that eighth fits: the gathers then
+// run at L2 rather than at fabric speed.  Each die leaves a plane of float
 // partial sums; a second kernel adds the planes in block order and applies the output scale.
 constexpr int kDies = 8;
 #ifndef GNN_SPMM_DIE_BYTES
@@ -77,9 +79,6 @@ constexpr int kDies = 8;
 #endif
 #ifndef GNN_SPMM_BLOCKED_MIN_SLAB
 #define GNN_SPMM_BLOCKED_MIN_SLAB (16ll << 20)   // below this slab size the plain route is already cache-resident
-#endif
-#ifndef GNN_SPMM_BLOCKED_MIN_SEG
-#define GNN_SPMM_BLOCKED_MIN_SEG 8          // average neighbours of a row inside one column block
 #endif
 constexpr int kSlabBytes = 256;
 
@@ -691,21 +690,16 @@ __global__ __launch_bounds__(256, NCH == 1 ? (LPR == 64 ? GNN_SPMM_MINB_WIDE : G
 // groups behind its first one leave their sums ("heads") in LDS, and after a barrier the first one adds them in
 // stream order and stores the row, or hands the sum to the next piece.  So power-law rows cost no imbalance inside the
 // workgroup, and the result is a fixed-order sum (bit-reproducible).
-// It serves the column-blocked route: the workgroup id carries (chunk, die) = (id / 8, id % 8); every row is cut to
-// the die's column block through `seg`, and the unscaled float sums go to plane `die` of the partial buffer
+// It serves the column-blocked route of row lists (other calls: spmm_fours.h): the workgroup id carries (chunk, die) = (id / 8, id % 8);
+// every row is cut to the die's column block through `seg`, and the unscaled float sums go to plane `die` of the partial buffer
 // (a.Y, row index = position in the row list), not to the output matrix.
 //
-// What bounds it: gathers out of a 4 MB L2 run at 33 TB/s on this card and at 17 out of a 7.4 MB block (random 256-byte
-// rows, all dies), so beside the misses every instruction per edge counts: a CU takes 16 clocks for a 1 KB load, the time
+// Beside the L2 misses of a 7.4 MB block every instruction per edge counts: a CU takes 16 clocks for a 1 KB load, the time
 // of 16 vector instructions.  Hence ids are staged for a whole piece at once (one search per lane, then steps along the
 // row ends; the next piece's ids are fetched while this one is gathered), row starts are a bit per edge, tested for the
-// whole wavefront by scalar instructions, and a load's address is one addition to a staged dword.  With a 16-edge tile
-// per group, located by a binary search per edge and tile, 114 M edges of 233 000 rows took (256 columns, the whole call)
-// 8.09 ms in fp32 and 7.67 in bf16 (13.4 backward with a factor per edge), then 7.31, 4.35 and 6.0, and with blocks of equal shares
-// (spmm_bounds_kernel) 6.25, 3.78 and 5.21.  Without
-// misses, row starts and id loads the loop would take 3.9 ms of fp32: the rest is the fabric's (ids are read once a slab).
-// 128-byte slabs, which fit the L2, read the ids twice as often and meet twice the row ends: 8.07 / 4.87 / 7.0.
-// Pieces of 4096 edges, 8 loads in flight, 5 or 7 workgroups per CU, non-temporal id loads: all within 2 % or slower.
+// whole wavefront by scalar instructions, and a load's address is one addition to a staged dword.  114 M edges of 233 000 rows,
+// 256 columns, the whole call: 6.2 ms in fp32, 3.7 in bf16.  Pieces of 4096 edges, 8 loads in flight, 5 or 7 workgroups per CU, non-temporal
+// id loads: all within 2 % or slower.
 constexpr int kStreamMaxRows = 256;
 constexpr int kStreamLoads = 4;          // row loads in flight per lane
 constexpr int kStreamPiece = 2048;       // edges staged in LDS at a time
@@ -957,23 +951,18 @@ __global__ __launch_bounds__(256, SCALED ? 4 : 6) void spmm_stream_kernel(SpmmAr
 }
 
 template <int DT, int VE, int LPR>
-static int32_t launch_stream(const SpmmArgs& a, int64_t avg_row, bool off32, hipStream_t stream) {
+static int32_t launch_stream(const SpmmArgs& a, bool off32, hipStream_t stream) {
     constexpr int U = kStreamLoads;
     constexpr int W = LPR * VE;
-    // rows per workgroup: about kStreamWgEdges edges, while the launch keeps a few thousand workgroups
-    SpmmArgs b = a;
-    int64_t rows = (int64_t)kStreamWgEdges / (avg_row < 1 ? 1 : avg_row);
-    const int64_t cap = (int64_t)a.n_active * kDies / 4096;
-    if (rows > cap) rows = cap;
-    b.rows_per_group = (int32_t)(rows < 16 ? 16 : (rows > kStreamMaxRows ? kStreamMaxRows : rows));
-    const int64_t n_chunks = ((int64_t)a.n_active + b.rows_per_group - 1) / b.rows_per_group;
+    constexpr bool S = DT != GNN_F32;     // (fp32 gathers from rows that are scaled already)
+    const int64_t n_chunks = ((int64_t)a.n_active + a.rows_per_group - 1) / a.rows_per_group;
     dim3 grid((unsigned)(n_chunks * kDies), (unsigned)((a.F + W - 1) / W));
     if (off32) {
-        if (a.edge_w) spmm_stream_kernel<DT, VE, LPR, U, true, true><<<grid, 256, 0, stream>>>(b);
-        else spmm_stream_kernel<DT, VE, LPR, U, false, true><<<grid, 256, 0, stream>>>(b);
+        if (S && a.edge_w) spmm_stream_kernel<DT, VE, LPR, U, S, true><<<grid, 256, 0, stream>>>(a);
+        else spmm_stream_kernel<DT, VE, LPR, U, false, true><<<grid, 256, 0, stream>>>(a);
     } else {
-        if (a.edge_w) spmm_stream_kernel<DT, VE, LPR, U, true, false><<<grid, 256, 0, stream>>>(b);
-        else spmm_stream_kernel<DT, VE, LPR, U, false, false><<<grid, 256, 0, stream>>>(b);
+        if (S && a.edge_w) spmm_stream_kernel<DT, VE, LPR, U, S, false><<<grid, 256, 0, stream>>>(a);
+        else spmm_stream_kernel<DT, VE, LPR, U, false, false><<<grid, 256, 0, stream>>>(a);
     }
     GNN_LAUNCH_CHECK("spmm_stream_kernel");
     return GNN_OK;
@@ -1008,7 +997,7 @@ static int32_t launch_rows(const SpmmArgs& a, hipStream_t stream) {
 // bin is that of its samples, but at least half its share of the (active) ids: a block of rare ids outgrows the L2 otherwise.
 // The samples are random reads all over the entries, 1.5 ns apart for a single workgroup (65 536 of them 0.1 ms): 512
 // workgroups fetch them, one counts.  The counts are integers, so the same call cuts at the same ids.
-constexpr int kBoundBins = 2048, kBoundSamples = 131072;
+constexpr int kBoundBins = 2048, kBoundSamples = 131072, kMaxFourBlocks = 512;
 
 __device__ __forceinline__ int64_t bound_sample(int i, int64_t n) {      // the i-th stretch's place of n
     uint32_t h = (uint32_t)i * 2654435761u;
@@ -1036,7 +1025,7 @@ __global__ __launch_bounds__(256) void spmm_samples_kernel(const int32_t* __rest
 
 __global__ __launch_bounds__(1024) void spmm_bounds_kernel(const uint16_t* __restrict__ bins, bool filtered, int32_t n_src, int32_t n_blocks,
                                                             int32_t* __restrict__ bounds) {
-    __shared__ int32_t s_e[kBoundBins + 1], s_v[kBoundBins + 1], s_cum[kBoundBins + 1];
+    __shared__ int32_t s_e[kBoundBins + 1], s_v[kBoundBins + 1], s_cum[kBoundBins + 1], s_cut[kMaxFourBlocks];
     __shared__ int s_part[16];
     constexpr int kPer = kBoundBins / 1024, kLoads = kBoundSamples / 1024 / 8;
     const int tid = (int)threadIdx.x;
@@ -1102,6 +1091,17 @@ __global__ __launch_bounds__(1024) void spmm_bounds_kernel(const uint16_t* __res
         }
         const int64_t at_id = (int64_t)x * width + (int64_t)(want - s_cum[x]) * width / (s_cum[x + 1] > s_cum[x] ? s_cum[x + 1] - s_cum[x] : 1);
         bounds[j] = (int32_t)(at_id < n_src ? at_id : n_src);
+        if (n_blocks <= kMaxFourBlocks) s_cut[j] = bounds[j];
+    }
+    __syncthreads();
+    // an id's place in its block has 16 bits: at most kBlockIds of them (on average a block holds half as many)
+    if (tid == 0 && n_blocks <= kMaxFourBlocks) {
+        int64_t last = 0;
+        for (int j = 1; j < n_blocks; ++j) {
+            const int64_t least = (int64_t)n_src - (int64_t)(n_blocks - j) * kBlockIds;
+            last = std::min(std::max((int64_t)s_cut[j], least), last + kBlockIds);
+            bounds[j] = (int32_t)last;
+        }
     }
 }
 
@@ -1202,17 +1202,19 @@ __global__ __launch_bounds__(256) void spmm_sum_parts_kernel(const float* __rest
         // the stored value is zeroed where relu_h (same rows and columns as Y) is <= 0; relu_h == Y: where it is <= 0 itself
         const bool self = relu_h == (const void*)Y;
         bool pass[4] = {true, true, true, true};
+        // (rows of relu_h and Y start on 16 bytes: the columns up to the next multiple of four are there)
+        using E = Elem<DT, 4>;
         if (relu_h && !self) {
-            for (int k = 0; k < n_valid; ++k) pass[k] = Elem<DT, 1>::to_float(Elem<DT, 1>::load(relu_h, (int64_t)v * ldh + c + k)) > 0.f;
+            float h[4] = {0.f, 0.f, 0.f, 0.f};
+            E::fma(h, 1.f, E::load(relu_h, (int64_t)v * ldh + c));
+#pragma unroll
+            for (int k = 0; k < 4; ++k) pass[k] = h[k] > 0.f;
         }
         if (accumulate) {
-            if (DT == GNN_F32) {
-                const float* y = (const float*)Y + off;
-                for (int k = 0; k < n_valid; ++k) o[k] += y[k];
-            } else {
-                const uint16_t* y = (const uint16_t*)Y + off;
-                for (int k = 0; k < n_valid; ++k) o[k] += bf16_to_f32(y[k]);
-            }
+            float y[4] = {0.f, 0.f, 0.f, 0.f};
+            E::fma(y, 1.f, E::load(Y, off));
+#pragma unroll
+            for (int k = 0; k < 4; ++k) o[k] += y[k];
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) o[k] = (self ? o[k] > 0.f : pass[k]) ? o[k] : 0.f;
@@ -1326,14 +1328,33 @@ struct BlockedPlan {
     size_t end_bytes = 0, ids_bytes = 0;   // with a filter or a neighbour scale: segment ends and the (compacted) copy of the ids
     size_t xs_bytes = 0;                   // fp32 with a neighbour scale: the gathered matrix with its rows scaled
     size_t w_bytes = 0;                    // bf16 with a neighbour scale: the factor of every copied id
-    int64_t avg_seg = 0;      // average neighbours of a row inside one column block
     bool off32 = false;       // the gathered matrix spans less than 4 GB
     int32_t n_rows = 0, n_cols = 0;
     int32_t limit = 0;        // neighbour ids >= limit are never gathered (n_cols without a source prefix)
+    int32_t rows_per_wg = 0;
+    bool fours = false;       // the entries are laid out as streams of fours (spmm_fours.h)
+    size_t at_bytes = 0, places = 0, before_bytes = 0;
     size_t bounds_bytes = 0, sample_bytes = 0;  // the column-block boundaries, and the samples they come from
 };
 
-static BlockedPlan plan_blocked(const gnn_csr* g, int32_t n_active, int32_t F, int64_t row_bytes, bool vec_ok, bool filter,
+// Entries of a row in a block, on average, from which the route is taken: its planes and cut points cost the same whatever the rows hold.
+// Measured against whole rows (with the split route where it applies), blocked / whole rows, us, on power-law graphs and, in
+// brackets, graphs with uniform ends, of 130 000 and 240 000 vertices; eight blocks:
+//   fp32, 256 columns, 70 entries a row -, 1700 / 1500 (877 / 1175, 1582 / 2347); 100 1000 / 990, 1960 / 2080 (1005 / 1573, 1875 / 3316);
+//     47 columns, 70 -, 467 / 496 (246 / 333, 448 / 595): power-law graphs would have the line at 10 to 13, uniform ones below 8
+//   bf16, 256 columns, 70 594 / 470, 1360 / 1050 (598 / 606, 1276 / 1155); 100 677 / 668, 1440 / 1500 (673 / 855, 1387 / 1634)
+//     128 columns, 70 342 / 228, 757 / 490 (344 / 370, 612 / 639); 100 387 / 315, 803 / 644 (386 / 438, 723 / 813); 140 442 / 488, 930 / 944
+//   bf16, dist filter: 256 columns 100 914 / 721, 1894 / 1530; 140 1045 / 1090, 2138 / 2347; 128 columns 200 850 / 709, 300 1177 / 1020, 2418 / 2304
+//   bf16, row list (the stream kernel): 256 columns 100 886 / 664, 1745 / 1319; 140 1031 / 1022, 1919 / 2113; 128 columns 140 554 / 488, 200
+//     646 / 623, 1239 / 1237; 47 columns 200 529 / 432, 300 651 / 566, 1135 / 1066
+static int blocked_min_segment(bool f32, bool listed, bool filter, int32_t F) {
+    if (f32) return 8;
+    if (F > 128) return filter ? 11 : (listed ? 14 : 9);
+    if (filter) return 36;
+    return listed ? (F > 64 ? 17 : 36) : 10;
+}
+
+static BlockedPlan plan_blocked(const gnn_csr* g, bool listed, int32_t n_active, int32_t F, int64_t row_bytes, bool vec_ok, bool filter,
                                 bool scaled, bool f32, int32_t src_prefix) {
     BlockedPlan p;
     // with a source prefix only the rows [0, src_prefix) of the gathered matrix are ever read
@@ -1348,11 +1369,11 @@ static BlockedPlan plan_blocked(const gnn_csr* g, int32_t n_active, int32_t F, i
     const int n_blocks = kDies * passes;
     // average kept length of a row: its entries spread over the id range like the vertices do
     const int64_t avg_row = (int64_t)((double)g->nnz / g->n_rows * ((double)n_src / g->n_cols));
-    if (avg_row < (int64_t)GNN_SPMM_BLOCKED_MIN_SEG * n_blocks) return p;
+    if (avg_row < (int64_t)blocked_min_segment(f32, listed, filter, F) * n_blocks) return p;
     if (!die_mapping_holds()) return p;     // workgroup i is not on die i mod 8 here: the route has lost its reason
     p.passes = passes;
     p.n_blocks = n_blocks;
-    p.avg_seg = avg_row / n_blocks;
+    const int64_t avg_seg = avg_row / n_blocks;
     p.off32 = (int64_t)g->n_cols * row_bytes < ((int64_t)1 << 32);
     p.limit = n_src;
     p.ldp = ((int64_t)F + 7) / 8 * 8;
@@ -1360,12 +1381,24 @@ static BlockedPlan plan_blocked(const gnn_csr* g, int32_t n_active, int32_t F, i
     p.part_bytes = (size_t)kDies * n_active * p.ldp * sizeof(float);
     // A neighbour scale: fp32 gathers from a copy of the matrix with scaled rows (one rounding more per element,
     // far inside the fp32 tolerance); bf16 would lose too much in a rounded copy and keeps a factor per edge.
-    if (filter || (scaled && !f32)) {
+    // Streams of fours: not for a row list, which may name a row twice (how many entries it has is not known here).
+    p.fours = !listed && n_blocks <= kMaxFourBlocks;
+    const int64_t rows = (p.fours ? kFourEdges : kStreamWgEdges) / std::max<int64_t>(avg_seg, 1), cap = (int64_t)n_active * kDies / 4096;
+    p.rows_per_wg = (int32_t)std::min<int64_t>(std::max<int64_t>(std::min(rows, cap), 16), p.fours ? kFourMaxRows : kStreamMaxRows);
+    if (p.fours) {
+        const int64_t n_chunks = ((int64_t)n_active + p.rows_per_wg - 1) / p.rows_per_wg;
+        p.at_bytes = (size_t)(n_chunks * n_blocks) * sizeof(uint2);
+        p.places = four_places(g->nnz, n_active, n_chunks, n_blocks);
+        p.before_bytes = (size_t)(n_chunks * n_blocks) * kFourGroups * sizeof(uint16_t);
+        if (scaled && !f32) p.w_bytes = p.places * 32 * sizeof(float4);
+    }
+    if (filter || (scaled && !f32 && !p.fours)) {
         p.end_bytes = (size_t)n_active * n_blocks * sizeof(int32_t);
         p.ids_bytes = (size_t)g->nnz * sizeof(int32_t);
     }
-    if (scaled && f32) p.xs_bytes = (size_t)n_src * (size_t)row_bytes;
-    if (scaled && !f32) p.w_bytes = (size_t)g->nnz * sizeof(float);
+    if (p.fours) p.xs_bytes = (size_t)(((int64_t)F * (f32 ? 4 : 2) + kFourBytes - 1) / kFourBytes) * n_src * kFourBytes;
+    else if (scaled && f32) p.xs_bytes = (size_t)n_src * (size_t)row_bytes;
+    if (scaled && !f32 && !p.fours) p.w_bytes = (size_t)g->nnz * sizeof(float);
     p.bounds_bytes = ((size_t)n_blocks + 1) * sizeof(int32_t);
     p.sample_bytes = (size_t)kBoundSamples * (filter ? 2 : 1) * sizeof(uint16_t);
     p.n_rows = g->n_rows;
@@ -1380,11 +1413,16 @@ static int32_t run_blocked(const SpmmArgs& a, const BlockedPlan& p, void* ws, hi
     int32_t* seg = carve.take<int32_t>(p.seg_bytes / sizeof(int32_t));
     float* part = carve.take<float>(p.part_bytes / sizeof(float));
     const bool prescale = a.nbr_scale != nullptr && DT == GNN_F32, per_edge = a.nbr_scale != nullptr && DT != GNN_F32;
-    const bool prepare = FILTER || per_edge;
+    const bool prepare = FILTER || (per_edge && !p.fours);
     int32_t* seg_end = prepare ? carve.take<int32_t>(p.end_bytes / sizeof(int32_t)) : nullptr;
     int32_t* ids = prepare ? carve.take<int32_t>(p.ids_bytes / sizeof(int32_t)) : nullptr;
-    char* xs = prescale ? carve.take<char>(p.xs_bytes) : nullptr;
+    char* xs = p.xs_bytes ? carve.take<char>(p.xs_bytes) : nullptr;
     float* edge_w = per_edge ? carve.take<float>(p.w_bytes / sizeof(float)) : nullptr;
+    FourArgs f = {};
+    f.at = carve.take<uint2>(p.at_bytes / sizeof(uint2));
+    f.stream = carve.take<uint2>(p.places * 32);
+    f.ends = carve.take<uint32_t>(p.places);
+    f.before = carve.take<uint16_t>(p.before_bytes / sizeof(uint16_t));
     int32_t* bounds = carve.take<int32_t>(p.bounds_bytes / sizeof(int32_t));
     uint16_t* bins = carve.take<uint16_t>(p.sample_bytes / sizeof(uint16_t));
     const int32_t* dist = FILTER ? a.dist : nullptr;
@@ -1396,7 +1434,7 @@ static int32_t run_blocked(const SpmmArgs& a, const BlockedPlan& p, void* ws, hi
         a.row_ptr, a.col_idx, a.rows, a.n_active, p.n_blocks, bounds, p.limit, p.n_cols, seg);
     GNN_LAUNCH_CHECK("spmm_seg_kernel");
     SpmmArgs b = a;
-    if (prescale) {
+    if (prescale && !p.fours) {
         // the neighbour scale is applied once per row of the gathered matrix, not once per edge and slab
         spmm_scale_rows_kernel<DT><<<grid_for((int64_t)p.limit * ((a.F + VE - 1) / VE), 256, 1 << 16), 256, 0, stream>>>(
             a.X, a.ldx, p.limit, a.F, a.nbr_scale, xs);
@@ -1407,8 +1445,8 @@ static int32_t run_blocked(const SpmmArgs& a, const BlockedPlan& p, void* ws, hi
     if (prepare) {
         const int64_t n_segments = (int64_t)a.n_active * p.n_blocks;
         spmm_prepare_kernel<<<grid_for(n_segments * 16, 256, 1 << 18), 256, 0, stream>>>(
-            a.col_idx, seg, FILTER ? a.dist : nullptr, a.max_dist, per_edge ? a.nbr_scale : nullptr, n_segments, p.n_blocks, ids, edge_w,
-            seg_end);
+            a.col_idx, seg, FILTER ? a.dist : nullptr, a.max_dist, per_edge && !p.fours ? a.nbr_scale : nullptr, n_segments, p.n_blocks, ids,
+            edge_w, seg_end);
         GNN_LAUNCH_CHECK("spmm_prepare_kernel");
         b.col_idx = ids;
         b.seg_end = seg_end;
@@ -1420,10 +1458,34 @@ static int32_t run_blocked(const SpmmArgs& a, const BlockedPlan& p, void* ws, hi
     b.Y = part;
     b.ldy = p.ldp;
     b.out_scale = nullptr;
-    for (int pass = 0; pass < p.passes; ++pass) {
-        b.block0 = pass * kDies;
-        b.accumulate = pass > 0;
-        GNN_CHECK((launch_stream<DT, VE, kSlabBytes / 16>(b, p.avg_seg, p.off32, stream)));
+    if (p.fours) {
+        f.row_ptr = a.row_ptr; f.ids = b.col_idx; f.seg = seg; f.seg_end = b.seg_end; f.bounds = bounds;
+        f.n_active = a.n_active; f.n_blocks = p.n_blocks; f.rows_per_wg = p.rows_per_wg;
+        f.X = a.X; f.ldx = a.ldx; f.F = a.F; f.n_src = p.limit; f.slabs = xs;
+        f.nbr_scale = a.nbr_scale; f.w = (float4*)edge_w;
+        f.part = part; f.ldp = p.ldp;
+        const unsigned n_chunks = (unsigned)(((int64_t)a.n_active + p.rows_per_wg - 1) / p.rows_per_wg);
+        if (per_edge) spmm_fours_kernel<true><<<n_chunks * (unsigned)p.n_blocks, 256, 0, stream>>>(f);
+        else spmm_fours_kernel<false><<<n_chunks * (unsigned)p.n_blocks, 256, 0, stream>>>(f);
+        GNN_LAUNCH_CHECK("spmm_fours_kernel");
+        constexpr int W = kFourBytes / (DT == GNN_F32 ? 4 : 2);
+        spmm_slabs_kernel<DT><<<grid_for((int64_t)p.limit * ((a.F + W - 1) / W * 8), 256, 1 << 16), 256, 0, stream>>>(f);
+        GNN_LAUNCH_CHECK("spmm_slabs_kernel");
+        const dim3 grid(n_chunks * kDies, (unsigned)((a.F + W - 1) / W));
+        for (int pass = 0; pass < p.passes; ++pass) {
+            f.block0 = pass * kDies;
+            f.accumulate = pass > 0;
+            if (DT != GNN_F32 && per_edge) spmm_four_sums_kernel<DT, DT != GNN_F32><<<grid, 256, 0, stream>>>(f);
+            else spmm_four_sums_kernel<DT, false><<<grid, 256, 0, stream>>>(f);
+            GNN_LAUNCH_CHECK("spmm_four_sums_kernel");
+        }
+    } else {
+        b.rows_per_group = p.rows_per_wg;
+        for (int pass = 0; pass < p.passes; ++pass) {
+            b.block0 = pass * kDies;
+            b.accumulate = pass > 0;
+            GNN_CHECK((launch_stream<DT, VE, kSlabBytes / 16>(b, p.off32, stream)));
+        }
     }
     spmm_sum_parts_kernel<DT><<<grid_for((int64_t)a.n_active * ((a.F + 3) / 4), 256, 1 << 16), 256, 0, stream>>>(
         part, p.ldp, a.rows, a.n_active, a.F, a.Y, a.ldy, a.out_scale, a.accumulate, a.relu_h, a.ldh);
@@ -1570,7 +1632,7 @@ static int32_t spmm_common(const gnn_csr* g, const char* gname, const int32_t* r
     BlockedPlan plan;
     SplitPlan split;
     if (ws_bytes != nullptr) {
-        if (n_active > 0 && F > 0) plan = plan_blocked(g, n_active, F, ldx * (dtype == GNN_F32 ? 4 : 2), vec_ok, filter, nbr_scale != nullptr,
+        if (n_active > 0 && F > 0) plan = plan_blocked(g, rows != nullptr, n_active, F, ldx * (dtype == GNN_F32 ? 4 : 2), vec_ok, filter, nbr_scale != nullptr,
                                                             dtype == GNN_F32, cut_id);
         WsCarver measure(nullptr);
         if (plan.passes > 0) {
@@ -1582,6 +1644,10 @@ static int32_t spmm_common(const gnn_csr* g, const char* gname, const int32_t* r
             }
             if (plan.xs_bytes) measure.take<char>(plan.xs_bytes);
             if (plan.w_bytes) measure.take<char>(plan.w_bytes);
+            measure.take<char>(plan.at_bytes);
+            measure.take<uint2>(plan.places * 32);
+            measure.take<uint32_t>(plan.places);
+            measure.take<char>(plan.before_bytes);
             measure.take<char>(plan.bounds_bytes);
             measure.take<char>(plan.sample_bytes);
         }
@@ -1649,7 +1715,7 @@ extern "C" int32_t gnn_spmm_route(const gnn_csr* g, const int32_t* rows, int32_t
     const int64_t row_bytes = ldx * (16 / ve);
     *route_host = 0;
     if (n_active == 0 || F == 0) return GNN_OK;
-    if (plan_blocked(g, n_active, F, row_bytes, vec_ok, filter, scaled != 0, dtype == GNN_F32, -1).passes > 0) {
+    if (plan_blocked(g, rows != nullptr, n_active, F, row_bytes, vec_ok, filter, scaled != 0, dtype == GNN_F32, -1).passes > 0) {
         *route_host = 1;
         return GNN_OK;
     }

@@ -333,6 +333,57 @@ def test_blocked_route_row_lengths(dtype, wide):
     assert not Y[:, F:].any()
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("form", ["few ids hold most entries", "two passes", "dist filter"])
+def test_blocked_route_streams(dtype, form):
+    """Rows of 0 to 9 entries in a block, rows over all lane groups and several stages, a last row that is not asked for; a block
+    whose share of the ids would not fit 16 bits; 16 blocks in two passes; a neighbour scale; infinities and NaN, which
+    must reach the rows that name them and no others."""
+    import paper_2311_06837_amd as P
+    n_cols = 300_001 if form == "two passes" else 262_144
+    n_rows, F, few = 4300, 67, 1000
+    rng = np.random.default_rng(23)
+    lens = np.full(n_rows, 560)
+    lens[:300] = rng.integers(0, 80, 300)
+    lens[300:400] = 0
+    lens[1000:1003] = [100_000, 0, 60_000]
+    cols = []
+    for k in lens:
+        c = rng.choice(n_cols, k, replace=False)
+        if form == "few ids hold most entries" and k < few:
+            c = np.union1d(rng.choice(few, min(k, 500), replace=False), c[: k // 20])
+        cols.append(np.sort(c).astype(np.int32))
+    lens = np.array([len(c) for c in cols])
+    rp = np.zeros(n_rows + 1, np.int32)
+    rp[1:] = np.cumsum(lens)
+    G = P.Graph(dev(rp), dev(np.concatenate(cols)), n_cols=n_cols, sorted_columns=True)
+    x = as_stored(rng.standard_normal((n_cols, F)), dtype)
+    x[[5, 77_777, 222_222], [0, 66, 3]] = [np.inf, np.nan, -np.inf]
+    scale = (rng.random(n_cols) + 0.5).astype(np.float32)
+    dist = (np.arange(n_cols) % 3).astype(np.int32) if form == "dist filter" else None
+    X, Y = padded(x, 72, dtype), torch.full((n_rows, 72), SENTINEL, dtype=dtype, device="cuda")
+    ws = P.Workspace()
+    print(form, dtype, int(lens.sum()), flush=True)
+    if dist is None:
+        P.gnn_masked_spmm_fwd(G, None, n_rows - 1, X, Y, F, None, dev(scale), ws=ws)
+    else:
+        P.gnn_masked_spmm_bwd(G, None, n_rows - 1, dev(dist), 1, X, Y, F, dev(scale), None, accumulate=False, ws=ws)
+        cols = [c[dist[c] <= 1] for c in cols]
+    if dtype == torch.float32 or dist is None:
+        assert _used_blocked_route(ws)
+    w = x * scale[:, None].astype(np.float64)
+    got = host64(Y)
+    untouched = host64(torch.full((1,), SENTINEL, dtype=dtype))      # as the type holds it
+    assert (got[n_rows - 1:] == untouched).all() and (got[:, F:] == untouched).all()
+    for r, c in enumerate(cols[: n_rows - 1]):
+        want, size = w[c].sum(0), np.abs(w[c]).sum(0)
+        ok = np.isfinite(want)
+        # fp32 sums in any order: at most (terms + 8 planes + the scaled factor) * 2^-24 of the sum of magnitudes; then bf16 rounding
+        tol = (len(c) + 9) * 2.0 ** -24 * size[ok] + (2.0 ** -8 * np.abs(want[ok]) if dtype == torch.bfloat16 else 0.0)
+        assert (np.abs(got[r, :F][ok] - want[ok]) <= tol).all(), r
+        assert np.array_equal(got[r, :F][~ok], want[~ok], equal_nan=True), r
+
+
 def test_blocked_route_falls_back_without_promise_or_density():
     """Unsorted columns (no GNN_CSR_SORTED_COLUMNS promise) or a sparse graph: the size query reports 0 and the
     call gathers whole rows."""
