@@ -7,10 +7,12 @@
 //                        ballot that lane 0 ORs into the bitmap (at most two words), so the result does not depend
 //                        on which group runs first.  The threshold rule has a fixed pair; the fanout rule selects its
 //                        pair in registers (group_kth).
-//   lm_mask_long_kernel  the longer rows, a wavefront each.  Up to 1024 entries the fanout rule holds the row's keys in
-//                        registers; beyond, one sweep lists the entries between two guessed keys in LDS (the keys are uniform:
-//                        the pair lies between them, and they hold some 12 * sqrt(fanout) entries) and counts those below;
-//                        the pair is selected from that list and a second sweep writes the bits.  Where the guess fails, or
+//   lm_mask_long_kernel  the longer rows, a wavefront each.  Up to 1024 entries the fanout rule holds the upper halves of the row's
+//                        keys in registers (up to 256 entries in a quarter of them: the rounds look at every place); beyond,
+//                        one sweep lists the entries between two guessed keys in LDS (the keys are uniform: the pair lies
+//                        between them, and they hold some 12 * sqrt(fanout) entries) and counts those below; the pair is
+//                        selected from that list.  If nothing lies below (fanouts up to 58), the bits are written from the
+//                        list, else by a second sweep.  Where the guess fails, or
 //                        the fanout is too large for the list (above 4624), `fanout` rounds over the row itself find the pair.
 //   lm_transpose_kernel  the same mask in the positions of the transposed graph (backward aggregation): entry q =
 //                        (row u, column v) of the transposed graph looks up u in row v of the graph by binary search.
@@ -20,9 +22,11 @@
 //                        keys are equal.  A workgroup takes 4096 consecutive entries whatever rows they belong to, so
 //                        every word of the bitmap has one writer: no atomics, nothing to clear, no long rows.
 // Bound: the random reads (transposed), the hash (two 64-bit multiplications a mix) and the selection.  Measured on a
-// 1.2M-vertex / 60M-entry power-law graph, fanout 10: forward and transposed mask 2.61 -> 0.95 ms (forward 1.5 -> 0.53,
+// 1.2M-vertex / 60M-entry power-law graph, fanout 10: forward and transposed mask 2.61 -> 0.77 ms (forward 1.5 -> 0.35,
 // transposed 1.09 -> 0.42, its random reads into a 9.6 MB table), against `fanout` rounds over 64-bit pairs and a lane group
-// per row of the transposed graph.
+// per row of the transposed graph.  Of the forward mask, long rows 335 us with whole keys in all registers whatever the length and two
+// sweeps over rows above 1024, 288 by length and with upper halves, 177 with one sweep; short rows 196, 170 with half of the
+// places where no row of the wavefront has more than 32.  300 000 vertices of degree 190, fanout 15, both masks: 797 -> 575.
 #include "common.h"
 #include "hashkey.h"
 
@@ -81,9 +85,12 @@ __global__ __launch_bounds__(256) void lm_mask_kernel(const int32_t* __restrict_
             const uint32_t p = (uint32_t)s + j * kLmLanes + sl;   // (past the row's end, a position may not fit an int32_t)
             u[j] = p < (uint32_t)e ? col_idx[p] : -1;
         }
+        // most wavefronts have four rows of up to 32 entries: hash and select among half of the places then
+        const bool half = __ballot(e - s > kLmShortRow / 2) == 0ull;   // uniform over the wavefront
 #pragma unroll
         for (int j = 0; j < kPerLane; ++j) {
-            key[j] = edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)(u[j] >= 0 ? u[j] : 0));
+            key[j] = ~0ull;
+            if (j < kPerLane / 2 || !half) key[j] = edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)(u[j] >= 0 ? u[j] : 0));
             cand |= u[j] >= 0 ? 1u << j : 0u;
         }
         // pairs (key, id) <= (thr_k, thr_u) are kept
@@ -96,11 +103,20 @@ __global__ __launch_bounds__(256) void lm_mask_kernel(const int32_t* __restrict_
                 thr_u = -1;  // nothing is <= (0, -1): ids are non-negative
             }
             const bool need = fanout > 0 && e - s > fanout;  // uniform over the 16-lane group
-            if (__ballot(need) != 0ull) group_kth<kPerLane, kLmLanes>(key, u, cand, fanout, need, thr_k, thr_u);
+            if (__ballot(need) != 0ull) {
+                if (half) {
+                    const uint64_t k2[2] = {key[0], key[1]};
+                    const int32_t u2[2] = {u[0], u[1]};
+                    group_kth<2, kLmLanes>(k2, u2, cand, fanout, need, thr_k, thr_u);
+                } else {
+                    group_kth<kPerLane, kLmLanes>(key, u, cand, fanout, need, thr_k, thr_u);
+                }
+            }
         }
         int32_t kept = 0;
 #pragma unroll
         for (int j = 0; j < kPerLane; ++j) {
+            if (j >= kPerLane / 2 && half) break;   // uniform over the wavefront
             const bool keep = u[j] >= 0 && !pair_less(thr_k, thr_u, key[j], u[j]);
             const uint32_t m = lm_group_ballot(keep, sub);
             kept += __popc(m);
@@ -125,53 +141,10 @@ __device__ __forceinline__ void lm_or_tile(uint32_t* __restrict__ bits, int64_t 
     if (w != 0u) atomicOr(&bits[(p0 >> 5) + lane], w);
 }
 
-// The fanout rule's pair of a row of more than kLmRegRow (> fanout) entries; see the head of the file.
-template <int CAP>
-__device__ __forceinline__ void lm_pair_of_hub(const int32_t* __restrict__ col_idx, int32_t v, int32_t s, int32_t e, int32_t fanout,
-                                               uint64_t seed_layer_mixed, uint64_t* key, int32_t* id, uint64_t& thr_k, int32_t& thr_u) {
-    constexpr int kU = 4;
+// The fanout rule's pair of a row of more than `fanout` entries, one round over the row per kept entry.
+__device__ __forceinline__ void lm_pair_by_rounds(const int32_t* __restrict__ col_idx, int32_t v, int32_t s, int32_t e, int32_t fanout,
+                                                  uint64_t seed_layer_mixed, uint64_t& thr_k, int32_t& thr_u) {
     const int lane = lane_id();
-    const uint64_t lanes_below = (1ull << lane) - 1ull;
-    const int32_t spread = guess_spread(fanout);
-    int32_t n_list = 0, n_below = 0;
-    if (fanout <= CAP * 8) {   // (the list may hold it: see lm_list_need)
-        const uint64_t low = fanout > spread ? key_guess(fanout - spread, e - s) : 0ull, high = key_guess(fanout + spread, e - s);
-        for (int64_t p = s; p < e; p += kU * kWave) {
-            int32_t u[kU];
-#pragma unroll
-            for (int j = 0; j < kU; ++j) u[j] = p + j * kWave + lane < e ? col_idx[p + j * kWave + lane] : -1;
-#pragma unroll
-            for (int j = 0; j < kU; ++j) {
-                const uint64_t k = edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)(u[j] >= 0 ? u[j] : 0));
-                const bool take = u[j] >= 0 && k >= low && k <= high;
-                n_below += __popcll(__ballot(u[j] >= 0 && k < low));
-                const uint64_t m = __ballot(take);
-                const int32_t pos = n_list + __popcll(m & lanes_below);
-                if (take && pos < CAP) {
-                    key[pos] = k;
-                    id[pos] = u[j];
-                }
-                n_list += __popcll(m);
-            }
-        }
-        wave_lds_sync();
-    }
-    if (n_below < fanout && n_below + n_list >= fanout && n_list <= CAP) {   // uniform over the wavefront
-        constexpr int NP = CAP / kWave;
-        uint64_t k[NP];
-        int32_t u[NP];
-        uint32_t cand = 0u;
-#pragma unroll
-        for (int j = 0; j < NP; ++j) {
-            const bool in = j * kWave + lane < n_list;
-            k[j] = in ? key[j * kWave + lane] : ~0ull;
-            u[j] = in ? id[j * kWave + lane] : 0x7fffffff;
-            cand |= in ? 1u << j : 0u;
-        }
-        group_kth<NP, kWave>(k, u, cand, fanout - n_below, true, thr_k, thr_u);
-        wave_lds_sync();   // the list is read before the next row overwrites it
-        return;
-    }
     uint64_t prev_k = 0ull;
     int32_t prev_u = -1;
     for (int32_t round = 0; round < fanout; ++round) {
@@ -201,13 +174,145 @@ __device__ __forceinline__ void lm_pair_of_hub(const int32_t* __restrict__ col_i
     thr_u = prev_u;
 }
 
+// A row of up to NP * 64 entries by the fanout rule: finds the pair, writes the bits, returns how many are kept.  A lane holds ids and
+// the keys' upper halves; a whole key is made again where its half decides nothing: for the pair itself, and, where the half
+// of the k-th key is that of others too (about n^2 / 2^33 of the rows), in rounds over the row.
+template <int NP>
+__device__ __forceinline__ int32_t lm_row_in_registers(const int32_t* __restrict__ col_idx, uint32_t* __restrict__ bits, int32_t v, int32_t s,
+                                                       int32_t e, int32_t fanout, uint64_t seed_layer_mixed, uint64_t& thr_k, int32_t& thr_u) {
+    const int lane = lane_id();
+    int32_t u[NP];
+    uint32_t half[NP];
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+        const uint32_t p = (uint32_t)s + j * kWave + lane;
+        u[j] = p < (uint32_t)e ? col_idx[p] : -1;
+    }
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+        half[j] = ~0u;
+        if ((uint32_t)s + j * kWave < (uint32_t)e) {   // uniform over the wavefront
+            const uint64_t k = edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)(u[j] >= 0 ? u[j] : 0));
+            half[j] = u[j] >= 0 ? (uint32_t)(k >> 32) : ~0u;
+        }
+    }
+    uint32_t top = fanout > 0 ? ~0u : 0u;      // entries up to this half stay
+    bool whole = true;                         // the half decides
+    if (fanout > 0 && e - s > fanout) {
+        uint32_t base = 0u;
+        for (int32_t round = 0; round < fanout; ++round) {   // smallest above the previous one: what lies below wraps around to the top
+            uint32_t m = ~0u;
+#pragma unroll
+            for (int j = 0; j < NP; ++j) m = min(m, half[j] - base);
+            top = base + group_min<kWave>(m);
+            base = top + 1u;
+        }
+        int32_t upto = 0, id = 0;
+        uint64_t holders = 0ull;
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            upto += __popcll(__ballot(u[j] >= 0 && half[j] <= top));
+            const uint64_t h = __ballot(u[j] >= 0 && half[j] == top);
+            if (h != 0ull) {      // uniform over the wavefront
+                holders = h;
+                id = __builtin_amdgcn_readlane(u[j], __ffsll((unsigned long long)h) - 1);
+            }
+        }
+        whole = upto == fanout && holders != 0ull;
+        if (whole) {
+            thr_u = id;
+            thr_k = edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)id);
+        } else {
+            lm_pair_by_rounds(col_idx, v, s, e, fanout, seed_layer_mixed, thr_k, thr_u);
+        }
+    }
+    int32_t kept = 0;
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+        if ((uint32_t)s + j * kWave < (uint32_t)e) {   // uniform over the wavefront
+            bool keep = u[j] >= 0 && fanout > 0 && half[j] <= top;
+            if (!whole) keep = u[j] >= 0 && !pair_less(thr_k, thr_u, edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)(u[j] >= 0 ? u[j] : 0)), u[j]);
+            const uint64_t m = __ballot(keep);
+            kept += __popcll(m);
+            lm_or_tile(bits, (int64_t)s + j * kWave, m);
+        }
+    }
+    return kept;
+}
+
+// The fanout rule's pair of a row of more than kLmRegRow (> fanout) entries; see the head of the file.  Where the list holds every
+// entry below the pair it writes the bits, too, and returns how many are kept, else -1.
+template <int CAP>
+__device__ __forceinline__ int32_t lm_pair_of_hub(const int32_t* __restrict__ col_idx, uint32_t* __restrict__ bits, int32_t v, int32_t s, int32_t e,
+                                               int32_t fanout, uint64_t seed_layer_mixed, uint64_t* key, int32_t* at, uint64_t& thr_k,
+                                               int32_t& thr_u) {
+    constexpr int kU = 4;
+    const int lane = lane_id();
+    const uint64_t lanes_below = (1ull << lane) - 1ull;
+    const int32_t spread = guess_spread(fanout);
+    int32_t n_list = 0, n_below = 0;
+    if (fanout <= CAP * 8) {   // (the list may hold it: see lm_list_need)
+        const uint64_t low = fanout > spread ? key_guess(fanout - spread, e - s) : 0ull, high = key_guess(fanout + spread, e - s);
+        for (int64_t p = s; p < e; p += kU * kWave) {
+            int32_t u[kU];
+#pragma unroll
+            for (int j = 0; j < kU; ++j) u[j] = p + j * kWave + lane < e ? col_idx[p + j * kWave + lane] : -1;
+#pragma unroll
+            for (int j = 0; j < kU; ++j) {
+                const uint64_t k = edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)(u[j] >= 0 ? u[j] : 0));
+                const bool take = u[j] >= 0 && k >= low && k <= high;
+                n_below += __popcll(__ballot(u[j] >= 0 && k < low));
+                const uint64_t m = __ballot(take);
+                const int32_t pos = n_list + __popcll(m & lanes_below);
+                if (take && pos < CAP) {
+                    key[pos] = k;
+                    at[pos] = (int32_t)(p + j * kWave + lane);
+                }
+                n_list += __popcll(m);
+            }
+        }
+        wave_lds_sync();
+    }
+    if (n_below < fanout && n_below + n_list >= fanout && n_list <= CAP) {   // uniform over the wavefront
+        constexpr int NP = CAP / kWave;
+        uint64_t k[NP];
+        int32_t u[NP];
+        uint32_t cand = 0u;
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            const bool in = j * kWave + lane < n_list;
+            k[j] = in ? key[j * kWave + lane] : ~0ull;
+            u[j] = in ? col_idx[at[j * kWave + lane]] : 0x7fffffff;
+            cand |= in ? 1u << j : 0u;
+        }
+        group_kth<NP, kWave>(k, u, cand, fanout - n_below, true, thr_k, thr_u);
+        int32_t kept = -1;
+        if (n_below == 0) {     // uniform over the wavefront
+            kept = 0;
+#pragma unroll
+            for (int j = 0; j < NP; ++j) {
+                const bool keep = ((cand >> j) & 1u) != 0u && !pair_less(thr_k, thr_u, k[j], u[j]);
+                kept += __popcll(__ballot(keep));
+                if (keep) {
+                    const int32_t p = at[j * kWave + lane];
+                    atomicOr(&bits[p >> 5], 1u << (p & 31));
+                }
+            }
+        }
+        wave_lds_sync();   // the list is read before the next row overwrites it
+        return kept;
+    }
+    lm_pair_by_rounds(col_idx, v, s, e, fanout, seed_layer_mixed, thr_k, thr_u);
+    return -1;
+}
+
 // Rows longer than kLmShortRow: a wavefront looks at up to kLmLook rows of the list and takes the long ones one by one.
 // 64 wavefronts share a stretch of the list and take its rows in turn, one row of every 64: long rows that follow each other
 // (a graph numbered by degree, a list of hubs) go to different wavefronts, a list of fewer rows than the chip holds wavefronts
 // gives each of its rows one, and what runs at a time still lies close together.  From one group of 64 rows to the next the
 // wavefronts move by 37 places, so that long rows at regular distances do not meet in one of them.
 // Measured (fanout 10): 64 rows of 100 000 entries at the head of a list 10.5 ms with sixteen consecutive rows for a wavefront,
-// now 0.74; 2000 rows of 490 entries 121 us, now 39; 1.2M rows of 50 (with the short ones) 541 us, now 533 - 595 with
+// then 0.74; 2000 rows of 490 entries 121 us, then 39; 1.2M rows of 50 (with the short ones) 541 us, then 533 - 595 with
 // rows as far apart as there are wavefronts, which then run all over the graph at a time.
 constexpr int kLmLook = 32;
 constexpr int kLmShare = 64;
@@ -220,7 +325,7 @@ __global__ __launch_bounds__(256) void lm_mask_long_kernel(const int32_t* __rest
                                                            int32_t* __restrict__ kept_len, uint64_t* __restrict__ row_thr_key,
                                                            int32_t* __restrict__ row_thr_id, int32_t look) {
     __shared__ uint64_t s_key[4][CAP];
-    __shared__ int32_t s_id[4][CAP];
+    __shared__ int32_t s_at[4][CAP];
     const int lane = lane_id(), wave = (int)(threadIdx.x >> 6);
     const int64_t wave_g = (int64_t)blockIdx.x * 4 + wave;
     const int64_t group = wave_g / kLmShare * look + lane;       // of 64 rows; lanes 0 .. look - 1
@@ -244,38 +349,17 @@ __global__ __launch_bounds__(256) void lm_mask_long_kernel(const int32_t* __rest
             thr_k = fanout == 0 ? 0ull : ~0ull;
             thr_u = fanout == 0 ? -1 : 0x7fffffff;
         }
-        if (by_fanout && e - s <= kLmRegRow) {
-            constexpr int NP = kLmRegRow / kWave;
-            uint64_t key[NP];
-            int32_t u[NP];
-            uint32_t cand = 0u;
-#pragma unroll
-            for (int j = 0; j < NP; ++j) {
-                const uint32_t p = (uint32_t)s + j * kWave + lane;
-                u[j] = p < (uint32_t)e ? col_idx[p] : -1;
-            }
-#pragma unroll
-            for (int j = 0; j < NP; ++j) {
-                key[j] = ~0ull;
-                if ((uint32_t)s + j * kWave < (uint32_t)e) {   // uniform over the wavefront
-                    key[j] = edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)(u[j] >= 0 ? u[j] : 0));
-                    cand |= u[j] >= 0 ? 1u << j : 0u;
-                }
-            }
-            if (fanout > 0 && e - s > fanout) group_kth<NP, kWave>(key, u, cand, fanout, true, thr_k, thr_u);
-#pragma unroll
-            for (int j = 0; j < NP; ++j) {
-                if ((uint32_t)s + j * kWave < (uint32_t)e) {   // uniform over the wavefront
-                    const uint64_t m = __ballot(u[j] >= 0 && !pair_less(thr_k, thr_u, key[j], u[j]));
-                    kept += __popcll(m);
-                    lm_or_tile(bits, (int64_t)s + j * kWave, m);
-                }
-            }
+        if (by_fanout && e - s <= kLmRegRow / 4) {
+            kept = lm_row_in_registers<kLmRegRow / 4 / kWave>(col_idx, bits, v, s, e, fanout, seed_layer_mixed, thr_k, thr_u);
+        } else if (by_fanout && e - s <= kLmRegRow) {
+            kept = lm_row_in_registers<kLmRegRow / kWave>(col_idx, bits, v, s, e, fanout, seed_layer_mixed, thr_k, thr_u);
         } else {
+            int32_t written = -1;
             if (by_fanout && fanout > 0 && e - s > fanout)
-                lm_pair_of_hub<CAP>(col_idx, v, s, e, fanout, seed_layer_mixed, s_key[wave], s_id[wave], thr_k, thr_u);
+                written = lm_pair_of_hub<CAP>(col_idx, bits, v, s, e, fanout, seed_layer_mixed, s_key[wave], s_at[wave], thr_k, thr_u);
+            if (written >= 0) kept = written;
             constexpr int kU = 4;
-            for (int64_t p = s; p < e; p += kU * kWave) {
+            for (int64_t p = s; p < e && written < 0; p += kU * kWave) {
                 int32_t u[kU];
 #pragma unroll
                 for (int j = 0; j < kU; ++j) u[j] = p + j * kWave + lane < e ? col_idx[p + j * kWave + lane] : -1;

@@ -134,6 +134,14 @@ def _mix64(x):
         return x ^ (x >> np.uint64(31))
 
 
+@pytest.mark.parametrize("fanout", [1, 15, 16, 31, 32, 33, 58, 59, 255, 256])
+def test_fanouts_around_the_places_of_a_row(fanout):
+    """Four rows of a wavefront that fit half of their places, or of which one does not (32); a quarter of a wavefront's registers
+    (256); long rows whose list begins at nothing (58) or not."""
+    short = [1, 16, 17, 31, 32, 32, 5, 0, 33, 2, 3, 4, 32, 31, 30, 34, 48, 63, 64, 1]
+    _mask_case(_rows_of(short + [65, 128, 255, 256, 257, 258, 511, 1023, 1025, 2000, 9000] * 2, 30000, fanout + 1), None, "fanout", fanout, 2, 5)
+
+
 @pytest.mark.parametrize("length", [40, 64, 65, 700, 1024, 1025, 3000])
 def test_masks_when_the_upper_halves_of_two_keys_are_equal(length):
     """The selection compares upper halves of keys and falls back to whole pairs when the k-th is not alone with its half:
