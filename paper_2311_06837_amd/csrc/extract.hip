@@ -15,7 +15,8 @@
 // length (rowlists.h): sixteen lanes, a wavefront (both hold the whole row in registers and probe once) or a workgroup.
 // What bounds it is the random probe of every entry.  Measured, active sets + extraction of a 1M-vertex / 20M-entry
 // graph, eight rings: 2.25 -> 0.96 ms; the fill pass alone, 1.54 ms with sixteen lanes on every row and a sweep per
-// distance (the tail of the long rows most of it), takes 0.24 + 0.15 ms (short + queued rows).
+// distance (the tail of the long rows most of it), took 0.24 + 0.15 ms (short + queued rows), and takes 0.14 + 0.13 since the
+// workgroups that fill the queues no longer wait for each other's atomics (rowlists.h; the whole 0.90 -> 0.75).
 //
 // After boundary sampling (gnn_extract_sampled_partition) a target's local row is its KEPT row (the sampler's output,
 // addressed through a row_ptr over the full id range, gnn_expand_row_ptr) and an outside vertex's local row is the
@@ -131,16 +132,12 @@ __global__ __launch_bounds__(256) void ex_count_kernel(ExArgs a) {
     const int lane = lane_id(), sub = lane / kRowLanes, sl = lane % kRowLanes;
     const int grp = (int)threadIdx.x / kRowLanes;
     const int32_t n_rows = ex_rows<SAMPLED>(a);
+    RowWalk w{a.ring_ids, a.rp, a.n, n_rows, (int64_t)gridDim.x * kRowsPerWg};
+    w.begin((int64_t)blockIdx.x * kRowsPerWg + grp);
     for (int64_t c = blockIdx.x; c * kRowsPerWg < n_rows; c += gridDim.x) {   // uniform over the workgroup
         const int64_t i = c * kRowsPerWg + grp;
-        int32_t s = 0, e = 0;
-        if (i < n_rows) {
-            const int32_t v = a.ring_ids[i];
-            if (v >= 0 && v < a.n) {
-                s = a.rp[v];
-                e = a.rp[v + 1];
-            }
-        }
+        int32_t s = w.s, e = w.e;
+        const int32_t after = w.ahead(i);
         const bool is_long = e - s > kRowShort;   // uniform over the 16-lane group
         if (is_long) {
             if (sl == 0) row_lists_push(lists, (int32_t)i, e - s, a.medq, a.hubq, &a.ctrl->rows);
@@ -160,6 +157,7 @@ __global__ __launch_bounds__(256) void ex_count_kernel(ExArgs a) {
             if (SAMPLED && keep && id >= n_rows) atomicAdd(&a.counts[id], 1);
         }
         if (sl == 0 && i < n_rows && !is_long) a.counts[i] = cnt;
+        w.next(after);
     }
     row_lists_flush(lists, a.medq, a.hubq, &a.ctrl->rows);
 }
@@ -225,18 +223,13 @@ __global__ __launch_bounds__(256) void ex_fill_kernel(ExArgs a) {
     const int lane = lane_id(), sub = lane / kRowLanes, sl = lane % kRowLanes;
     const int grp = (int)threadIdx.x / kRowLanes;
     const int32_t n_rows = ex_rows<SAMPLED>(a);
+    RowWalk w{a.ring_ids, a.rp, a.n, n_rows, (int64_t)gridDim.x * kRowsPerWg};
+    w.begin((int64_t)blockIdx.x * kRowsPerWg + grp);
     for (int64_t c = blockIdx.x; c * kRowsPerWg < n_rows; c += gridDim.x) {   // uniform over the workgroup
         const int64_t i = c * kRowsPerWg + grp;
-        int32_t s = 0, e = 0;
-        int64_t out = 0;
-        if (i < n_rows) {
-            const int32_t v = a.ring_ids[i];
-            if (v >= 0 && v < a.n) {
-                s = a.rp[v];
-                e = a.rp[v + 1];
-            }
-            out = a.out_rp[i];
-        }
+        int32_t s = w.s, e = w.e;
+        int64_t out = i < n_rows ? a.out_rp[i] : 0;
+        const int32_t after = w.ahead(i);
         if (e - s > kRowShort) {   // uniform over the 16-lane group
             if (sl == 0) row_lists_push(lists, (int32_t)i, e - s, a.medq, a.hubq, &a.ctrl->rows);
             s = e = 0;
@@ -269,51 +262,58 @@ __global__ __launch_bounds__(256) void ex_fill_kernel(ExArgs a) {
                 out += __popc(m);
             }
         }
+        w.next(after);
     }
     row_lists_flush(lists, a.medq, a.hubq, &a.ctrl->rows);
 }
 
-// queued rows of up to kRowMedium entries: a wavefront, the whole row in registers
-template <bool SAMPLED>
-__device__ __forceinline__ void ex_fill_medium(const ExArgs& a, int32_t first) {
-    constexpr int EPL = kRowMedium / kWave;
+// queued rows of up to kRowMedium entries: a wavefront, the whole row in EPL registers a lane
+template <bool SAMPLED, int EPL>
+__device__ __forceinline__ void ex_fill_medium_row(const ExArgs& a, int32_t first, int32_t n_rows, int32_t i, int32_t s, int32_t e, int64_t out) {
     const int lane = lane_id();
     const uint64_t below = (1ull << lane) - 1ull;
+    int32_t id[EPL], cls[EPL];
+    uint32_t classes = 0u;
+#pragma unroll
+    for (int r = 0; r < EPL; ++r) {
+        const uint32_t p = (uint32_t)s + r * kWave + lane;
+        id[r] = p < (uint32_t)e ? a.ci[p] : -1;
+    }
+#pragma unroll
+    for (int r = 0; r < EPL; ++r) id[r] = id[r] >= 0 ? a.new_id[id[r]] : -1;
+#pragma unroll
+    for (int r = 0; r < EPL; ++r) {
+        cls[r] = id[r] >= 0 ? ex_class(first, a.L, id[r]) : -1;
+        if (id[r] >= 0) classes |= 1u << cls[r];
+        if (SAMPLED && id[r] >= n_rows) ex_reverse(a, id[r], i);
+    }
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) classes |= __shfl_xor(classes, d, kWave);
+    while (classes) {   // uniform over the wavefront
+        const int d = __ffs(classes) - 1;
+        classes &= classes - 1u;
+#pragma unroll
+        for (int r = 0; r < EPL; ++r) {
+            const uint64_t m = __ballot(cls[r] == d);
+            const int64_t q = out + __popcll(m & below);
+            if (cls[r] == d && q < a.capacity) a.out_ci[q] = id[r];
+            out += __popcll(m);
+        }
+    }
+}
+
+template <bool SAMPLED>
+__device__ __forceinline__ void ex_fill_medium(const ExArgs& a, int32_t first) {
+    constexpr int kAll = kRowMedium / kWave;
     const int64_t waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
     const int32_t n_rows = ex_rows<SAMPLED>(a), n_queue = a.ctrl->rows.n_medium;
     for (int64_t h = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; h < n_queue; h += waves) {   // uniform over the wavefront
         const int32_t i = a.medq[h];
         const int32_t v = a.ring_ids[i];
         const int32_t s = a.rp[v], e = a.rp[v + 1];
-        int32_t id[EPL], cls[EPL];
-        uint32_t classes = 0u;
-#pragma unroll
-        for (int r = 0; r < EPL; ++r) {
-            const uint32_t p = (uint32_t)s + r * kWave + lane;
-            id[r] = p < (uint32_t)e ? a.ci[p] : -1;
-        }
-#pragma unroll
-        for (int r = 0; r < EPL; ++r) id[r] = id[r] >= 0 ? a.new_id[id[r]] : -1;
-#pragma unroll
-        for (int r = 0; r < EPL; ++r) {
-            cls[r] = id[r] >= 0 ? ex_class(first, a.L, id[r]) : -1;
-            if (id[r] >= 0) classes |= 1u << cls[r];
-            if (SAMPLED && id[r] >= n_rows) ex_reverse(a, id[r], i);
-        }
-#pragma unroll
-        for (int d = 1; d < kWave; d <<= 1) classes |= __shfl_xor(classes, d, kWave);
-        int64_t out = a.out_rp[i];
-        while (classes) {   // uniform over the wavefront
-            const int d = __ffs(classes) - 1;
-            classes &= classes - 1u;
-#pragma unroll
-            for (int r = 0; r < EPL; ++r) {
-                const uint64_t m = __ballot(cls[r] == d);
-                const int64_t q = out + __popcll(m & below);
-                if (cls[r] == d && q < a.capacity) a.out_ci[q] = id[r];
-                out += __popcll(m);
-            }
-        }
+        const int64_t out = a.out_rp[i];
+        if (e - s <= kRowMedium / 4) ex_fill_medium_row<SAMPLED, kAll / 4>(a, first, n_rows, i, s, e, out);
+        else ex_fill_medium_row<SAMPLED, kAll>(a, first, n_rows, i, s, e, out);
     }
 }
 
@@ -600,7 +600,7 @@ static int32_t ex_fill_pass(const ExArgs& a, const int32_t* dist, int row_grid, 
     ex_fill_long_kernel<SAMPLED><<<long_grid, 256, 0, stream>>>(a);
     GNN_LAUNCH_CHECK("ex_fill_long_kernel");
     if (SAMPLED) {
-        ex_order_kernel<<<grid_for(a.n_local, 256, 4096), 256, 0, stream>>>(a);
+        ex_order_kernel<<<grid_for(a.n_local, 256, kRowGrid), 256, 0, stream>>>(a);
         GNN_LAUNCH_CHECK("ex_order_kernel");
         ex_order_long_kernel<<<long_grid, 256, 0, stream>>>(a);
         GNN_LAUNCH_CHECK("ex_order_long_kernel");
@@ -629,7 +629,7 @@ static int32_t extract_common(const gnn_csr* g, const gnn_csr* gs, const int32_t
     if (query) return GNN_OK;
     GNN_REQUIRE(new_id != nullptr && out_row_ptr != nullptr, GNN_ERR_INVALID_ARG, "new_id / out_row_ptr is NULL");
     GNN_REQUIRE(n_local == 0 || (ring_ids != nullptr && dist != nullptr), GNN_ERR_INVALID_ARG, "ring_ids / dist is NULL");
-    const int row_grid = grid_for((int64_t)n_local * kRowLanes, 256, 4096);   // grid-stride loops, here and over the queues
+    const int row_grid = grid_for((int64_t)n_local * kRowLanes, 256, kRowGrid);   // grid-stride loops, here and over the queues
     const int long_grid = grid_for(n_local, 4, 2048);
     ExArgs a;
     a.rp = gs ? gs->row_ptr : g->row_ptr; a.ci = gs ? gs->col_idx : g->col_idx;

@@ -121,6 +121,36 @@ __device__ __forceinline__ void group_kth(const uint64_t (&key)[NP], const int32
     }
 }
 
+// The same for a whole wavefront that holds only the upper halves: `cand` and `half` as there (~0u where there is no candidate), more
+// than k >= 1 candidates in all.  True: the k candidates with halves up to `top` are the k smallest, and `id` is the k-th's;
+// false: the halves do not decide.
+template <int NP>
+__device__ __forceinline__ bool wave_kth_half(const uint32_t (&half)[NP], const int32_t (&ids)[NP], uint32_t cand, int32_t k, uint32_t& top,
+                                              int32_t& id) {
+    uint32_t base = 0u;
+    top = 0u;
+    for (int32_t round = 0; round < k; ++round) {
+        uint32_t m = ~0u;
+#pragma unroll
+        for (int j = 0; j < NP; ++j) m = min(m, half[j] - base);
+        top = base + group_min<kWave>(m);
+        base = top + 1u;
+    }
+    int32_t upto = 0;
+    bool held = false;
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+        const bool c = (cand >> j) & 1u;
+        upto += __popcll(__ballot(c && half[j] <= top));
+        const uint64_t h = __ballot(c && half[j] == top);
+        if (h != 0ull) {      // uniform over the wavefront
+            held = true;
+            id = __builtin_amdgcn_readlane(ids[j], __ffsll((unsigned long long)h) - 1);
+        }
+    }
+    return held && upto == k;
+}
+
 // A key that about `want` of n uniformly distributed keys lie at or below (n >= want).
 __device__ __forceinline__ uint64_t key_guess(int32_t want, int32_t n) {
     return want >= n ? ~0ull : (~0ull / (uint64_t)n) * (uint64_t)want;

@@ -182,11 +182,12 @@ __device__ __forceinline__ int32_t lm_row_in_registers(const int32_t* __restrict
                                                        int32_t e, int32_t fanout, uint64_t seed_layer_mixed, uint64_t& thr_k, int32_t& thr_u) {
     const int lane = lane_id();
     int32_t u[NP];
-    uint32_t half[NP];
+    uint32_t half[NP], cand = 0u;
 #pragma unroll
     for (int j = 0; j < NP; ++j) {
         const uint32_t p = (uint32_t)s + j * kWave + lane;
         u[j] = p < (uint32_t)e ? col_idx[p] : -1;
+        cand |= u[j] >= 0 ? 1u << j : 0u;
     }
 #pragma unroll
     for (int j = 0; j < NP; ++j) {
@@ -199,32 +200,9 @@ __device__ __forceinline__ int32_t lm_row_in_registers(const int32_t* __restrict
     uint32_t top = fanout > 0 ? ~0u : 0u;      // entries up to this half stay
     bool whole = true;                         // the half decides
     if (fanout > 0 && e - s > fanout) {
-        uint32_t base = 0u;
-        for (int32_t round = 0; round < fanout; ++round) {   // smallest above the previous one: what lies below wraps around to the top
-            uint32_t m = ~0u;
-#pragma unroll
-            for (int j = 0; j < NP; ++j) m = min(m, half[j] - base);
-            top = base + group_min<kWave>(m);
-            base = top + 1u;
-        }
-        int32_t upto = 0, id = 0;
-        uint64_t holders = 0ull;
-#pragma unroll
-        for (int j = 0; j < NP; ++j) {
-            upto += __popcll(__ballot(u[j] >= 0 && half[j] <= top));
-            const uint64_t h = __ballot(u[j] >= 0 && half[j] == top);
-            if (h != 0ull) {      // uniform over the wavefront
-                holders = h;
-                id = __builtin_amdgcn_readlane(u[j], __ffsll((unsigned long long)h) - 1);
-            }
-        }
-        whole = upto == fanout && holders != 0ull;
-        if (whole) {
-            thr_u = id;
-            thr_k = edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)id);
-        } else {
-            lm_pair_by_rounds(col_idx, v, s, e, fanout, seed_layer_mixed, thr_k, thr_u);
-        }
+        whole = wave_kth_half<NP>(half, u, cand, fanout, top, thr_u);
+        if (whole) thr_k = edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)thr_u);
+        else lm_pair_by_rounds(col_idx, v, s, e, fanout, seed_layer_mixed, thr_k, thr_u);
     }
     int32_t kept = 0;
 #pragma unroll

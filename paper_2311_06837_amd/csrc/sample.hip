@@ -7,7 +7,7 @@
 // with many independent loads in flight (a partition grown breadth-first holds the graph's hubs: on the 10M-vertex
 // workload 15 % of the target rows are longer than 64 entries and hold 70 % of all candidates):
 //   up to 64 entries    sixteen lanes per row, four entries per lane;
-//   65 to 1024          one wavefront per row, sixteen entries per lane (second launch of the pass);
+//   65 to 1024          one wavefront per row, four entries per lane up to 256, else sixteen (second launch of the pass);
 //   longer              one workgroup per row, which strides the row four entries per thread and step (third launch).
 // Count pass: ballots give |row in T| and the number of outside neighbours; a scan turns counts into row offsets.  Fill
 // pass: a row with more than `fanout` outside neighbours finds the fanout-th smallest (key, id) - among its registers
@@ -16,7 +16,10 @@
 // Which lane group, wavefront or workgroup takes a row does not matter: every row's result depends on the row alone.
 // Bound: HBM (streaming reads of the target rows) and the hash.  Kernel time of both passes on a 5M-vertex / 75M-entry graph,
 // 625 000 targets, fanout 5: 0.80 -> 0.59 ms against `fanout` rounds over 64-bit pairs with the long rows re-read in every
-// round (long rows 0.33 -> 0.16); 700 000 vertices of 100 entries, fanout 10, with the extraction: 2.26 -> 1.76 ms.
+// round (long rows 0.33 -> 0.16); 700 000 vertices of 100 entries, fanout 10, with the extraction: 2.26 -> 1.76 ms.  Since then
+// 0.48 and 1.19: a long row's outside neighbours follow from its share of the output instead of a sweep, and its kept entries are
+// placed 1024 at a time (fill 162 us -> 102), medium rows hold upper halves of keys (71 -> 62), one atomic a workgroup and half the
+// workgroups (rowlists.h: count 119 -> 75).
 #include "common.h"
 #include "hashkey.h"
 #include "rowlists.h"
@@ -35,16 +38,12 @@ __global__ __launch_bounds__(256) void sb_count_kernel(const int32_t* __restrict
     row_lists_init(lists);
     const int lane = lane_id(), sub = lane / kRowLanes, sl = lane % kRowLanes;
     const int grp = (int)threadIdx.x / kRowLanes;
+    RowWalk w{targets, row_ptr, n, n_targets, (int64_t)gridDim.x * kRowsPerWg};
+    w.begin((int64_t)blockIdx.x * kRowsPerWg + grp);
     for (int64_t c = blockIdx.x; c * kRowsPerWg < n_targets; c += gridDim.x) {   // uniform over the workgroup
         const int64_t i = c * kRowsPerWg + grp;
-        int32_t s = 0, e = 0;
-        if (i < n_targets) {
-            const int32_t v = targets[i];
-            if (v >= 0 && v < n) {
-                s = row_ptr[v];
-                e = row_ptr[v + 1];
-            }
-        }
+        int32_t s = w.s, e = w.e;
+        const int32_t after = w.ahead(i);
         const bool is_long = e - s > kRowShort;   // uniform over the 16-lane group
         if (is_long) {
             if (sl == 0) row_lists_push(lists, (int32_t)i, e - s, medq, hubq, ctrl);
@@ -65,6 +64,7 @@ __global__ __launch_bounds__(256) void sb_count_kernel(const int32_t* __restrict
             n_ext += __popc(group_ballot(valid && !inner, sub));
         }
         if (sl == 0 && i < n_targets && !is_long) counts[i] = n_in + (n_ext < fanout ? n_ext : fanout);
+        w.next(after);
     }
     row_lists_flush(lists, medq, hubq, ctrl);
 }
@@ -80,16 +80,14 @@ __global__ __launch_bounds__(256) void sb_fill_kernel(const int32_t* __restrict_
     row_lists_init(lists);
     const int lane = lane_id(), sub = lane / kRowLanes, sl = lane % kRowLanes;
     const int grp = (int)threadIdx.x / kRowLanes;
+    RowWalk w{targets, row_ptr, n, n_targets, (int64_t)gridDim.x * kRowsPerWg};
+    w.begin((int64_t)blockIdx.x * kRowsPerWg + grp);
     for (int64_t c = blockIdx.x; c * kRowsPerWg < n_targets; c += gridDim.x) {   // uniform over the workgroup
     const int64_t i = c * kRowsPerWg + grp;
-    int32_t v = 0, s = 0, e = 0;
-    if (i < n_targets) {
-        v = targets[i];
-        if (v >= 0 && v < n) {
-            s = row_ptr[v];
-            e = row_ptr[v + 1];
-        }
-    }
+    const int32_t v = w.v;
+    int32_t s = w.s, e = w.e;
+    int64_t at = i < n_targets ? (int64_t)out_row_ptr[i] : 0;
+    const int32_t after = w.ahead(i);
     if (e - s > kRowShort) {   // uniform over the 16-lane group: a wavefront or a workgroup of the later launches takes this row
         if (sl == 0) row_lists_push(lists, (int32_t)i, e - s, medq, hubq, ctrl);
         s = e = 0;
@@ -125,7 +123,6 @@ __global__ __launch_bounds__(256) void sb_fill_kernel(const int32_t* __restrict_
         for (int r = 0; r < 4; ++r) cand |= rf[r] == 2 ? 1u << r : 0u;
         group_kth<4, kRowLanes>(rk, ru, cand, fanout, want, tk, tu);
     }
-    int64_t at = i < n_targets ? (int64_t)out_row_ptr[i] : 0;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const bool keep = rf[r] == 1 || (rf[r] == 2 && !pair_less(tk, tu, rk[r], ru[r]));
@@ -134,11 +131,90 @@ __global__ __launch_bounds__(256) void sb_fill_kernel(const int32_t* __restrict_
         if (keep && my < capacity) out_col_idx[my] = ru[r];
         at += __popc(m);
     }
+    w.next(after);
     }   // grid-stride loop
     row_lists_flush(lists, medq, hubq, ctrl);
 }
 
-// ---- rows of 65 to 1024 entries: one wavefront per queued row, sixteen entries per lane, everything in registers --------
+// ---- rows of 65 to 1024 entries: one wavefront per queued row, everything in registers -----------------------------------
+// A row of up to EPL * 64 entries.  The selection compares the upper halves of the keys; where they do not decide (about
+// n^2 / 2^33 of the rows) rounds over whole pairs do.
+template <bool FILL, int EPL>
+__device__ __forceinline__ void sb_medium_row(const int32_t* __restrict__ col_idx, const uint32_t* __restrict__ tbits, int32_t v, int32_t s, int32_t e,
+                                              int32_t fanout, uint64_t seed_hop_mixed, int32_t* __restrict__ count, int64_t at,
+                                              int32_t* __restrict__ out_col_idx, int64_t capacity) {
+    const int lane = lane_id();
+    int32_t ru[EPL];
+    uint32_t inner = 0u, outer = 0u;     // bit r: the lane's r-th entry is a neighbour inside the target set, outside
+#pragma unroll
+    for (int r = 0; r < EPL; ++r) {
+        const uint32_t p = (uint32_t)s + r * kWave + lane;
+        ru[r] = p < (uint32_t)e ? col_idx[p] : 0;
+    }
+    int32_t n_in = 0, n_ext = 0;
+#pragma unroll
+    for (int r = 0; r < EPL; ++r) {
+        const bool there = (uint32_t)s + r * kWave + lane < (uint32_t)e, in = there && in_set(tbits, ru[r]);
+        inner |= in ? 1u << r : 0u;
+        outer |= there && !in ? 1u << r : 0u;
+        n_in += __popcll(__ballot(in));
+        n_ext += __popcll(__ballot(there && !in));
+    }
+    if (!FILL) {
+        if (lane == 0) *count = n_in + (n_ext < fanout ? n_ext : fanout);
+        return;
+    }
+    uint32_t half[EPL];
+#pragma unroll
+    for (int r = 0; r < EPL; ++r) {
+        half[r] = ~0u;
+        if ((uint32_t)s + r * kWave < (uint32_t)e)     // uniform over the wavefront
+            half[r] = (outer >> r) & 1u ? (uint32_t)(edge_key(seed_hop_mixed, (uint64_t)v, (uint64_t)ru[r]) >> 32) : ~0u;
+    }
+    uint32_t top = fanout > 0 ? ~0u : 0u;
+    bool whole = true;
+    uint64_t tk = 0ull;
+    int32_t tu = -1;
+    if (fanout > 0 && n_ext > fanout) {   // uniform over the wavefront
+        whole = wave_kth_half<EPL>(half, ru, outer, fanout, top, tu);
+        for (int32_t round = 0; round < fanout && !whole; ++round) {     // the smallest pair above (tk, tu)
+            uint64_t best_k = ~0ull;
+            int32_t best_u = 0x7fffffff;
+#pragma unroll
+            for (int r = 0; r < EPL; ++r) {
+                if (((outer >> r) & 1u) == 0u) continue;
+                const uint64_t k = edge_key(seed_hop_mixed, (uint64_t)v, (uint64_t)ru[r]);
+                if ((round == 0 || pair_less(tk, tu, k, ru[r])) && pair_less(k, ru[r], best_k, best_u)) {
+                    best_k = k;
+                    best_u = ru[r];
+                }
+            }
+#pragma unroll
+            for (int d = 32; d >= 1; d >>= 1) {
+                const uint64_t ok = __shfl_xor(best_k, d, kWave);
+                const int32_t ou = __shfl_xor(best_u, d, kWave);
+                if (pair_less(ok, ou, best_k, best_u)) {
+                    best_k = ok;
+                    best_u = ou;
+                }
+            }
+            tk = best_k;
+            tu = best_u;
+        }
+    }
+    const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int r = 0; r < EPL; ++r) {
+        bool keep = fanout > 0 && half[r] <= top;
+        if (!whole) keep = !pair_less(tk, tu, edge_key(seed_hop_mixed, (uint64_t)v, (uint64_t)ru[r]), ru[r]);
+        keep = ((inner >> r) & 1u) != 0u || (((outer >> r) & 1u) != 0u && keep);
+        const uint64_t m = __ballot(keep);
+        const int64_t my = at + __popcll(m & below);
+        if (keep && my < capacity) out_col_idx[my] = ru[r];
+        at += __popcll(m);
+    }
+}
+
 template <bool FILL>
 __global__ __launch_bounds__(256) void sb_medium_rows_kernel(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
                                                              const uint32_t* __restrict__ tbits, const int32_t* __restrict__ targets,
@@ -146,8 +222,6 @@ __global__ __launch_bounds__(256) void sb_medium_rows_kernel(const int32_t* __re
                                                              int32_t fanout, uint64_t seed_hop_mixed, int32_t* __restrict__ counts,
                                                              const int32_t* __restrict__ out_row_ptr, int32_t* __restrict__ out_col_idx,
                                                              int64_t capacity) {
-    constexpr int EPL = kRowMedium / kWave;   // entries per lane
-    const int lane = lane_id();
     const int64_t wave_g = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int64_t n_waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
     const int32_t n_med = ctrl->n_medium;
@@ -155,50 +229,11 @@ __global__ __launch_bounds__(256) void sb_medium_rows_kernel(const int32_t* __re
         const int32_t i = medq[h];
         const int32_t v = targets[i];
         const int32_t s = row_ptr[v], e = row_ptr[v + 1];
-        int32_t ru[EPL];
-        int rf[EPL];  // 0: no entry, 1: neighbour inside the target set, 2: outside
-#pragma unroll
-        for (int r = 0; r < EPL; ++r) {
-            const uint32_t p = (uint32_t)s + r * kWave + lane;
-            ru[r] = p < (uint32_t)e ? col_idx[p] : 0;
-        }
-        int32_t n_in = 0, n_ext = 0;
-#pragma unroll
-        for (int r = 0; r < EPL; ++r) {
-            const uint32_t p = (uint32_t)s + r * kWave + lane;
-            rf[r] = p < (uint32_t)e ? (in_set(tbits, ru[r]) ? 1 : 2) : 0;
-            n_in += __popcll(__ballot(rf[r] == 1));
-            n_ext += __popcll(__ballot(rf[r] == 2));
-        }
-        if (!FILL) {
-            if (lane == 0) counts[i] = n_in + (n_ext < fanout ? n_ext : fanout);
-            continue;
-        }
-        uint64_t rk[EPL];
-#pragma unroll
-        for (int r = 0; r < EPL; ++r) rk[r] = rf[r] == 2 ? edge_key(seed_hop_mixed, (uint64_t)v, (uint64_t)ru[r]) : ~0ull;
-        uint64_t tk = ~0ull;
-        int32_t tu = 0x7fffffff;
-        if (fanout == 0) {
-            tk = 0ull;
-            tu = -1;
-        }
-        if (fanout > 0 && n_ext > fanout) {   // uniform over the wavefront
-            uint32_t cand = 0u;
-#pragma unroll
-            for (int r = 0; r < EPL; ++r) cand |= rf[r] == 2 ? 1u << r : 0u;
-            group_kth<EPL, kWave>(rk, ru, cand, fanout, true, tk, tu);
-        }
-        int64_t at = out_row_ptr[i];
-        const uint64_t below = (1ull << lane) - 1ull;
-#pragma unroll
-        for (int r = 0; r < EPL; ++r) {
-            const bool keep = rf[r] == 1 || (rf[r] == 2 && !pair_less(tk, tu, rk[r], ru[r]));
-            const uint64_t m = __ballot(keep);
-            const int64_t my = at + __popcll(m & below);
-            if (keep && my < capacity) out_col_idx[my] = ru[r];
-            at += __popcll(m);
-        }
+        int32_t* const count = FILL ? nullptr : counts + i;
+        const int64_t at = FILL ? (int64_t)out_row_ptr[i] : 0;
+        constexpr int kAll = kRowMedium / kWave;
+        if (e - s <= kRowMedium / 4) sb_medium_row<FILL, kAll / 4>(col_idx, tbits, v, s, e, fanout, seed_hop_mixed, count, at, out_col_idx, capacity);
+        else sb_medium_row<FILL, kAll>(col_idx, tbits, v, s, e, fanout, seed_hop_mixed, count, at, out_col_idx, capacity);
     }
 }
 
@@ -275,7 +310,9 @@ __global__ __launch_bounds__(256) void sb_long_rows_kernel(const int32_t* __rest
         const int32_t v = targets[i];
         const int32_t s = row_ptr[v], e = row_ptr[v + 1];
         int n_in = 0, n_ext = 0;
-        for (uint32_t base = s; base < (uint32_t)e; base += 1024) {
+        // the row's share of the output says how many lie outside: all entries, or the inner ones and `fanout`
+        if (FILL) n_ext = e - s - (out_row_ptr[i + 1] - out_row_ptr[i]) + fanout;
+        for (uint32_t base = s; base < (uint32_t)e && !FILL; base += 1024) {
             int32_t u[4];
             bool ok[4];
 #pragma unroll
@@ -291,8 +328,8 @@ __global__ __launch_bounds__(256) void sb_long_rows_kernel(const int32_t* __rest
                 n_ext += ok[r] && !inner;
             }
         }
-        block_sum2(n_in, n_ext, s_a, s_b);
         if (!FILL) {
+            block_sum2(n_in, n_ext, s_a, s_b);
             if (tid == 0) counts[i] = n_in + (n_ext < fanout ? n_ext : fanout);
             continue;
         }
@@ -392,20 +429,38 @@ __global__ __launch_bounds__(256) void sb_long_rows_kernel(const int32_t* __rest
             thr_k = prev_k;
             thr_u = prev_u;
         }
+        // a wavefront takes 256 entries in a row of a step's 1024
         int64_t pos = out_row_ptr[i];
-        for (uint32_t base = s; base < (uint32_t)e; base += 256) {
-            const uint32_t p = base + tid;
-            bool keep = false;
-            int32_t u = 0;
-            if (p < (uint32_t)e) {
-                u = col_idx[p];
-                if (in_set(tbits, u)) keep = true;
-                else keep = !pair_less(thr_k, thr_u, edge_key(seed_hop_mixed, (uint64_t)v, (uint64_t)u), u);
+        const int lane = tid & 63, wave = tid >> 6;
+        for (uint32_t base = s; base < (uint32_t)e; base += 1024) {
+            int32_t u[4];
+            uint64_t m[4];
+            bool keep[4];
+            const uint32_t p0 = base + wave * 256 + lane;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) u[r] = p0 + r * kWave < (uint32_t)e ? col_idx[p0 + r * kWave] : 0;
+            int mine = 0;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                keep[r] = in_set(tbits, u[r]) || !pair_less(thr_k, thr_u, edge_key(seed_hop_mixed, (uint64_t)v, (uint64_t)u[r]), u[r]);
+                keep[r] = keep[r] && p0 + r * kWave < (uint32_t)e;
+                m[r] = __ballot(keep[r]);
+                mine += __popcll(m[r]);
             }
-            int total;
-            const int before = block_exclusive_scan<256>(keep ? 1 : 0, s_part, &total);
-            if (keep && pos + before < capacity) out_col_idx[pos + before] = u;
-            pos += total;
+            if (lane == 0) s_part[wave] = mine;
+            __syncthreads();
+            int64_t my = pos;
+            for (int w = 0; w < 4; ++w) {
+                if (w < wave) my += s_part[w];
+                pos += s_part[w];
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int64_t q = my + __popcll(m[r] & ((1ull << lane) - 1ull));
+                if (keep[r] && q < capacity) out_col_idx[q] = u[r];
+                my += __popcll(m[r]);
+            }
+            __syncthreads();     // s_part has been read
         }
     }
 }
@@ -435,7 +490,7 @@ extern "C" int32_t gnn_sample_boundary(const gnn_csr* g, const uint32_t* target_
     if (query) return GNN_OK;
     GNN_REQUIRE(out_row_ptr != nullptr, GNN_ERR_INVALID_ARG, "out_row_ptr is NULL");
     GNN_REQUIRE(n_targets == 0 || (targets != nullptr && target_bitmap != nullptr), GNN_ERR_INVALID_ARG, "targets / bitmap is NULL");
-    const int wave_grid = grid_for((int64_t)n_targets * kRowLanes, 256, 4096);   // grid-stride: one queue append per workgroup
+    const int wave_grid = grid_for((int64_t)n_targets * kRowLanes, 256, kRowGrid);   // grid-stride: one queue append per workgroup
     if (n_targets > 0) {   // both passes queue their long rows afresh (workspace contents do not survive a call)
         fill_kernel<int32_t><<<1, 64, 0, stream>>>((int32_t*)ctrl, (int64_t)(sizeof(RowCtrl) / sizeof(int32_t)), 0);
         GNN_LAUNCH_CHECK("fill_kernel");

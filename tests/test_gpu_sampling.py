@@ -71,3 +71,39 @@ def test_row_lengths_around_the_sixteen_lane_limit():
     T = np.concatenate([np.arange(len(lens)), np.arange(100, n, 2)]).astype(np.int32)   # about half of every row is inside
     for fanout in (0, 1, 3, 40, 150, 250, 600):    # the long rows: from the listed keys up to 150, then by sweeps over the row
         _compare(g, T, fanout, 0xABCDEF)
+
+
+def _mix64(x):
+    with np.errstate(over="ignore"):
+        x = x + np.uint64(0x9E3779B97F4A7C15)
+        x = (x ^ (x >> np.uint64(30))) * np.uint64(0xBF58476D1CE4E5B9)
+        x = (x ^ (x >> np.uint64(27))) * np.uint64(0x94D049BB133111EB)
+        return x ^ (x >> np.uint64(31))
+
+
+@pytest.mark.parametrize("length", [64, 65, 256, 257, 1024])
+def test_rows_in_which_the_upper_halves_of_two_keys_are_equal(length):
+    """The selection compares upper halves and falls back to whole pairs where the k-th is not alone with its half: rows built
+    around two outside neighbours whose keys share it, kept both, one of them, or neither."""
+    n, seed, v = 1_500_000, 77, 5
+    keys = _mix64(_mix64(_mix64(np.uint64(seed + 1)) ^ np.uint64(v)) ^ np.arange(n, dtype=np.uint64))
+    assert int(keys[123]) == oracle.edge_key(seed, v, 123, 1)
+    order = np.argsort(keys)
+    half = keys[order] >> np.uint64(32)
+    at = np.flatnonzero(half[1:] == half[:-1])
+    at = int(at[at > length][0])                               # the pair is order[at], order[at + 1]
+    for k in (1, 2, 10):
+        for before in sorted({max(k - 1, 0), max(k - 2, 0), k}):
+            low = order[np.random.default_rng(before).choice(at, before, replace=False)]
+            high = order[at + 2:][np.random.default_rng(k).choice(n - at - 2, length - before - 2, replace=False)]
+            cols = np.sort(np.concatenate([low, order[at: at + 2], high])).astype(np.int32)
+            row_ptr = np.zeros(n + 1, dtype=np.int32)
+            row_ptr[v + 1:] = length
+            inner = [int(c) for c in high[:3] if c != v]
+            _compare(gg.CSR(n, n, row_ptr, cols), np.array([v] + inner, dtype=np.int32), k, seed)
+
+
+def test_more_targets_than_a_launch_takes_at_a_time():
+    """Every lane group takes several rows, one after the other, of every length class."""
+    g = gg.chung_lu(150_000, 12.0, 2.1, 36)
+    _compare(g, np.arange(0, 150_000, 2).astype(np.int32), 3, 21)
