@@ -236,8 +236,10 @@ __device__ __forceinline__ uint4 post_apply(uint4 v, uint4 old, bool has_old, ui
     return make_uint4(r[0], r[1], r[2], r[3]);
 }
 
-template <int DT, int BN, int WM, int WN, bool VEC>
+// BKN: the right operand is [K][N] as the caller stores a forward weight, fp32: four reads down a column instead of one along a row.
+template <int DT, int BN, int WM, int WN, bool VEC, bool BKN = false>
 __global__ __launch_bounds__(256, BN == 128 ? GNN_NT_MINB : GNN_NT_MINB_NARROW) void gemm_nt_kernel(GemmNT a) {
+    static_assert(!BKN || (DT == GNN_F32 && VEC), "columns of floats");
     constexpr int BM = 128;
     constexpr int EPV = DTy<DT>::EPV;
     constexpr int BK = 8 * EPV;  // elements per 128-byte tile row
@@ -275,7 +277,7 @@ __global__ __launch_bounds__(256, BN == 128 ? GNN_NT_MINB : GNN_NT_MINB_NARROW) 
     for (int c = 0; c < B_CH; ++c) {
         const int n = n0 + ld_row + 32 * c;
         b_ok[c] = n < a.N;
-        b_off[c] = (int64_t)(b_ok[c] ? n : 0) * a.ldb;
+        b_off[c] = BKN ? (b_ok[c] ? n : 0) : (int64_t)(b_ok[c] ? n : 0) * a.ldb;
     }
 
     v16f acc[MT][NT];
@@ -300,7 +302,17 @@ __global__ __launch_bounds__(256, BN == 128 ? GNN_NT_MINB : GNN_NT_MINB_NARROW) 
 #pragma unroll
             for (int c = 0; c < A_CH; ++c) ra[c] = load_raw<DT>(Ab, a_off[c] + ke, a_ok[c] && nv > 0);
 #pragma unroll
-            for (int c = 0; c < B_CH; ++c) rb[c] = load_raw<DT>(Bb, b_off[c] + ke, b_ok[c] && nv > 0);
+            for (int c = 0; c < B_CH; ++c) {
+                if constexpr (BKN) {
+                    const uint32_t* const w = (const uint32_t*)Bb + b_off[c];     // (past K: the column's first element, zeroed by stash)
+                    rb[c].x = w[(int64_t)(nv > 0 ? ke : 0) * a.ldb];
+                    rb[c].y = w[(int64_t)(nv > 1 ? ke + 1 : 0) * a.ldb];
+                    rb[c].z = w[(int64_t)(nv > 2 ? ke + 2 : 0) * a.ldb];
+                    rb[c].w = w[(int64_t)(nv > 3 ? ke + 3 : 0) * a.ldb];
+                } else {
+                    rb[c] = load_raw<DT>(Bb, b_off[c] + ke, b_ok[c] && nv > 0);
+                }
+            }
         } else {
 #pragma unroll
             for (int c = 0; c < A_CH; ++c) ra[c] = load16<DT>(Ab, a_off[c] + ke, a_ok[c] ? nv : 0, a.a_vec != 0);
@@ -497,8 +509,9 @@ __device__ __forceinline__ u32x4 mask_chunk(u32x4 r, int n_valid) {
 // masked to its valid elements when it is moved to LDS, so neither padding nor a neighbouring row reaches the MFMAs.
 // MINB: workgroups that share a CU; the registers of a lane follow from it.
 constexpr int64_t kLargeOutput = 128ll << 20;     // bytes of an output from which a short reduction is bound by writing it
-template <int DT, int NTW, bool KTAIL, int MINB = NTW == 4 ? 2 : NTW == 2 ? 3 : 4>
+template <int DT, int NTW, bool KTAIL, int MINB = NTW == 4 ? 2 : NTW == 2 ? 3 : 4, bool BKN = false>
 __global__ __launch_bounds__(256, MINB) void gemm_nt_wide_kernel(GemmNT a) {
+    static_assert(!BKN || (DT == GNN_F32 && NTW == 1), "columns of floats, one chunk a thread");
     constexpr int BM = 128, BN = 64 * NTW, MT = 2, NT = NTW, WTN = 32 * NTW;
     constexpr int ES = DTy<DT>::ES, EPV = DTy<DT>::EPV;
     constexpr int EPS = 64 / ES;                  // reduction elements per slice
@@ -538,7 +551,7 @@ __global__ __launch_bounds__(256, MINB) void gemm_nt_wide_kernel(GemmNT a) {
     };
     auto b_row = [&](int c) -> int64_t {
         const int n = n0 + ld_row + 64 * c;
-        return ((int64_t)(n < a.N ? n : 0) * a.ldb + (KTAIL ? 0 : ld_c * EPV)) * ES;
+        return BKN ? (int64_t)(n < a.N ? n : 0) * ES : ((int64_t)(n < a.N ? n : 0) * a.ldb + (KTAIL ? 0 : ld_c * EPV)) * ES;
     };
     const int64_t ao0 = a_row(0), ao1 = a_row(1);
     const int64_t bo0 = b_row(0), bo1 = B_CH > 1 ? b_row(1) : 0, bo2 = B_CH > 2 ? b_row(2) : 0, bo3 = B_CH > 2 ? b_row(3) : 0;
@@ -571,10 +584,19 @@ __global__ __launch_bounds__(256, MINB) void gemm_nt_wide_kernel(GemmNT a) {
         int64_t kb_ = (int64_t)sl_ * 64;                                           \
         if (KTAIL) kb_ = a.K - (sl_ * EPS + ld_c * EPV) > 0 ? kb_ + ld_c * 16 : 0; \
         const char* Ab_ = (const char*)(src_ ? a.A[1] : a.A[0]) + kb_;             \
-        const char* Bb_ = (const char*)(src_ ? a.Bt[1] : a.Bt[0]) + kb_;           \
+        const char* Bb_ = (const char*)(src_ ? a.Bt[1] : a.Bt[0]) + (BKN ? 0 : kb_); \
         a##S##x0 = *(const u32x4*)(Ab_ + ao0);                                     \
         a##S##x1 = *(const u32x4*)(Ab_ + ao1);                                     \
-        b##S##x0 = *(const u32x4*)(Bb_ + bo0);                                     \
+        if (BKN) {                                                                 \
+            const int k_ = sl_ * EPS + ld_c * EPV;                                 \
+            const uint32_t* w_ = (const uint32_t*)(Bb_ + bo0);                     \
+            b##S##x0[0] = w_[(int64_t)(!KTAIL || k_ < a.K ? k_ : 0) * a.ldb];      \
+            b##S##x0[1] = w_[(int64_t)(!KTAIL || k_ + 1 < a.K ? k_ + 1 : 0) * a.ldb]; \
+            b##S##x0[2] = w_[(int64_t)(!KTAIL || k_ + 2 < a.K ? k_ + 2 : 0) * a.ldb]; \
+            b##S##x0[3] = w_[(int64_t)(!KTAIL || k_ + 3 < a.K ? k_ + 3 : 0) * a.ldb]; \
+        } else {                                                                   \
+            b##S##x0 = *(const u32x4*)(Bb_ + bo0);                                 \
+        }                                                                          \
         if (B_CH > 1) b##S##x1 = *(const u32x4*)(Bb_ + bo1);                       \
         if (B_CH > 2) {                                                            \
             b##S##x2 = *(const u32x4*)(Bb_ + bo2);                                 \
@@ -1039,9 +1061,55 @@ __global__ __launch_bounds__(256, NTW == 4 ? 2 : 3) void gemm_nt_line_kernel(Gem
 #undef GNN_QUARTERS
 }
 
+// Wt[n][k] = W[k][n]; Wt rows are padded to ldt elements (pad left untouched, never read).
 template <int DT>
-static int32_t launch_gemm_nt(const GemmNT& a, hipStream_t stream) {
+__global__ __launch_bounds__(256) void transpose_kernel(const void* __restrict__ W0, const void* __restrict__ W1, int32_t K, int32_t N,
+                                                        void* __restrict__ Wt0, void* __restrict__ Wt1, int64_t ldt) {
+    const void* const W = blockIdx.z ? W1 : W0;      // one launch for both sources
+    void* const Wt = blockIdx.z ? Wt1 : Wt0;
+    __shared__ uint32_t tile[32][33];
+    const int k0 = blockIdx.x * 32, n0 = blockIdx.y * 32;
+    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
+    for (int r = ty; r < 32; r += 8) {
+        const int k = k0 + r, n = n0 + tx;
+        uint32_t v = 0;
+        if (k < K && n < N) v = DT == GNN_F32 ? ((const uint32_t*)W)[(int64_t)k * N + n] : ((const uint16_t*)W)[(int64_t)k * N + n];
+        tile[r][tx] = v;
+    }
+    __syncthreads();
+    for (int r = ty; r < 32; r += 8) {
+        const int n = n0 + r, k = k0 + tx;
+        if (k < K && n < N) {
+            if (DT == GNN_F32) ((uint32_t*)Wt)[(int64_t)n * ldt + k] = tile[tx][r];
+            else ((uint16_t*)Wt)[(int64_t)n * ldt + k] = (uint16_t)tile[tx][r];
+        }
+    }
+}
+
+// W: nullable, the right operands as [K][N]; a.Bt then names room for their transposed copies, which are made unless the product
+// reads W itself.
+template <int DT>
+static int32_t launch_gemm_nt(const GemmNT& a, hipStream_t stream, const void* const* W = nullptr) {
     if (a.M <= 0 || a.N <= 0) return GNN_OK;
+    auto transpose = [&]() -> int32_t {
+        if (W == nullptr) return GNN_OK;
+        const dim3 grid((a.K + 31) / 32, (a.N + 31) / 32, a.n_src);
+        transpose_kernel<DT><<<grid, 256, 0, stream>>>(W[0], W[1], a.K, a.N, const_cast<void*>(a.Bt[0]), const_cast<void*>(a.Bt[1]), a.ldb);
+        GNN_LAUNCH_CHECK("transpose_kernel");
+        return GNN_OK;
+    };
+    // A transposed copy is a launch of its own, some 3 us; a product that reads the weights down their columns asks for four times as
+    // many pieces of them.  fp32, 64 columns a tile, us, columns / copy: 64 -> 64 2000 to 20 000 rows 8.3 / 10.7, 160 000 (five tiles a CU) 27.5 /
+    // 29.6; 100 -> 47 20 000 12.8 / 14.9, 160 000 42.3 / 42.4, 400 000 90.1 / 85.9; 128 -> 128 2000 10.4 / 12.2, 80 000 39.1 / 40.2, 160 000 69.1 / 66.0;
+    // 64 + 64 -> 256 2000 10.9 / 12.8, 40 000 39.7 / 40.0, 80 000 68.5 / 65.3; 256 -> 64 10 000 16.2 / 17.4, 40 000 28.9 / 27.9; 256 -> 16 2000 14.5 / 16.3,
+    // 100 000 31.0 / 32.1; but 256 + 256 -> 256 2000 27.0 / 27.0, 20 000 71.4 / 64.2; 602 + 602 -> 41 2000 65.3 / 60.9.
+    const bool reads_weights = W != nullptr && (int64_t)a.K * a.n_src <= 256;
+    GemmNT b = a;
+    if (W != nullptr) {
+        b.Bt[0] = W[0];
+        b.Bt[1] = W[1];
+        b.ldb = a.N;
+    }
     const int64_t tiles_m = ((int64_t)a.M + 127) / 128;
     const bool vec = a.a_vec && a.b_vec;  // both operands aligned: the branch-free loader
     if (vec && a.N > 32 && a.K > 0) {
@@ -1094,6 +1162,7 @@ static int32_t launch_gemm_nt(const GemmNT& a, hipStream_t stream) {
         if constexpr (GNN_NT_LINE && (DT == GNN_BF16 || GNN_NT_LINE_F32))
         if ((int64_t)a.K * DTy<DT>::ES % 128 == 0 && ntw > 1 && a.N % (64 * ntw) == 0 && a.c_vec && (!a.mask || a.m_vec)) {
             const unsigned lgrid = (unsigned)(tiles_m * (a.N / (64 * ntw)));
+            GNN_CHECK(transpose());
             if (ntw == 4) gemm_nt_line_kernel<DT, 4><<<lgrid, 256, 0, stream>>>(a);
             else gemm_nt_line_kernel<DT, 2><<<lgrid, 256, 0, stream>>>(a);
             GNN_LAUNCH_CHECK("gemm_nt_line_kernel");
@@ -1101,6 +1170,16 @@ static int32_t launch_gemm_nt(const GemmNT& a, hipStream_t stream) {
         }
         const unsigned grid = (unsigned)((tiles_m + 7) / 8 * 8 * (ntw == 4 ? p256 / 256 : (ntw == 2 ? p128 / 128 : p64 / 64)));
         const bool ktail = a.K % (64 / DTy<DT>::ES) != 0;
+        if constexpr (DT == GNN_F32) {
+            if (reads_weights && ntw == 1 && grid <= (a.K * a.n_src <= 128 ? 5u : 1u) * 256) {
+                if (ktail && (int64_t)(grid + 7) / 8 <= 64) gemm_nt_wide_kernel<DT, 1, true, 2, true><<<grid, 256, 0, stream>>>(b);
+                else if (ktail) gemm_nt_wide_kernel<DT, 1, true, 4, true><<<grid, 256, 0, stream>>>(b);
+                else gemm_nt_wide_kernel<DT, 1, false, 4, true><<<grid, 256, 0, stream>>>(b);
+                GNN_LAUNCH_CHECK("gemm_nt_wide_kernel");
+                return GNN_OK;
+            }
+        }
+        GNN_CHECK(transpose());
 #define GNN_WIDE(NTW_)                                                                                  \
     {                                                                                                   \
         if (ktail) gemm_nt_wide_kernel<DT, NTW_, true><<<grid, 256, 0, stream>>>(a);                    \
@@ -1116,6 +1195,14 @@ static int32_t launch_gemm_nt(const GemmNT& a, hipStream_t stream) {
         GNN_LAUNCH_CHECK("gemm_nt_wide_kernel");
         return GNN_OK;
     }
+    if constexpr (DT == GNN_F32) {
+        if (reads_weights && vec && a.N <= 32 && tiles_m <= 5 * 256) {
+            gemm_nt_kernel<DT, 32, 4, 1, true, true><<<(unsigned)((tiles_m + 7) / 8 * 8), 256, 0, stream>>>(b);
+            GNN_LAUNCH_CHECK("gemm_nt_kernel");
+            return GNN_OK;
+        }
+    }
+    GNN_CHECK(transpose());
     if (a.N > 64) {
         const unsigned grid = (unsigned)((tiles_m * ((a.N + 127) / 128) + 7) / 8 * 8);
         if (vec) gemm_nt_kernel<DT, 128, 2, 2, true><<<grid, 256, 0, stream>>>(a);
@@ -1421,29 +1508,6 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __res
     }
 }
 
-// Wt[n][k] = W[k][n]; Wt rows are padded to ldt elements (pad left untouched, never read).
-template <int DT>
-__global__ __launch_bounds__(256) void transpose_kernel(const void* __restrict__ W, int32_t K, int32_t N, void* __restrict__ Wt,
-                                                        int64_t ldt) {
-    __shared__ uint32_t tile[32][33];
-    const int k0 = blockIdx.x * 32, n0 = blockIdx.y * 32;
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
-    for (int r = ty; r < 32; r += 8) {
-        const int k = k0 + r, n = n0 + tx;
-        uint32_t v = 0;
-        if (k < K && n < N) v = DT == GNN_F32 ? ((const uint32_t*)W)[(int64_t)k * N + n] : ((const uint16_t*)W)[(int64_t)k * N + n];
-        tile[r][tx] = v;
-    }
-    __syncthreads();
-    for (int r = ty; r < 32; r += 8) {
-        const int n = n0 + r, k = k0 + tx;
-        if (k < K && n < N) {
-            if (DT == GNN_F32) ((uint32_t*)Wt)[(int64_t)n * ldt + k] = tile[tx][r];
-            else ((uint16_t*)Wt)[(int64_t)n * ldt + k] = (uint16_t)tile[tx][r];
-        }
-    }
-}
-
 // dZ[i][0:N] = relu ? dH[row(i)] * [H[row(i)] > 0] : dH[row(i)], rows compacted (pad columns of dZ
 // are written as zero; dZ == NULL: nothing is stored); column sums of each block of kDzRows rows go to part[block][0:N].
 // Threads: cx 16-byte column vectors x 256/cx row lanes.
@@ -1519,7 +1583,10 @@ __global__ __launch_bounds__(256) void dz_kernel(const int32_t* __restrict__ row
 
 // Wp[k][0:ldp] = W[k][0:N] followed by zeros: rows of an unaligned width become 16-byte aligned.
 template <int DT>
-__global__ __launch_bounds__(256) void pad_rows_kernel(const void* __restrict__ W, int32_t K, int32_t N, void* __restrict__ Wp, int32_t ldp) {
+__global__ __launch_bounds__(256) void pad_rows_kernel(const void* __restrict__ W0, const void* __restrict__ W1, int32_t K, int32_t N,
+                                                        void* __restrict__ Wp0, void* __restrict__ Wp1, int32_t ldp) {
+    const void* const W = blockIdx.y ? W1 : W0;      // one launch for both sources
+    void* const Wp = blockIdx.y ? Wp1 : Wp0;
     const int64_t total = (int64_t)K * ldp;
     for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
         const int32_t k = (int32_t)(t / ldp), c = (int32_t)(t % ldp);
@@ -1554,13 +1621,6 @@ static int32_t linear_fwd_impl(const int32_t* rows, int32_t n_active, const void
                                const void* Wn, const void* Ws, const float* bias, int32_t N, void* H, int64_t ld_out,
                                int32_t relu, void* Wt0, void* Wt1, int64_t ldt, hipStream_t stream) {
     constexpr int ES = DTy<DT>::ES;
-    dim3 tg((K + 31) / 32, (N + 31) / 32);
-    transpose_kernel<DT><<<tg, 256, 0, stream>>>(Wn, K, N, Wt0, ldt);
-    GNN_LAUNCH_CHECK("transpose_kernel");
-    if (Xs) {
-        transpose_kernel<DT><<<tg, 256, 0, stream>>>(Ws, K, N, Wt1, ldt);
-        GNN_LAUNCH_CHECK("transpose_kernel");
-    }
     GemmNT g;
     g.A[0] = A; g.A[1] = Xs; g.Bt[0] = Wt0; g.Bt[1] = Wt1; g.n_src = Xs ? 2 : 1;
     g.lda = ld_in; g.ldb = ldt;
@@ -1569,7 +1629,8 @@ static int32_t linear_fwd_impl(const int32_t* rows, int32_t n_active, const void
     g.a_rows = rows; g.c_rows = rows; g.M = n_active; g.N = N; g.K = K;
     g.bias = bias; g.relu = relu; g.C = H; g.ldc = ld_out; g.c_vec = vec_ok(H, ld_out, ES);
     g.mask = nullptr; g.ldm = 0; g.m_vec = 0; g.n_acc = 0; g.M1 = INT32_MAX;
-    return launch_gemm_nt<DT>(g, stream);
+    const void* const W[2] = {Wn, Ws};
+    return launch_gemm_nt<DT>(g, stream, W);
 }
 
 template <int DT>
@@ -1636,7 +1697,7 @@ static int32_t linear_bwd_impl(const int32_t* rows, int32_t M, const void* dH, c
         void* Wpad = which == 0 ? Wpad0 : Wpad1;
         if (Wpad != nullptr) {
             // rows of N elements are not 16-byte aligned (41 or 47 classes): the product reads a padded copy with vector loads
-            pad_rows_kernel<DT><<<grid_for((int64_t)K * ldwp, 256, 1024), 256, 0, stream>>>(W, K, N, Wpad, ldwp);
+            pad_rows_kernel<DT><<<grid_for((int64_t)K * ldwp, 256, 1024), 256, 0, stream>>>(W, nullptr, K, N, Wpad, nullptr, ldwp);
             GNN_LAUNCH_CHECK("pad_rows_kernel");
             W = Wpad;
             ldw = ldwp;
@@ -1877,8 +1938,8 @@ extern "C" int32_t gnn_linear_bwd_input(const int32_t* rows, int32_t n_active, c
     GNN_REQUIRE(dZ && W && dX, GNN_ERR_INVALID_ARG, "dZ, W or dX is NULL");
     int64_t ldw = N;
     if (pad_w) {
-        if (dtype == GNN_F32) pad_rows_kernel<GNN_F32><<<grid_for((int64_t)K * ldwp, 256, 1024), 256, 0, stream>>>(W, K, N, Wpad, ldwp);
-        else pad_rows_kernel<GNN_BF16><<<grid_for((int64_t)K * ldwp, 256, 1024), 256, 0, stream>>>(W, K, N, Wpad, ldwp);
+        if (dtype == GNN_F32) pad_rows_kernel<GNN_F32><<<grid_for((int64_t)K * ldwp, 256, 1024), 256, 0, stream>>>(W, nullptr, K, N, Wpad, nullptr, ldwp);
+        else pad_rows_kernel<GNN_BF16><<<grid_for((int64_t)K * ldwp, 256, 1024), 256, 0, stream>>>(W, nullptr, K, N, Wpad, nullptr, ldwp);
         GNN_LAUNCH_CHECK("pad_rows_kernel");
         W = Wpad;
         ldw = ldwp;
@@ -1916,13 +1977,10 @@ extern "C" int32_t gnn_linear_bwd_input2(const int32_t* rows, int32_t n_active, 
     const bool two = n_self > 0;
     int64_t ldw = N;
     if (pad_w) {   // weight rows of an unaligned width (41 or 47 classes): the product reads padded copies with vector loads
-        for (int which = 0; which < (two ? 2 : 1); ++which) {
-            const void* W = which == 0 ? W_neigh : W_self;
-            char* Wp = which == 0 ? Wpad0 : Wpad1;
-            if (dtype == GNN_F32) pad_rows_kernel<GNN_F32><<<grid_for((int64_t)K * ldwp, 256, 1024), 256, 0, stream>>>(W, K, N, Wp, ldwp);
-            else pad_rows_kernel<GNN_BF16><<<grid_for((int64_t)K * ldwp, 256, 1024), 256, 0, stream>>>(W, K, N, Wp, ldwp);
-            GNN_LAUNCH_CHECK("pad_rows_kernel");
-        }
+        const dim3 grid(grid_for((int64_t)K * ldwp, 256, 1024), two ? 2 : 1);
+        if (dtype == GNN_F32) pad_rows_kernel<GNN_F32><<<grid, 256, 0, stream>>>(W_neigh, W_self, K, N, Wpad0, Wpad1, ldwp);
+        else pad_rows_kernel<GNN_BF16><<<grid, 256, 0, stream>>>(W_neigh, W_self, K, N, Wpad0, Wpad1, ldwp);
+        GNN_LAUNCH_CHECK("pad_rows_kernel");
         W_neigh = Wpad0;
         W_self = Wpad1;
         ldw = ldwp;

@@ -375,6 +375,30 @@ def test_tile_widths_of_the_forward_product(dtype, M, K, N):
     assert (out[M:] == torch.tensor(SENT, dtype=dtype)).all()
 
 
+@pytest.mark.parametrize("M,K,N,two", [(1, 5, 1, False), (1, 16, 33, True), (129, 128, 64, True), (1025, 1, 100, False), (1000, 255, 64, False),
+                                       (1000, 256, 65, False), (1000, 257, 64, False), (163_841, 64, 64, False), (300, 17, 32, True), (300, 100, 31, True)])
+def test_forward_products_that_read_the_weights_down_their_columns(M, K, N, two):
+    """Short reductions over few tiles read W as it is stored, the others a transposed copy: both sides of the line, ragged
+    reductions and widths, weights that start at any float."""
+    import paper_2311_06837_amd as P
+    rng = np.random.default_rng(M + K)
+    ld, ldo = _pad(K, 4), _pad(N, 4)
+    a, x = (as_stored(rng.standard_normal((M, K)), torch.float32) for _ in range(2))
+    odd = torch.zeros(2 * K * N + 1, device="cuda")
+    Wn, Ws = odd[1: 1 + K * N].view(K, N), odd[1 + K * N:].view(K, N)      # 4 bytes past a 16-byte boundary
+    Wn.copy_(torch.randn(K, N, device="cuda") / K ** 0.5)
+    Ws.copy_(torch.randn(K, N, device="cuda") / K ** 0.5)
+    bias = torch.randn(N, device="cuda")
+    A, X = padded(a, ld, torch.float32, fill=float("nan")), padded(x, ld, torch.float32, fill=float("nan"))
+    out = torch.full((M, ldo), 7.0, device="cuda")
+    P.gnn_linear_fwd(None, M, A, X if two else None, K, Wn, Ws if two else None, bias, out, relu=False, ws=P.Workspace())
+    want = a @ host64(Wn) + host64(bias) + (x @ host64(Ws) if two else 0.0)
+    size = np.abs(a) @ np.abs(host64(Wn)) + np.abs(host64(bias)) + (np.abs(x) @ np.abs(host64(Ws)) if two else 0.0)
+    # a sum of n products in fp32, in any order: at most (n + 1) * 2^-24 of the sum of magnitudes
+    assert (np.abs(host64(out)[:, :N] - want) <= ((2 * K if two else K) + 2) * 2.0 ** -24 * size).all()
+    assert (host64(out)[:, N:] == 7.0).all()
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("K,N,two", [(64, 8, False), (72, 48, True), (256, 256, True), (512, 512, True)])
 def test_weight_gradients_at_any_number_of_splits(dtype, K, N, two):
