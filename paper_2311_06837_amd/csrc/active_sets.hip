@@ -49,6 +49,7 @@
 #include "common.h"
 #include "hashkey.h"
 #include "scan.h"
+#include <type_traits>
 
 namespace gnnhot {
 
@@ -695,11 +696,15 @@ __global__ __launch_bounds__(256) void eas_expand_long_kernel(const int32_t* __r
 //   two levels: 2000 vertices of degree 5 71 / 32, 34 / 13; 10 000 of 10 78 / 55, 41 / 36; 15 000 of 8 80 / 63, 43 / 44; 30 000 of 2 81 / 59, 46 / 39,
 //   of 4 83 / 74, 46 / 54; three: 20 000 of 5 94 / 75, 56 / 56; 30 000 of 4 97 / 95, 60 / 75; 32 000 around one hub, 96 000 entries, 83 / 102, 42 / 82
 //   eight: 12 000 of 10 142 / 75, 100 / 55; 32 000 of 4 151 / 118, 112 / 99
+// With the transposed graph a level behind which few vertices are left starts from those (10 000 of 10, two levels 61.5 -> 51.7; 15 000 of 8
+// 69.8 -> 58.4; 5000 of 20, three 64.4 -> 52.2), and nothing is looked for once all are reached.
 static bool as_takes_small(int32_t n, int64_t nnz, int32_t L) { return nnz + 3 * (int64_t)n <= 168000 || L >= 5; }
 constexpr int32_t kAsSmallRows = 32 * 1024;
 constexpr int64_t kAsSmallEntries = (int64_t)1 << 17;
 
-__global__ __launch_bounds__(1024) void as_small_kernel(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int32_t n,
+template <bool BOTH>     // with the transposed graph
+__global__ __launch_bounds__(1024) void as_small_kernel(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
+                                                        const int32_t* __restrict__ row_ptr_t, const int32_t* __restrict__ col_idx_t, int32_t n,
                                                         const int32_t* __restrict__ targets, int32_t n_targets, int32_t L,
                                                         int32_t* __restrict__ dist, int32_t* ring_ids, int64_t* __restrict__ hop_offsets) {
     constexpr int kRows = 4096, kPer = kRows / 1024, kWords = (int)(kAsSmallEntries / 32), kU = 8, kRowBit = 18, kRow = 1 << kRowBit;
@@ -709,6 +714,7 @@ __global__ __launch_bounds__(1024) void as_small_kernel(const int32_t* __restric
     __shared__ int32_t s_first[kRows];        // of the rows with entries: position of the first, less the edges before it
     __shared__ uint32_t s_begin[kWords];      // bit: the edge begins a row
     __shared__ uint16_t s_rank[kWords];       // rows that begin before the word's edges
+    __shared__ uint16_t s_left[BOTH ? kRows : 1];        // unreached vertices, then those of them with entries
     __shared__ int s_part[16];
     const int tid = (int)threadIdx.x;
     s_seen[tid] = 0u;
@@ -740,64 +746,87 @@ __global__ __launch_bounds__(1024) void as_small_kernel(const int32_t* __restric
             dist[v] = ring;
         }
         if (ring == L) break;
-        if (count == 0) {      // nothing more is reached
+        if (count == 0 || total == n) {      // nothing more is reached
             for (int32_t r = ring + 1 + tid; r <= L; r += 1024) hop_offsets[r + 1] = total;
             break;
         }
-        __syncthreads();       // the ring's ids are there
-        for (int32_t c0 = begin; c0 < total; c0 += kRows) {
-            int32_t s[kPer], len[kPer], v[kPer], sum = 0;
-#pragma unroll
-            for (int k = 0; k < kPer; ++k) v[k] = ring_ids[c0 + tid * kPer + k < total ? c0 + tid * kPer + k : begin];
-#pragma unroll
-            for (int k = 0; k < kPer; ++k) {
-                s[k] = row_ptr[v[k]];
-                len[k] = row_ptr[v[k] + 1] - s[k];
-            }
-#pragma unroll
-            for (int k = 0; k < kPer; ++k) {
-                if (c0 + tid * kPer + k >= total) len[k] = 0;
-                sum += len[k] | (len[k] > 0 ? kRow : 0);      // edges (2^17 at most) and rows with some (4096: 2^30), in one sum
-            }
-            int all;
-            int at = block_exclusive_scan<1024>(sum, s_part, &all);
-            const int edges = all & (kRow - 1), words = (edges + 31) / 32;
-            for (int w = tid; w < words; w += 1024) s_begin[w] = 0u;
-            __syncthreads();
-#pragma unroll
-            for (int k = 0; k < kPer; ++k) {
-                if (len[k] == 0) continue;
-                const int off = at & (kRow - 1);
-                s_first[at >> kRowBit] = s[k] - off;
-                atomicOr(&s_begin[off >> 5], 1u << (off & 31));
-                at += len[k] | kRow;
-            }
-            __syncthreads();
-            const int each = (words + 1023) / 1024;              // words a thread, one after the other
-            int mine = 0, rank_all;
-            for (int w = tid * each; w < (tid + 1) * each && w < words; ++w) mine += __popc(s_begin[w]);
-            int rank = block_exclusive_scan<1024>(mine, s_part, &rank_all);
-            for (int w = tid * each; w < (tid + 1) * each && w < words; ++w) {
-                s_rank[w] = (uint16_t)rank;
-                rank += __popc(s_begin[w]);
-            }
-            __syncthreads();
-            for (int32_t e0 = tid; e0 < edges; e0 += kU * 1024) {
-                int32_t u[kU];
-#pragma unroll
-                for (int j = 0; j < kU; ++j) {
-                    const int32_t e = e0 + j * 1024 < edges ? e0 + j * 1024 : edges - 1;
-                    const int row = s_rank[e >> 5] + __popc(s_begin[e >> 5] & (~0u >> (31 - (e & 31)))) - 1;
-                    u[j] = col_idx[s_first[row] + e];
-                }
-#pragma unroll
-                for (int j = 0; j < kU; ++j) {
-                    const uint32_t bit = 1u << (u[j] & 31);
-                    if ((s_seen[u[j] >> 5] & bit) == 0u) atomicOr(&s_seen[u[j] >> 5], bit);
-                }
-            }
-            __syncthreads();
+        // From the unreached vertices instead, where few are left: a transposed row with an entry in the ring is reached.
+        const int32_t left = n - total;
+        const bool pull = BOTH && left <= kRows && 2 * left < count;      // uniform
+        if (pull) {
+            uint32_t rest = ~visited & (tid * 32 + 32 <= n ? ~0u : tid * 32 < n ? (1u << (n & 31)) - 1u : 0u);
+            int place, all;
+            place = block_exclusive_scan<1024>(__popc(rest), s_part, &all);
+            for (; rest; rest &= rest - 1u) s_left[place++] = (uint16_t)(tid * 32 + __ffs(rest) - 1);
         }
+        __syncthreads();       // the ring's ids are there
+        auto expand = [&](auto from_left, const int32_t* __restrict__ rows, const int32_t* __restrict__ cols, int32_t from, int32_t end) {
+            constexpr bool kLeft = decltype(from_left)::value;
+            for (int32_t c0 = from; c0 < end; c0 += kRows) {
+                int32_t s[kPer], len[kPer], v[kPer], sum = 0;
+#pragma unroll
+                for (int k = 0; k < kPer; ++k) {
+                    const int32_t i = c0 + tid * kPer + k < end ? c0 + tid * kPer + k : from;
+                    v[k] = kLeft ? (int32_t)s_left[i] : ring_ids[i];
+                }
+#pragma unroll
+                for (int k = 0; k < kPer; ++k) {
+                    s[k] = rows[v[k]];
+                    len[k] = rows[v[k] + 1] - s[k];
+                }
+#pragma unroll
+                for (int k = 0; k < kPer; ++k) {
+                    if (c0 + tid * kPer + k >= end) len[k] = 0;
+                    sum += len[k] | (len[k] > 0 ? kRow : 0);      // edges (2^17 at most) and rows with some (4096: 2^30), in one sum
+                }
+                int all;
+                int at = block_exclusive_scan<1024>(sum, s_part, &all);
+                const int edges = all & (kRow - 1), words = (edges + 31) / 32;
+                for (int w = tid; w < words; w += 1024) s_begin[w] = 0u;
+                __syncthreads();
+#pragma unroll
+                for (int k = 0; k < kPer; ++k) {
+                    if (len[k] == 0) continue;
+                    const int off = at & (kRow - 1);
+                    s_first[at >> kRowBit] = s[k] - off;
+                    if (kLeft) s_left[at >> kRowBit] = (uint16_t)v[k];      // (one chunk: all have been read)
+                    atomicOr(&s_begin[off >> 5], 1u << (off & 31));
+                    at += len[k] | kRow;
+                }
+                __syncthreads();
+                const int each = (words + 1023) / 1024;              // words a thread, one after the other
+                int mine = 0, rank_all;
+                for (int w = tid * each; w < (tid + 1) * each && w < words; ++w) mine += __popc(s_begin[w]);
+                int rank = block_exclusive_scan<1024>(mine, s_part, &rank_all);
+                for (int w = tid * each; w < (tid + 1) * each && w < words; ++w) {
+                    s_rank[w] = (uint16_t)rank;
+                    rank += __popc(s_begin[w]);
+                }
+                __syncthreads();
+                for (int32_t e0 = tid; e0 < edges; e0 += kU * 1024) {
+                    int32_t u[kU];
+                    int row[kU];
+#pragma unroll
+                    for (int j = 0; j < kU; ++j) {
+                        const int32_t e = e0 + j * 1024 < edges ? e0 + j * 1024 : edges - 1;
+                        row[j] = s_rank[e >> 5] + __popc(s_begin[e >> 5] & (~0u >> (31 - (e & 31)))) - 1;
+                        u[j] = cols[s_first[row[j]] + e];
+                    }
+#pragma unroll
+                    for (int j = 0; j < kU; ++j) {
+                        if (kLeft) {
+                            if ((s_new[u[j] >> 5] >> (u[j] & 31) & 1u) == 0u) continue;
+                            u[j] = s_left[row[j]];
+                        }
+                        const uint32_t bit = 1u << (u[j] & 31);
+                        if ((s_seen[u[j] >> 5] & bit) == 0u) atomicOr(&s_seen[u[j] >> 5], bit);
+                    }
+                }
+                __syncthreads();
+            }
+        };
+        if (BOTH && pull) expand(std::true_type{}, row_ptr_t, col_idx_t, 0, left);
+        else expand(std::false_type{}, row_ptr, col_idx, begin, total);
     }
 }
 
@@ -861,7 +890,8 @@ extern "C" int32_t gnn_build_active_sets(const gnn_csr* g, const gnn_csr* gt, co
 
     const bool small = n > 0 && n <= kAsSmallRows && g->nnz <= kAsSmallEntries && as_takes_small(n, g->nnz, L);
     if (small) {
-        as_small_kernel<<<1, 1024, 0, stream>>>(g->row_ptr, g->col_idx, n, targets, n_targets, L, dist, ring_ids, hop_offsets);
+        if (gt != nullptr) as_small_kernel<true><<<1, 1024, 0, stream>>>(g->row_ptr, g->col_idx, gt->row_ptr, gt->col_idx, n, targets, n_targets, L, dist, ring_ids, hop_offsets);
+        else as_small_kernel<false><<<1, 1024, 0, stream>>>(g->row_ptr, g->col_idx, nullptr, nullptr, n, targets, n_targets, L, dist, ring_ids, hop_offsets);
         GNN_LAUNCH_CHECK("as_small_kernel");
     } else {
         as_init_kernel<<<grid_for(n > L + 2 ? n : L + 2, 256, 2048), 256, 0, stream>>>(dist, n, visited[0], seen, nw, ctrl, (int32_t)ctrl_words,

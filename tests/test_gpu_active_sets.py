@@ -244,3 +244,23 @@ def test_a_hub_in_a_small_graph_costs_no_more_than_in_a_larger_one():
             times.append(a.elapsed_time(b) * 50)
         return min(times)
     assert time_us(32_000) < 1.4 * time_us(32_800)
+
+
+@pytest.mark.parametrize("n_targets,n_left", [(8193, 4096), (8192, 4096), (20_000, 4097), (20_000, 31), (3, 1), (2, 1), (70, 0)])
+def test_small_graphs_whose_last_vertices_look_for_themselves(n_targets, n_left):
+    """One launch with the transposed graph: a level behind which few vertices are left starts from those (at most 4096, fewer than half
+    of the ring).  Some are reached at once, some by the others one level on, one has many entries, some have none."""
+    rng = np.random.default_rng(n_left)
+    n = n_targets + n_left
+    left = np.arange(n_targets, n)
+    first, second = left[: n_left // 2], left[n_left // 2: n_left - n_left // 4]      # the rest is never reached
+    rows = [rng.integers(0, n_targets, first.size), rng.integers(0, n_targets, n_targets)]
+    cols = [first, rng.integers(0, n_targets, n_targets)]
+    if first.size:
+        rows += [first[rng.integers(0, first.size, second.size)], rng.integers(0, n_targets, 3000)]
+        cols += [second, np.full(3000, first[0])]
+    rows += [second, left]
+    cols += [rng.integers(0, n_targets, second.size), left]
+    g = gg.csr_from_edges(n, n, np.concatenate(rows).astype(np.int64), np.concatenate(cols).astype(np.int64))
+    for L in (1, 2, 4):
+        _compare(g, rng.permutation(n_targets).astype(np.int32), L)
