@@ -776,6 +776,176 @@ __global__ __launch_bounds__(256, MINB) void gemm_nt_wide_kernel(GemmNT a) {
 }
 
 // ------------------------------------------------------------------------------------------
+// gemm_nt, small tile: fp32 products of so few rows that tiles of 128 leave CUs without work.
+//
+// A CU that has one tile is bound by the chain of its slices: barrier, LDS, the matrix instructions of a wavefront one after another.
+// 64 x 64 quarters the last (16 of 32x32x2 a slice of 32 elements, a block of 32 x 32 a wavefront), and three slices are on their way in
+// registers while one is multiplied from one half of the LDS and the next is put into the other: one barrier a slice.  256 + 256 -> 256,
+// 2000 rows: 27.1 -> 17.3 us, 0.9 us a slice of 32 with the tile of 128 and 0.55 here.  Twice the operand bytes a product of the larger tiles: see the
+// dispatch for where those win.
+// ------------------------------------------------------------------------------------------
+template <bool KTAIL, bool BKN>
+__global__ __launch_bounds__(256, 3) void gemm_nt_small_kernel(GemmNT a) {
+    constexpr int B = 64, EPS = 32, CROW = 36;    // tile, reduction elements of a slice, words of a staged output row
+    constexpr int HALF = B * EPS;                 // words of an operand's slice
+    __shared__ __attribute__((aligned(16))) uint32_t s_mem[4 * HALF];
+    uint32_t* const smem = s_mem;                 // (an access through the array itself counts as aligned to one word only, and is split)
+    __shared__ float s_bias[B];
+    __shared__ int32_t s_crow[B];
+    const int tiles_n = (a.N + B - 1) / B;
+    const int turn = (int)(blockIdx.x >> 3);
+    const int m0 = ((turn / tiles_n) * 8 + (int)(blockIdx.x & 7)) * B, n0 = (turn % tiles_n) * B;
+    if (m0 >= a.M) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave >> 1, wn = wave & 1;
+    const int li = lane & 31, g = lane >> 5;
+    // loader: eight lanes fetch a line of a row, rows r and r + 32; down the columns of W a wavefront takes 64 columns of four elements
+    const int row = tid >> 3, ch = tid & 7;
+    auto a_row = [&](int m) -> int64_t {
+        const int64_t r = m < a.M ? (a.a_rows ? (int64_t)a.a_rows[m] : (int64_t)m) : (a.a_rows ? (int64_t)a.a_rows[0] : 0);
+        return r * a.lda * 4;
+    };
+    const int64_t ao0 = a_row(m0 + row), ao1 = a_row(m0 + row + 32);
+    const int bn0 = BKN ? n0 + lane : n0 + row, bn1 = BKN ? bn0 : bn0 + 32;
+    const int64_t bo0 = (int64_t)(bn0 < a.N ? bn0 : 0) * (BKN ? 4 : a.ldb * 4), bo1 = (int64_t)(bn1 < a.N ? bn1 : 0) * (BKN ? 4 : a.ldb * 4);
+    const int bch0 = BKN ? wave : ch, bch1 = BKN ? wave + 4 : ch;      // the chunk of the slice
+    const int k_slices = (a.K + EPS - 1) / EPS;
+    const int n_steps = k_slices * ((a.n_src == 2 && m0 >= a.M1) ? 1 : a.n_src);
+    const bool z0 = m0 + row >= a.M1, z1 = m0 + row + 32 >= a.M1;
+
+    struct Slice {
+        uint4 a0, a1, b0, b1;
+    };
+    auto at = [&](int step, int& src, int& sl) {     // (a fetch beyond the last slice repeats it)
+        const int st = step < n_steps ? step : n_steps - 1;
+        src = st >= k_slices ? 1 : 0;
+        sl = st - src * k_slices;
+    };
+    auto fetch = [&](Slice& x, int step) {
+        int src, sl;
+        at(step, src, sl);
+        const char* const A = (const char*)(src ? a.A[1] : a.A[0]);
+        const char* const W = (const char*)(src ? a.Bt[1] : a.Bt[0]);
+        const int k = sl * EPS + ch * 4;
+        const int64_t ko = (int64_t)(!KTAIL || k < a.K ? k : 0) * 4;
+        x.a0 = *(const uint4*)(A + ao0 + ko);
+        x.a1 = *(const uint4*)(A + ao1 + ko);
+        if constexpr (BKN) {
+            auto column = [&](int64_t off, int k0) -> uint4 {
+                auto w = [&](int kk) { return *(const uint32_t*)(W + off + (int64_t)(!KTAIL || kk < a.K ? kk : 0) * a.ldb * 4); };
+                return make_uint4(w(k0), w(k0 + 1), w(k0 + 2), w(k0 + 3));
+            };
+            x.b0 = column(bo0, sl * EPS + bch0 * 4);
+            x.b1 = column(bo1, sl * EPS + bch1 * 4);
+        } else {
+            x.b0 = *(const uint4*)(W + bo0 + ko);
+            x.b1 = *(const uint4*)(W + bo1 + ko);
+        }
+    };
+    auto place = [&](int r, int c) { return r * EPS + ((c ^ ((r >> 1) & 7)) << 2); };     // of chunk c of row r: no bank conflicts
+    const int sa0 = place(row, ch), sa1 = place(row + 32, ch);
+    const int sb0 = HALF + (BKN ? place(lane, bch0) : sa0), sb1 = HALF + (BKN ? place(lane, bch1) : sa1);
+    auto stash = [&](Slice& x, int step, int buf) {
+        int src, sl;
+        at(step, src, sl);
+        if (KTAIL) {
+            const int left = a.K - sl * EPS;
+            x.a0 = fix_chunk<GNN_F32>(x.a0, left - ch * 4);
+            x.a1 = fix_chunk<GNN_F32>(x.a1, left - ch * 4);
+            x.b0 = fix_chunk<GNN_F32>(x.b0, left - bch0 * 4);
+            x.b1 = fix_chunk<GNN_F32>(x.b1, left - bch1 * 4);
+        }
+        if (src != 0) {
+            if (z0) x.a0 = make_uint4(0u, 0u, 0u, 0u);
+            if (z1) x.a1 = make_uint4(0u, 0u, 0u, 0u);
+        }
+        *(uint4*)&smem[buf + sa0] = x.a0;
+        *(uint4*)&smem[buf + sa1] = x.a1;
+        *(uint4*)&smem[buf + sb0] = x.b0;
+        *(uint4*)&smem[buf + sb1] = x.b1;
+    };
+    v16f acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    const int fa = (wm * 32 + li) * EPS, fb = HALF + (wn * 32 + li) * EPS, sw = (li >> 1) & 7;
+    auto multiply = [&](int buf) {
+        uint4 x[4], y[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int slot = ((g * 4 + q) ^ sw) << 2;
+            x[q] = *(const uint4*)&smem[buf + fa + slot];
+            y[q] = *(const uint4*)&smem[buf + fb + slot];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const uint32_t xt = t == 0 ? x[q].x : t == 1 ? x[q].y : t == 2 ? x[q].z : x[q].w, yt = t == 0 ? y[q].x : t == 1 ? y[q].y : t == 2 ? y[q].z : y[q].w;
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(xt), __uint_as_float(yt), acc, 0, 0, 0);
+            }
+    };
+    // top of step s: LDS half s % 2 holds slice s, the register sets s + 1, s + 2 and s + 3 (mod 3), possibly in flight
+    Slice x0, x1, x2;
+    fetch(x0, 0);
+    fetch(x1, 1);
+    fetch(x2, 2);
+    if (tid < B) {
+        s_bias[tid] = (a.bias && n0 + tid < a.N) ? a.bias[n0 + tid] : 0.f;
+        s_crow[tid] = m0 + tid < a.M ? (a.c_rows ? a.c_rows[m0 + tid] : m0 + tid) : -1;
+    }
+    stash(x0, 0, 0);
+    fetch(x0, 3);
+    __syncthreads();
+    int buf = 0;
+    auto step = [&](Slice& x, int s) {
+        multiply(buf);
+        buf ^= 2 * HALF;
+        stash(x, s + 1, buf);
+        fetch(x, s + 4);
+        __syncthreads();
+    };
+    int s = 0;
+    for (; s + 3 <= n_steps; s += 3) {      // nothing in here is conditional: the compiler then knows which loads a step waits for
+        step(x1, s);
+        step(x2, s + 1);
+        step(x0, s + 2);
+    }
+    if (s < n_steps) step(x1, s);
+    if (s + 1 < n_steps) step(x2, s + 1);
+    // epilogue: as in the wide variant, a piece of 32 rows x 32 columns a wavefront
+    uint32_t* const stg = smem + wave * 32 * CROW;
+    const float bv = s_bias[wn * 32 + li];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        float v = acc[r] + bv;
+        if (a.relu) v = v > 0.f ? v : 0.f;
+        stg[((r >> 2) * 8 + g * 4 + (r & 3)) * CROW + li] = __float_as_uint(v);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int pass = 0; pass < 4; ++pass) {
+        const int r = pass * 8 + (lane >> 3), c = lane & 7;
+        const int m = m0 + wm * 32 + r, n = n0 + wn * 32 + c * 4;
+        const int64_t crow = s_crow[wm * 32 + r];
+        if (crow >= 0 && n < a.N) {
+            uint4 v = *(const uint4*)&stg[r * CROW + c * 4];
+            float* const dst = (float*)a.C + crow * a.ldc + n;
+            if (n + 4 <= a.N && a.c_vec && (!a.mask || a.m_vec)) {
+                if (a.mask) v = post_vec<GNN_F32>(v, a.C, crow * a.ldc + n, m < a.n_acc, a.mask, crow * a.ldm + n);
+                *(uint4*)dst = v;
+            } else {
+                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+                for (int e = 0; e < 4 && n + e < a.N; ++e) {
+                    float o = __uint_as_float(w[e]);
+                    if (a.mask) o = post_elem<GNN_F32>(o, a.C, crow * a.ldc + n + e, m < a.n_acc, a.mask, crow * a.ldm + n + e);
+                    dst[e] = o;
+                }
+            }
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------
 // gemm_nt, line tile.  Same tile as the wide variant (128 rows x the whole output width, a wave
 // 64 x 32*NTW), two things done differently.
 // (1) The reduction moves in slices of 128 bytes - one whole cache line of every operand row.  With
@@ -1112,6 +1282,31 @@ static int32_t launch_gemm_nt(const GemmNT& a, hipStream_t stream, const void* c
     }
     const int64_t tiles_m = ((int64_t)a.M + 127) / 128;
     const bool vec = a.a_vec && a.b_vec;  // both operands aligned: the branch-free loader
+    if constexpr (DT == GNN_F32) {
+        // Tiles of 64 where they are at most one a CU, or three where tiles of 128 rows are two.  us, small / as below, with one a CU:
+        // 256 + 256 -> 256 300 rows 16.8 / 27.1, 2000 17.3 / 27.1; 256 -> 64 10 000 10.4 / 16.3; 602 + 602 -> 41 16 000 38.3 / 61.1; 512 + 512 -> 128
+        // 7000 30.3 / 47.2; 128 -> 128 2000 7.8 / 10.3; 256 -> 16 16 000 10.6 / 14.8; with three: 256 + 256 -> 256 10 000 36.8 / 45.2; 256 -> 64 33 000 20.8 / 26.4;
+        // 602 + 602 -> 41 33 000 78 / 97; 100 + 100 -> 256 10 000 24.1 / 27.2.  With two, against one of 128 rows: 256 + 256 -> 256 7000 27.2 / 29.0, but
+        // 100 + 100 -> 256 18.4 / 17.0; with more: 256 + 256 -> 256 60 000 146 / 141, 100 + 100 -> 256 24 000 39 / 36.  64 elements in one tile of
+        // columns are all latency, and down the columns of W both wait alike: 64 -> 64 2000 8.7 / 8.6, 64 -> 16 8.9 / 8.8 (64 -> 602 3500 rows 10.3 / 17.9);
+        // without a copy to make (input gradients) 64 -> 64 2000 6.9 / 8.3, 16 -> 64 7.0 / 8.9, 16 -> 16 6.8 / 8.0,
+        // 256 -> 256 10.1 / 16.2, 8 -> 64 6.8 / 6.7.
+        // The weights as they are stored / a copy: 256 + 256 -> 256 2000 17.3 / 18.2, 512 + 512 -> 128 29.6 / 28.6, 602 -> 41 9500 23.4 / 21.7.
+        const int64_t small = (((int64_t)a.M + 63) / 64 + 7) / 8 * 8 * ((a.N + 63) / 64);
+        if (vec && a.K > 0 && (small <= 256 || (small > 512 && small <= 768 && a.N > 32)) && ((int64_t)a.K * a.n_src > 64 || a.N > 64 || W == nullptr)) {
+            const bool direct = W != nullptr && (int64_t)a.K * a.n_src <= 512;
+            const bool tail = a.K % 32 != 0;
+            if (direct && tail) gemm_nt_small_kernel<true, true><<<(unsigned)small, 256, 0, stream>>>(b);
+            else if (direct) gemm_nt_small_kernel<false, true><<<(unsigned)small, 256, 0, stream>>>(b);
+            else {
+                GNN_CHECK(transpose());
+                if (tail) gemm_nt_small_kernel<true, false><<<(unsigned)small, 256, 0, stream>>>(a);
+                else gemm_nt_small_kernel<false, false><<<(unsigned)small, 256, 0, stream>>>(a);
+            }
+            GNN_LAUNCH_CHECK("gemm_nt_small_kernel");
+            return GNN_OK;
+        }
+    }
     if (vec && a.N > 32 && a.K > 0) {
         // wide tile: the tile width that pads the output width least (256 on a tie)
         const int64_t p256 = ((int64_t)a.N + 255) / 256 * 256, p128 = ((int64_t)a.N + 127) / 128 * 128, p64 = ((int64_t)a.N + 63) / 64 * 64;

@@ -399,6 +399,36 @@ def test_forward_products_that_read_the_weights_down_their_columns(M, K, N, two)
     assert (host64(out)[:, N:] == 7.0).all()
 
 
+@pytest.mark.parametrize("M", [1, 63, 64, 65, 513, 4096, 4097, 8193, 12_288, 12_289])
+@pytest.mark.parametrize("K,N,two", [(256, 256, True), (260, 256, True), (97, 100, False), (600, 64, False), (128, 31, False), (33, 48, True), (12, 65, False)])
+def test_fp32_products_on_small_tiles(M, K, N, two):
+    """Tiles of 64 and of 128 rows, both sides of where they change, ragged reductions, widths and rows; forward with a row list, the
+    input gradient with the second operand for the first rows only and the mask of the activation."""
+    import paper_2311_06837_amd as P
+    gen = torch.Generator(device="cuda").manual_seed(M * 1000 + K)
+    ints = lambda *shape: torch.randint(-3, 4, shape, generator=gen, device="cuda").float()     # every sum is exact
+    ld, ldo = _pad(K, 4), _pad(N, 4)
+    a, x, Wn, Ws, bias = ints(M + 5, ld), ints(M + 5, ld), ints(K, N), ints(K, N), ints(N)
+    a[:, K:] = x[:, K:] = float("nan")
+    rows = torch.randperm(M + 5, generator=gen, device="cuda")[:M].sort().values
+    out = torch.full((M + 5, ldo), SENT, device="cuda")
+    P.gnn_linear_fwd(rows.int(), M, a, x if two else None, K, Wn, Ws if two else None, bias, out, True)
+    want = torch.full_like(out, SENT)
+    want[rows, :N] = (a[rows, :K] @ Wn + (x[rows, :K] @ Ws if two else 0.0) + bias).clamp(min=0.0)
+    assert torch.equal(out, want)
+
+    n_self = M // 2 + 1
+    dg, dz, h = ints(M, ldo), ints(M, ldo), ints(M, ld)
+    dg[:, N:] = dz[:, N:] = float("nan")
+    dx = torch.full((M, ld), SENT, device="cuda")
+    P.gnn_linear_bwd_input2(None, M, dg, Wn, dz if two else None, Ws if two else None, n_self if two else 0, N, K, h, dx)
+    want = dg[:, :N] @ Wn.T
+    if two:
+        want[:n_self] += dz[:n_self, :N] @ Ws.T
+    assert torch.equal(dx[:, :K], torch.where(h[:, :K] > 0, want, torch.zeros_like(want)))
+    assert (dx[:, K:] == SENT).all()
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("K,N,two", [(64, 8, False), (72, 48, True), (256, 256, True), (512, 512, True)])
 def test_weight_gradients_at_any_number_of_splits(dtype, K, N, two):
