@@ -513,8 +513,8 @@ __global__ __launch_bounds__(256, NCH == 1 ? (LPR == 64 ? GNN_SPMM_MINB_WIDE : G
             const float* q = a.split_plane + part * a.split_ld + col_off[c];
 #pragma unroll
             for (int k = 0; k < VE; k += 4) {
-                const float4 t = *(const float4*)(q + k);
-                to[c][k] += t.x; to[c][k + 1] += t.y; to[c][k + 2] += t.z; to[c][k + 3] += t.w;
+                const FourRaw t = __builtin_nontemporal_load((const FourRaw*)(q + k));
+                to[c][k] += __uint_as_float(t[0]); to[c][k + 1] += __uint_as_float(t[1]); to[c][k + 2] += __uint_as_float(t[2]); to[c][k + 3] += __uint_as_float(t[3]);
             }
         }
     };
