@@ -405,6 +405,10 @@ int32_t gnn_layer_edge_mask(const gnn_csr *g, const int32_t *rows, int32_t n_act
  */
 int32_t gnn_layer_edge_mask_transposed(const gnn_csr *gT, const uint64_t *row_thr_key, const int32_t *row_thr_id,
                                        uint64_t seed, int32_t layer, uint32_t *keep_t, void *stream);
+/* The same with an optional workspace (ws_bytes NULL: none; the query says 0 where it would not help): large graphs are faster with it. */
+int32_t gnn_layer_edge_mask_transposed_ws(const gnn_csr *gT, const uint64_t *row_thr_key, const int32_t *row_thr_id,
+                                          uint64_t seed, int32_t layer, uint32_t *keep_t, void *ws, size_t *ws_bytes,
+                                          void *stream);
 
 /*
  * The same mask in the positions of the transposed graph, for the backward aggregation: bit q of keep_t (entry v

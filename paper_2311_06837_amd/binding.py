@@ -27,7 +27,8 @@ EXPORTS = ["gnn_version", "gnn_last_error", "gnn_build_active_sets", "gnn_norm_s
            "gnn_sample_boundary", "gnn_extract_partition", "gnn_gather_rows", "gnn_expand_row_ptr",
            "gnn_extract_sampled_partition", "gnn_eas_traverse", "gnn_layer_edge_mask", "gnn_transpose_edge_mask",
            "gnn_layer_edge_mask_transposed", "gnn_layer_norm_relu_fwd", "gnn_layer_norm_relu_bwd", "gnn_add_rows", "gnn_add_rows_masked", "gnn_bias_grad", "gnn_linear_bwd_input",
-           "gnn_linear_fwd_static", "gnn_linear_bwd_input2", "gnn_die_mapping", "gnn_fused_layer_fwd", "gnn_spmm_route"]
+           "gnn_linear_fwd_static", "gnn_linear_bwd_input2", "gnn_die_mapping", "gnn_fused_layer_fwd", "gnn_spmm_route",
+           "gnn_layer_edge_mask_transposed_ws"]
 
 
 class GnnError(RuntimeError):
@@ -51,7 +52,8 @@ _SIGNATURES = {
     "gnn_linear_bwd_input2": "pi" + "pppp" + "ilii" + "pl" + "pli" + "ppp",
     "gnn_bias_grad": "pipliip" + "ppp", "gnn_softmax_ce": "pi" + "plip" + "plip" + "ppp", "gnn_make_bitmap": "piipp",
     "gnn_sample_boundary": "ppp" + "iiiu" + "pplpp" + "ppp", "gnn_eas_traverse": "ppi" + "iiiu" + "pppp" + "ppp",
-    "gnn_layer_edge_mask": "ppiiiuuipppp" + "p", "gnn_layer_edge_mask_transposed": "pppuipp", "gnn_transpose_edge_mask": "ppppp",
+    "gnn_layer_edge_mask": "ppiiiuuipppp" + "p", "gnn_layer_edge_mask_transposed": "pppuipp",
+    "gnn_layer_edge_mask_transposed_ws": "pppuip" + "ppp", "gnn_transpose_edge_mask": "ppppp",
     "gnn_layer_norm_relu_fwd": "pipli" + "ppf" + "pli" + "p",
     "gnn_layer_norm_relu_bwd": "pi" + "plplpli" + "pf" + "pli" + "plppi" + "ppp",
     "gnn_add_rows": "piplplii" + "p", "gnn_add_rows_masked": "pipl" + "ipl" + "ipl" + "i" + "p",
@@ -274,8 +276,15 @@ def gnn_layer_edge_mask_transposed(gT: Graph, thr_k: torch.Tensor, thr_u: torch.
     """The layer's mask as a bit per entry of gT, from the threshold pairs of gnn_layer_edge_mask(with_thresholds=True)."""
     assert thr_k.dtype == torch.int64 and thr_u.dtype == torch.int32 and thr_k.numel() >= gT.n_cols and thr_u.numel() >= gT.n_cols
     keep_t = torch.empty(max((gT.nnz + 31) // 32, 1), dtype=torch.int32, device=thr_k.device)
-    _check(lib().gnn_layer_edge_mask_transposed(C.byref(gT.c), _ptr(thr_k), _ptr(thr_u), C.c_uint64(seed & (2 ** 64 - 1)),
-                                                C.c_int32(layer), _ptr(keep_t), _stream()))
+    fn, need, ws = lib().gnn_layer_edge_mask_transposed_ws, C.c_size_t(0), None
+    args = (C.byref(gT.c), _ptr(thr_k), _ptr(thr_u), seed & (2 ** 64 - 1), layer, _ptr(keep_t))
+    _check(fn(*args, None, C.byref(need), _stream()))
+    if need.value > 0:
+        try:
+            ws = torch.empty(need.value, dtype=torch.uint8, device=thr_k.device)
+        except torch.cuda.OutOfMemoryError:     # it can do without
+            pass
+    _check(fn(*args, _ptr(ws), None if ws is None else C.byref(need), _stream()))
     return keep_t
 
 

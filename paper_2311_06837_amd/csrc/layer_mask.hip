@@ -22,8 +22,8 @@
 //                        keys are equal.  A workgroup takes 4096 consecutive entries whatever rows they belong to, so
 //                        every word of the bitmap has one writer: no atomics, nothing to clear, no long rows.
 // Bound: the random reads (transposed), the hash (two 64-bit multiplications a mix) and the selection.  Measured on a
-// 1.2M-vertex / 60M-entry power-law graph, fanout 10: forward and transposed mask 2.61 -> 0.77 ms (forward 1.5 -> 0.35,
-// transposed 1.09 -> 0.42, its random reads into a 9.6 MB table), against `fanout` rounds over 64-bit pairs and a lane group
+// 1.2M-vertex / 60M-entry power-law graph, fanout 10: forward and transposed mask 2.61 -> 0.66 ms (forward 1.5 -> 0.34,
+// transposed 1.09 -> 0.31, its random reads into a 2.4 MB table), against `fanout` rounds over 64-bit pairs and a lane group
 // per row of the transposed graph.  Of the forward mask, long rows 335 us with whole keys in all registers whatever the length and two
 // sweeps over rows above 1024, 288 by length and with upper halves, 177 with one sweep; short rows 196, 170 with half of the
 // places where no row of the wavefront has more than 32.  300 000 vertices of degree 190, fanout 15, both masks: 797 -> 575.
@@ -370,10 +370,14 @@ constexpr int kLmChunk = 4096;   // entries per workgroup
 // 8.9 ms, searched 31 / 38 us (without any 23 us).
 constexpr int kLmWalk = 8 * kLmChunk;
 
+// TOPS: an entry reads the upper 16 bits of its row's key out of a table of their own; the pair itself is read where those of both
+// keys are equal, one entry in 65 536.  What bounds the entries is a line out of an L2 each (200 G/s, 25 TB/s) where the table fits, else the
+// misses: 1.2 M rows of 50, power-law 428 -> 313 us, uniform 660 -> 321, the copy (10 us) included; 2 M of 30 599 -> 373, 831 -> 415.
+template <bool TOPS>
 __global__ __launch_bounds__(256) void lm_mask_t_kernel(int32_t n_t, int64_t nnz, const int32_t* __restrict__ rpT,
                                                         const int32_t* __restrict__ ciT, const uint64_t* __restrict__ row_thr_key,
-                                                        const int32_t* __restrict__ row_thr_id, uint64_t seed_layer_mixed,
-                                                        uint32_t* __restrict__ keep_t) {
+                                                        const int32_t* __restrict__ row_thr_id, const uint16_t* __restrict__ tops,
+                                                        uint64_t seed_layer_mixed, uint32_t* __restrict__ keep_t) {
     constexpr int kTiles = kLmChunk / 256;          // 64-entry tiles per wavefront
     __shared__ int32_t s_start[kLmChunk];           // at the first entry of a row: its number relative to the chunk's first row
     __shared__ int32_t s_last[4], s_row[2];
@@ -437,7 +441,8 @@ __global__ __launch_bounds__(256) void lm_mask_t_kernel(int32_t n_t, int64_t nnz
         const int64_t p0 = q0 + (wave * kTiles + t) * kWave;
         if (p0 >= q1) break;   // uniform over the wavefront
         int32_t u[kU], v[kU];
-        uint64_t thr[kU];
+        uint64_t thr[TOPS ? 1 : kU];
+        uint32_t top[TOPS ? kU : 1];
 #pragma unroll
         for (int j = 0; j < kU; ++j) v[j] = p0 + j * kWave + lane < q1 ? ciT[p0 + j * kWave + lane] : -1;
 #pragma unroll
@@ -450,18 +455,38 @@ __global__ __launch_bounds__(256) void lm_mask_t_kernel(int32_t n_t, int64_t nnz
             if (starts) row = __shfl(st, 63 - __clzll((long long)starts), kWave);   // uniform over the wavefront
         }
 #pragma unroll
-        for (int j = 0; j < kU; ++j) thr[j] = row_thr_key[v[j] >= 0 ? v[j] : 0];
+        for (int j = 0; j < kU; ++j) {
+            if (TOPS) top[TOPS ? j : 0] = tops[v[j] >= 0 ? v[j] : 0];
+            else thr[TOPS ? 0 : j] = row_thr_key[v[j] >= 0 ? v[j] : 0];
+        }
 #pragma unroll
         for (int j = 0; j < kU; ++j) {
             const uint64_t k = edge_key(seed_layer_mixed, (uint64_t)(v[j] >= 0 ? v[j] : 0), (uint64_t)u[j]);
-            bool bit = v[j] >= 0 && k <= thr[j];
-            if (bit && k == thr[j]) bit = u[j] <= row_thr_id[v[j]];
+            bool bit;
+            if (TOPS) {
+                const uint32_t t = (uint32_t)(k >> 48);
+                bit = v[j] >= 0 && t < top[TOPS ? j : 0];
+                if (v[j] >= 0 && t == top[TOPS ? j : 0]) bit = !pair_less(row_thr_key[v[j]], row_thr_id[v[j]], k, u[j]);
+            } else {
+                bit = v[j] >= 0 && k <= thr[TOPS ? 0 : j];
+                if (bit && k == thr[TOPS ? 0 : j]) bit = u[j] <= row_thr_id[v[j]];
+            }
             const uint64_t m = __ballot(bit);
             const int64_t p = p0 + j * kWave + lane * 32;
             if (lane < 2 && p < q1) keep_t[p >> 5] = (uint32_t)(m >> (32 * lane));
         }
     }
 }
+
+__global__ __launch_bounds__(256) void lm_tops_kernel(const uint64_t* __restrict__ row_thr_key, uint16_t* __restrict__ tops, int64_t n) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        tops[i] = (uint16_t)(row_thr_key[i] >> 48);
+}
+
+// The line: a table of keys that an L2 (4 MB) holds anyway gains nothing, and fewer entries a row would not pay for the copy (measured down to
+// 5).  us, keys / tops, power-law and uniform graphs: 300 000 rows of 5 14.5 / 14.5, 13.4 / 15.3, of 10 22.5 / 22.9, 23.0 / 25.8, of 190 245 / 226,
+// 254 / 251; 500 000 of 20 62.2 / 58.5, 68.7 / 63.4, of 100 253 / 214, 268 / 233; 1.2 M of 5 45.5 / 42.2, 64.6 / 40.5, of 10 88 / 71, 142 / 79.
+static bool lm_takes_tops(const gnn_csr* gT) { return gT->n_cols >= 400000 && gT->nnz >= 4 * (int64_t)gT->n_cols; }
 
 // thresholds of the rows that are not listed: nothing is <= (0, -1)
 __global__ __launch_bounds__(256) void lm_thr_init_kernel(uint64_t* __restrict__ k, int32_t* __restrict__ u, int64_t n) {
@@ -575,17 +600,40 @@ extern "C" int32_t gnn_transpose_edge_mask(const gnn_csr* g, const gnn_csr* gT, 
     return GNN_OK;
 }
 
-extern "C" int32_t gnn_layer_edge_mask_transposed(const gnn_csr* gT, const uint64_t* row_thr_key, const int32_t* row_thr_id, uint64_t seed,
-                                                  int32_t layer, uint32_t* keep_t, void* stream_) {
-    hipStream_t stream = (hipStream_t)stream_;
+static int32_t mask_transposed(const gnn_csr* gT, const uint64_t* row_thr_key, const int32_t* row_thr_id, uint64_t seed, int32_t layer,
+                               uint32_t* keep_t, void* ws, size_t* ws_bytes, hipStream_t stream) {
     GNN_CHECK(check_csr(gT, "gT"));
     GNN_REQUIRE(layer >= 0, GNN_ERR_INVALID_ARG, "layer < 0");
+    WsCarver carve(ws);
+    uint16_t* const tops = ws_bytes != nullptr && lm_takes_tops(gT) ? carve.take<uint16_t>((size_t)gT->n_cols) : nullptr;
+    if (ws_bytes != nullptr) {
+        bool query;
+        GNN_CHECK(ws_protocol(ws, ws_bytes, carve.used, &query));
+        if (query) return GNN_OK;
+    }
     const int64_t n_words = (gT->nnz + 31) / 32;
     GNN_REQUIRE(n_words == 0 || (row_thr_key && row_thr_id && keep_t), GNN_ERR_INVALID_ARG, "row_thr_key, row_thr_id or keep_t is NULL");
-    if (n_words > 0) {
-        lm_mask_t_kernel<<<(int)((gT->nnz + kLmChunk - 1) / kLmChunk), 256, 0, stream>>>(
-            gT->n_rows, gT->nnz, gT->row_ptr, gT->col_idx, row_thr_key, row_thr_id, mix64(seed + (uint64_t)layer), keep_t);
-        GNN_LAUNCH_CHECK("lm_mask_t_kernel");
+    if (n_words == 0) return GNN_OK;
+    const int grid = (int)((gT->nnz + kLmChunk - 1) / kLmChunk);
+    const uint64_t mixed = mix64(seed + (uint64_t)layer);
+    if (tops != nullptr) {
+        lm_tops_kernel<<<grid_for(gT->n_cols, 256, 4096), 256, 0, stream>>>(row_thr_key, tops, gT->n_cols);
+        GNN_LAUNCH_CHECK("lm_tops_kernel");
+        lm_mask_t_kernel<true><<<grid, 256, 0, stream>>>(gT->n_rows, gT->nnz, gT->row_ptr, gT->col_idx, row_thr_key, row_thr_id, tops, mixed, keep_t);
+    } else {
+        lm_mask_t_kernel<false><<<grid, 256, 0, stream>>>(gT->n_rows, gT->nnz, gT->row_ptr, gT->col_idx, row_thr_key, row_thr_id, nullptr, mixed,
+                                                          keep_t);
     }
+    GNN_LAUNCH_CHECK("lm_mask_t_kernel");
     return GNN_OK;
+}
+
+extern "C" int32_t gnn_layer_edge_mask_transposed(const gnn_csr* gT, const uint64_t* row_thr_key, const int32_t* row_thr_id, uint64_t seed,
+                                                  int32_t layer, uint32_t* keep_t, void* stream_) {
+    return mask_transposed(gT, row_thr_key, row_thr_id, seed, layer, keep_t, nullptr, nullptr, (hipStream_t)stream_);
+}
+
+extern "C" int32_t gnn_layer_edge_mask_transposed_ws(const gnn_csr* gT, const uint64_t* row_thr_key, const int32_t* row_thr_id, uint64_t seed,
+                                                     int32_t layer, uint32_t* keep_t, void* ws, size_t* ws_bytes, void* stream_) {
+    return mask_transposed(gT, row_thr_key, row_thr_id, seed, layer, keep_t, ws, ws_bytes, (hipStream_t)stream_);
 }

@@ -213,6 +213,50 @@ def test_transposed_mask_across_long_runs_of_empty_rows(run):
     assert np.array_equal(_bits(kt, gt.nnz), oracle.transpose_mask(g.row_ptr, g.col_idx, ok, gt.row_ptr, gt.col_idx))
 
 
+@pytest.mark.parametrize("n_cols,per_col", [(399_999, 4), (400_000, 4), (400_003, 5)])
+def test_transposed_mask_of_many_columns(n_cols, per_col):
+    """From 400 000 columns on an entry looks at the upper 16 bits of its column's key first.  Pairs that are an entry's own, one less or
+    one more in key or id, with equal upper bits all of them, and the keys' extremes; with a workspace and without."""
+    import ctypes as C
+    import paper_2311_06837_amd as P
+    from paper_2311_06837_amd import binding as B
+    rng = np.random.default_rng(n_cols)
+    n, nnz, layer, seed = 999, n_cols * per_col, 2, 12345
+    cols = rng.permutation(np.arange(nnz, dtype=np.int64) % n_cols).astype(np.int32)
+    at = np.sort(rng.integers(0, nnz + 1, n - 1))
+    gt = gg.CSR(n, n_cols, np.concatenate([[0], at, [nnz]]).astype(np.int32), cols)
+    u = np.repeat(np.arange(n, dtype=np.uint64), np.diff(gt.row_ptr))
+
+    def mix(x):      # splitmix64's finaliser, as the header's key
+        x = x + np.uint64(0x9E3779B97F4A7C15)
+        x = (x ^ (x >> np.uint64(30))) * np.uint64(0xBF58476D1CE4E5B9)
+        x = (x ^ (x >> np.uint64(27))) * np.uint64(0x94D049BB133111EB)
+        return x ^ (x >> np.uint64(31))
+    key = mix(mix(mix(np.full(1, seed + layer, dtype=np.uint64)) ^ cols.astype(np.uint64)) ^ u)
+    own = np.zeros(n_cols, dtype=np.int64)
+    own[cols] = np.arange(nnz)                                  # one entry of every column
+    thr_k, thr_u = key[own].copy(), u[own].astype(np.int32)
+    how = rng.integers(0, 8, n_cols)
+    thr_u[how == 1] -= 1
+    thr_u[how == 2] += 1
+    thr_k[how == 3] -= np.uint64(1)
+    thr_k[how == 4] += np.uint64(1)
+    thr_k[how == 5] ^= np.uint64(1 << 47)                       # the upper bits stay
+    thr_k[how == 6], thr_u[how == 6] = 0, -1
+    thr_k[how == 7], thr_u[how == 7] = np.uint64(2 ** 64 - 1), 2 ** 31 - 1
+    want = (key < thr_k[cols]) | ((key == thr_k[cols]) & (u.astype(np.int64) <= thr_u[cols]))
+    GT = P.Graph.from_numpy(gt.row_ptr, gt.col_idx, n_cols=n_cols)
+    tk, tu = dev(thr_k.view(np.int64)), dev(thr_u)
+    need = C.c_size_t(1)
+    args = (C.byref(GT.c), tk.data_ptr(), tu.data_ptr(), seed, layer)
+    B._check(B.lib().gnn_layer_edge_mask_transposed_ws(*args, None, None, C.byref(need), None))
+    assert (need.value > 0) == (n_cols >= 400_000)
+    assert np.array_equal(_bits(P.gnn_layer_edge_mask_transposed(GT, tk, tu, layer, seed), nnz), want)
+    plain = torch.empty((nnz + 31) // 32, dtype=torch.int32, device="cuda")
+    B._check(B.lib().gnn_layer_edge_mask_transposed(*args, plain.data_ptr(), B._stream()))
+    assert np.array_equal(_bits(plain, nnz), want)
+
+
 def test_cost_of_empty_rows_in_the_transposed_mask():
     """Four million empty rows between two entries are not walked by the one workgroup that meets them (200 times the cost of
     the same rows behind the last entry)."""
