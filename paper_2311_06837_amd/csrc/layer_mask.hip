@@ -29,6 +29,7 @@
 // places where no row of the wavefront has more than 32.  300 000 vertices of degree 190, fanout 15, both masks: 797 -> 575.
 #include "common.h"
 #include "hashkey.h"
+#include <algorithm>
 
 namespace gnnhot {
 
@@ -488,9 +489,15 @@ __global__ __launch_bounds__(256) void lm_tops_kernel(const uint64_t* __restrict
 // 254 / 251; 500 000 of 20 62.2 / 58.5, 68.7 / 63.4, of 100 253 / 214, 268 / 233; 1.2 M of 5 45.5 / 42.2, 64.6 / 40.5, of 10 88 / 71, 142 / 79.
 static bool lm_takes_tops(const gnn_csr* gT) { return gT->n_cols >= 400000 && gT->nnz >= 4 * (int64_t)gT->n_cols; }
 
-// thresholds of the rows that are not listed: nothing is <= (0, -1)
-__global__ __launch_bounds__(256) void lm_thr_init_kernel(uint64_t* __restrict__ k, int32_t* __restrict__ u, int64_t n) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+// Clears the bitmap and gives the rows from `first` on the threshold of a row that is not listed (k nullable): nothing is <= (0, -1).
+// One launch and only the rows that no other launch writes, against two over everything, the whole forward mask, us: 50 000 rows of 20 24.4 ->
+// 21.3, 300 000 of 5 26.2 -> 24.0, 1.2 M of 50 341 -> 334.  (Bits put together per row, one atomic a word, plain stores inside a row: 241 -> 295.)
+__global__ __launch_bounds__(256) void lm_init_kernel(uint32_t* __restrict__ bits, int64_t n_words, uint64_t* __restrict__ k, int32_t* __restrict__ u,
+                                                      int64_t first, int64_t n) {
+    const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = tid; i < n_words; i += stride) bits[i] = 0u;
+    if (k == nullptr) return;
+    for (int64_t i = first + tid; i < n; i += stride) {
         k[i] = 0ull;
         u[i] = -1;
     }
@@ -549,13 +556,10 @@ extern "C" int32_t gnn_layer_edge_mask(const gnn_csr* g, const int32_t* rows, in
     GNN_REQUIRE(n_words == 0 || edge_keep != nullptr, GNN_ERR_INVALID_ARG, "edge_keep is NULL");
     GNN_REQUIRE(n_active == 0 || kept_len != nullptr, GNN_ERR_INVALID_ARG, "kept_len is NULL");
     GNN_REQUIRE((row_thr_key == nullptr) == (row_thr_id == nullptr), GNN_ERR_INVALID_ARG, "row_thr_key and row_thr_id go together");
-    if (row_thr_key && g->n_rows > 0) {
-        lm_thr_init_kernel<<<grid_for(g->n_rows, 256, 4096), 256, 0, stream>>>(row_thr_key, row_thr_id, g->n_rows);
-        GNN_LAUNCH_CHECK("lm_thr_init_kernel");
-    }
-    if (n_words > 0) {
-        fill_kernel<uint32_t><<<grid_for(n_words, 256, 4096), 256, 0, stream>>>(edge_keep, n_words, 0u);
-        GNN_LAUNCH_CHECK("fill_kernel");
+    const int64_t first = rows == nullptr ? n_active : 0, n_clear = std::max(n_words, row_thr_key ? g->n_rows - first : 0);
+    if (n_clear > 0) {
+        lm_init_kernel<<<grid_for(n_clear, 256, 4096), 256, 0, stream>>>(edge_keep, n_words, row_thr_key, row_thr_id, first, g->n_rows);
+        GNN_LAUNCH_CHECK("lm_init_kernel");
     }
     if (n_active > 0) {
         lm_mask_kernel<<<grid_for((int64_t)n_active * kLmLanes, 256, 1 << 15), 256, 0, stream>>>(
