@@ -22,7 +22,7 @@
 //                        keys are equal.  A workgroup takes 4096 consecutive entries whatever rows they belong to, so
 //                        every word of the bitmap has one writer: no atomics, nothing to clear, no long rows.
 // Bound: the random reads (transposed), the hash (two 64-bit multiplications a mix) and the selection.  Measured on a
-// 1.2M-vertex / 60M-entry power-law graph, fanout 10: forward and transposed mask 2.61 -> 0.66 ms (forward 1.5 -> 0.34,
+// 1.2M-vertex / 60M-entry power-law graph, fanout 10: forward and transposed mask 2.61 -> 0.65 ms (forward 1.5 -> 0.33,
 // transposed 1.09 -> 0.31, its random reads into a 2.4 MB table), against `fanout` rounds over 64-bit pairs and a lane group
 // per row of the transposed graph.  Of the forward mask, long rows 335 us with whole keys in all registers whatever the length and two
 // sweeps over rows above 1024, 288 by length and with upper halves, 177 with one sweep; short rows 196, 170 with half of the

@@ -340,3 +340,18 @@ def test_more_vertices_than_a_limited_grid_has_threads(all_reached):
     else:       # the targets in order, then vertex n - m, the last target's neighbour, whose own neighbour is out of reach
         assert torch.equal(local.row_ptr, torch.arange(3002, dtype=torch.int32, device="cuda").clamp(max=3000))
         assert torch.equal(local.col_idx, torch.arange(1, 3001, dtype=torch.int32, device="cuda"))
+
+
+@pytest.mark.parametrize("n", [1, 1023, 8192, 8193, 9216, 9217, 1 << 23, (1 << 23) + 1])
+def test_offsets_across_the_forms_of_the_scan(n):
+    """One block up to 8192 counts, blocks that add up the sums before their own up to 8192 blocks of 1024, a launch for the sums above."""
+    import paper_2311_06837_amd as P
+    print(f"offsets of {n} counts", flush=True)
+    ids = torch.arange(0, n, 3, dtype=torch.int32, device="cuda")
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    length = torch.randint(0, 200, (ids.numel(),), device="cuda", generator=gen)
+    rp = torch.zeros(ids.numel() + 1, dtype=torch.int32, device="cuda")
+    rp[1:] = torch.cumsum(length, 0)
+    full = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+    full[1 + ids.long()] = length
+    assert torch.equal(P.gnn_expand_row_ptr(n, ids, rp).long(), torch.cumsum(full, 0))
