@@ -354,7 +354,8 @@ def run_workload(args, name, steps, warmup, cpu_flops):
             del route_ws
         blocked = route != "rows"   # a route whose point is reuse in the L2s
         kernels = {"rows": "spmm_rows_kernel",
-                   "columns": "spmm_stream_kernel (+ spmm_samples, _bounds, _seg_kernel before and spmm_sum_parts_kernel after it: column-blocked route)",
+                   "columns": ("spmm_four_sums_kernel (+ spmm_samples, _bounds, _seg, _fours, _slabs" if model.rows is None else
+                               "spmm_stream_kernel (+ spmm_samples, _bounds, _seg") + "_kernel before and spmm_sum_parts_kernel after it: column-blocked route)",
                    "split": "split_sum_kernel (frequent neighbours, from a table) and spmm_rows_kernel (the others; + split_degrees, _assign, "
                             "_table, _entries before them: split route)"}[route]
     c_dom = side.get("spmm_fwd_dom") if side.get("dominant_layer") == dom else None
