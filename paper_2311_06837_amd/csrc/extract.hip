@@ -591,7 +591,7 @@ static int32_t ex_count_pass(ExArgs a, const int32_t* dist, int32_t* new_id, uin
 }
 
 template <bool SAMPLED>
-static int32_t ex_fill_pass(const ExArgs& a, const int32_t* dist, int row_grid, int long_grid, hipStream_t stream) {
+static int32_t ex_fill_pass(const ExArgs& a, const int32_t* dist, int64_t nnz, int row_grid, int long_grid, hipStream_t stream) {
     ex_number_kernel<<<ex_grid(a.n_local), 256, 0, stream>>>(a.ring_ids, a.n_local, a.n, dist, nullptr, SAMPLED ? a.counts : nullptr,
                                                                    a.out_rp, a.ctrl);
     GNN_LAUNCH_CHECK("ex_number_kernel");
@@ -600,7 +600,7 @@ static int32_t ex_fill_pass(const ExArgs& a, const int32_t* dist, int row_grid, 
     ex_fill_long_kernel<SAMPLED><<<long_grid, 256, 0, stream>>>(a);
     GNN_LAUNCH_CHECK("ex_fill_long_kernel");
     if (SAMPLED) {
-        ex_order_kernel<<<grid_for(a.n_local, 256, kRowGrid), 256, 0, stream>>>(a);
+        ex_order_kernel<<<queue_grid(a.n_local, nnz, 256), 256, 0, stream>>>(a);
         GNN_LAUNCH_CHECK("ex_order_kernel");
         ex_order_long_kernel<<<long_grid, 256, 0, stream>>>(a);
         GNN_LAUNCH_CHECK("ex_order_long_kernel");
@@ -629,7 +629,8 @@ static int32_t extract_common(const gnn_csr* g, const gnn_csr* gs, const int32_t
     if (query) return GNN_OK;
     GNN_REQUIRE(new_id != nullptr && out_row_ptr != nullptr, GNN_ERR_INVALID_ARG, "new_id / out_row_ptr is NULL");
     GNN_REQUIRE(n_local == 0 || (ring_ids != nullptr && dist != nullptr), GNN_ERR_INVALID_ARG, "ring_ids / dist is NULL");
-    const int row_grid = grid_for((int64_t)n_local * kRowLanes, 256, kRowGrid);   // grid-stride loops, here and over the queues
+    const int64_t nnz = gs ? gs->nnz : g->nnz;
+    const int row_grid = queue_grid(n_local, nnz, kRowsPerWg);   // grid-stride loops, here and over the queues
     const int long_grid = grid_for(n_local, 4, 2048);
     ExArgs a;
     a.rp = gs ? gs->row_ptr : g->row_ptr; a.ci = gs ? gs->col_idx : g->col_idx;
@@ -654,7 +655,8 @@ static int32_t extract_common(const gnn_csr* g, const gnn_csr* gs, const int32_t
     }
     GNN_REQUIRE(out_capacity >= 0, GNN_ERR_INVALID_ARG, "out_capacity < 0");
     if (n_local > 0) {
-        GNN_CHECK(gs ? ex_fill_pass<true>(a, dist, row_grid, long_grid, stream) : ex_fill_pass<false>(a, dist, row_grid, long_grid, stream));
+        GNN_CHECK(gs ? ex_fill_pass<true>(a, dist, nnz, row_grid, long_grid, stream)
+                     : ex_fill_pass<false>(a, dist, nnz, row_grid, long_grid, stream));
     }
     return GNN_OK;
 }

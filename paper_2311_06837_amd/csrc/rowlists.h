@@ -18,7 +18,18 @@ constexpr int kRowsPerWg = 256 / kRowLanes;    // rows one workgroup of 256 thre
 // after the other (ex_fill_kernel of 1 M rows, 20 M entries, us: 4096 workgroups with an atomic a class 243, with one for both
 // 215, 2048 140; 1024 are too few: 3 M vertices of degree 10, three rings, the whole extraction 1311 / 1238 / 1430).
 constexpr int kRowGrid = 2048;
-constexpr int kRowListCap = 1024;              // entries of a workgroup's LDS list per class; what does not fit goes out one by one
+// Entries of a workgroup's LDS list of medium rows; what does not fit goes out one by one, on one address: 3 M rows of 100, lists of 1024 /
+// 2048, sampling 25.1 / 4.7 ms, extraction 27.1 / 6.7.  Of rows above kRowMedium a graph of 2^31 entries has 2 M at most, 1024 a workgroup.
+constexpr int kRowListCap = 2048, kHubListCap = 1024;
+
+// Workgroups of a launch over n rows of nnz entries that takes rows_a_step of them at a time: at_least, fewer for few rows, more where the
+// lists (to 7/8, the rows are dealt in turn) would not hold the medium rows there can be.  5 M rows of 100, sampling 25.9 -> 7.7 ms, extraction 30.3 -> 12.2;
+// of 15, none more: with 2442 workgroups for its 1.1 M the extraction would take 2.13 ms instead of 1.84.
+inline int queue_grid(int64_t n, int64_t nnz, int rows_a_step, int at_least = kRowGrid) {
+    const int64_t queued = nnz / (kRowShort + 1) < n ? nnz / (kRowShort + 1) : n;
+    const int64_t full = (queued + kRowListCap / 8 * 7 - 1) / (kRowListCap / 8 * 7);
+    return grid_for(n, rows_a_step, full > at_least ? (int)full : at_least);
+}
 
 struct __attribute__((aligned(8))) RowCtrl {
     int32_t n_medium;        // the first two as one 64-bit word: row_lists_flush
@@ -27,7 +38,7 @@ struct __attribute__((aligned(8))) RowCtrl {
 };
 
 struct RowLists {
-    int32_t med[kRowListCap], hub[kRowListCap];
+    int32_t med[kRowListCap], hub[kHubListCap];
     int32_t n_med, n_hub, base_med, base_hub;
 };
 
@@ -45,7 +56,7 @@ __device__ __forceinline__ void row_lists_push(RowLists& L, int32_t i, int32_t l
         else medq[atomicAdd(&ctrl->n_medium, 1)] = i;
     } else {
         const int pos = atomicAdd(&L.n_hub, 1);
-        if (pos < kRowListCap) L.hub[pos] = i;
+        if (pos < kHubListCap) L.hub[pos] = i;
         else hubq[atomicAdd(&ctrl->n_hub, 1)] = i;
     }
 }
@@ -53,7 +64,7 @@ __device__ __forceinline__ void row_lists_push(RowLists& L, int32_t i, int32_t l
 // every thread of the workgroup calls this once, after its last push
 __device__ __forceinline__ void row_lists_flush(RowLists& L, int32_t* __restrict__ medq, int32_t* __restrict__ hubq, RowCtrl* ctrl) {
     __syncthreads();
-    const int nm = L.n_med < kRowListCap ? L.n_med : kRowListCap, nh = L.n_hub < kRowListCap ? L.n_hub : kRowListCap;
+    const int nm = L.n_med < kRowListCap ? L.n_med : kRowListCap, nh = L.n_hub < kHubListCap ? L.n_hub : kHubListCap;
     if (threadIdx.x == 0 && nm + nh > 0) {      // both counters at once: one atomic on one address
         const unsigned long long base = atomicAdd((unsigned long long*)ctrl, (unsigned long long)(uint32_t)nh << 32 | (uint32_t)nm);
         L.base_med = (int32_t)(uint32_t)base;

@@ -136,6 +136,11 @@ __global__ __launch_bounds__(256) void sb_fill_kernel(const int32_t* __restrict_
     row_lists_flush(lists, medq, hubq, ctrl);
 }
 
+// Targets from which twice the workgroups are worth their appends: the later half evens out the end of the launch.  us, 2048 / 4096: 1 M
+// targets of 30 342 / 311, 2 M 940 / 870, 4 M 1666 / 1531; power-law 2.5 M of 15 976 / 913, 3 M of 40 1848 / 1748; but 625 000 of 100 1225 / 1243, 125 000
+// 301 / 346.
+constexpr int32_t kSbManyRows = 800000;
+
 // ---- rows of 65 to 1024 entries: one wavefront per queued row, everything in registers -----------------------------------
 // A row of up to EPL * 64 entries.  The selection compares the upper halves of the keys; where they do not decide (about
 // n^2 / 2^33 of the rows) rounds over whole pairs do.
@@ -490,7 +495,8 @@ extern "C" int32_t gnn_sample_boundary(const gnn_csr* g, const uint32_t* target_
     if (query) return GNN_OK;
     GNN_REQUIRE(out_row_ptr != nullptr, GNN_ERR_INVALID_ARG, "out_row_ptr is NULL");
     GNN_REQUIRE(n_targets == 0 || (targets != nullptr && target_bitmap != nullptr), GNN_ERR_INVALID_ARG, "targets / bitmap is NULL");
-    const int wave_grid = grid_for((int64_t)n_targets * kRowLanes, 256, kRowGrid);   // grid-stride: one queue append per workgroup
+    // grid-stride: one queue append per workgroup
+    const int wave_grid = queue_grid(n_targets, g->nnz, kRowsPerWg, n_targets < kSbManyRows ? kRowGrid : 2 * kRowGrid);
     if (n_targets > 0) {   // both passes queue their long rows afresh (workspace contents do not survive a call)
         fill_kernel<int32_t><<<1, 64, 0, stream>>>((int32_t*)ctrl, (int64_t)(sizeof(RowCtrl) / sizeof(int32_t)), 0);
         GNN_LAUNCH_CHECK("fill_kernel");

@@ -107,3 +107,45 @@ def test_more_targets_than_a_launch_takes_at_a_time():
     """Every lane group takes several rows, one after the other, of every length class."""
     g = gg.chung_lu(150_000, 12.0, 2.1, 36)
     _compare(g, np.arange(0, 150_000, 2).astype(np.int32), 3, 21)
+
+
+@pytest.mark.parametrize("n", [1_000_003, 3_000_001])
+def test_queues_of_millions_of_medium_rows(n):
+    """Rows of 100 entries all go to the queue of the medium rows.  A workgroup appends a whole list of them with one atomic however
+    many there are: three times the rows take about three times as long (fifteen, where the lists overflow)."""
+    import torch
+    import paper_2311_06837_amd as P
+    deg = 100
+
+    def graph(rows):
+        step = rows // deg
+        cols = torch.arange(deg, device="cuda")[None] * step + torch.randint(step, (rows, deg), device="cuda")      # ascending, distinct
+        return P.Graph((torch.arange(rows + 1, device="cuda") * deg).int(), cols.int().reshape(-1), sorted_columns=True)
+
+    def calls(g):
+        ids = torch.arange(g.n_rows, device="cuda").int()
+        bits = P.gnn_make_bitmap(ids[:-1], g.n_rows)
+        dist = torch.zeros_like(ids)
+        ws = P.Workspace()
+        both = (lambda: P.gnn_sample_boundary(g, bits, ids, 3, 7, ws=ws),
+                lambda: P.gnn_extract_partition(g, ids, g.n_rows, dist, 1, ws=ws))
+        out, us = [], []
+        for f in both:
+            out.append(f())
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(3):
+                f()
+            b.record()
+            b.synchronize()
+            us.append(a.elapsed_time(b) / 3e-3)
+        return out, us
+    g = graph(n)
+    (sampled, (local, _)), us = calls(g)
+    for got in (sampled, (local.row_ptr, local.col_idx)):        # at most one neighbour of a row lies outside: all are kept
+        assert torch.equal(got[0], g.row_ptr) and torch.equal(got[1], g.col_idx)
+    del sampled, local
+    few = 500_000
+    _, us_few = calls(graph(few))
+    print(n, us, us_few, flush=True)
+    assert all(t <= 2.0 * n / few * t_few for t, t_few in zip(us, us_few))
