@@ -45,7 +45,6 @@
 // Bound: a push level reads each edge of the frontier once (4 B, streaming) and makes one
 // 1-byte probe per edge into n bytes that stay in L2: the probes, not the bytes, are what
 // limits it (the L2s serve a fixed number of requests per clock).
-#include <type_traits>
 #include "common.h"
 #include "hashkey.h"
 #include "scan.h"
@@ -697,15 +696,25 @@ __global__ __launch_bounds__(256) void eas_expand_long_kernel(const int32_t* __r
 //   of 4 83 / 74, 46 / 54; three: 20 000 of 5 94 / 75, 56 / 56; 30 000 of 4 97 / 95, 60 / 75; 32 000 around one hub, 96 000 entries, 83 / 102, 42 / 82
 //   eight: 12 000 of 10 142 / 75, 100 / 55; 32 000 of 4 151 / 118, 112 / 99
 // With the transposed graph a level behind which few vertices are left starts from those (10 000 of 10, two levels 61.5 -> 51.7; 15 000 of 8
-// 69.8 -> 58.4; 5000 of 20, three 64.4 -> 52.2), and nothing is looked for once all are reached.
+// 69.8 -> 58.4; 5000 of 20, three 64.4 -> 52.2), and nothing is looked for once all are reached.  Theirs are not always the fewer entries:
+// as_pull_pays.
 static bool as_takes_small(int32_t n, int64_t nnz, int32_t L) { return nnz + 3 * (int64_t)n <= 168000 || L >= 5; }
 constexpr int32_t kAsSmallRows = 32 * 1024;
 constexpr int64_t kAsSmallEntries = (int64_t)1 << 17;
 
+// Whether a level of a small graph starts from the `left` unreached vertices, which have `edges` transposed entries: a vertex costs as
+// much as four entries.  The ring's `count` vertices stand for their share of the entries of all `total` reached ones.
+// us, from the ring / from the last vertices: 3900 vertices with all of 101 000 entries behind 8100 17.1 / 32.6, 1000 of 100 behind 11 000 of
+// one 27.0 / 31.9, 4000 of 20 behind 20 000 38.3 / 41.8; but 3000 of 26 behind 25 000 43.3 / 41.7, 2000 of 40 behind 18 000 of one 38.7 / 31.7.
+// The question costs 2.5 where the answer is no: it is asked once their rows' bounds are there.
+__device__ __forceinline__ bool as_pull_pays(int32_t edges, int32_t left, int32_t count, int32_t total, int32_t nnz) {
+    return (float)edges + 4.f * (float)left <= (float)(nnz - edges) * (float)count / (float)total + 4.f * (float)count;
+}
+
 template <bool BOTH>     // with the transposed graph
 __global__ __launch_bounds__(1024) void as_small_kernel(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
                                                         const int32_t* __restrict__ row_ptr_t, const int32_t* __restrict__ col_idx_t, int32_t n,
-                                                        const int32_t* __restrict__ targets, int32_t n_targets, int32_t L,
+                                                        int32_t nnz, const int32_t* __restrict__ targets, int32_t n_targets, int32_t L,
                                                         int32_t* __restrict__ dist, int32_t* ring_ids, int64_t* __restrict__ hop_offsets) {
     constexpr int kRows = 4096, kPer = kRows / 1024, kWords = (int)(kAsSmallEntries / 32), kU = 8, kRowBit = 18, kRow = 1 << kRowBit;
     static_assert(kAsSmallEntries < kRow && (int64_t)kRows << kRowBit <= INT32_MAX, "edges and rows share an int");
@@ -760,7 +769,7 @@ __global__ __launch_bounds__(1024) void as_small_kernel(const int32_t* __restric
             for (; rest; rest &= rest - 1u) s_left[place++] = (uint16_t)(tid * 32 + __ffs(rest) - 1);
         }
         __syncthreads();       // the ring's ids are there
-        auto expand = [&](auto from_left, const int32_t* __restrict__ rows, const int32_t* __restrict__ cols, int32_t from, int32_t end) {
+        auto expand = [&](auto from_left, const int32_t* __restrict__ rows, const int32_t* __restrict__ cols, int32_t from, int32_t end) -> bool {
             constexpr bool kLeft = decltype(from_left)::value;
             for (int32_t c0 = from; c0 < end; c0 += kRows) {
                 int32_t s[kPer], len[kPer], v[kPer], sum = 0;
@@ -782,6 +791,7 @@ __global__ __launch_bounds__(1024) void as_small_kernel(const int32_t* __restric
                 int all;
                 int at = block_exclusive_scan<1024>(sum, s_part, &all);
                 const int edges = all & (kRow - 1), words = (edges + 31) / 32;
+                if (kLeft && !as_pull_pays(edges, left, count, total, nnz)) return false;      // uniform (one chunk: nothing has been changed)
                 for (int w = tid; w < words; w += 1024) s_begin[w] = 0u;
                 __syncthreads();
 #pragma unroll
@@ -824,9 +834,9 @@ __global__ __launch_bounds__(1024) void as_small_kernel(const int32_t* __restric
                 }
                 __syncthreads();
             }
+            return true;
         };
-        if (BOTH && pull) expand(std::true_type{}, row_ptr_t, col_idx_t, 0, left);
-        else expand(std::false_type{}, row_ptr, col_idx, begin, total);
+        if (!(BOTH && pull && expand(std::true_type{}, row_ptr_t, col_idx_t, 0, left))) expand(std::false_type{}, row_ptr, col_idx, begin, total);
     }
 }
 
@@ -890,8 +900,8 @@ extern "C" int32_t gnn_build_active_sets(const gnn_csr* g, const gnn_csr* gt, co
 
     const bool small = n > 0 && n <= kAsSmallRows && g->nnz <= kAsSmallEntries && as_takes_small(n, g->nnz, L);
     if (small) {
-        if (gt != nullptr) as_small_kernel<true><<<1, 1024, 0, stream>>>(g->row_ptr, g->col_idx, gt->row_ptr, gt->col_idx, n, targets, n_targets, L, dist, ring_ids, hop_offsets);
-        else as_small_kernel<false><<<1, 1024, 0, stream>>>(g->row_ptr, g->col_idx, nullptr, nullptr, n, targets, n_targets, L, dist, ring_ids, hop_offsets);
+        if (gt != nullptr) as_small_kernel<true><<<1, 1024, 0, stream>>>(g->row_ptr, g->col_idx, gt->row_ptr, gt->col_idx, n, (int32_t)g->nnz, targets, n_targets, L, dist, ring_ids, hop_offsets);
+        else as_small_kernel<false><<<1, 1024, 0, stream>>>(g->row_ptr, g->col_idx, nullptr, nullptr, n, (int32_t)g->nnz, targets, n_targets, L, dist, ring_ids, hop_offsets);
         GNN_LAUNCH_CHECK("as_small_kernel");
     } else {
         as_init_kernel<<<grid_for(n > L + 2 ? n : L + 2, 256, 2048), 256, 0, stream>>>(dist, n, visited[0], seen, nw, ctrl, (int32_t)ctrl_words,

@@ -264,3 +264,34 @@ def test_small_graphs_whose_last_vertices_look_for_themselves(n_targets, n_left)
     g = gg.csr_from_edges(n, n, np.concatenate(rows).astype(np.int64), np.concatenate(cols).astype(np.int64))
     for L in (1, 2, 4):
         _compare(g, rng.permutation(n_targets).astype(np.int32), L)
+
+
+def test_last_vertices_that_hold_the_entries_do_not_look_for_themselves():
+    """12 000 vertices, of which 3900 hold all entries among themselves and are never reached: nothing to walk from the ring, 100 000
+    entries from the last vertices.  Knowing the transposed graph must not cost (17 us without it, 33 from the last vertices)."""
+    import paper_2311_06837_amd as P
+    n, n_left = 12_000, 3900
+    rng = np.random.default_rng(4)
+    a, b = rng.integers(n - n_left, n, (2, n_left * 13))
+    g = gg.csr_from_edges(n, n, np.concatenate([a, b]).astype(np.int64), np.concatenate([b, a]).astype(np.int64))
+    targets = np.arange(n - n_left, dtype=np.int32)
+    G = P.Graph(dev(g.row_ptr), dev(g.col_idx))
+    T, ws = dev(targets), P.Workspace()
+
+    def time_us(gt):
+        times = []
+        for _ in range(6):
+            x, y = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            x.record()
+            for _ in range(20):
+                P.gnn_build_active_sets(G, T, 2, sync=False, ws=ws, gt=gt)
+            y.record()
+            y.synchronize()
+            times.append(x.elapsed_time(y) * 50)
+        return min(times)
+    od, oring, ooff = oracle.active_sets(g.row_ptr, g.col_idx, targets, 2)
+    dist, ring, off, hop = P.gnn_build_active_sets(G, T, 2, gt=G)
+    assert list(hop) == list(ooff) and np.array_equal(dist.cpu().numpy(), od)
+    with_gt, without = time_us(G), time_us(None)
+    print(with_gt, without, flush=True)
+    assert with_gt < 1.4 * without
