@@ -70,7 +70,7 @@ constexpr int kMaxChunk = 256;                  // rows of the list per workgrou
 // range [0, n_cols) is cut into 8 * passes blocks of about as many entries; in pass p workgroup i gathers, for its
 // rows, only the neighbours inside block 8p + (i mod 8).  Workgroups are dealt round-robin to the 8
 // compute dies, so every die's L2 sees one eighth of the matrix - and with the feature axis walked
-// in slabs of 128 bytes per row (row lists: 256; grid.y, the slow grid axis) that eighth fits: the gathers then
+// in slabs of 128 bytes per row (row lists, short calls: 256; grid.y, the slow grid axis) that eighth fits: the gathers then
 // run at L2 rather than at fabric speed.  Each die leaves a plane of float
 // partial sums; a second kernel adds the planes in block order and applies the output scale.
 constexpr int kDies = 8;
@@ -690,7 +690,7 @@ __global__ __launch_bounds__(256, NCH == 1 ? (LPR == 64 ? GNN_SPMM_MINB_WIDE : G
 // groups behind its first one leave their sums ("heads") in LDS, and after a barrier the first one adds them in
 // stream order and stores the row, or hands the sum to the next piece.  So power-law rows cost no imbalance inside the
 // workgroup, and the result is a fixed-order sum (bit-reproducible).
-// It serves the column-blocked route of row lists (other calls: spmm_fours.h): the workgroup id carries (chunk, die) = (id / 8, id % 8);
+// It serves the column-blocked route of row lists and of short calls (others: spmm_fours.h, fours_pay): the workgroup id carries (chunk, die) = (id / 8, id % 8);
 // every row is cut to the die's column block through `seg`, and the unscaled float sums go to plane `die` of the partial buffer
 // (a.Y, row index = position in the row list), not to the output matrix.
 //
@@ -1354,6 +1354,25 @@ static int blocked_min_segment(bool f32, bool listed, bool filter, int32_t F) {
     return listed ? (F > 64 ? 17 : 36) : 10;
 }
 
+// Streams of fours or the stream kernel, for a call without a row list.  The fours pay for a copy of the gathered rows (without a neighbour
+// scale or in bfloat16 the stream kernel makes none) and take chunks of at least 16 rows, of which short calls fill no stage; what
+// they save grows with the call's entries, and least of all where the stream kernel has a single slab and stages its ids once, too.  Rows that one
+// line holds are half a slab of the stream kernel.  us, stream / fours, power-law graphs and, in brackets, uniform ends, by rows asked for:
+//   fp32, 256 columns: 233 000 ids, 490 entries a row, 4096 rows 185 / 289, 16 000 502 / 572, 32 000 957 / 916, 64 000 1842 / 1631; 150 000 ids,
+//     160 entries, 4096 94 / 170, 32 000 433 / 476, 64 000 799 / 750 (400 entries, 4096 136 / 165, 16 000 394 / 414, 32 000 777 / 734)
+//     with a neighbour scale: 490 entries 4096 291 / 289, 64 000 1928 / 1631; 160 4096 149 / 171, 32 000 486 / 476 (400, 4096 191 / 168)
+//   fp32, 64 columns: 150 000 ids, 160 entries, 16 000 84 / 107, 64 000 218 / 221, all 502 / 438 (233 000 ids, 100 entries, 64 000 201 / 185)
+//   bf16, 256 columns: 490 entries 4096 128 / 152, 32 000 605 / 534; 160 8000 109 / 164, 32 000 315 / 289; scaled 490 8000 251 / 280, 16 000 436 / 411
+//   one line, 490 entries: bf16, 64 columns 4096 84 / 70, scaled 120 / 81; (100 entries, 8000 54 / 71, 32 000 106 / 96, scaled 8000 68 / 81, 16 000 98 / 88).
+// Over 1780 calls (70 000 to 400 000 ids, 100 to 490 entries, 32 to 602 columns, 4096 rows to all) the lines below are 1.01 times as slow
+// as the faster form on average and 1.24 at most; fours for all of them 1.21 (fp32), 1.05 (scaled), 1.14 and 1.10 (bf16), up to 2.7.
+static bool fours_pay(int64_t n_active, int64_t avg_row, int64_t n_src, int64_t row_bytes_used, bool f32, bool scaled) {
+    const int64_t entries = n_active * avg_row;
+    if (row_bytes_used <= kFourBytes) return entries >= (scaled ? 1000000 : 2000000);
+    if (f32 && row_bytes_used <= kSlabBytes) return n_active >= n_src / (scaled ? 6 : 3) && entries >= (scaled ? 4000000 : 6000000);
+    return n_active >= n_src / (scaled ? 16 : 10) && entries >= (scaled ? 4000000 : 6000000);
+}
+
 static BlockedPlan plan_blocked(const gnn_csr* g, bool listed, int32_t n_active, int32_t F, int64_t row_bytes, bool vec_ok, bool filter,
                                 bool scaled, bool f32, int32_t src_prefix) {
     BlockedPlan p;
@@ -1382,7 +1401,7 @@ static BlockedPlan plan_blocked(const gnn_csr* g, bool listed, int32_t n_active,
     // A neighbour scale: fp32 gathers from a copy of the matrix with scaled rows (one rounding more per element,
     // far inside the fp32 tolerance); bf16 would lose too much in a rounded copy and keeps a factor per edge.
     // Streams of fours: not for a row list, which may name a row twice (how many entries it has is not known here).
-    p.fours = !listed && n_blocks <= kMaxFourBlocks;
+    p.fours = !listed && n_blocks <= kMaxFourBlocks && fours_pay(n_active, avg_row, n_src, (int64_t)F * (f32 ? 4 : 2), f32, scaled);
     const int64_t rows = (p.fours ? kFourEdges : kStreamWgEdges) / std::max<int64_t>(avg_seg, 1), cap = (int64_t)n_active * kDies / 4096;
     p.rows_per_wg = (int32_t)std::min<int64_t>(std::max<int64_t>(std::min(rows, cap), 16), p.fours ? kFourMaxRows : kStreamMaxRows);
     if (p.fours) {

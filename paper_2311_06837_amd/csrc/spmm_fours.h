@@ -1,5 +1,5 @@
-// Column-blocked aggregation over the first rows of a graph (no row list): the entries that a workgroup gathers are laid out once a
-// call as a stream of fours and summed up slab by slab.
+// Column-blocked aggregation over the first rows of a graph (no row list, and enough of them: fours_pay): the entries that a
+// workgroup gathers are laid out once a call as a stream of fours and summed up slab by slab.
 //
 // A slab is one cache line of every row (32 floats or 64 bfloat16), so a die's block of up to 32 768 neighbours stays in its 4 MB L2,
 // and a load of 1 KB (eight rows) takes the vector cache as long as sixteen vector instructions.  What the ids cost is

@@ -384,6 +384,101 @@ def test_blocked_route_streams(dtype, form):
         assert np.array_equal(got[r, :F][~ok], want[~ok], equal_nan=True), r
 
 
+def _random_rows(n_rows, n_cols, longest, seed):
+    """Rows of 0 to `longest` entries, ascending and distinct; made on the GPU.  -> Graph, row of every entry, columns"""
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    lens = torch.randint(longest + 1, (n_rows,), generator=gen, device="cuda")
+    lens[17], lens[18], lens[-1] = 0, longest, longest
+    row = torch.repeat_interleave(torch.arange(n_rows, device="cuda"), lens)
+    keys = torch.unique(row * n_cols + torch.randint(n_cols, row.shape, generator=gen, device="cuda"))
+    row, col = keys // n_cols, keys % n_cols
+    row_ptr = torch.zeros(n_rows + 1, dtype=torch.int64, device="cuda")
+    row_ptr[1:] = torch.cumsum(torch.bincount(row, minlength=n_rows), 0)
+    return _graph(row_ptr, col, n_cols), row, col
+
+
+def _graph(row_ptr, col, n_cols):
+    import paper_2311_06837_amd as P
+    return P.Graph(row_ptr.int(), col.int(), n_cols=n_cols, sorted_columns=True)
+
+
+def _check_sums(got, row, col, n_rows, x, scale, dtype):
+    """got[0:n_rows] against float64 sums over the entries (row, col): fp32 sums in any order are off by at most (terms + 8 planes +
+    the scaled factor) * 2^-24 of the sum of magnitudes; then bf16 rounding, 2^-8 of the value."""
+    keep = row < n_rows
+    row, col = row[keep], col[keep]
+    lens = torch.bincount(row, minlength=n_rows)
+    w = x.double() * (1.0 if scale is None else scale.double()[:, None])
+    for c0 in range(0, x.shape[1], 64):
+        terms = w[:, c0: c0 + 64]
+        want = torch.segment_reduce(terms[col], "sum", lengths=lens, axis=0, initial=0.0)
+        size = torch.segment_reduce(terms.abs()[col], "sum", lengths=lens, axis=0, initial=0.0)
+        tol = (lens[:, None] + 9) * 2.0 ** -24 * size + (2.0 ** -8 * want.abs() if dtype == torch.bfloat16 else 0.0)
+        assert ((got[:n_rows, c0: c0 + 64].double() - want).abs() <= tol).all()
+
+
+def _stream_bytes(G, n_active, F, ld, dtype, scaled):
+    """Workspace of the stream kernel's form in one pass: cut points, planes, prepared ids and factors (bf16) or scaled rows (fp32),
+    boundaries, samples."""
+    up = lambda nbytes: -(-nbytes // 256) * 256
+    need = up(n_active * 9 * 4) + up(8 * n_active * (-(-F // 8) * 8) * 4) + up(9 * 4) + up(131072 * 2)
+    if scaled and dtype == torch.bfloat16:
+        need += up(n_active * 8 * 4) + 2 * up(G.nnz * 4)
+    elif scaled:
+        need += up(G.n_cols * ld * 4)
+    return need
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("scaled", [False, True])
+@pytest.mark.parametrize("F", [256, 60, 40, 24])
+def test_blocked_route_copies_rows_only_where_the_call_pays_for_it(F, scaled, dtype):
+    """A call over few of the rows takes the stream kernel, which gathers in place, and one over many the fours, which have a copy of
+    the gathered rows in the workspace; the sums agree with float64 on either side of the line."""
+    import paper_2311_06837_amd as P
+    one_line, one_slab = F * dtype.itemsize <= 128, dtype == torch.float32 and F * 4 <= 256
+    if dtype == torch.bfloat16 and F < 60:
+        pytest.skip("as 60 columns: one line")
+    n_cols, longest = 66_000, 400 if one_line and not (scaled and dtype == torch.bfloat16) else 1100       # half as many on average
+    if one_line:
+        entries, share = (1e6 if scaled else 2e6), 0.0
+    else:
+        entries, share = (4e6 if scaled else 6e6), 1 / ((6 if scaled else 3) if one_slab else (16 if scaled else 10))
+    at = max(int(entries / (longest / 2)), int(n_cols * share))
+    few, many = max(4096, int(0.95 * at)), max(4096, int(1.05 * at))
+    G, row, col = _random_rows(int(1.1 * many), n_cols, longest, 5)
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    ld = P.row_stride(F, dtype)
+    X = torch.full((n_cols, ld), float("nan"), dtype=dtype, device="cuda")
+    X[:, :F] = torch.randn(n_cols, F, generator=gen, device="cuda").to(dtype)
+    scale = torch.rand(n_cols, generator=gen, device="cuda") + 0.5 if scaled else None
+    for n_active in (few, many):
+        Y = torch.full((G.n_rows, ld), SENTINEL, dtype=dtype, device="cuda")
+        ws = P.Workspace()
+        P.gnn_masked_spmm_fwd(G, None, n_active, X, Y, F, None, scale, ws=ws)
+        more = ws.buf.numel() - _stream_bytes(G, n_active, F, ld, dtype, scaled)
+        print(n_active, F, dtype, scaled, ws.buf.numel(), more, flush=True)
+        if n_active == few < many:
+            assert more == 0
+        else:      # a copy of the rows, where the stream kernel makes none
+            assert more >= (-(-F * dtype.itemsize // 128) * 128 * n_cols if not scaled else 1)
+        _check_sums(Y[:, :F], row, col, n_active, X[:, :F], scale, dtype)
+        untouched = torch.tensor(SENTINEL, dtype=dtype, device="cuda")
+        assert (Y[n_active:] == untouched).all() and (Y[:, F:] == untouched).all()
+
+
+def test_a_call_over_few_rows_needs_no_copy_of_the_matrix():
+    """7500 rows of 400 entries over 150 000 ids, 256 floats: planes and ids, 90 MB, and no copy of the 154 MB of the gathered matrix."""
+    import paper_2311_06837_amd as P
+    n_rows, n_cols, F = 7500, 150_000, 256
+    step = n_cols // 400
+    col = torch.arange(400, device="cuda")[None] * step + torch.randint(step, (n_rows, 400), device="cuda")
+    G = _graph(torch.arange(n_rows + 1, device="cuda") * 400, col.reshape(-1), n_cols)
+    X, Y = torch.zeros(n_cols, F, device="cuda"), torch.zeros(n_rows, F, device="cuda")
+    need = P.binding.spmm_workspace_bytes(G, n_rows, X, Y, F)
+    assert 0 < need < X.numel() * 4
+
+
 def test_blocked_route_falls_back_without_promise_or_density():
     """Unsorted columns (no GNN_CSR_SORTED_COLUMNS promise) or a sparse graph: the size query reports 0 and the
     call gathers whole rows."""
