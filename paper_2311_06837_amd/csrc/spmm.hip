@@ -1338,20 +1338,29 @@ struct BlockedPlan {
 };
 
 // Entries of a row in a block, on average, from which the route is taken: its planes and cut points cost the same whatever the rows hold.
-// Measured against whole rows (with the split route where it applies), blocked / whole rows, us, on power-law graphs and, in
-// brackets, graphs with uniform ends, of 130 000 and 240 000 vertices; eight blocks:
-//   fp32, 256 columns, 70 entries a row -, 1700 / 1500 (877 / 1175, 1582 / 2347); 100 1000 / 990, 1960 / 2080 (1005 / 1573, 1875 / 3316);
-//     47 columns, 70 -, 467 / 496 (246 / 333, 448 / 595): power-law graphs would have the line at 10 to 13, uniform ones below 8
-//   bf16, 256 columns, 70 594 / 470, 1360 / 1050 (598 / 606, 1276 / 1155); 100 677 / 668, 1440 / 1500 (673 / 855, 1387 / 1634)
-//     128 columns, 70 342 / 228, 757 / 490 (344 / 370, 612 / 639); 100 387 / 315, 803 / 644 (386 / 438, 723 / 813); 140 442 / 488, 930 / 944
-//   bf16, dist filter: 256 columns 100 914 / 721, 1894 / 1530; 140 1045 / 1090, 2138 / 2347; 128 columns 200 850 / 709, 300 1177 / 1020, 2418 / 2304
-//   bf16, row list (the stream kernel): 256 columns 100 886 / 664, 1745 / 1319; 140 1031 / 1022, 1919 / 2113; 128 columns 140 554 / 488, 200
-//     646 / 623, 1239 / 1237; 47 columns 200 529 / 432, 300 651 / 566, 1135 / 1066
-static int blocked_min_segment(bool f32, bool listed, bool filter, int32_t F) {
+// fp32 has one line, 8: whole rows, with the split route where it applies, cross it at 8 to 13 on power-law graphs and below 8 on graphs
+// with uniform ends (256 columns, 70 entries a row 1700 / 1500, uniform 1582 / 2347; with a dist filter not below 20).  In bfloat16 a row is half as
+// long and the planes are not, so the line depends on what a call adds to an entry: no call measured above it was more than some 5 % slower than whole rows.
+// Time of the route over that of whole rows, eight blocks, 130 000 and 240 000 vertices, power-law graphs (uniform ends), by entries a row:
+//   fours         32 columns 100 1.10 1.14, 120 1.03 1.04 (0.99 0.81); 64 80 0.94 1.06, 100 0.96 0.98; 128 100 1.20 1.14 (0.88 0.90), 120 1.09 1.03, 140 0.88 0.94;
+//                 256 80 1.07 1.26 (0.87 1.01), 100 1.00 1.06, 120 0.88 0.85; 602 72 1.01 1.11, 80 1.04 1.02, 90 0.87 0.91
+//     a factor    32 400 1.17 1.00, 600 1.02 1.01; 64 200 0.97 1.02 (1.14 1.03), 300 0.99 0.92; 128 140 1.01 1.07, 170 1.02 1.01; 256 100 1.08 1.05; 602 80 1.03 1.03
+//     dist filter 32 600 1.03 1.04 (1.15 1.08); 64 200 0.94 0.92 (1.21 1.15), 260 0.89 0.83 (1.04 0.97); 128 260 1.06 0.99, 300 1.05 0.94; 256 170 1.15 1.05, 200 1.08
+//                 0.92; 602 120 1.18 1.00, 140 0.98 0.88
+//     both        32 600 1.14 1.13 (1.21 1.12); 64 400 1.07 0.94 (1.18 1.04), 600 0.94 0.96; 128 600 1.05 0.93; 256 200 1.09 0.97; 602 120 1.16 0.97, 140 0.96 0.86
+//   stream kernel (row lists, short calls; here half of the rows)
+//                 32 300 1.12 1.21, 400 1.08 1.04; 64 260 0.96 0.96 (1.12 1.07), 400 0.91 0.96 (1.06 0.96); 128 140 1.07 1.14, 170 1.02 1.02; 256 120 1.14 1.09, 140 0.99
+//                 0.91; 602 100 1.04 1.00 (1.04 1.11), 120 0.87 0.89
+//     a factor    64 600 1.49 1.50; 128 300 1.14 1.04, 400 1.03 0.86; 256 140 1.16 1.05, 170 1.05 0.95; 602 100 1.15 1.09, 120 0.98 0.99
+//     dist filter 32 600 1.17 1.18; 64 600 0.96 0.96 (1.16 1.11); 128 400 1.10 0.97, 600 0.93 0.88; 256 300 1.09 0.88; 602 140 1.01 1.14, 200 0.98 0.90
+//     both        64 600 1.19 1.20; 128 600 1.09 0.97; 256 300 1.18 0.94, 400 1.03 0.85; 602 140 1.08 1.20, 200 1.06 0.94
+static int blocked_min_segment(bool f32, bool fours, bool filter, bool scaled, int32_t F) {
     if (f32) return 8;
-    if (F > 128) return filter ? 11 : (listed ? 14 : 9);
-    if (filter) return 36;
-    return listed ? (F > 64 ? 17 : 36) : 10;
+    constexpr int kNever = 1 << 20;      // no length measured, up to 600 entries, was faster
+    static const int line[2][2][2][5] = {      // up to 32, 64, 128, 256 and more columns
+        {{{48, 40, 22, 17, 14}, {kNever, kNever, 48, 21, 15}}, {{kNever, 80, 52, 40, 22}, {kNever, kNever, 76, 48, 24}}},
+        {{{15, 10, 16, 13, 10}, {64, 32, 20, 13, 10}}, {{80, 32, 36, 26, 17}, {kNever, 64, 72, 28, 17}}}};
+    return line[fours][filter][scaled][F <= 32 ? 0 : F <= 64 ? 1 : F <= 128 ? 2 : F <= 256 ? 3 : 4];
 }
 
 // Streams of fours or the stream kernel, for a call without a row list.  The fours pay for a copy of the gathered rows (without a neighbour
@@ -1388,7 +1397,9 @@ static BlockedPlan plan_blocked(const gnn_csr* g, bool listed, int32_t n_active,
     const int n_blocks = kDies * passes;
     // average kept length of a row: its entries spread over the id range like the vertices do
     const int64_t avg_row = (int64_t)((double)g->nnz / g->n_rows * ((double)n_src / g->n_cols));
-    if (avg_row < (int64_t)blocked_min_segment(f32, listed, filter, F) * n_blocks) return p;
+    // Streams of fours: not for a row list, which may name a row twice (how many entries it has is not known here).
+    p.fours = !listed && n_blocks <= kMaxFourBlocks && fours_pay(n_active, avg_row, n_src, (int64_t)F * (f32 ? 4 : 2), f32, scaled);
+    if (avg_row < (int64_t)blocked_min_segment(f32, p.fours, filter, scaled, F) * n_blocks) return p;
     if (!die_mapping_holds()) return p;     // workgroup i is not on die i mod 8 here: the route has lost its reason
     p.passes = passes;
     p.n_blocks = n_blocks;
@@ -1400,8 +1411,6 @@ static BlockedPlan plan_blocked(const gnn_csr* g, bool listed, int32_t n_active,
     p.part_bytes = (size_t)kDies * n_active * p.ldp * sizeof(float);
     // A neighbour scale: fp32 gathers from a copy of the matrix with scaled rows (one rounding more per element,
     // far inside the fp32 tolerance); bf16 would lose too much in a rounded copy and keeps a factor per edge.
-    // Streams of fours: not for a row list, which may name a row twice (how many entries it has is not known here).
-    p.fours = !listed && n_blocks <= kMaxFourBlocks && fours_pay(n_active, avg_row, n_src, (int64_t)F * (f32 ? 4 : 2), f32, scaled);
     const int64_t rows = (p.fours ? kFourEdges : kStreamWgEdges) / std::max<int64_t>(avg_seg, 1), cap = (int64_t)n_active * kDies / 4096;
     p.rows_per_wg = (int32_t)std::min<int64_t>(std::max<int64_t>(std::min(rows, cap), 16), p.fours ? kFourMaxRows : kStreamMaxRows);
     if (p.fours) {

@@ -240,58 +240,62 @@ def test_empty_calls_are_noops():
 _DENSE = {}
 
 
-def _dense_graph():
-    """70k vertices (a 256-byte feature slab of 17.9 MB), average row length 90, plus one vertex adjacent to
-    20k others, so that one of its column blocks alone is longer than the hub threshold."""
-    if "g" not in _DENSE:
+def _dense_graph(deg=88.0):
+    """70k vertices (a 256-byte feature slab of 17.9 MB), average row length 90 (bfloat16 takes the route from longer rows on), plus one
+    vertex adjacent to 20k others, so that one of its column blocks alone is longer than the hub threshold."""
+    if deg not in _DENSE:
         n = 70000
-        base = gg.erdos_renyi(n, 88.0, 31)
+        base = gg.erdos_renyi(n, deg, 31)
         rng = np.random.default_rng(32)
         nb = rng.choice(n - 1, 20000, replace=False).astype(np.int64) + 1      # neighbours of vertex 0
         r = np.repeat(np.arange(n, dtype=np.int64), np.diff(base.row_ptr))
         c = base.col_idx.astype(np.int64)
         z = np.zeros_like(nb)
-        _DENSE["g"] = gg.csr_from_edges(n, n, np.concatenate([r, z, nb]), np.concatenate([c, nb, z]))
-    return _DENSE["g"]
+        _DENSE[deg] = gg.csr_from_edges(n, n, np.concatenate([r, z, nb]), np.concatenate([c, nb, z]))
+    return _DENSE[deg]
+
+
+def _dense_enough(dtype):
+    return _dense_graph(88.0 if dtype == torch.float32 else 190.0)
+
+
+def _blocked(case, *args, **kwargs):
+    """A case with a workspace of its own, which must have taken the column-blocked route."""
+    import paper_2311_06837_amd as P
+    ws = P.Workspace()
+    case(*args, ws=ws, **kwargs)
+    assert _used_blocked_route(ws), (args[1:], kwargs)
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_blocked_route_forward(dtype):
-    import paper_2311_06837_amd as P
-    g = _dense_graph()
+    g, f32 = _dense_enough(dtype), dtype == torch.float32
     assert g.nnz / g.n_rows >= 64 and g.degrees()[0] > 8 * 1024
-    ws = P.Workspace()
-    _fwd_case(g, 200, 200, dtype, None, True, 41, ws=ws)                  # 4 (fp32) / 2 (bf16) slabs, ragged last slab
-    assert _used_blocked_route(ws)
+    _blocked(_fwd_case, g, 200, 200, dtype, None, True, 41)               # 7 (fp32) / 4 (bf16) lines, ragged last line
     rows = np.random.default_rng(5).permutation(g.n_rows)[:40001].astype(np.int32)   # unsorted list, ragged count
     if 0 not in rows:
         rows[17] = 0
-    _fwd_case(g, 602, 608, dtype, rows, False, 42, ws=ws)
-    _fwd_case(g, 64, 64, dtype, rows, True, 43, ws=ws)                    # a single slab
+    _blocked(_fwd_case, g, 602, 608, dtype, rows, False, 42)
+    _blocked(_fwd_case, g, 200, 200, dtype, rows, True, 48)
+    _blocked(_fwd_case, g, 64 if f32 else 128, 64 if f32 else 128, dtype, rows, f32, 43)       # a single slab
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_blocked_route_forward_add(dtype):
-    import paper_2311_06837_amd as P
-    g = _dense_graph()
-    ws = P.Workspace()
-    _fwd_add_case(g, 200, 200, dtype, None, True, 44, ws=ws)
-    assert _used_blocked_route(ws)
+    g, f32 = _dense_enough(dtype), dtype == torch.float32
+    _blocked(_fwd_add_case, g, 200, 200, dtype, None, True, 44)
     rows = np.random.default_rng(6).permutation(g.n_rows)[:40001].astype(np.int32)
-    _fwd_add_case(g, 256, 256, dtype, rows, False, 45, ws=ws)
-    _fwd_add_case(g, 90, 96, dtype, rows, True, 46, ws=ws)
-    _fwd_add_case(g, 200, 200, dtype, rows, True, 47, ws=ws, bias=True)
+    _blocked(_fwd_add_case, g, 256, 256, dtype, rows, False, 45)
+    _blocked(_fwd_add_case, g, 90, 96, dtype, rows, f32, 46)
+    _blocked(_fwd_add_case, g, 200, 200, dtype, rows, True, 47, bias=True)
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("accumulate", [False, True])
 def test_blocked_route_backward_with_filter(dtype, accumulate):
-    import paper_2311_06837_amd as P
-    g = _dense_graph()
-    ws = P.Workspace()
-    _bwd_case(g, 136, 136, dtype, 2, 2, accumulate, 44, ws=ws)            # forward rows = targets only: most neighbours filtered out
-    assert _used_blocked_route(ws)
-    _bwd_case(g, 136, 136, dtype, 2, 2, accumulate, 45, ws=ws, relu=True)  # the plane sum undoes the ReLU in front
+    g, F = (_dense_graph(), 136) if dtype == torch.float32 else (_dense_graph(205.0), 264)      # a ragged last slab
+    _blocked(_bwd_case, g, F, F, dtype, 2, 2, accumulate, 44)            # forward rows = targets only: most neighbours filtered out
+    _blocked(_bwd_case, g, F, F, dtype, 2, 2, accumulate, 45, relu=True)  # the plane sum undoes the ReLU in front
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
@@ -341,7 +345,8 @@ def test_blocked_route_streams(dtype, form):
     must reach the rows that name them and no others."""
     import paper_2311_06837_amd as P
     n_cols = 300_001 if form == "two passes" else 262_144
-    n_rows, F, few = 4300, 67, 1000
+    n_rows, few = 4300, 1000
+    F = 27 if dtype == torch.float32 else 59           # a line, which takes the fours from few rows on
     rng = np.random.default_rng(23)
     lens = np.full(n_rows, 560)
     lens[:300] = rng.integers(0, 80, 300)
@@ -358,7 +363,7 @@ def test_blocked_route_streams(dtype, form):
     rp[1:] = np.cumsum(lens)
     G = P.Graph(dev(rp), dev(np.concatenate(cols)), n_cols=n_cols, sorted_columns=True)
     x = as_stored(rng.standard_normal((n_cols, F)), dtype)
-    x[[5, 77_777, 222_222], [0, 66, 3]] = [np.inf, np.nan, -np.inf]
+    x[[5, 77_777, 222_222], [0, F - 1, 3]] = [np.inf, np.nan, -np.inf]
     scale = (rng.random(n_cols) + 0.5).astype(np.float32)
     dist = (np.arange(n_cols) % 3).astype(np.int32) if form == "dist filter" else None
     X, Y = padded(x, 72, dtype), torch.full((n_rows, 72), SENTINEL, dtype=dtype, device="cuda")
@@ -369,8 +374,9 @@ def test_blocked_route_streams(dtype, form):
     else:
         P.gnn_masked_spmm_bwd(G, None, n_rows - 1, dev(dist), 1, X, Y, F, dev(scale), None, accumulate=False, ws=ws)
         cols = [c[dist[c] <= 1] for c in cols]
-    if dtype == torch.float32 or dist is None:
-        assert _used_blocked_route(ws)
+    assert _used_blocked_route(ws)
+    blocks = 16 if form == "two passes" else 8
+    assert ws.buf.numel() != _stream_bytes(G, n_rows - 1, F, 72, dtype, True, dist is not None, blocks)      # the fours, not the stream kernel
     w = x * scale[:, None].astype(np.float64)
     got = host64(Y)
     untouched = host64(torch.full((1,), SENTINEL, dtype=dtype))      # as the type holds it
@@ -417,13 +423,16 @@ def _check_sums(got, row, col, n_rows, x, scale, dtype):
         assert ((got[:n_rows, c0: c0 + 64].double() - want).abs() <= tol).all()
 
 
-def _stream_bytes(G, n_active, F, ld, dtype, scaled):
-    """Workspace of the stream kernel's form in one pass: cut points, planes, prepared ids and factors (bf16) or scaled rows (fp32),
+def _stream_bytes(G, n_active, F, ld, dtype, scaled, filtered=False, blocks=8):
+    """Workspace of the stream kernel's form: cut points, planes, prepared ids (filter) and factors (bf16) or scaled rows (fp32),
     boundaries, samples."""
     up = lambda nbytes: -(-nbytes // 256) * 256
-    need = up(n_active * 9 * 4) + up(8 * n_active * (-(-F // 8) * 8) * 4) + up(9 * 4) + up(131072 * 2)
-    if scaled and dtype == torch.bfloat16:
-        need += up(n_active * 8 * 4) + 2 * up(G.nnz * 4)
+    factors = scaled and dtype == torch.bfloat16
+    need = up(n_active * (blocks + 1) * 4) + up(8 * n_active * (-(-F // 8) * 8) * 4) + up((blocks + 1) * 4) + up(131072 * (4 if filtered else 2))
+    if filtered or factors:
+        need += up(n_active * blocks * 4) + up(G.nnz * 4)
+    if factors:
+        need += up(G.nnz * 4)
     elif scaled:
         need += up(G.n_cols * ld * 4)
     return need
@@ -439,7 +448,7 @@ def test_blocked_route_copies_rows_only_where_the_call_pays_for_it(F, scaled, dt
     one_line, one_slab = F * dtype.itemsize <= 128, dtype == torch.float32 and F * 4 <= 256
     if dtype == torch.bfloat16 and F < 60:
         pytest.skip("as 60 columns: one line")
-    n_cols, longest = 66_000, 400 if one_line and not (scaled and dtype == torch.bfloat16) else 1100       # half as many on average
+    n_cols, longest = 66_000, (400 if dtype == torch.float32 else 1100 if scaled else 900) if one_line else 1100       # half as many on average
     if one_line:
         entries, share = (1e6 if scaled else 2e6), 0.0
     else:
@@ -465,6 +474,35 @@ def test_blocked_route_copies_rows_only_where_the_call_pays_for_it(F, scaled, dt
         _check_sums(Y[:, :F], row, col, n_active, X[:, :F], scale, dtype)
         untouched = torch.tensor(SENTINEL, dtype=dtype, device="cuda")
         assert (Y[n_active:] == untouched).all() and (Y[:, F:] == untouched).all()
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("form", ["two passes", "dist filter"])
+def test_blocked_route_fours_of_several_slabs(form, dtype):
+    """Scaled rows of several lines: sixteen blocks in two passes, or the entries that pass a filter."""
+    import paper_2311_06837_amd as P
+    two, f32 = form == "two passes", dtype == torch.float32
+    n_rows, n_cols = (20_500, 300_001) if two else (8_000, 70_001)
+    longest = (460 if f32 else 680) if two else 1150
+    F = 67 if two or f32 else 150
+    G, row, col = _random_rows(n_rows, n_cols, longest, 7)
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    ld = P.row_stride(F, dtype)
+    X = torch.full((n_cols, ld), float("nan"), dtype=dtype, device="cuda")
+    X[:, :F] = torch.randn(n_cols, F, generator=gen, device="cuda").to(dtype)
+    scale = torch.rand(n_cols, generator=gen, device="cuda") + 0.5
+    dist = None if two else (torch.arange(n_cols, device="cuda") % 3).int()
+    Y = torch.full((n_rows, ld), SENTINEL, dtype=dtype, device="cuda")
+    ws = P.Workspace()
+    if two:
+        P.gnn_masked_spmm_fwd(G, None, n_rows, X, Y, F, None, scale, ws=ws)
+    else:
+        P.gnn_masked_spmm_bwd(G, None, n_rows, dist, 1, X, Y, F, scale, None, accumulate=False, ws=ws)
+        keep = dist[col] <= 1
+        row, col = row[keep], col[keep]
+    assert _used_blocked_route(ws) and ws.buf.numel() != _stream_bytes(G, n_rows, F, ld, dtype, True, not two, 16 if two else 8)
+    _check_sums(Y[:, :F], row, col, n_rows, X[:, :F], scale, dtype)
+    assert (Y[:, F:] == torch.tensor(SENTINEL, dtype=dtype, device="cuda")).all()
 
 
 def test_a_call_over_few_rows_needs_no_copy_of_the_matrix():
@@ -581,7 +619,7 @@ def test_bwd_source_prefix(dtype, sorted_promise):
 def test_blocked_route_backward_with_source_prefix(dtype):
     """The column-blocked route cuts its blocks out of [0, src_prefix) only."""
     import paper_2311_06837_amd as P
-    g = _dense_graph()
+    g = _dense_enough(dtype)
     ws = P.Workspace()
     _prefix_case(g, 68001, 96, dtype, 78, ws=ws, relu=True)          # 68001 * 256 B is still above the route's threshold
     assert _used_blocked_route(ws)

@@ -345,7 +345,7 @@ def test_the_route_that_a_call_took(graph, dtype, route):
     if graph == "skewed":
         n, (row_ptr, col) = 60_000, _graph(60_000, 46, 1)
     else:
-        n, deg = (140_000, 46) if graph == "even" else (70_000, 80)
+        n, deg = (140_000, 46) if graph == "even" else (70_000, 80 if dtype == torch.float32 else 120)
         rng = np.random.default_rng(2)
         keys = np.unique(np.repeat(np.arange(n, dtype=np.int64), deg) * n + rng.integers(0, n, deg * n))
         row_ptr, col = np.searchsorted(keys, np.arange(n + 1, dtype=np.int64) * n).astype(np.int32), (keys % n).astype(np.int32)
