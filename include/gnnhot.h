@@ -124,16 +124,19 @@ int32_t gnn_norm_scales(int32_t norm, const int32_t *len, const int32_t *row_ptr
  *
  * Workspace (optional).  ws_bytes == NULL: no workspace, one kernel launch that gathers whole rows.
  * With a workspace the call may take the column-blocked route for dense graphs whose gathered
- * matrix is far larger than a cache (on average at least 8 entries of a row per column block, columns sorted:
- * GNN_CSR_SORTED_COLUMNS, 16-byte aligned operands): the neighbour-id range is cut into 8 blocks
+ * matrix is far larger than a cache (columns sorted: GNN_CSR_SORTED_COLUMNS, 16-byte aligned operands, on average enough entries of a row per
+ * column block: 8 in float; in bfloat16 10 to 80 without col_scale and 10 upwards with it, by width, filter and row list, and for narrow
+ * rows with both or with a list and col_scale never): the neighbour-id range is cut into 8 blocks
  * per pass that hold about as many of the call's entries, workgroup i works on block i mod 8 (the compute die it runs on), so each die's L2
- * only ever holds a part of a 256-byte-wide feature slab; the per-block partial sums (float)
- * go to ws and are added in block order.
+ * only ever holds a part of a slab of every row; the per-block partial sums (float) go to ws and are added in block order.  A call over
+ * a row list or few rows gathers slabs of 256 bytes from X (float with col_scale: from a scaled copy in ws); one over more rows lays
+ * its entries out in ws and gathers slabs of 128 bytes from a copy of all rows of X there.  A ws that holds what the former needs
+ * but not the latter is no error: the call runs in that form.
  * Or it may take the split route (float, rows == NULL and no filter but a source prefix, more than 96 columns, on
  * average at least 40 entries a row, a matrix of 48 MB or more, and enough rows and neighbours in the call): the entries that name one of up to 65 535 frequent
  * neighbours are added up from a table in ws, the others as without a workspace.  Whether a graph has such
  * neighbours is decided on the GPU.  A ws too small for this route is no error: the call runs as without one.
- * The size query (ws == NULL) reports 0 when neither route applies; their sums differ by float rounding only.
+ * The size query (ws == NULL) reports 0 when neither route applies; the sums of all these forms differ by float rounding only.
  */
 int32_t gnn_masked_spmm_fwd(const gnn_csr *g, const int32_t *rows, int32_t n_active,
                             const void *X, int64_t ldx, void *Y, int64_t ldy, int32_t F, int32_t dtype,

@@ -306,18 +306,39 @@ def gnn_norm_scales(norm: int, n: int, length: torch.Tensor | None = None, row_p
 
 def _with_optional_ws(fn, args_before, args_after, ws: Workspace | None, gathered: int):
     """ws None: the call runs without a workspace (ws_bytes = NULL); else the usual size query + call.  gathered: bytes the call
-    gathers; from 1 GB on it may use a workspace without insisting on it (a smaller one is no error then), so the size is asked
+    gathers; from 128 MB on it may use a workspace without insisting on all of it (a smaller one is no error then), so the size is asked
     for first and the workspace grows if there is room."""
     if ws is None:
         return _check(fn(*args_before, None, None, *args_after))
-    if gathered >= 1 << 30:
+    if gathered >= 1 << 27:
         if ws.calls_without > 0:
             ws.calls_without -= 1
         else:
             need = C.c_size_t(0)
             _check(fn(*args_before, None, C.byref(need), *args_after))
             ws.offer(need.value)
-    _with_ws(fn, args_before, args_after, ws)
+    try:
+        _with_ws(fn, args_before, args_after, ws)
+    except torch.cuda.OutOfMemoryError:
+        if not _with_less(fn, args_before, args_after, ws):
+            raise
+
+
+def _with_less(fn, args_before, args_after, ws: Workspace) -> bool:
+    """The call in as many sixteenths of its workspace as the card still has; False: not enough for any form of its route."""
+    need = C.c_size_t(0)
+    _check(fn(*args_before, None, C.byref(need), *args_after))
+    for sixteenths in range(15, 0, -1):
+        try:
+            buf = ws.get(need.value * sixteenths // 16)
+        except torch.cuda.OutOfMemoryError:
+            continue
+        status = fn(*args_before, _ptr(buf), C.byref(C.c_size_t(buf.numel())), *args_after)
+        if status != GNN_ERR_WORKSPACE:
+            _check(status)
+            return True
+        return False
+    return False
 
 
 def gnn_masked_spmm_fwd(g: Graph, rows, n_active: int, X: torch.Tensor, Y: torch.Tensor, F: int,

@@ -1382,7 +1382,7 @@ static bool fours_pay(int64_t n_active, int64_t avg_row, int64_t n_src, int64_t 
     return n_active >= n_src / (scaled ? 16 : 10) && entries >= (scaled ? 4000000 : 6000000);
 }
 
-static BlockedPlan plan_blocked(const gnn_csr* g, bool listed, int32_t n_active, int32_t F, int64_t row_bytes, bool vec_ok, bool filter,
+static BlockedPlan plan_blocked(const gnn_csr* g, bool listed, bool copies, int32_t n_active, int32_t F, int64_t row_bytes, bool vec_ok, bool filter,
                                 bool scaled, bool f32, int32_t src_prefix) {
     BlockedPlan p;
     // with a source prefix only the rows [0, src_prefix) of the gathered matrix are ever read
@@ -1400,6 +1400,7 @@ static BlockedPlan plan_blocked(const gnn_csr* g, bool listed, int32_t n_active,
     // Streams of fours: not for a row list, which may name a row twice (how many entries it has is not known here).
     p.fours = !listed && n_blocks <= kMaxFourBlocks && fours_pay(n_active, avg_row, n_src, (int64_t)F * (f32 ? 4 : 2), f32, scaled);
     if (avg_row < (int64_t)blocked_min_segment(f32, p.fours, filter, scaled, F) * n_blocks) return p;
+    p.fours = p.fours && copies;
     if (!die_mapping_holds()) return p;     // workgroup i is not on die i mod 8 here: the route has lost its reason
     p.passes = passes;
     p.n_blocks = n_blocks;
@@ -1432,6 +1433,27 @@ static BlockedPlan plan_blocked(const gnn_csr* g, bool listed, int32_t n_active,
     p.n_rows = g->n_rows;
     p.n_cols = g->n_cols;
     return p;
+}
+
+// Bytes of the arrays that run_blocked lays out.
+static size_t blocked_bytes(const BlockedPlan& p) {
+    if (p.passes == 0) return 0;
+    WsCarver measure(nullptr);
+    measure.take<char>(p.seg_bytes);
+    measure.take<char>(p.part_bytes);
+    if (p.end_bytes) {
+        measure.take<char>(p.end_bytes);
+        measure.take<char>(p.ids_bytes);
+    }
+    if (p.xs_bytes) measure.take<char>(p.xs_bytes);
+    if (p.w_bytes) measure.take<char>(p.w_bytes);
+    measure.take<char>(p.at_bytes);
+    measure.take<uint2>(p.places * 32);
+    measure.take<uint32_t>(p.places);
+    measure.take<char>(p.before_bytes);
+    measure.take<char>(p.bounds_bytes);
+    measure.take<char>(p.sample_bytes);
+    return measure.used;
 }
 
 template <int DT, bool FILTER>
@@ -1660,36 +1682,28 @@ static int32_t spmm_common(const gnn_csr* g, const char* gname, const int32_t* r
     BlockedPlan plan;
     SplitPlan split;
     if (ws_bytes != nullptr) {
-        if (n_active > 0 && F > 0) plan = plan_blocked(g, rows != nullptr, n_active, F, ldx * (dtype == GNN_F32 ? 4 : 2), vec_ok, filter, nbr_scale != nullptr,
-                                                            dtype == GNN_F32, cut_id);
-        WsCarver measure(nullptr);
-        if (plan.passes > 0) {
-            measure.take<char>(plan.seg_bytes);
-            measure.take<char>(plan.part_bytes);
-            if (plan.end_bytes) {
-                measure.take<char>(plan.end_bytes);
-                measure.take<char>(plan.ids_bytes);
-            }
-            if (plan.xs_bytes) measure.take<char>(plan.xs_bytes);
-            if (plan.w_bytes) measure.take<char>(plan.w_bytes);
-            measure.take<char>(plan.at_bytes);
-            measure.take<uint2>(plan.places * 32);
-            measure.take<uint32_t>(plan.places);
-            measure.take<char>(plan.before_bytes);
-            measure.take<char>(plan.bounds_bytes);
-            measure.take<char>(plan.sample_bytes);
+        auto blocked = [&](bool copies) {
+            return plan_blocked(g, rows != nullptr, copies, n_active, F, ldx * (dtype == GNN_F32 ? 4 : 2), vec_ok, filter, nbr_scale != nullptr,
+                                dtype == GNN_F32, cut_id);
+        };
+        if (n_active > 0 && F > 0) plan = blocked(true);
+        size_t need = blocked_bytes(plan);
+        if (plan.fours && ws != nullptr && *ws_bytes < need) {
+            // no room for the copy of the rows and the streams: the stream kernel makes none
+            plan = blocked(false);
+            need = blocked_bytes(plan);
         }
         if (plan.passes == 0 && n_active > 0 && F > 0) {
             split = plan_split(g, rows, n_active, F, dtype, ldx * (dtype == GNN_F32 ? 4 : 2), vec_ok, filter, cut_id, stream);
             if (split.n_chunks > 0) {
                 WsCarver wanted(nullptr);
                 carve_split(split, n_active, wanted);
-                if (ws == nullptr) measure.used = wanted.used;              // asked for
+                if (ws == nullptr) need = wanted.used;                      // asked for
                 else if (*ws_bytes < wanted.used) split.n_chunks = 0;       // the row kernel needs none
             }
         }
         bool query_only = false;
-        GNN_CHECK(ws_protocol(ws, ws_bytes, measure.used, &query_only));
+        GNN_CHECK(ws_protocol(ws, ws_bytes, need, &query_only));
         if (query_only) return GNN_OK;
     }
     if (n_active == 0 || F == 0) return GNN_OK;
@@ -1743,7 +1757,7 @@ extern "C" int32_t gnn_spmm_route(const gnn_csr* g, const int32_t* rows, int32_t
     const int64_t row_bytes = ldx * (16 / ve);
     *route_host = 0;
     if (n_active == 0 || F == 0) return GNN_OK;
-    if (plan_blocked(g, rows != nullptr, n_active, F, row_bytes, vec_ok, filter, scaled != 0, dtype == GNN_F32, -1).passes > 0) {
+    if (plan_blocked(g, rows != nullptr, true, n_active, F, row_bytes, vec_ok, filter, scaled != 0, dtype == GNN_F32, -1).passes > 0) {
         *route_host = 1;
         return GNN_OK;
     }
