@@ -276,8 +276,11 @@ def gnn_layer_edge_mask_transposed(gT: Graph, thr_k: torch.Tensor, thr_u: torch.
     """The layer's mask as a bit per entry of gT, from the threshold pairs of gnn_layer_edge_mask(with_thresholds=True)."""
     assert thr_k.dtype == torch.int64 and thr_u.dtype == torch.int32 and thr_k.numel() >= gT.n_cols and thr_u.numel() >= gT.n_cols
     keep_t = torch.empty(max((gT.nnz + 31) // 32, 1), dtype=torch.int32, device=thr_k.device)
-    fn, need, ws = lib().gnn_layer_edge_mask_transposed_ws, C.c_size_t(0), None
     args = (C.byref(gT.c), _ptr(thr_k), _ptr(thr_u), seed & (2 ** 64 - 1), layer, _ptr(keep_t))
+    if gT.nnz < 1 << 20:      # a call of some 10 us, for which the size query says 0 after 3 us of its own
+        _check(lib().gnn_layer_edge_mask_transposed(*args, _stream()))
+        return keep_t
+    fn, need, ws = lib().gnn_layer_edge_mask_transposed_ws, C.c_size_t(0), None
     _check(fn(*args, None, C.byref(need), _stream()))
     if need.value > 0:
         try:

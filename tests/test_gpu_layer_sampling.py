@@ -257,6 +257,24 @@ def test_transposed_mask_of_many_columns(n_cols, per_col):
     assert np.array_equal(_bits(plain, nnz), want)
 
 
+def test_a_short_transposed_mask_asks_for_no_workspace(monkeypatch):
+    """Below a million entries the answer is always none, and the question costs as much as a third of the call."""
+    import paper_2311_06837_amd as P
+    from paper_2311_06837_amd import binding as B
+    g = gg.erdos_renyi(30_000, 20.0, 9)
+    G = P.Graph.from_numpy(g.row_ptr, g.col_idx)
+    _, _, tk, tu = P.gnn_layer_edge_mask(G, None, G.n_rows, "fanout", 1, 5, fanout=4, with_thresholds=True)
+    want = P.gnn_layer_edge_mask_transposed(G, tk, tu, 1, 5)
+
+    def refuse(*args):
+        raise AssertionError("asked")
+    monkeypatch.setattr(B.lib(), "gnn_layer_edge_mask_transposed_ws", refuse)
+    assert torch.equal(P.gnn_layer_edge_mask_transposed(G, tk, tu, 1, 5), want)
+    keep = P.gnn_layer_edge_mask(G, None, G.n_rows, "fanout", 1, 5, fanout=4)[0]
+    assert torch.equal(P.gnn_transpose_edge_mask(G, G, keep), want)
+    assert G.nnz < 1 << 20
+
+
 def test_cost_of_empty_rows_in_the_transposed_mask():
     """Four million empty rows between two entries are not walked by the one workgroup that meets them (200 times the cost of
     the same rows behind the last entry)."""
