@@ -142,32 +142,26 @@ __device__ __forceinline__ void lm_or_tile(uint32_t* __restrict__ bits, int64_t 
     if (w != 0u) atomicOr(&bits[(p0 >> 5) + lane], w);
 }
 
-// The fanout rule's pair of a row of more than `fanout` entries, one round over the row per kept entry.
-__device__ __forceinline__ void lm_pair_by_rounds(const int32_t* __restrict__ col_idx, int32_t v, int32_t s, int32_t e, int32_t fanout,
-                                                  uint64_t seed_layer_mixed, uint64_t& thr_k, int32_t& thr_u) {
+// The `rank`-th smallest pair of a row, one round over the row for each; HALF: among those whose keys have this upper half.
+template <bool HALF>
+__device__ __forceinline__ void lm_pair_by_rounds(const int32_t* __restrict__ col_idx, int32_t v, int32_t s, int32_t e, int32_t rank,
+                                                  uint64_t seed_layer_mixed, uint32_t half, uint64_t& thr_k, int32_t& thr_u) {
     const int lane = lane_id();
     uint64_t prev_k = 0ull;
     int32_t prev_u = -1;
-    for (int32_t round = 0; round < fanout; ++round) {
+    for (int32_t round = 0; round < rank; ++round) {
         uint64_t best_k = ~0ull;
         int32_t best_u = 0x7fffffff;
         for (uint32_t p = (uint32_t)s + lane; p < (uint32_t)e; p += kWave) {
             const int32_t u = col_idx[p];
             const uint64_t k = edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)u);
+            if (HALF && (uint32_t)(k >> 32) != half) continue;
             if (pair_less(prev_k, prev_u, k, u) && pair_less(k, u, best_k, best_u)) {
                 best_k = k;
                 best_u = u;
             }
         }
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) {
-            const uint64_t ok = __shfl_xor(best_k, d, kWave);
-            const int32_t ou = __shfl_xor(best_u, d, kWave);
-            if (pair_less(ok, ou, best_k, best_u)) {
-                best_k = ok;
-                best_u = ou;
-            }
-        }
+        wave_min_pair(best_k, best_u);
         prev_k = best_k;
         prev_u = best_u;
     }
@@ -176,8 +170,8 @@ __device__ __forceinline__ void lm_pair_by_rounds(const int32_t* __restrict__ co
 }
 
 // A row of up to NP * 64 entries by the fanout rule: finds the pair, writes the bits, returns how many are kept.  A lane holds ids and
-// the keys' upper halves; a whole key is made again where its half decides nothing: for the pair itself, and, where the half
-// of the k-th key is that of others too (about n^2 / 2^33 of the rows), in rounds over the row.
+// the keys' upper halves; a whole key is made again where its half decides nothing: for the pair itself, and where two of the
+// smallest halves are equal (about n^2 / 2^33 of the rows).
 template <int NP>
 __device__ __forceinline__ int32_t lm_row_in_registers(const int32_t* __restrict__ col_idx, uint32_t* __restrict__ bits, int32_t v, int32_t s,
                                                        int32_t e, int32_t fanout, uint64_t seed_layer_mixed, uint64_t& thr_k, int32_t& thr_u) {
@@ -203,7 +197,11 @@ __device__ __forceinline__ int32_t lm_row_in_registers(const int32_t* __restrict
     if (fanout > 0 && e - s > fanout) {
         whole = wave_kth_half<NP>(half, u, cand, fanout, top, thr_u);
         if (whole) thr_k = edge_key(seed_layer_mixed, (uint64_t)v, (uint64_t)thr_u);
-        else lm_pair_by_rounds(col_idx, v, s, e, fanout, seed_layer_mixed, thr_k, thr_u);
+        else {
+            uint32_t kth;
+            const int32_t rank = wave_kth_rank<NP>(half, cand, fanout, kth);
+            lm_pair_by_rounds<true>(col_idx, v, s, e, rank, seed_layer_mixed, kth, thr_k, thr_u);
+        }
     }
     int32_t kept = 0;
 #pragma unroll
@@ -281,7 +279,7 @@ __device__ __forceinline__ int32_t lm_pair_of_hub(const int32_t* __restrict__ co
         wave_lds_sync();   // the list is read before the next row overwrites it
         return kept;
     }
-    lm_pair_by_rounds(col_idx, v, s, e, fanout, seed_layer_mixed, thr_k, thr_u);
+    lm_pair_by_rounds<false>(col_idx, v, s, e, fanout, seed_layer_mixed, 0u, thr_k, thr_u);
     return -1;
 }
 

@@ -143,7 +143,7 @@ constexpr int32_t kSbManyRows = 800000;
 
 // ---- rows of 65 to 1024 entries: one wavefront per queued row, everything in registers -----------------------------------
 // A row of up to EPL * 64 entries.  The selection compares the upper halves of the keys; where they do not decide (about
-// n^2 / 2^33 of the rows) rounds over whole pairs do.
+// n^2 / 2^33 of the rows) whole pairs do.
 template <bool FILL, int EPL>
 __device__ __forceinline__ void sb_medium_row(const int32_t* __restrict__ col_idx, const uint32_t* __restrict__ tbits, int32_t v, int32_t s, int32_t e,
                                               int32_t fanout, uint64_t seed_hop_mixed, int32_t* __restrict__ count, int64_t at,
@@ -182,27 +182,21 @@ __device__ __forceinline__ void sb_medium_row(const int32_t* __restrict__ col_id
     int32_t tu = -1;
     if (fanout > 0 && n_ext > fanout) {   // uniform over the wavefront
         whole = wave_kth_half<EPL>(half, ru, outer, fanout, top, tu);
-        for (int32_t round = 0; round < fanout && !whole; ++round) {     // the smallest pair above (tk, tu)
+        uint32_t kth = 0u;
+        const int32_t rank = whole ? 0 : wave_kth_rank<EPL>(half, outer, fanout, kth);
+        for (int32_t round = 0; round < rank; ++round) {     // of the pairs with that half, the smallest above (tk, tu)
             uint64_t best_k = ~0ull;
             int32_t best_u = 0x7fffffff;
 #pragma unroll
             for (int r = 0; r < EPL; ++r) {
-                if (((outer >> r) & 1u) == 0u) continue;
+                if (((outer >> r) & 1u) == 0u || half[r] != kth) continue;
                 const uint64_t k = edge_key(seed_hop_mixed, (uint64_t)v, (uint64_t)ru[r]);
                 if ((round == 0 || pair_less(tk, tu, k, ru[r])) && pair_less(k, ru[r], best_k, best_u)) {
                     best_k = k;
                     best_u = ru[r];
                 }
             }
-#pragma unroll
-            for (int d = 32; d >= 1; d >>= 1) {
-                const uint64_t ok = __shfl_xor(best_k, d, kWave);
-                const int32_t ou = __shfl_xor(best_u, d, kWave);
-                if (pair_less(ok, ou, best_k, best_u)) {
-                    best_k = ok;
-                    best_u = ou;
-                }
-            }
+            wave_min_pair(best_k, best_u);
             tk = best_k;
             tu = best_u;
         }

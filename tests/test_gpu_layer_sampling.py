@@ -168,6 +168,52 @@ def test_masks_when_the_upper_halves_of_two_keys_are_equal(length):
             _mask_case(gg.CSR(n, n, row_ptr, cols), np.array([v]), "fanout", k, layer, seed)
 
 
+@pytest.mark.parametrize("sampler", [False, True])
+def test_two_equal_upper_halves_cost_no_round_for_every_entry_kept(sampler):
+    """One row of 1000 entries, fanout 600: with two equal halves among the smallest (0.5 ms, when the rounds went over all
+    pairs) and without."""
+    import paper_2311_06837_amd as P
+    n, layer, seed, v, length, k = 1_500_000, 1, 77, 5, 1000, 600
+    keys = _mix64(_mix64(_mix64(np.uint64(seed + layer)) ^ np.uint64(v)) ^ np.arange(n, dtype=np.uint64))
+    order = np.argsort(keys)
+    half = keys[order] >> np.uint64(32)
+    at = np.flatnonzero(half[1:] == half[:-1])
+    at = int(at[at > length][0])
+    rng = np.random.default_rng(0)
+    before = np.sort(rng.choice(at, k - 2, replace=False))
+    after = at + 2 + rng.choice(n - at - 2, length - k, replace=False)
+    us = []
+    for pair in ([at, at + 1], [at, at + 2]):
+        cols = np.unique(order[np.concatenate([before, pair, after])])
+        cols = cols[cols != v].astype(np.int32)
+        row_ptr = np.zeros(n + 1, np.int32)
+        row_ptr[v + 1:] = cols.size
+        G = P.Graph(dev(row_ptr), dev(cols), sorted_columns=True)
+        rows, ws = dev(np.array([v], np.int32)), P.Workspace()
+        bits = P.gnn_make_bitmap(rows, n)
+        if sampler:
+            call = lambda: P.gnn_sample_boundary(G, bits, rows, k, seed, ws=ws)
+            got = call()[1]
+            assert got.numel() == k
+        else:
+            call = lambda: P.gnn_layer_edge_mask(G, rows, 1, "fanout", layer, seed, fanout=k)
+            got = dev(cols)[torch.from_numpy(_bits(call()[0], cols.size).astype(bool)).cuda()]
+        want = cols[np.argsort(keys[cols])[:k]]
+        assert np.array_equal(np.sort(got.cpu().numpy()), np.sort(want))
+        times = []
+        for _ in range(5):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(5):
+                call()
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b) * 200)
+        us.append(min(times))
+    print(us, flush=True)
+    assert us[0] < 1.3 * us[1]
+
+
 def test_transposed_mask_rows_across_chunks():
     """A workgroup decides 4096 consecutive entries: rows that span several, runs of empty rows at the joints, a last chunk
     that ends inside a word."""
