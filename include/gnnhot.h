@@ -125,8 +125,8 @@ int32_t gnn_norm_scales(int32_t norm, const int32_t *len, const int32_t *row_ptr
  * Workspace (optional).  ws_bytes == NULL: no workspace, one kernel launch that gathers whole rows.
  * With a workspace the call may take the column-blocked route for dense graphs whose gathered
  * matrix is far larger than a cache (columns sorted: GNN_CSR_SORTED_COLUMNS, 16-byte aligned operands, on average enough entries of a row per
- * column block: 8 in float; in bfloat16 10 to 80 without col_scale and 10 upwards with it, by width, filter and row list, and for narrow
- * rows with both or with a list and col_scale never): the neighbour-id range is cut into 8 blocks
+ * column block: 8 in float; in bfloat16 8 to 80 by the width, the number of rows, a row list, col_scale and a filter, with some of them for
+ * narrow rows never): the neighbour-id range is cut into 8 blocks
  * per pass that hold about as many of the call's entries, workgroup i works on block i mod 8 (the compute die it runs on), so each die's L2
  * only ever holds a part of a slab of every row; the per-block partial sums (float) go to ws and are added in block order.  A call over
  * a row list or few rows gathers slabs of 256 bytes from X (float with col_scale: from a scaled copy in ws); one over more rows lays

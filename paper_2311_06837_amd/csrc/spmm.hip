@@ -1340,7 +1340,7 @@ struct BlockedPlan {
 // Entries of a row in a block, on average, from which the route is taken: its planes and cut points cost the same whatever the rows hold.
 // fp32 has one line, 8: whole rows, with the split route where it applies, cross it at 8 to 13 on power-law graphs and below 8 on graphs
 // with uniform ends (256 columns, 70 entries a row 1700 / 1500, uniform 1582 / 2347; with a dist filter not below 20).  In bfloat16 a row is half as
-// long and the planes are not, so the line depends on what a call adds to an entry: no call measured above it was more than some 5 % slower than whole rows.
+// long and the planes are not, so the line depends on what a call adds to an entry: over many rows no call above it was some 5 % slower than whole rows.
 // Time of the route over that of whole rows, eight blocks, 130 000 and 240 000 vertices, power-law graphs (uniform ends), by entries a row:
 //   fours         32 columns 100 1.10 1.14, 120 1.03 1.04 (0.99 0.81); 64 80 0.94 1.06, 100 0.96 0.98; 128 100 1.20 1.14 (0.88 0.90), 120 1.09 1.03, 140 0.88 0.94;
 //                 256 80 1.07 1.26 (0.87 1.01), 100 1.00 1.06, 120 0.88 0.85; 602 72 1.01 1.11, 80 1.04 1.02, 90 0.87 0.91
@@ -1348,19 +1348,32 @@ struct BlockedPlan {
 //     dist filter 32 600 1.03 1.04 (1.15 1.08); 64 200 0.94 0.92 (1.21 1.15), 260 0.89 0.83 (1.04 0.97); 128 260 1.06 0.99, 300 1.05 0.94; 256 170 1.15 1.05, 200 1.08
 //                 0.92; 602 120 1.18 1.00, 140 0.98 0.88
 //     both        32 600 1.14 1.13 (1.21 1.12); 64 400 1.07 0.94 (1.18 1.04), 600 0.94 0.96; 128 600 1.05 0.93; 256 200 1.09 0.97; 602 120 1.16 0.97, 140 0.96 0.86
-//   stream kernel (row lists, short calls; here half of the rows)
+//   stream kernel (row lists; here half of the rows)
 //                 32 300 1.12 1.21, 400 1.08 1.04; 64 260 0.96 0.96 (1.12 1.07), 400 0.91 0.96 (1.06 0.96); 128 140 1.07 1.14, 170 1.02 1.02; 256 120 1.14 1.09, 140 0.99
 //                 0.91; 602 100 1.04 1.00 (1.04 1.11), 120 0.87 0.89
 //     a factor    64 600 1.49 1.50; 128 300 1.14 1.04, 400 1.03 0.86; 256 140 1.16 1.05, 170 1.05 0.95; 602 100 1.15 1.09, 120 0.98 0.99
 //     dist filter 32 600 1.17 1.18; 64 600 0.96 0.96 (1.16 1.11); 128 400 1.10 0.97, 600 0.93 0.88; 256 300 1.09 0.88; 602 140 1.01 1.14, 200 0.98 0.90
 //     both        64 600 1.19 1.20; 128 600 1.09 0.97; 256 300 1.18 0.94, 400 1.03 0.85; 602 140 1.08 1.20, 200 1.06 0.94
-static int blocked_min_segment(bool f32, bool fours, bool filter, bool scaled, int32_t F) {
+// A call over few rows: whole rows take some 100 us however few they are on a power-law graph (a hub's row), not on one with uniform ends.
+// Route over whole rows, power-law (uniform) of 130 000 and 240 000 vertices, by rows asked for and entries a row; stream kernel
+//   64 columns 8000 of 80 0.66 0.69 (1.04 1.02), 16 000 of 100 0.94 0.78 (1.46 1.45), 32 000 of 100 1.04 0.95 (1.07 1.10); 128 8000 of 80 0.65 0.66 (1.03 1.08), 32 000 of
+//   100 0.98 0.89 (1.00 1.12); 256 8000 of 100 0.80 0.54 (1.56 1.61), of 140 0.73 0.59 (1.22 1.34), 32 000 of 100 1.11 1.07 (1.09 1.24); 602 8000 of 100 0.82 0.45 (1.44
+//   1.55); a factor, 64 16 000 of 140 1.02 0.96 (1.91 1.93), 256 8000 of 100 1.02 0.69 (1.77 1.80)
+// fours 32 columns 32 000 of 120 0.92 0.88 (1.08 1.07); 64 32 000 of 80 0.98 0.75 (0.86 0.91); a factor, 32 32 000 of 120 0.98 0.97 (1.20 1.21); 64 32 000 of 100 0.96 0.90
+//   (1.06 1.13).  Rows of 32 bytes gain little (16 columns, 10 800 rows of 150 0.90) and lose more (9400 of 136, uniform, 2.2): as calls over many
+// rows.  With a dist filter uniform ends lose more by the route (2 to 3 times up to 200 entries) than power-law graphs gain: one line.
+constexpr int32_t kBlockedFewRows = 20000, kBlockedSomeRows = 48000;
+
+static int blocked_min_segment(bool f32, bool fours, bool filter, bool scaled, int32_t n_active, int32_t F) {
     if (f32) return 8;
     constexpr int kNever = 1 << 20;      // no length measured, up to 600 entries, was faster
-    static const int line[2][2][2][5] = {      // up to 32, 64, 128, 256 and more columns
-        {{{48, 40, 22, 17, 14}, {kNever, kNever, 48, 21, 15}}, {{kNever, 80, 52, 40, 22}, {kNever, kNever, 76, 48, 24}}},
-        {{{15, 10, 16, 13, 10}, {64, 32, 20, 13, 10}}, {{80, 32, 36, 26, 17}, {kNever, 64, 72, 28, 17}}}};
-    return line[fours][filter][scaled][F <= 32 ? 0 : F <= 64 ? 1 : F <= 128 ? 2 : F <= 256 ? 3 : 4];
+    const int width = F <= 32 ? 0 : F <= 64 ? 1 : F <= 128 ? 2 : F <= 256 ? 3 : 4;
+    static const int filtered[2][2][5] = {{{kNever, 80, 52, 40, 22}, {kNever, kNever, 76, 48, 24}}, {{80, 32, 36, 26, 17}, {kNever, 64, 72, 28, 17}}};
+    static const int line[3][2][2][5] = {{{{8, 8, 8, 13, 12}, {25, 17, 17, 13, 12}}, {{13, 8, 8, 8, 8}, {17, 14, 17, 8, 8}}},
+                                         {{{21, 12, 12, 13, 12}, {kNever, kNever, 21, 19, 12}}, {{13, 8, 8, 8, 8}, {17, 14, 17, 8, 8}}},
+                                         {{{48, 40, 22, 17, 14}, {kNever, kNever, 48, 21, 15}}, {{15, 10, 16, 13, 10}, {64, 32, 20, 13, 10}}}};
+    if (filter) return filtered[fours][scaled][width];
+    return line[F <= 16 ? 2 : n_active <= kBlockedFewRows ? 0 : n_active <= kBlockedSomeRows ? 1 : 2][fours][scaled][width];
 }
 
 // Streams of fours or the stream kernel, for a call without a row list.  The fours pay for a copy of the gathered rows (without a neighbour
@@ -1399,7 +1412,7 @@ static BlockedPlan plan_blocked(const gnn_csr* g, bool listed, bool copies, int3
     const int64_t avg_row = (int64_t)((double)g->nnz / g->n_rows * ((double)n_src / g->n_cols));
     // Streams of fours: not for a row list, which may name a row twice (how many entries it has is not known here).
     p.fours = !listed && n_blocks <= kMaxFourBlocks && fours_pay(n_active, avg_row, n_src, (int64_t)F * (f32 ? 4 : 2), f32, scaled);
-    if (avg_row < (int64_t)blocked_min_segment(f32, p.fours, filter, scaled, F) * n_blocks) return p;
+    if (avg_row < (int64_t)blocked_min_segment(f32, p.fours, filter, scaled, n_active, F) * n_blocks) return p;
     p.fours = p.fours && copies;
     if (!die_mapping_holds()) return p;     // workgroup i is not on die i mod 8 here: the route has lost its reason
     p.passes = passes;
