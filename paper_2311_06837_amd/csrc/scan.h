@@ -122,35 +122,32 @@ static __global__ __launch_bounds__(256) void scan_offsets_kernel(const int32_t*
 // gnn_expand_row_ptr, three launches / two, us: 33 000 ids 15.9 / 12.8, 1 M 16.6 / 14.8, 3 M 31.7 / 29.5, 5 M 45.5 / 44.6, 8.4 M 68.8 / 67.4.
 constexpr int32_t kScanSelf = 8192;
 
-// Short arrays: one block does it all (a launch costs as much as the scan of these).  Sixteen counts per thread and
-// sweep keep a sweep's latency at one trip to memory.  The same call, one block / two launches, us: 1500 ids 10.5 / 13.5, 4000 10.0 / 13.1, 8000
-// 12.5 / 13.1, 16 000 19.5 / 13.1, 30 000 32.6 / 13.4.
-constexpr int32_t kScanOneBlock = 8192;
+// Short arrays: one block does it all (a launch costs as much as the scan of these), ten counts a thread.  The same call, one block / two
+// launches, us: 5000 ids 11.4 / 14.1, 10 000 11.3 / 14.1; with sixteen counts a thread and more than one sweep above them 12 000 15.9 / 14.1, 16 000 19.4.
+constexpr int32_t kScanOneBlock = 10240;
 
 static __global__ __launch_bounds__(1024) void scan_one_block_kernel(const int32_t* __restrict__ counts, int32_t n,
                                                                       int32_t* __restrict__ offsets, int64_t* __restrict__ out_total) {
+    constexpr int kPer = 10;
+    static_assert(kScanOneBlock <= kPer * 1024, "one sweep");
     __shared__ int s_part[16];
-    int base = 0;
-    for (int32_t lo = 0; lo < n; lo += 16 * 1024) {   // uniform over the block
-        const int32_t at = lo + (int32_t)threadIdx.x * 16;
-        int c[16], tot = 0;
+    const int32_t at = (int32_t)threadIdx.x * kPer;
+    int c[kPer], tot = 0;
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            c[k] = at + k < n ? counts[at + k] : 0;
-            tot += c[k];
-        }
-        int total;
-        int run = base + block_exclusive_scan<1024>(tot, s_part, &total);
+    for (int k = 0; k < kPer; ++k) {
+        c[k] = at + k < n ? counts[at + k] : 0;
+        tot += c[k];
+    }
+    int total;
+    int run = block_exclusive_scan<1024>(tot, s_part, &total);
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            if (at + k < n) offsets[at + k] = run;
-            run += c[k];
-        }
-        base += total;
+    for (int k = 0; k < kPer; ++k) {
+        if (at + k < n) offsets[at + k] = run;
+        run += c[k];
     }
     if (threadIdx.x == 0) {
-        offsets[n] = base;
-        *out_total = base;
+        offsets[n] = total;
+        *out_total = total;
     }
 }
 

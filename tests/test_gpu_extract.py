@@ -342,9 +342,9 @@ def test_more_vertices_than_a_limited_grid_has_threads(all_reached):
         assert torch.equal(local.col_idx, torch.arange(1, 3001, dtype=torch.int32, device="cuda"))
 
 
-@pytest.mark.parametrize("n", [1, 1023, 8192, 8193, 9216, 9217, 1 << 23, (1 << 23) + 1])
+@pytest.mark.parametrize("n", [1, 1023, 8192, 8193, 9216, 9217, 10240, 10241, 1 << 23, (1 << 23) + 1])
 def test_offsets_across_the_forms_of_the_scan(n):
-    """One block up to 8192 counts, blocks that add up the sums before their own up to 8192 blocks of 1024, a launch for the sums above."""
+    """One block up to 10 240 counts, blocks that add up the sums before their own up to 8192 blocks of 1024, a launch for the sums above."""
     import paper_2311_06837_amd as P
     print(f"offsets of {n} counts", flush=True)
     ids = torch.arange(0, n, 3, dtype=torch.int32, device="cuda")
