@@ -115,7 +115,8 @@ def sampled_partition_cfg4(w):
 
 
 def roofline_of_call(kernels, what, t_s, gather_bytes, compulsory_bytes, blocked, counters):
-    """HBM roofline record of one aggregation call.
+    """HBM roofline record of one aggregation call.  `bound` names the roof the figure is held against; what limits the
+    column-blocked route is another (the vector caches of the compute units).
 
     gather model   every neighbour row of every edge comes from memory (no reuse): index + row per edge, row_ptr +
                    output row per active row.  What a gather kernel WITHOUT designed reuse must move.
@@ -353,9 +354,13 @@ def run_workload(args, name, steps, warmup, cpu_flops):
             route = ask(route_ws)
             del route_ws
         blocked = route != "rows"   # a route whose point is reuse in the L2s
+        # a third of the rows and 6 M entries take the streams of fours whatever the width; fewer may take the stream kernel, a list always does
+        fours = model.rows is None and 3 * nd >= n_in and edges[dom]["fwd"] >= 6_000_000
         kernels = {"rows": "spmm_rows_kernel",
-                   "columns": ("spmm_four_sums_kernel (+ spmm_samples, _bounds, _seg, _fours, _slabs" if model.rows is None else
-                               "spmm_stream_kernel (+ spmm_samples, _bounds, _seg") + "_kernel before and spmm_sum_parts_kernel after it: column-blocked route)",
+                   "columns": ("spmm_four_sums_kernel (+ spmm_samples, _bounds, _seg, _fours, _slabs" if fours else
+                               "spmm_stream_kernel (+ spmm_samples, _bounds, _seg" if model.rows is not None else
+                               "spmm_stream_kernel or spmm_four_sums_kernel (+ spmm_samples, _bounds, _seg") +
+                              "_kernel before and spmm_sum_parts_kernel after it: column-blocked route, bound by the vector caches)",
                    "split": "split_sum_kernel (frequent neighbours, from a table) and spmm_rows_kernel (the others; + split_degrees, _assign, "
                             "_table, _entries before them: split route)"}[route]
     c_dom = side.get("spmm_fwd_dom") if side.get("dominant_layer") == dom else None

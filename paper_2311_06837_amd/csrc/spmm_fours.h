@@ -1,9 +1,9 @@
 // Column-blocked aggregation over the first rows of a graph (no row list, and enough of them: fours_pay): the entries that a
 // workgroup gathers are laid out once a call as a stream of fours and summed up slab by slab.
 //
-// A slab is one cache line of every row (32 floats or 64 bfloat16), so a die's block of up to 32 768 neighbours stays in its 4 MB L2,
-// and a load of 1 KB (eight rows) takes the vector cache as long as sixteen vector instructions.  What the ids cost is
-// therefore paid once a call and not once a slab:
+// A slab is one cache line of every row (32 floats or 64 bfloat16), so a die's block of 32 768 neighbours on average stays in its 4 MB L2
+// (65 535 at most, 8 MB, where few ids hold most entries and the others share a block), and a load of 1 KB (eight rows) takes the
+// vector cache as long as sixteen vector instructions.  What the ids cost is therefore paid once a call and not once a slab:
 //   spmm_fours_kernel      per (chunk of rows, block): every row's entries in the block as ids of 16 bits relative to the block's first, in
 //                          fours that belong to one row; what is left of a row's last four names no id.  A row without
 //                          entries there has one four all the same, so the rows of a chunk follow each other.

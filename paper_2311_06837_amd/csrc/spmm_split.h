@@ -22,12 +22,13 @@
 // No atomics on sums: which entries meet in which sum depends on the graph alone, and so do the results, bit for bit.
 //
 // Measured, fp32, rows of 50 (us): 1.2 M x 256 columns, 61 M entries, 55 % of them hot: row kernel alone 8900; now
-// 6980 = 50 (first three) + 380 + 1750 (35 GB out of the table) + 4850 (row kernel, 33 GB from the fabric at 6.8 TB/s).  2.45 M x 100
-// columns: 9900; now 8400 = 50 + 790 + 1650 + 5900.  A table of 32 768 rows gathers faster (27 TB/s, not 23) but leaves more to
+// 6880 = 50 (first three) + 380 + 1650 (35 GB out of the table) + 4800 (row kernel, 33 GB from the fabric at 6.8 TB/s).  2.45 M x 100
+// columns: 9900; now 8250 = 50 + 790 + 1550 + 5850.  A table of 32 768 rows gathers faster (27 TB/s, not 23) but leaves more to
 // the fabric (gathers alone 1.08 + 4.45 ms, not 1.51 + 3.74); 131 072 rows 2.2 + 3.07.  Hot and other rows in one kernel, slab by
 // slab: 6.8 ms gathers alone (the others push the hot ones out, whatever the cache hint of their loads).
 #pragma once
 #include "scan.h"
+#include "spmm_fours.h"
 
 namespace gnnhot {
 

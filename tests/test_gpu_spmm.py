@@ -326,7 +326,7 @@ def test_blocked_route_row_lengths(dtype, wide):
     Y = torch.zeros((n_rows, 80), dtype=dtype, device="cuda")
     ws = P.Workspace()
     P.gnn_masked_spmm_fwd(G, None, n_rows, X, Y, F, ws=ws)
-    assert _used_blocked_route(ws)
+    assert _used_blocked_route(ws) and ws.buf.numel() == _stream_bytes(G, n_rows, F, ld, dtype, False)      # too few rows for the fours
     x = X[:, :F].double().cpu().numpy()
     want = np.stack([x[c].sum(0) for c in cols])
     size = np.stack([np.abs(x[c]).sum(0) for c in cols])
