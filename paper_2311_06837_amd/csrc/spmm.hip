@@ -1325,9 +1325,9 @@ struct BlockedPlan {
     int n_blocks = 0;
     int64_t ldp = 0;          // leading dimension of a partial plane, in floats
     size_t seg_bytes = 0, part_bytes = 0;
-    size_t end_bytes = 0, ids_bytes = 0;   // with a filter or a neighbour scale: segment ends and the (compacted) copy of the ids
-    size_t xs_bytes = 0;                   // fp32 with a neighbour scale: the gathered matrix with its rows scaled
-    size_t w_bytes = 0;                    // bf16 with a neighbour scale: the factor of every copied id
+    size_t end_bytes = 0, ids_bytes = 0;   // with a filter (stream kernel, bf16: or a neighbour scale): segment ends and the (compacted) copy of the ids
+    size_t xs_bytes = 0;                   // fours: the gathered rows slab by slab; stream kernel, fp32 with a neighbour scale: the rows scaled
+    size_t w_bytes = 0;                    // bf16 with a neighbour scale: the factor of every copied id, fours: of every place
     bool off32 = false;       // the gathered matrix spans less than 4 GB
     int32_t n_rows = 0, n_cols = 0;
     int32_t limit = 0;        // neighbour ids >= limit are never gathered (n_cols without a source prefix)

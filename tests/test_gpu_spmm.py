@@ -479,7 +479,8 @@ def test_blocked_route_copies_rows_only_where_the_call_pays_for_it(F, scaled, dt
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("form", ["two passes", "dist filter"])
 def test_blocked_route_fours_of_several_slabs(form, dtype):
-    """Scaled rows of several lines: sixteen blocks in two passes, or the entries that pass a filter."""
+    """Scaled rows of several lines: sixteen blocks in two passes, or the entries that pass a filter.  Two passes also of the stream
+    kernel, over a list of the same rows."""
     import paper_2311_06837_amd as P
     two, f32 = form == "two passes", dtype == torch.float32
     n_rows, n_cols = (20_500, 300_001) if two else (8_000, 70_001)
@@ -503,6 +504,13 @@ def test_blocked_route_fours_of_several_slabs(form, dtype):
     assert _used_blocked_route(ws) and ws.buf.numel() != _stream_bytes(G, n_rows, F, ld, dtype, True, not two, 16 if two else 8)
     _check_sums(Y[:, :F], row, col, n_rows, X[:, :F], scale, dtype)
     assert (Y[:, F:] == torch.tensor(SENTINEL, dtype=dtype, device="cuda")).all()
+    if two:
+        listed = torch.randperm(n_rows, generator=gen, device="cuda").int()
+        Y.fill_(SENTINEL)
+        ws = P.Workspace()
+        P.gnn_masked_spmm_fwd(G, listed, n_rows, X, Y, F, ws=ws)
+        assert ws.buf.numel() == _stream_bytes(G, n_rows, F, ld, dtype, False, False, 16)
+        _check_sums(Y[:, :F], row, col, n_rows, X[:, :F], None, dtype)
 
 
 def test_a_call_over_few_rows_needs_no_copy_of_the_matrix():
