@@ -354,8 +354,9 @@ def run_workload(args, name, steps, warmup, cpu_flops):
             route = ask(route_ws)
             del route_ws
         blocked = route != "rows"   # a route whose point is reuse in the L2s
-        # a third of the rows and 6 M entries take the streams of fours whatever the width; fewer may take the stream kernel, a list always does
-        fours = model.rows is None and 3 * nd >= n_in and edges[dom]["fwd"] >= 6_000_000
+        # in one pass (up to 262 144 ids) a third of the rows and 6 M entries take the streams of fours whatever the width; fewer may take the
+        # stream kernel, a list always does
+        fours = model.rows is None and n_in <= 262_144 and 3 * nd >= n_in and edges[dom]["fwd"] >= 6_000_000
         kernels = {"rows": "spmm_rows_kernel",
                    "columns": ("spmm_four_sums_kernel (+ spmm_samples, _bounds, _seg, _fours, _slabs" if fours else
                                "spmm_stream_kernel (+ spmm_samples, _bounds, _seg" if model.rows is not None else

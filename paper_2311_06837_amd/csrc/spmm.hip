@@ -1388,11 +1388,13 @@ static int blocked_min_segment(bool f32, bool fours, bool filter, bool scaled, i
 //   one line, 490 entries: bf16, 64 columns 4096 84 / 70, scaled 120 / 81; (100 entries, 8000 54 / 71, 32 000 106 / 96, scaled 8000 68 / 81, 16 000 98 / 88).
 // Over 1780 calls (70 000 to 400 000 ids, 100 to 490 entries, 32 to 602 columns, 4096 rows to all) the lines below are 1.01 times as slow
 // as the faster form on average and 1.24 at most; fours for all of them 1.21 (fp32), 1.05 (scaled), 1.14 and 1.10 (bf16), up to 2.7.
-static bool fours_pay(int64_t n_active, int64_t avg_row, int64_t n_src, int64_t row_bytes_used, bool f32, bool scaled) {
-    const int64_t entries = n_active * avg_row;
+// Two passes have twice the segments: fp32, 256 columns, 300 000 ids of 140 32 000 rows 0.79 (stream over fours), 64 000 0.94, 128 000 1.07; 500 000 64 000 0.89,
+// 128 000 1.05; bf16 32 000 0.91, 64 000 1.04; 32 columns 16 000 0.88, 32 000 1.06: twice the lines.
+static bool fours_pay(int64_t n_active, int64_t avg_row, int64_t n_src, int64_t row_bytes_used, int passes, bool f32, bool scaled) {
+    const int64_t rows = n_active / passes, entries = rows * avg_row;
     if (row_bytes_used <= kFourBytes) return entries >= (scaled ? 1000000 : 2000000);
-    if (f32 && row_bytes_used <= kSlabBytes) return n_active >= n_src / (scaled ? 6 : 3) && entries >= (scaled ? 4000000 : 6000000);
-    return n_active >= n_src / (scaled ? 16 : 10) && entries >= (scaled ? 4000000 : 6000000);
+    if (f32 && row_bytes_used <= kSlabBytes) return rows >= n_src / (scaled ? 6 : 3) && entries >= (scaled ? 4000000 : 6000000);
+    return rows >= n_src / (scaled ? 16 : 10) && entries >= (scaled ? 4000000 : 6000000);
 }
 
 static BlockedPlan plan_blocked(const gnn_csr* g, bool listed, bool copies, int32_t n_active, int32_t F, int64_t row_bytes, bool vec_ok, bool filter,
@@ -1411,7 +1413,7 @@ static BlockedPlan plan_blocked(const gnn_csr* g, bool listed, bool copies, int3
     // average kept length of a row: its entries spread over the id range like the vertices do
     const int64_t avg_row = (int64_t)((double)g->nnz / g->n_rows * ((double)n_src / g->n_cols));
     // Streams of fours: not for a row list, which may name a row twice (how many entries it has is not known here).
-    p.fours = !listed && n_blocks <= kMaxFourBlocks && fours_pay(n_active, avg_row, n_src, (int64_t)F * (f32 ? 4 : 2), f32, scaled);
+    p.fours = !listed && n_blocks <= kMaxFourBlocks && fours_pay(n_active, avg_row, n_src, (int64_t)F * (f32 ? 4 : 2), passes, f32, scaled);
     if (avg_row < (int64_t)blocked_min_segment(f32, p.fours, filter, scaled, n_active, F) * n_blocks) return p;
     p.fours = p.fours && copies;
     if (!die_mapping_holds()) return p;     // workgroup i is not on die i mod 8 here: the route has lost its reason

@@ -483,8 +483,8 @@ def test_blocked_route_fours_of_several_slabs(form, dtype):
     kernel, over a list of the same rows."""
     import paper_2311_06837_amd as P
     two, f32 = form == "two passes", dtype == torch.float32
-    n_rows, n_cols = (20_500, 300_001) if two else (8_000, 70_001)
-    longest = (460 if f32 else 680) if two else 1150
+    n_rows, n_cols = (38_000, 300_001) if two else (8_000, 70_001)
+    longest = (460 if f32 else 580) if two else 1150
     F = 67 if two or f32 else 150
     G, row, col = _random_rows(n_rows, n_cols, longest, 7)
     gen = torch.Generator(device="cuda").manual_seed(8)
